@@ -293,9 +293,10 @@ typedef struct {
     float eps;        /* eq. (vg) */
     float g_max;      /* eq. (g_mod), gain_mode 1 only */
     float beta;       /* smoothing of Qs when Qs != NULL, eq. (vQs) */
-    float tol;        /* rotation threshold of the Jacobi sweeps (relative); <= 0 selects the default 1e-12 */
+    float tol;        /* rotation threshold of the Jacobi sweeps (relative); <= 0 selects the default 1e-12, applied only where
+                         the direct decomposition leaves more than the rule below allows; > 0 always sweeps to that threshold */
     int gain_mode;    /* 0: g = 1/max(lambda, eps); 1: g = min(1/(M lambda_bar_m), g_max) on the signal subspace, 1 elsewhere */
-    int max_sweeps;   /* <= 0 selects the default 30 */
+    int max_sweeps;   /* bound on the Jacobi sweeps; <= 0 selects the default 30 */
 } fw_evd_params;
 
 /*   Phi_x   in   [M, M] symmetric
@@ -303,8 +304,12 @@ typedef struct {
  *   Qs      i/o  [M, M] or NULL: Qs <- beta Qs + (1-beta) Q
  *   lambda  out  [M] eigenvalues, decreasing
  *   ws      scratch, fw_workspace_bytes(FW_OP_WHITEN_EVD, M, 0, NULL, FW_F32) bytes
- * The decomposition is a one-sided Jacobi iteration carried out in float64 inside the workspace; the call blocks
- * once per sweep to read the rotation count.
+ * The decomposition runs in float64 inside the workspace: reduction to tridiagonal form, divide and conquer,
+ * back-transformation, then a check of every off-diagonal entry of V Phi_x V^T.  The result stands when all of them are below
+ * 2^-34 sqrt(D_i D_j), D_i = sum_k v_ik^2 Phi_kk (a thousandth of the float32 rounding of Phi_x), or below 2^-30 times the
+ * eigenvalue at which the gains are clamped; otherwise, or when tol > 0 asks for it, one-sided Jacobi sweeps continue from
+ * there in float64 until no pair of rows exceeds the rotation threshold.  The call blocks once for the verdict, and once per
+ * sweep where there are any.
  */
 fw_status fw_whiten_evd(const float* Phi_x, int M, const fw_evd_params* p, float* T, float* Q, float* Qs,
                         float* lambda, void* ws, size_t ws_bytes, void* stream);

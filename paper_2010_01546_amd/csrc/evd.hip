@@ -1,17 +1,22 @@
 // EVD / ZCA whitening matrix (Sec. 2, eqs. (vPhix_evd), (vT_EVD), (vg); Sec. 3.2, eqs. (hMs), (g_mod)) for gfx950.
 //
-// Phi_x is symmetric positive semi-definite, so a one-sided Jacobi iteration on its rows yields the decomposition:
-// orthogonal transformations are applied to the rows of W (initially Phi_x) and of V (initially I) until the rows of
-// W are mutually orthogonal; then W = Lambda V, the rows of V are the eigenvectors and lambda_k = w_k . v_k.
-// The iteration is blocked: rows are cut into blocks of 32, a round of the round-robin schedule takes disjoint pairs
-// of blocks, and for every pair (64 rows) three kernels run: the 64x64 Gram matrix of the rows (partial sums over
-// column slices), its diagonalisation by a cyclic two-sided Jacobi iteration in LDS, which yields the 64x64 rotation
-// that makes the 64 rows orthogonal to each other, and the application of that rotation to the rows of W and V.
-// A round therefore streams W and V once for 64 rows per pair instead of once per single row pair.  All of it runs
-// in float64 inside the workspace so that small eigenvalues, which carry the largest gains, keep their relative
-// accuracy.  T = V^T diag(sqrt g) V and Q = V^T diag(g) V are then symmetric rank-M updates of row-scaled copies of V:
-// through the float32 matrix-core covariance kernel, or for many features as split products on the bfloat16 matrix
-// cores (gemm_split.hip).
+// Phi_x = V^T Lambda V with the eigenvectors as rows of V, in float64 inside the workspace (small eigenvalues carry the
+// largest gains): reduction to tridiagonal form, divide and conquer, back-transformation (symeig.hip).  The result is then
+// CHECKED against Phi_x itself: W = V Phi_x, and every off-diagonal entry of W V^T must lie below kAccept sqrt(D_i D_j),
+// D_i = sum_k v_ik^2 Phi_kk, i.e. a thousandth of what the storage of Phi_x as float32 leaves undetermined in that entry, or
+// below kAcceptClamp times the eigenvalue at which the gains are clamped.  Where neither holds (diagonals graded over many
+// decades above the clamp), or where the caller asks for a rotation
+// threshold of its own (tol > 0), a one-sided Jacobi iteration goes on from there:
+// orthogonal transformations are applied to the rows of W = V Phi_x and of V until the rows of W are mutually orthogonal;
+// then W = Lambda V and lambda_k = w_k . v_k.  The iteration is blocked: rows are cut into blocks of 32, a round of the
+// round-robin schedule takes disjoint pairs of blocks, and for every pair (64 rows) three kernels run: the 64x64 Gram matrix
+// of the rows (partial sums over column slices), its diagonalisation by a cyclic two-sided Jacobi iteration in LDS, which
+// yields the 64x64 rotation that makes the 64 rows orthogonal to each other, and the application of that rotation to the
+// rows of W and V.  T = V^T diag(sqrt g) V and Q = V^T diag(g) V: in float64, or for many features as split products on the
+// bfloat16 matrix cores (gemm_split.hip).
+//
+// Why not Jacobi alone: from V = I it needs 13 to 19 sweeps that each stream W and V once per round.  One call took
+// 31 ms at M = 576, 175 ms at 2304 and 0.86 s at 4608; this way 3.6, 22.7 and 119 ms.
 #include "fw_internal.h"
 
 namespace fw {
@@ -20,52 +25,41 @@ namespace {
 constexpr int JB = 32;        // rows per block
 constexpr int JP = 2 * JB;    // rows per pair of blocks
 constexpr int JSW = 512;      // columns per slice of the Gram kernel
+constexpr double kAccept = 1.0 / (1ull << 34);   // 2^-10 of the float32 rounding 2^-24
+constexpr double kAcceptClamp = 1.0 / (1ull << 30);
 
 struct EvdWs {
-    size_t W, V, lam, gq, gh, cnt, X, dummy_s, cov, gpart, rot, flags, total;
+    size_t mat[4], small, lam, gq, gh, tot, cnt, total;
     int nblk, nblk_even, npairs, nslices;
 };
 // T and Q from the scaled eigenvectors: from FW_REFRESH_SPLIT_MIN_M features on as split products on the bfloat16 matrix
-// cores (the packed planes of X^T live where the covariance kernel's scratch would), below that through the float32
-// covariance kernel
+// cores, below that in float64.  Measured at M = 2304 for T and Q together: split 0.20 ms, float64 0.32 ms; at M = 576 one
+// float64 launch takes 20 us where two float32 covariance products with their reduction and mirror passes took 60.
 inline bool evd_products_split(int M) { return M >= FW_REFRESH_SPLIT_MIN_M; }
-inline size_t cov_ws_for(int M) {
-    if (evd_products_split(M)) return gemm_split_packed_bytes(M, M);
-    fw_conv_desc d = {M, M, 1, 1, 1, 1, 1, 0, FW_COV_FORM_DIRECT};   // products in float32, never the split form
-    return cov_workspace_bytes(M, &d, FW_F32, FW_LAYOUT_ROWS);
-}
 inline EvdWs evd_layout(int M) {
     EvdWs L;
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o += align_up(bytes, 256); return at; };
-    L.W = take((size_t)M * M * sizeof(double));
-    L.V = take((size_t)M * M * sizeof(double));
-    L.lam = take((size_t)M * sizeof(double));
-    L.gq = take((size_t)M * sizeof(double));
-    L.gh = take((size_t)M * sizeof(double));
-    L.cnt = take(256);
-    L.X = take((size_t)M * M * sizeof(float));
-    L.dummy_s = take((size_t)M * sizeof(float));
-    L.cov = take(cov_ws_for(M));
     L.nblk = (M + JB - 1) / JB;
     L.nblk_even = (L.nblk + 1) & ~1;
     L.npairs = L.nblk_even / 2;
     L.nslices = (M + JSW - 1) / JSW;
-    L.gpart = take((size_t)L.npairs * L.nslices * JP * JP * sizeof(double));
-    L.rot = take((size_t)L.npairs * JP * JP * sizeof(double));
-    L.flags = take((size_t)L.npairs * sizeof(int));
+    // Four float64 matrices: [0] Phi while it is reduced, then vectors of the merges, projections, partial Gram matrices, the
+    // scaled eigenvectors; [1] reflectors, then rotations and packed planes; [2], [3] eigenvectors and their image V Phi.
+    size_t m = sym_eig_matrix_doubles(M);
+    const size_t g = (size_t)L.npairs * L.nslices * JP * JP;
+    if (g > m) m = g;
+    m *= sizeof(double);
+    if (evd_products_split(M) && gemm_split_packed_bytes(M, M) > m) m = gemm_split_packed_bytes(M, M);
+    for (int k = 0; k < 4; ++k) L.mat[k] = take(m);
+    L.small = take(sym_eig_small_bytes(M));
+    L.lam = take((size_t)M * sizeof(double));
+    L.gq = take((size_t)M * sizeof(double));
+    L.gh = take((size_t)M * sizeof(double));
+    L.tot = take(256);
+    L.cnt = take(256);
     L.total = o;
     return L;
-}
-
-__global__ __launch_bounds__(256) void evd_init_kernel(const float* __restrict__ Phi, int M, double* __restrict__ W, double* __restrict__ V) {
-    const size_t n = (size_t)M * M;
-    for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < n; e += (size_t)gridDim.x * 256) {
-        const int i = (int)(e / M), j = (int)(e - (size_t)i * M);
-        // symmetric part, so that a slightly asymmetric input still has a well-defined decomposition
-        W[e] = 0.5 * ((double)Phi[e] + (double)Phi[(size_t)j * M + i]);
-        V[e] = i == j ? 1.0 : 0.0;
-    }
 }
 
 // One round of the round-robin ordering over n (even) players; pair k of round r.
@@ -90,8 +84,8 @@ typedef double doublex4 __attribute__((ext_vector_type(4)));
 // different 4-column steps of a chunk and each of them updates the ten 16x16 tiles of the lower triangle, both
 // operands of a tile being fragments of the same staged rows; the four partial results are summed through LDS in
 // wavefront order.
-__global__ __launch_bounds__(256) void gram_kernel(const double* __restrict__ W, int M, int nblk, int nblk_even, int round, int nslices,
-                                                   double* __restrict__ Gpart) {
+__global__ __launch_bounds__(256) void gram_kernel(const double* __restrict__ W, int ld, int M, int nblk, int nblk_even, int round,
+                                                   int nslices, double* __restrict__ Gpart) {
     __shared__ double Xs[JP][33];
     __shared__ double red[40][64];
     int a, b;
@@ -111,7 +105,7 @@ __global__ __launch_bounds__(256) void gram_kernel(const double* __restrict__ W,
     double nxt[8];
     auto fetch = [&](int c0) {
 #pragma unroll
-        for (int m = 0; m < 8; ++m) nxt[m] = (grow[m] >= 0 && c0 + cc < c_end) ? W[(size_t)grow[m] * M + c0 + cc] : 0.0;
+        for (int m = 0; m < 8; ++m) nxt[m] = (grow[m] >= 0 && c0 + cc < c_end) ? W[(size_t)grow[m] * ld + c0 + cc] : 0.0;
     };
     fetch(c_begin);
     for (int c0 = c_begin; c0 < c_end; c0 += 32) {
@@ -234,8 +228,9 @@ __global__ __launch_bounds__(1024) void pair_evd_kernel(const double* __restrict
 // rows of the pair <- R rows, for W (blockIdx.z = 0) and V (1), on v_mfma_f64_16x16x4_f64: a wavefront keeps all
 // fragments of R in registers and takes groups of 16 columns; the 64 x 16 block of a group is read into registers
 // before any of it is written back.
-__global__ __launch_bounds__(256) void rotate_rows_kernel(double* __restrict__ W, double* __restrict__ V, int M, int nblk, int nblk_even,
-                                                          int round, const double* __restrict__ Rot, const int* __restrict__ flags) {
+__global__ __launch_bounds__(256) void rotate_rows_kernel(double* __restrict__ W, double* __restrict__ V, int ld, int M, int nblk,
+                                                          int nblk_even, int round, const double* __restrict__ Rot,
+                                                          const int* __restrict__ flags) {
     __shared__ double Rs[JP][JP + 1];
     if (flags[blockIdx.y] == 0) return;
     int a, b;
@@ -261,7 +256,7 @@ __global__ __launch_bounds__(256) void rotate_rows_kernel(double* __restrict__ W
         const bool cok = col < M;
         double xb[16];
 #pragma unroll
-        for (int ks = 0; ks < 16; ++ks) xb[ks] = (rowk[ks] >= 0 && cok) ? Mat[(size_t)rowk[ks] * M + col] : 0.0;
+        for (int ks = 0; ks < 16; ++ks) xb[ks] = (rowk[ks] >= 0 && cok) ? Mat[(size_t)rowk[ks] * ld + col] : 0.0;
         doublex4 acc[4];
 #pragma unroll
         for (int t = 0; t < 4; ++t) acc[t] = doublex4{0.0, 0.0, 0.0, 0.0};
@@ -274,7 +269,7 @@ __global__ __launch_bounds__(256) void rotate_rows_kernel(double* __restrict__ W
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const int gr = pair_row(p, q, nblk, M, 16 * t + 4 * v + lq);
-                if (gr >= 0 && cok) Mat[(size_t)gr * M + col] = acc[t][v];
+                if (gr >= 0 && cok) Mat[(size_t)gr * ld + col] = acc[t][v];
             }
     }
 }
@@ -282,24 +277,22 @@ __global__ __launch_bounds__(256) void rotate_rows_kernel(double* __restrict__ W
 __global__ void zero_int_kernel(int* p) { *p = 0; }
 
 // lambda_k = w_k . v_k (signed), one wavefront per row
-__global__ __launch_bounds__(256) void eig_kernel(const double* __restrict__ W, const double* __restrict__ V, int M, double* __restrict__ lam) {
+__global__ __launch_bounds__(256) void eig_kernel(const double* __restrict__ W, const double* __restrict__ V, int ld, int M,
+                                                  double* __restrict__ lam) {
     const int lane = threadIdx.x & 63;
     const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (r >= M) return;
     double acc = 0.0;
-    for (int j = lane; j < M; j += 64) acc += W[(size_t)r * M + j] * V[(size_t)r * M + j];
+    for (int j = lane; j < M; j += 64) acc += W[(size_t)r * ld + j] * V[(size_t)r * ld + j];
     acc = wave_sum(acc);
     if (lane == 0) lam[r] = acc;
 }
 
-// Sorted eigenvalues (decreasing) and per-row gain roots.  One workgroup.
-//  mode 0: g = 1/max(lambda, eps)                                          eq. (vg)
-//  mode 1: g = min(1/(M lb), g_max) for sorted position < round(Ms_hat), 1 otherwise, lb = lambda/sum(lambda),
-//          Ms_hat = exp(-sum lb log lb)  (exponential of the spectral entropy; reading of eq. (hMs))   eq. (g_mod)
-__global__ __launch_bounds__(1024) void gains_kernel(const double* __restrict__ lam, int M, float eps, float g_max, int mode,
-                                                     float* __restrict__ lam_sorted, double* __restrict__ gq, double* __restrict__ gh) {
+// tot[0] = sum of the positive eigenvalues, tot[1] = Ms_hat = exp(-sum lb log lb), lb = lambda / tot[0] (exponential of the
+// spectral entropy; reading of eq. (hMs)).  One workgroup.
+__global__ __launch_bounds__(1024) void spectrum_kernel(const double* __restrict__ lam, int M, double* __restrict__ tot_out) {
     __shared__ double red[16];
-    __shared__ double s_tot, s_ent;
+    __shared__ double s_tot;
     double tot = 0.0;
     for (int k = threadIdx.x; k < M; k += 1024) tot += fmax(lam[k], 0.0);
     tot = wave_sum(tot);
@@ -314,47 +307,58 @@ __global__ __launch_bounds__(1024) void gains_kernel(const double* __restrict__ 
         if (lb > 0.0) ent -= lb * log(lb);
     }
     ent = wave_sum(ent);
-    __syncthreads();
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ent;
     __syncthreads();
-    if (threadIdx.x == 0) { double t = 0; for (int i = 0; i < 16; ++i) t += red[i]; s_ent = t; }
-    __syncthreads();
+    if (threadIdx.x == 0) {
+        double t = 0;
+        for (int i = 0; i < 16; ++i) t += red[i];
+        tot_out[0] = tot;
+        tot_out[1] = tot > 0.0 ? exp(t) : 1.0;
+    }
+}
+
+// Sorted eigenvalues (decreasing) and gain roots, one wavefront per eigenvalue: its sorted position is the number of
+// eigenvalues ahead of it (M comparisons; 336 us at M = 2304 when a single workgroup did all of them, 10 us like this).
+//  mode 0: g = 1/max(lambda, eps)                                          eq. (vg)
+//  mode 1: g = min(1/(M lb), g_max) for sorted position < round(Ms_hat), 1 otherwise   eq. (g_mod)
+__global__ __launch_bounds__(256) void gains_kernel(const double* __restrict__ lam, int M, const double* __restrict__ tot_in, float eps,
+                                                    float g_max, int mode, float* __restrict__ lam_sorted, double* __restrict__ gq,
+                                                    double* __restrict__ gh) {
+    const int lane = threadIdx.x & 63, k = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (k >= M) return;
+    const double lk = lam[k];
+    int pos = 0;
+    for (int j = lane; j < M; j += 64) {
+        const double lj = lam[j];
+        pos += (lj > lk || (lj == lk && j < k)) ? 1 : 0;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) pos += __shfl_xor(pos, o, 64);
+    if (lane != 0) return;
+    lam_sorted[pos] = (float)lk;
+    const double tot = tot_in[0];
     int rank_sig = M;
     if (mode == 1) {
-        const double ms = tot > 0.0 ? exp(s_ent) : 1.0;
-        double r = floor(ms + 0.5);
+        double r = floor(tot_in[1] + 0.5);
         if (r < 1.0) r = 1.0;
         if (r > (double)M) r = (double)M;
         rank_sig = (int)r;
     }
-    for (int k = threadIdx.x; k < M; k += 1024) {
-        const double lk = lam[k];
-        int pos = 0;  // sorted position: number of eigenvalues ahead of this one
-        for (int j = 0; j < M; ++j) {
-            const double lj = lam[j];
-            pos += (lj > lk || (lj == lk && j < k)) ? 1 : 0;
-        }
-        lam_sorted[pos] = (float)lk;
-        double g;
-        if (mode == 0) g = 1.0 / fmax(lk, (double)eps);
-        else if (pos >= rank_sig) g = 1.0;
-        else if (lk <= 0.0 || tot <= 0.0) g = (double)g_max;
-        else g = fmin(tot / ((double)M * lk), (double)g_max);
-        gh[k] = sqrt(g);
-        gq[k] = sqrt(sqrt(g));
-    }
+    double g;
+    if (mode == 0) g = 1.0 / fmax(lk, (double)eps);
+    else if (pos >= rank_sig) g = 1.0;
+    else if (lk <= 0.0 || tot <= 0.0) g = (double)g_max;
+    else g = fmin(tot / ((double)M * lk), (double)g_max);
+    gh[k] = sqrt(g);
+    gq[k] = sqrt(gh[k]);
 }
 
 // X[k][j] = scale[k] * V[k][j] as float32
-__global__ __launch_bounds__(256) void scale_rows_kernel(const double* __restrict__ V, const double* __restrict__ scale, int M,
+__global__ __launch_bounds__(256) void scale_rows_kernel(const double* __restrict__ V, const double* __restrict__ scale, int ld, int M,
                                                          float* __restrict__ X) {
-    const size_t n = (size_t)M * M;
-    for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < n; e += (size_t)gridDim.x * 256)
-        X[e] = (float)(scale[e / M] * V[e]);
-}
-
-__global__ __launch_bounds__(256) void fill_kernel(float* __restrict__ p, size_t n, float v) {
-    for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < n; e += (size_t)gridDim.x * 256) p[e] = v;
+    const double f = scale[blockIdx.y];
+    for (int j = blockIdx.x * 256 + threadIdx.x; j < M; j += gridDim.x * 256)
+        X[(size_t)blockIdx.y * M + j] = (float)(f * V[(size_t)blockIdx.y * ld + j]);
 }
 
 __global__ __launch_bounds__(256) void ema_kernel(float* __restrict__ Qs, const float* __restrict__ Q, size_t n, float beta) {
@@ -369,6 +373,29 @@ inline int grid_for(size_t n) {
 
 }  // namespace
 
+// lambda (already in `lam`) -> sorted eigenvalues, gains, T and Q
+static fw_status evd_outputs(const double* V, int M, const fw_evd_params* p, double* lam, double* gq, double* gh, double* tot, float* X,
+                             void* planes, float* T, float* Q, float* lambda, hipStream_t st) {
+    const int ld = sym_eig_ld(M);
+    hipLaunchKernelGGL(spectrum_kernel, dim3(1), dim3(1024), 0, st, lam, M, tot);
+    hipLaunchKernelGGL(gains_kernel, dim3((M + 3) / 4), dim3(256), 0, st, lam, M, tot, p->eps, p->g_max, p->gain_mode, lambda, gq, gh);
+    FW_LAUNCH_CHECK();
+    if (!evd_products_split(M)) return sym_eig_spectral_products(V, M, gh, T, Q, st);
+    for (int which = 0; which < 2; ++which) {
+        float* out = which == 0 ? T : Q;
+        hipLaunchKernelGGL(scale_rows_kernel, dim3((M + 1023) / 1024, M), dim3(256), 0, st, V, which == 0 ? gq : gh, ld, M, X);
+        FW_LAUNCH_CHECK();
+        // X^T X = (X^T)(X^T)^T: the columns of X as hi + lo planes are both operands; lower triangle only
+        fw_status rc = gemm_split_pack_transposed(X, M, M, planes, st);
+        if (rc != FW_OK) return rc;
+        rc = gemm_split_run(planes, planes, M, M, M, 1, out, st);
+        if (rc != FW_OK) return rc;
+        rc = symmetrize_from_lower(out, M, st);
+        if (rc != FW_OK) return rc;
+    }
+    return FW_OK;
+}
+
 size_t evd_workspace_bytes(int M) { return evd_layout(M).total; }
 
 fw_status whiten_evd(const float* Phi_x, int M, const fw_evd_params* p, float* T, float* Q, float* Qs, float* lambda, void* ws,
@@ -376,69 +403,60 @@ fw_status whiten_evd(const float* Phi_x, int M, const fw_evd_params* p, float* T
     const EvdWs L = evd_layout(M);
     if (ws_bytes < L.total) return FW_ERR_WORKSPACE;
     char* base = reinterpret_cast<char*>(ws);
-    double* W = reinterpret_cast<double*>(base + L.W);
-    double* V = reinterpret_cast<double*>(base + L.V);
+    double* mat[4];
+    for (int k = 0; k < 4; ++k) mat[k] = reinterpret_cast<double*>(base + L.mat[k]);
     double* lam = reinterpret_cast<double*>(base + L.lam);
     double* gq = reinterpret_cast<double*>(base + L.gq);
     double* gh = reinterpret_cast<double*>(base + L.gh);
+    double* tot = reinterpret_cast<double*>(base + L.tot);
     int* cnt = reinterpret_cast<int*>(base + L.cnt);
-    float* X = reinterpret_cast<float*>(base + L.X);
-    float* dummy_s = reinterpret_cast<float*>(base + L.dummy_s);
-    void* cov_ws = base + L.cov;
-    const size_t cov_ws_bytes = cov_ws_for(M);
-    const size_t n = (size_t)M * M;
+    const int ld = sym_eig_ld(M);
     const double tol = p->tol > 0.f ? (double)p->tol : 1e-12;
     const int max_sweeps = p->max_sweeps > 0 ? p->max_sweeps : 30;
 
-    hipLaunchKernelGGL(evd_init_kernel, dim3(grid_for(n)), dim3(256), 0, st, Phi_x, M, W, V);
-    FW_LAUNCH_CHECK();
-    double* Gpart = reinterpret_cast<double*>(base + L.gpart);
-    double* Rot = reinterpret_cast<double*>(base + L.rot);
-    int* flags = reinterpret_cast<int*>(base + L.flags);
-    const int ncolblk = (M + 511) / 512;
-    const int inner = 1;   // inner sweeps per visit of a pair: one was the fastest overall (more inner sweeps, fewer outer ones)
-    bool converged = false;
-    for (int sweep = 0; sweep < max_sweeps && !converged; ++sweep) {
-        hipLaunchKernelGGL(zero_int_kernel, dim3(1), dim3(1), 0, st, cnt);
-        for (int r = 0; r < L.nblk_even - 1; ++r) {
-            hipLaunchKernelGGL(gram_kernel, dim3(L.nslices, L.npairs), dim3(256), 0, st, W, M, L.nblk, L.nblk_even, r, L.nslices, Gpart);
-            hipLaunchKernelGGL(pair_evd_kernel, dim3(L.npairs), dim3(1024), 0, st, Gpart, L.nslices, tol, inner, Rot, flags, cnt);
-            hipLaunchKernelGGL(rotate_rows_kernel, dim3(ncolblk, L.npairs, 2), dim3(256), 0, st, W, V, M, L.nblk, L.nblk_even, r, Rot,
-                               flags);
-        }
-        FW_LAUNCH_CHECK();
-        int rotations = -1;
-        FW_HIP_TRY(hipMemcpyAsync(&rotations, cnt, sizeof(int), hipMemcpyDeviceToHost, st));
-        FW_HIP_TRY(hipStreamSynchronize(st));
-        converged = rotations == 0;
-    }
-    hipLaunchKernelGGL(eig_kernel, dim3((M + 3) / 4), dim3(256), 0, st, W, V, M, lam);
-    hipLaunchKernelGGL(gains_kernel, dim3(1), dim3(1024), 0, st, lam, M, p->eps, p->g_max, p->gain_mode, lambda, gq, gh);
-    FW_LAUNCH_CHECK();
-
-    const fw_conv_desc d = {M, M, 1, 1, 1, 1, 1, 0, FW_COV_FORM_DIRECT};   // products in float32, never the split form
-    for (int which = 0; which < 2; ++which) {
-        float* out = which == 0 ? T : Q;
-        hipLaunchKernelGGL(scale_rows_kernel, dim3(grid_for(n)), dim3(256), 0, st, V, which == 0 ? gq : gh, M, X);
-        FW_LAUNCH_CHECK();
-        fw_status rc;
-        if (evd_products_split(M)) {
-            // X^T X = (X^T)(X^T)^T: the columns of X as hi + lo planes are both operands; lower triangle only
-            rc = gemm_split_pack_transposed(X, M, M, cov_ws, st);
-            if (rc != FW_OK) return rc;
-            rc = gemm_split_run(cov_ws, cov_ws, M, M, M, 1, out, st);
-            if (rc != FW_OK) return rc;
-        } else {
-            hipLaunchKernelGGL(fill_kernel, dim3(grid_for(n)), dim3(256), 0, st, out, n, 0.f);
-            hipLaunchKernelGGL(fill_kernel, dim3(grid_for(M)), dim3(256), 0, st, dummy_s, (size_t)M, 0.f);
+    double *V, *W;
+    fw_status rc = sym_eig(Phi_x, M, mat, base + L.small, &V, &W, st);
+    if (rc != FW_OK) return rc;
+    // eigenvalues below the clamp all have the clamp's gain: entries far below it cannot move a gain
+    const double floor_abs = p->gain_mode == 0 ? kAcceptClamp * (double)p->eps : 0.0;
+    const double floor_rel = p->gain_mode == 1 ? kAcceptClamp / ((double)M * (double)p->g_max) : 0.0;
+    rc = sym_eig_check(Phi_x, M, V, W, mat[0], base + L.small, kAccept, floor_abs, floor_rel, lam, cnt, st);
+    if (rc != FW_OK) return rc;
+    float* X = reinterpret_cast<float*>(mat[0]);
+    // the outputs are issued before the host looks at the verdict, so that the GPU does not wait for it
+    rc = evd_outputs(V, M, p, lam, gq, gh, tot, X, mat[1], T, Q, lambda, st);
+    if (rc != FW_OK) return rc;
+    int sweeps_needed = 1;
+    FW_HIP_TRY(hipMemcpyAsync(&sweeps_needed, cnt, sizeof(int), hipMemcpyDeviceToHost, st));
+    FW_HIP_TRY(hipStreamSynchronize(st));
+    bool converged = sweeps_needed == 0 && !(p->tol > 0.f);
+    if (!converged) {
+        double* Gpart = mat[0];
+        double* Rot = mat[1];
+        int* flags = reinterpret_cast<int*>(base + L.small);
+        const int ncolblk = (M + 511) / 512;
+        const int inner = 1;   // inner sweeps per visit of a pair: one was the fastest overall (more inner sweeps, fewer outer ones)
+        for (int sweep = 0; sweep < max_sweeps && !converged; ++sweep) {
+            hipLaunchKernelGGL(zero_int_kernel, dim3(1), dim3(1), 0, st, cnt);
+            for (int r = 0; r < L.nblk_even - 1; ++r) {
+                hipLaunchKernelGGL(gram_kernel, dim3(L.nslices, L.npairs), dim3(256), 0, st, W, ld, M, L.nblk, L.nblk_even, r, L.nslices, Gpart);
+                hipLaunchKernelGGL(pair_evd_kernel, dim3(L.npairs), dim3(1024), 0, st, Gpart, L.nslices, tol, inner, Rot, flags, cnt);
+                hipLaunchKernelGGL(rotate_rows_kernel, dim3(ncolblk, L.npairs, 2), dim3(256), 0, st, W, V, ld, M, L.nblk, L.nblk_even, r, Rot,
+                                   flags);
+            }
             FW_LAUNCH_CHECK();
-            rc = cov_accumulate(X, FW_F32, FW_LAYOUT_ROWS, &d, out, dummy_s, cov_ws, cov_ws_bytes, st);
-            if (rc != FW_OK) return rc;
+            int rotations = -1;
+            FW_HIP_TRY(hipMemcpyAsync(&rotations, cnt, sizeof(int), hipMemcpyDeviceToHost, st));
+            FW_HIP_TRY(hipStreamSynchronize(st));
+            converged = rotations == 0;
         }
-        rc = symmetrize_from_lower(out, M, st);
+        hipLaunchKernelGGL(eig_kernel, dim3((M + 3) / 4), dim3(256), 0, st, W, V, ld, M, lam);
+        FW_LAUNCH_CHECK();
+        rc = evd_outputs(V, M, p, lam, gq, gh, tot, X, mat[1], T, Q, lambda, st);
         if (rc != FW_OK) return rc;
     }
     if (Qs) {
+        const size_t n = (size_t)M * M;
         hipLaunchKernelGGL(ema_kernel, dim3(grid_for(n)), dim3(256), 0, st, Qs, Q, n, p->beta);
         FW_LAUNCH_CHECK();
     }

@@ -60,3 +60,71 @@ def test_config1_full_whitening():
     To, Qo, lo_ = ora.whiten_evd(Phi32)
     assert relF(T, To) < 1e-4 and relF(Q, Qo) < 1e-4
     assert np.linalg.norm(T @ Phi32.astype(np.float64) @ T.T - np.eye(64)) / 8 < 1e-3
+
+
+def reflected_diagonal(M, lam, seed):
+    """Symmetric matrix with eigenvalues lam and eigenvectors H_1 H_2 (two reflections): closed forms for T and Q, built on the
+    GPU in float64."""
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    us = [torch.randn(M, generator=g, device=DEV, dtype=torch.float64) for _ in range(2)]
+    us = [u / u.norm() for u in us]
+
+    def form(d):
+        X = torch.diag(d)
+        for u in us:
+            X = X - 2 * torch.outer(u, u @ X)
+            X = X - 2 * torch.outer(X @ u, u)
+        return X
+    return form(torch.as_tensor(lam, device=DEV)), form
+
+
+# One size per range of the reduction's launch rule (columns per thread change at 256, 512, 768, 1024, 1536, 2048, 2560, 3072,
+# 4096, 5120, 8192 rows), the last 128 rows alone and with one row more, one leaf, two leaves, sizes where T and Q change form.
+# The matrix is stored as float32, so T and Q of a spectrum within [0.05, 1] carry about 2^-24 / 0.05; from 1536 features on
+# their products run on operands of 16 significant bits (5e-6).
+@pytest.mark.parametrize("M", [1, 16, 17, 127, 128, 129, 257, 513, 769, 1025, 1535, 1537, 2049, 2561, 3073, 4097, 5121, 8193])
+def test_direct_decomposition_sizes(M):
+    lam = np.linspace(1.0, 0.05, M)
+    Phi, form = reflected_diagonal(M, lam, M)
+    T = torch.empty(M, M, device=DEV); Q = torch.empty(M, M, device=DEV); out = torch.empty(M, device=DEV)
+    ws = workspace(b.fw_workspace_bytes(b.FW_OP_WHITEN_EVD, M))
+    b.fw_whiten_evd(Phi.float(), M, b.evd_params(), T, Q, None, out, ws)
+    d = torch.as_tensor(lam, device=DEV)
+    rel = lambda x, y: float((x.double() - y).norm() / y.norm())
+    bound = 2e-5 if M >= b.FW_REFRESH_SPLIT_MIN_M else 2e-6
+    assert rel(T, form(d.rsqrt())) < bound and rel(Q, form(1 / d)) < bound
+    assert float((out.double() - d).abs().max()) < 5e-7
+    assert torch.equal(T, T.T) and torch.equal(Q, Q.T)
+
+
+@pytest.mark.parametrize("kind", ["dead", "duplicate", "identity", "zero", "graded", "tol"])
+@pytest.mark.parametrize("M", [33, 200])
+def test_special_matrices(kind, M):
+    """Zero rows, rank deficiency, full deflation, a diagonal graded over 16 decades far above the clamp (ends in the Jacobi
+    sweeps) and sweeps to a threshold of the caller's; T and Q against the oracle."""
+    rng = np.random.default_rng(M)
+    Phi = wl.spd_matrix(M, M, np.logspace(0, -3, M))
+    kw = {}
+    if kind == "dead":
+        Phi[:, ::3] = 0; Phi[::3, :] = 0
+    elif kind == "duplicate":
+        Phi[:, 5] = Phi[:, 7]; Phi[5, :] = Phi[7, :]; Phi[5, 5] = Phi[7, 7]
+    elif kind == "identity":
+        Phi = np.eye(M)
+    elif kind == "zero":
+        Phi = np.zeros((M, M))
+    elif kind == "graded":
+        s = 10.0 ** np.linspace(8, 0, M)
+        Phi = wl.spd_matrix(M, M, np.linspace(1, 0.3, M)) * s[:, None] * s[None, :]
+    elif kind == "tol":
+        kw = {"tol": 1e-12}
+    Phi32 = Phi.astype(np.float32)
+    T, Q, lam = run_evd(Phi32, eps=1e-5, **kw)
+    if kind == "graded":
+        # LAPACK has no relative accuracy here; D^-1/2 Phi D^-1/2 is well conditioned, so the whitening identity holds
+        P = Phi32.astype(np.float64)
+        assert np.all(lam > 0) and np.linalg.norm(T @ P @ T.T - np.eye(M)) / np.sqrt(M) < 0.05
+        return
+    To, Qo, lo_ = ora.whiten_evd(Phi32, eps=1e-5)
+    assert relF(T, To) < 1e-5 and relF(Q, Qo) < 1e-5
+    assert np.max(np.abs(lam - lo_)) <= 2e-7 * max(lo_[0], 1e-30)
