@@ -167,6 +167,13 @@ def test_condition_probe_against_the_oracle(M, k):
     assert g_cond <= w[-1] / w[0] * (1 + 1e-5)
 
 
+@pytest.mark.parametrize("M,k", [(63, 17), (525, 32), (1023, 16), (1025, 16), (2047, 9), (2048, 32), (2049, 5)])
+def test_condition_probe_orthogonalisation_edges(M, k):
+    """Around the strips of the orthogonalisation (64 entries, 1024 threads), with odd M, with more basis vectors than
+    wavefronts, and on both sides of the size at which a step is spread over several workgroups."""
+    test_condition_probe_against_the_oracle(M, k)
+
+
 def test_condition_probe_special_cases():
     # invariant subspace: the start vector lives in the span of two eigenvectors -> stops at dimension 2, exact there
     P = np.diag([7.0, 3.0, 2.0, 1.0, 0.5]).astype(np.float32)
