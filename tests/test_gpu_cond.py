@@ -51,6 +51,14 @@ def test_teacher_forced_steps(M, kw):
     assert applied >= 2
 
 
+@pytest.mark.parametrize("M", [2, 15, 17, 63, 64, 65])
+def test_teacher_forced_steps_around_the_one_launch_form(M):
+    """Rows per wavefront (16), full and ragged, and the last size of the one-launch form with its neighbours."""
+    Phi = spd(M, 300 + M, hi=1.0, lo=-1.0)
+    teacher_forced(Phi, np.trace(Phi) / M, dict(), steps=6)
+    teacher_forced(Phi, np.trace(Phi) / M, dict(gamma=1.0, beta=0.0, n_power_iters=1), steps=6)
+
+
 def test_invariants_free_running():
     """After many free-running steps Q = T^T T and Phi_y = T Phi_x T^T still hold, and the condition number has dropped."""
     M = 96
