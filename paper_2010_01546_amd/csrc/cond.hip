@@ -802,6 +802,89 @@ __global__ __launch_bounds__(256) void rownorm2_kernel(const float* __restrict__
     if (lane == 0) out[r] = acc;
 }
 
+// ---- the refresh in one launch, for few features
+// Two products, the mirror image and the row norms are four launches that do little work each.  The strip of 16 rows of
+// Phi_y needs only the same strip of Psi, so a workgroup forms its strip of Psi, keeps it in LDS and multiplies on: one
+// wavefront per tile of 16 columns, v_mfma_f32_16x16x4_f32, operands straight from L2 (16 bytes per lane and load).  The
+// matrix is written from its lower triangle (an element below the diagonal also goes to the mirrored position); the row norms are taken
+// from the strip as computed, whose part above the diagonal differs from the stored one by rounding only.
+// Only M / 16 compute units work, at 4 M^2 words each, so the form ends early.  Measured, this form against the four
+// launches: 7.0 / 15.6 us at 64 features, 10.2 / 15.6 at 128, 16.5 / 15.4 at 160; with rows that are not 16-byte aligned
+// (single loads) 11.0 / 14.9 at 75 and 26.9 / 18.5 at 147.
+constexpr int REFRESH_ROWS_MAX_M = 128, REFRESH_ROWS_MAX_M_UNALIGNED = 80;
+template <bool V4>
+__device__ __forceinline__ void refresh_tile(const float* a_row, const float* __restrict__ b_row, int K, int kq, floatx4& acc) {
+    constexpr int U = 4;
+    for (int k0 = 0; k0 < K; k0 += 16 * U) {
+        float a[U][4], b[U][4];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = k0 + 16 * u + 4 * kq;
+            if (V4) {
+                const float4 y = *reinterpret_cast<const float4*>(b_row + (k < K ? k : 0));
+                const float4 x = *reinterpret_cast<const float4*>(a_row + (k < K ? k : 0));
+                a[u][0] = x.x; a[u][1] = x.y; a[u][2] = x.z; a[u][3] = x.w;
+                b[u][0] = y.x; b[u][1] = y.y; b[u][2] = y.z; b[u][3] = y.w;
+            } else {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) { a[u][q] = a_row[k + q < K ? k + q : 0]; b[u][q] = b_row[k + q < K ? k + q : 0]; }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = k0 + 16 * u + 4 * kq;
+            // beyond the end both factors are zero (a value of entry 0 may be infinite)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const bool ok = k + q < K;
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(ok ? a[u][q] : 0.f, ok ? b[u][q] : 0.f, acc, 0, 0, 0);
+            }
+        }
+    }
+}
+template <bool V4>
+__global__ __launch_bounds__(512) void refresh_rows_kernel(const float* __restrict__ T, const float* __restrict__ Phi_x, int M,
+                                                            float* __restrict__ Psi, float* __restrict__ Phi_y, float* __restrict__ xi2) {
+    constexpr int PITCH = REFRESH_ROWS_MAX_M + 4;      // 16 rows of one column group fall into distinct banks
+    __shared__ __attribute__((aligned(16))) float Ps[16][PITCH];
+    __shared__ float red[8][16];
+    const int lane = threadIdx.x & 63, r = lane & 15, kq = lane >> 4;
+    const int tile = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), ntiles = blockDim.x >> 6;
+    const int row0 = blockIdx.x * 16, col = tile * 16 + r;
+    const float* Trow = T + (size_t)min(row0 + r, M - 1) * M;    // rows past the end feed results that are not stored
+    const size_t coff = (size_t)min(col, M - 1) * M;
+    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+    refresh_tile<V4>(Trow, Phi_x + coff, M, kq, acc);     // Phi_x is symmetric: its rows stand for its columns
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int row = row0 + 4 * kq + i;
+        Ps[4 * kq + i][col] = acc[i];
+        if (row < M && col < M) Psi[(size_t)row * M + col] = acc[i];
+        acc[i] = 0.f;
+    }
+    __syncthreads();
+    refresh_tile<V4>(Ps[r], T + coff, M, kq, acc);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int row = row0 + 4 * kq + i;
+        const float y = acc[i];
+        if (row < M && col <= row) {
+            Phi_y[(size_t)row * M + col] = y;
+            if (col < row) Phi_y[(size_t)col * M + row] = y;
+        }
+        float q = col < M ? y * y : 0.f;
+#pragma unroll
+        for (int o = 8; o > 0; o >>= 1) q += __shfl_xor(q, o, 64);
+        if (r == 0) red[tile][4 * kq + i] = q;
+    }
+    __syncthreads();
+    if (threadIdx.x < 16 && row0 + (int)threadIdx.x < M) {
+        float q = 0.f;
+        for (int k = 0; k < ntiles; ++k) q += red[k][threadIdx.x];
+        xi2[row0 + threadIdx.x] = q;
+    }
+}
+
 }  // namespace
 
 size_t cond_workspace_bytes(int M) { return ws_layout(M).total; }
@@ -845,6 +928,13 @@ fw_status cond_state_refresh(const fw_cond_state* s, void* ws, size_t ws_bytes, 
     const size_t psi_bytes = align_up((size_t)M * M * sizeof(float), 256);
     char* base = reinterpret_cast<char*>(ws);
     float* Psi = s->Psi ? s->Psi : reinterpret_cast<float*>(base);
+    if (M <= ((M & 3) == 0 ? REFRESH_ROWS_MAX_M : REFRESH_ROWS_MAX_M_UNALIGNED)) {
+        const dim3 grid((M + 15) / 16), blk(64 * ((M + 15) / 16));
+        if ((M & 3) == 0) hipLaunchKernelGGL(refresh_rows_kernel<true>, grid, blk, 0, st, s->T, s->Phi_x, M, Psi, s->Phi_y, s->xi2);
+        else hipLaunchKernelGGL(refresh_rows_kernel<false>, grid, blk, 0, st, s->T, s->Phi_x, M, Psi, s->Phi_y, s->xi2);
+        FW_LAUNCH_CHECK();
+        return FW_OK;
+    }
     fw_status rc;
     // Below about 1500 features the float32 kernel is as fast (too few 256-wide tiles for 256 compute units, and the
     // three packing passes cost as much as a product); FW_REFRESH_SPLIT_MIN_M is where the split form starts.

@@ -59,6 +59,27 @@ def test_teacher_forced_steps_around_the_one_launch_form(M):
     teacher_forced(Phi, np.trace(Phi) / M, dict(gamma=1.0, beta=0.0, n_power_iters=1), steps=6)
 
 
+@pytest.mark.parametrize("M", [1, 16, 18, 48, 79, 80, 81, 100, 127, 128, 129, 132])
+def test_refresh_around_the_one_launch_form(M):
+    """Psi = T Phi_x, Phi_y = T Phi_x T^T and its squared row norms against float64 at the strips (16 rows) and sizes where the
+    one-launch form ends; sums of M float32 products: relative error of order sqrt(M) 2^-24."""
+    rng = np.random.default_rng(M)
+    P = spd(M, M, 1.0, -1.0).astype(np.float32) if M > 1 else np.full((1, 1), 0.7, np.float32)
+    P = ((P + P.T) / 2).astype(np.float32)
+    T = (np.eye(M) + 0.3 * rng.standard_normal((M, M)) / np.sqrt(M)).astype(np.float32)
+    z = lambda *sh: torch.full(sh, float("nan"), device="cuda:0")  # noqa: E731
+    Py, Psi, xi2, lbar = z(M, M), z(M, M), z(M), torch.ones(4, device="cuda:0")
+    Q = dev(np.eye(M))
+    st = b.cond_state(M, dev(P), lbar, dev(T), Q, Q.clone(), Py, Psi, xi2)
+    b.fw_cond_state_refresh(st, workspace(b.fw_workspace_bytes(b.FW_OP_COND_STATE_REFRESH, M)))
+    torch.cuda.synchronize()
+    P64, T64 = P.astype(np.float64), T.astype(np.float64)
+    want = T64 @ P64 @ T64.T
+    assert relF(Psi.cpu().numpy(), T64 @ P64) < 2e-6 and relF(Py.cpu().numpy(), want) < 4e-6
+    assert np.array_equal(Py.cpu().numpy(), Py.cpu().numpy().T)
+    assert relF(xi2.cpu().numpy(), (want ** 2).sum(0)) < 8e-6
+
+
 def test_invariants_free_running():
     """After many free-running steps Q = T^T T and Phi_y = T Phi_x T^T still hold, and the condition number has dropped."""
     M = 96
