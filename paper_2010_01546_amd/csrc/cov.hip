@@ -782,7 +782,7 @@ size_t cov_workspace_bytes(int /*M*/, const fw_conv_desc* d, fw_dtype dt, fw_lay
 
 bool cov_plan(const fw_conv_desc* d, fw_dtype dt, fw_layout lay, fw_cov_plan* plan) {
     *plan = fw_cov_plan{};
-    if (cov_skinny_plan(d, lay, plan)) return true;
+    if (cov_few_rows_plan(d, dt, lay, plan) || cov_skinny_plan(d, lay, plan)) return true;
     if (dt == FW_BF16) return cov_bf16_plan(d, lay, plan);
     if (nchw_through_copy(d, dt, lay)) lay = FW_LAYOUT_NHWC;
     {
@@ -804,6 +804,8 @@ bool cov_plan(const fw_conv_desc* d, fw_dtype dt, fw_layout lay, fw_cov_plan* pl
 
 fw_status cov_accumulate(const void* X, fw_dtype dt, fw_layout lay, const fw_conv_desc* d, float* A, float* s, void* ws,
                          size_t ws_bytes, hipStream_t st) {
+    // few rows, 1x1 window: one launch (cov_skinny.hip; it leaves the workspace, which is that of the general form, alone)
+    if (cov_few_rows_applies(d, dt, lay)) return cov_few_rows_accumulate(X, dt, d, A, s, st);
     // few features, many rows, 1x1 window: streamed once, no staging (cov_skinny.hip)
     if (cov_skinny_applies(d, lay)) return cov_skinny_accumulate(X, dt, lay, d, A, s, ws, ws_bytes, st);
     if (dt == FW_BF16) return cov_bf16_accumulate(X, lay, d, A, s, ws, ws_bytes, st);

@@ -303,4 +303,105 @@ fw_status cov_skinny_accumulate(const void* X, fw_dtype dt, fw_layout lay, const
     return FW_OK;
 }
 
+// ---- few rows, 1x1 windows: one launch, no workspace
+// A fully connected layer with a small batch: the products are nothing, the general forms spend their time between two to
+// four launches and in a serial walk over the rows by a few workgroups.  Here a workgroup owns a 16 x 16 tile of the
+// lower triangle; its eight wavefronts take every eighth group of four rows, eight loads per operand in flight, and are added
+// in float64 into A by the same launch.  bfloat16 values are widened in registers.
+// The fully connected layers of 64 features (batch 128, float32) and of 512 (batch 256, bfloat16): 2 launches fewer of
+// 48 us a pass, 3 fewer of 90 us; see the rule below for the call by itself.
+// Panels are re-read once per 16 columns, which grows with rows x M^2: hence the line in cov_few_rows_applies.
+namespace {
+template <bool BF16>
+__global__ __launch_bounds__(512) void cov_few_rows_kernel(const void* __restrict__ Xv, int n_rows, int M, float* __restrict__ A,
+                                                           float* __restrict__ s) {
+    constexpr int U = 8;
+    __shared__ float red[8][256];
+    __shared__ float sred[8][64];
+    const int lane = threadIdx.x & 63, c = lane & 15, kq = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // tile index -> (I, J), I >= J
+    int I = (int)((sqrtf(8.f * (float)blockIdx.x + 1.f) - 1.f) * 0.5f);
+    while ((I + 1) * (I + 2) / 2 <= (int)blockIdx.x) ++I;
+    while (I * (I + 1) / 2 > (int)blockIdx.x) --I;
+    const int J = (int)blockIdx.x - I * (I + 1) / 2;
+    const int fa = 16 * I + c, fb = 16 * J + c;
+    const bool a_ok = fa < M, b_ok = fb < M;
+    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+    float cs = 0.f;
+    auto value = [&](size_t e) {
+        return BF16 ? __uint_as_float((unsigned)reinterpret_cast<const unsigned short*>(Xv)[e] << 16) : reinterpret_cast<const float*>(Xv)[e];
+    };
+    for (int r0 = 4 * wave; r0 < n_rows; r0 += 32 * U) {
+        float a[U], b[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int r = r0 + 32 * u + kq;
+            const bool ok = r < n_rows;          // masked lanes read element 0
+            a[u] = value(ok && a_ok ? (size_t)r * M + fa : 0);
+            b[u] = value(ok && b_ok ? (size_t)r * M + fb : 0);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool ok = r0 + 32 * u + kq < n_rows;
+            const float x = ok && a_ok ? a[u] : 0.f, y = ok && b_ok ? b[u] : 0.f;
+            cs += x;
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x, y, acc, 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) red[wave][(4 * kq + i) * 16 + c] = acc[i];
+    sred[wave][lane] = cs;
+    __syncthreads();
+    const int t = threadIdx.x;
+    if (t < 256) {
+        const int i = 16 * I + (t >> 4), j = 16 * J + (t & 15);
+        if (i < M && j <= i) {
+            double v = 0.0;
+#pragma unroll
+            for (int w = 0; w < 8; ++w) v += (double)red[w][t];
+            float* dst = A + (size_t)i * M + j;
+            *dst = (float)((double)*dst + v);
+        }
+    } else if (t < 272 && I == J && 16 * I + (t - 256) < M) {
+        double v = 0.0;
+#pragma unroll
+        for (int w = 0; w < 8; ++w)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v += (double)sred[w][16 * q + t - 256];
+        float* dst = s + 16 * I + (t - 256);
+        *dst = (float)((double)*dst + v);
+    }
+}
+}  // namespace
+
+bool cov_few_rows_applies(const fw_conv_desc* d, fw_dtype dt, fw_layout lay) {
+    if (!d || d->form != FW_COV_FORM_AUTO || d->kh != 1 || d->kw != 1 || d->pad != 0) return false;
+    const bool single = d->H == 1 && d->W == 1;
+    if (!single && (d->stride != 1 || lay == FW_LAYOUT_NCHW)) return false;
+    const long long n_rows = (long long)d->B * d->H * d->W, M = d->Cin;
+    // Measured against the general forms (us, this form first).  float32: 7 / 15 at 512 rows x 512 features, 25 / 34 at
+    // 1024 x 1024, 48 / 67 at 512 x 2048, 94 / 99 at 1024 x 2048.  bfloat16, whose general form multiplies sixteen times
+    // faster: 7 / 21 at 512 x 512, 26 / 28 at 1024 x 1024, 29 / 28 at 2048 x 768, 33 / 20 at 64 x 2048.
+    if (n_rows > 2048) return false;
+    return dt == FW_BF16 ? M <= 1024 && n_rows * M * M <= (1ll << 30) : M <= 2048 && n_rows * M * M <= (1ll << 31);
+}
+
+bool cov_few_rows_plan(const fw_conv_desc* d, fw_dtype dt, fw_layout lay, fw_cov_plan* plan) {
+    if (!cov_few_rows_applies(d, dt, lay)) return false;
+    const long long nb = (d->Cin + 15) / 16;
+    plan->workgroups = (int)(nb * (nb + 1) / 2); plan->ranges = 1;
+    plan->mfma_flops_issued = 2.0 * 256.0 * (double)plan->workgroups * (double)align_up((size_t)d->B * d->H * d->W, 256);
+    return true;
+}
+
+fw_status cov_few_rows_accumulate(const void* X, fw_dtype dt, const fw_conv_desc* d, float* A, float* s, hipStream_t st) {
+    const int n_rows = d->B * d->H * d->W, M = d->Cin, nb = (M + 15) / 16;
+    const dim3 grid(nb * (nb + 1) / 2), blk(512);
+    if (dt == FW_BF16) hipLaunchKernelGGL(cov_few_rows_kernel<true>, grid, blk, 0, st, X, n_rows, M, A, s);
+    else hipLaunchKernelGGL(cov_few_rows_kernel<false>, grid, blk, 0, st, X, n_rows, M, A, s);
+    FW_LAUNCH_CHECK();
+    return FW_OK;
+}
+
 }  // namespace fw

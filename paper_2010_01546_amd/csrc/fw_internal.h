@@ -132,6 +132,10 @@ bool cov_skinny_plan(const fw_conv_desc* d, fw_layout lay, fw_cov_plan* plan);
 fw_status cov_skinny_accumulate(const void* X, fw_dtype dt, fw_layout lay, const fw_conv_desc* d, float* A, float* s, void* ws,
                                 size_t ws_bytes, hipStream_t st);
 
+bool cov_few_rows_applies(const fw_conv_desc* d, fw_dtype dt, fw_layout lay);
+bool cov_few_rows_plan(const fw_conv_desc* d, fw_dtype dt, fw_layout lay, fw_cov_plan* plan);
+fw_status cov_few_rows_accumulate(const void* X, fw_dtype dt, const fw_conv_desc* d, float* A, float* s, hipStream_t st);
+
 // ---- cov_bf16.hip
 bool cov_bf16_plan(const fw_conv_desc* d, fw_layout lay, fw_cov_plan* plan);
 size_t cov_bf16_workspace_bytes(const fw_conv_desc* d, fw_layout lay);

@@ -4,7 +4,7 @@ import pytest
 import torch
 
 import workloads as wl
-from gpu_common import (b, lower, oracle_rows, ora, relF, run_cov, run_finalize, workspace, DEV)
+from gpu_common import (b, dev, lower, oracle_rows, ora, relF, run_cov, run_finalize, workspace, DEV)
 
 pytestmark = pytest.mark.gpu
 
@@ -130,6 +130,27 @@ def test_few_features_many_rows(n_rows, M, dtype):
 def test_pointwise_windows(B, Cin, H, W, stride, layout, dtype):
     """1x1 windows (the per-channel variant, shortcut convolutions): strided pixel subsets of a channels-last tensor."""
     check_layer(wl.small_conv(B + Cin, B, Cin, H, W, 1, stride, 0, 8, dtype=dtype), layout)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("n_rows,M", [(1, 1), (3, 15), (4, 17), (31, 16), (33, 48), (255, 65), (256, 33), (257, 64), (2047, 50), (2048, 129), (300, 1001)])
+def test_few_rows_in_one_launch(n_rows, M, dtype):
+    """Tiles of 16 features, groups of 4 rows, batches of 256 rows: full, ragged and single; the general form (asked for by
+    its name) has to agree as well, up to the order of the sums (float32 accumulation: sqrt(rows) 2^-24 and a few ulp)."""
+    rng = np.random.default_rng(7 * n_rows + M)
+    x = rng.standard_normal((n_rows, M)).astype(np.float32) + 0.5
+    X = dev(x).to(torch.bfloat16) if dtype == "bf16" else dev(x)
+    x64 = X.double().cpu().numpy()
+    dt = b.FW_BF16 if dtype == "bf16" else b.FW_F32
+    A0 = np.tril(rng.standard_normal((M, M))).astype(np.float32)
+    for lay, d in ((b.FW_LAYOUT_ROWS, b.conv_desc(n_rows, M)), (b.FW_LAYOUT_NHWC, b.conv_desc(1, M, n_rows, 1, kh=1, kw=1)),
+                   (b.FW_LAYOUT_ROWS, b.conv_desc(n_rows, M, form=b.FW_COV_FORM_DIRECT))):
+        A, s = dev(A0), torch.ones(M, device="cuda:0")
+        b.fw_cov_accumulate(X, dt, lay, d, A, s, workspace(b.fw_workspace_bytes(b.FW_OP_COV_ACCUMULATE, M, 0, d, dt)))
+        torch.cuda.synchronize()
+        assert relF(np.tril(A.cpu().numpy()), np.tril(A0 + x64.T @ x64)) < 5e-6
+        assert relF(s.cpu().numpy(), 1.0 + x64.sum(0)) < 5e-6
+        assert np.array_equal(np.triu(A.cpu().numpy(), 1), np.triu(A0, 1))     # nothing above the diagonal is touched
 
 
 def test_accumulates_over_batches_and_two_block_recursion():
