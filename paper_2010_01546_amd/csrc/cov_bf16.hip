@@ -73,6 +73,7 @@ struct TileCore {
     int B, Bg, Cin, H, W, Hp, Wp, kh, kw, stride, pad, Ho, Wo;
     int layout;
     int n_units, nchunks, chunks_per_split, nsplit;
+    int sym;      // all features in one tile: cov_bf16_sym_kernel
     int direct;   // one range per tile and external order == internal order: tiles are added straight into A
     int bg_chunks, bg_per_chunk;   // the pre-pass deals the image groups to this many thread groups
     int zero_off;                  // 16-byte element of P that is always zero (target of masked-off loads)
@@ -101,26 +102,15 @@ __host__ __device__ inline int cols_of_row(int I, int tr, int tc, int ncb) {
 
 typedef unsigned short u16;
 
-// ---- pre-pass: pack 8 images per 16 bytes, zero border; per-pixel sums for the column sums ----------------------
-// One thread per (chunk of image groups, padded pixel, channel); it walks its image groups, so the sum it leaves in
-// S8[chunk][yp][xp][c] has a fixed order of additions.
-// The first row of workgroups also writes the unit table: offset (in 16-byte elements) of the top-left tap of every
-// unit, -1 for the padding up to a whole number of chunks.
-// SPLIT: the source is a float32 tensor with g.Cin / 2 channels; packed channel c < Cin / 2 takes hi = bf16(x) of source
-// channel c, packed channel Cin / 2 + c takes lo = bf16(x - hi) (the split form of float32 moments, see cov.hip).
-template <bool SHIFT, bool SPLIT>
-__global__ __launch_bounds__(256) void pack_images_kernel(const void* __restrict__ Xv, std::conditional_t<SHIFT, TileGeom, TileCore> g,
-                                                          uint4* __restrict__ P,
-                                                          float* __restrict__ S8, int* __restrict__ utab) {
-    const u16* __restrict__ X = reinterpret_cast<const u16*>(Xv);
-    const float* __restrict__ Xf = reinterpret_cast<const float*>(Xv);
-    const int per_img = g.Hp * g.Wp * g.Cin;
-    const int e = blockIdx.x * 256 + threadIdx.x;
-    const int chunk = blockIdx.y;
-    if (blockIdx.x == 0 && chunk == 0 && threadIdx.x < 16) P[g.zero_off + threadIdx.x] = make_uint4(0, 0, 0, 0);
-    if (chunk == 0 && !SHIFT) {
+// The zero element behind P and the unit table, by the nthreads threads e = 0 ..: offset (in 16-byte elements) of the
+// top-left tap of every unit, -1 for the padding up to a whole number of chunks.
+template <bool SHIFT>
+__device__ __forceinline__ void write_unit_table(const std::conditional_t<SHIFT, TileGeom, TileCore>& g, int e, int nthreads, uint4* __restrict__ P,
+                                                 int* __restrict__ utab) {
+    if (e < 16) P[g.zero_off + e] = make_uint4(0, 0, 0, 0);
+    if constexpr (!SHIFT) {
         const int npos = g.Ho * g.Wo;
-        for (int u = e; u < g.nchunks * KU; u += gridDim.x * 256) {
+        for (int u = e; u < g.nchunks * KU; u += nthreads) {
             int v = -1;
             if (u < g.n_units) {
                 const int bg = u / npos, p = u - bg * npos;
@@ -130,9 +120,9 @@ __global__ __launch_bounds__(256) void pack_images_kernel(const void* __restrict
             utab[u] = v;
         }
     }
-    if constexpr (SHIFT) if (chunk == 0) {
+    if constexpr (SHIFT) {
         // units are pixels (of an image group), listed region by region, every region padded to whole chunks
-        for (int u = e; u < g.nchunks * KU; u += gridDim.x * 256) {
+        for (int u = e; u < g.nchunks * KU; u += nthreads) {
             int ri = 0;
             for (int r = 0; r < g.nreg; ++r)
                 if (u >= g.reg[r].chunk_begin * KU) ri = r;
@@ -147,29 +137,44 @@ __global__ __launch_bounds__(256) void pack_images_kernel(const void* __restrict
             utab[u] = v;
         }
     }
+}
+
+// does any window cover padded pixel (yp, xp)?  (Not all do where the stride is larger than the window.)
+__device__ __forceinline__ bool pixel_is_covered(const TileCore& g, int yp, int xp) {
+    if (g.stride <= g.kh && g.stride <= g.kw) return true;
+    bool ry = false, rx = false;
+    for (int ky = 0; ky < g.kh; ++ky) { const int o = yp - ky; ry |= o >= 0 && o % g.stride == 0 && o / g.stride < g.Ho; }
+    for (int kx = 0; kx < g.kw; ++kx) { const int o = xp - kx; rx |= o >= 0 && o % g.stride == 0 && o / g.stride < g.Wo; }
+    return ry && rx;
+}
+
+// ---- pre-pass: pack 8 images per 16 bytes, zero border; per-pixel sums for the column sums ----------------------
+// One thread per (chunk of image groups, padded pixel, channel); it walks its image groups, so the sum it leaves in
+// S8[chunk][yp][xp][c] has a fixed order of additions.
+// The first row of workgroups also writes the unit table.
+// Channels-last sources: a wavefront reads and writes along the channels (NCHW has a kernel of its own below).
+// SPLIT: the source is a float32 tensor with g.Cin / 2 channels; packed channel c < Cin / 2 takes hi = bf16(x) of source
+// channel c, packed channel Cin / 2 + c takes lo = bf16(x - hi) (the split form of float32 moments, see cov.hip).
+template <bool SHIFT, bool SPLIT>
+__global__ __launch_bounds__(256) void pack_images_kernel(const void* __restrict__ Xv, std::conditional_t<SHIFT, TileGeom, TileCore> g,
+                                                          uint4* __restrict__ P,
+                                                          float* __restrict__ S8, int* __restrict__ utab) {
+    const u16* __restrict__ X = reinterpret_cast<const u16*>(Xv);
+    const float* __restrict__ Xf = reinterpret_cast<const float*>(Xv);
+    const int per_img = g.Hp * g.Wp * g.Cin;
+    const int e = blockIdx.x * 256 + threadIdx.x;
+    const int chunk = blockIdx.y;
+    if (chunk == 0) write_unit_table<SHIFT>(g, e, (int)gridDim.x * 256, P, utab);
     if (e >= per_img) return;
-    int c, xp, yp;
-    if (g.layout == FW_LAYOUT_NCHW) {  // walk the source along x for coalescing; the packed order stays [yp][xp][c]
-        xp = e % g.Wp; const int t = e / g.Wp;
-        yp = t % g.Hp; c = t / g.Hp;
-    } else {
-        c = e % g.Cin; const int t = e / g.Cin;
-        xp = t % g.Wp; yp = t / g.Wp;
-    }
-    // a padded pixel that no window touches (stride larger than the window) is neither read nor written
-    if (g.stride > g.kh || g.stride > g.kw) {
-        bool ry = false, rx = false;
-        for (int ky = 0; ky < g.kh; ++ky) { const int o = yp - ky; ry |= o >= 0 && o % g.stride == 0 && o / g.stride < g.Ho; }
-        for (int kx = 0; kx < g.kw; ++kx) { const int o = xp - kx; rx |= o >= 0 && o % g.stride == 0 && o / g.stride < g.Wo; }
-        if (!(ry && rx)) return;
-    }
+    const int c = e % g.Cin, pix = e / g.Cin, xp = pix % g.Wp, yp = pix / g.Wp;
+    if (!pixel_is_covered(g, yp, xp)) return;            // neither read nor written
     const int y = yp - g.py, x = xp - g.px;
     const bool inside = (unsigned)y < (unsigned)g.H && (unsigned)x < (unsigned)g.W;
     const int Csrc = SPLIT ? g.Cin >> 1 : g.Cin;            // channels of the source tensor
     const int csrc = SPLIT ? (c >= Csrc ? c - Csrc : c) : c;
     const bool lo_plane = SPLIT && c >= Csrc;
     const long long img_stride = (long long)Csrc * g.H * g.W;
-    const long long src0 = g.layout == FW_LAYOUT_NCHW ? ((long long)csrc * g.H + y) * g.W + x : ((long long)y * g.W + x) * Csrc + csrc;
+    const long long src0 = ((long long)y * g.W + x) * Csrc + csrc;
     const int dst0 = (yp * g.Wp + xp) * g.Cin + c;
     const int bg0 = chunk * g.bg_per_chunk, bg1 = min(g.Bg, bg0 + g.bg_per_chunk);
     float acc = 0.f;
@@ -201,6 +206,68 @@ __global__ __launch_bounds__(256) void pack_images_kernel(const void* __restrict
         P[(long long)bg * per_img + dst0] = o;
     }
     S8[(size_t)chunk * per_img + dst0] = acc;
+}
+
+// The same pre-pass for NCHW sources: the reads want to run along x, the writes along the channels.  A workgroup takes
+// PT padded pixels x CT channels (1024 elements, four per thread), reads each channel's pixels along the row, and turns
+// the tile in LDS, so that what it writes is whole runs of CT x 16 bytes (of the full tile where CT covers all channels).
+// The tile has two buffers: the next image group is read while this one is written.
+// Element by element (reads along x, writes scattered at Cin x 16 bytes) this pass took 59 us for 256 x 3 x 224 x 224 and
+// 58 us for 256 x 128 x 28 x 28, against 27 and 18 us at the rate of a copy.
+template <bool SHIFT, int CT>
+__global__ __launch_bounds__(256) void pack_nchw_kernel(const u16* __restrict__ X, std::conditional_t<SHIFT, TileGeom, TileCore> g,
+                                                        uint4* __restrict__ P, float* __restrict__ S8, int* __restrict__ utab) {
+    constexpr int PT = CT == 16 ? 64 : 256, NE = PT * CT / 256, LD = CT | 1;   // odd pitch: writes across pixels spread over the banks
+    __shared__ uint4 tile[2][PT * LD];
+    const int per_img = g.Hp * g.Wp * g.Cin, npix = g.Hp * g.Wp;
+    const int chunk = blockIdx.y;
+    if (chunk == 0) write_unit_table<SHIFT>(g, (int)blockIdx.x * 256 + (int)threadIdx.x, (int)gridDim.x * 256, P, utab);
+    const int ncb = (g.Cin + CT - 1) / CT;
+    const int pix0 = ((int)blockIdx.x / ncb) * PT, c0 = ((int)blockIdx.x % ncb) * CT;
+    const long long img_stride = (long long)g.Cin * g.H * g.W;
+    // element k of this thread on the reading side: pixel ri % PT, channel ri / PT; on the writing side: channel fastest
+    int src[NE];
+    float acc[NE];
+#pragma unroll
+    for (int k = 0; k < NE; ++k) {
+        const int ri = threadIdx.x + 256 * k, pix = pix0 + ri % PT, c = c0 + ri / PT;
+        const int yp = pix / g.Wp, xp = pix - yp * g.Wp, y = yp - g.py, x = xp - g.px;
+        const bool inside = pix < npix && c < g.Cin && (unsigned)y < (unsigned)g.H && (unsigned)x < (unsigned)g.W && pixel_is_covered(g, yp, xp);
+        src[k] = inside ? (c * g.H + y) * g.W + x : -1;
+        acc[k] = 0.f;
+    }
+    const int bg0 = chunk * g.bg_per_chunk, bg1 = min(g.Bg, bg0 + g.bg_per_chunk);
+    for (int bg = bg0; bg < bg1; ++bg) {
+        uint4* t = tile[(bg - bg0) & 1];
+        unsigned v[NE][8];
+#pragma unroll
+        for (int k = 0; k < NE; ++k)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[k][i] = X[src[k] >= 0 && bg * 8 + i < g.B ? (long long)(bg * 8 + i) * img_stride + src[k] : 0];
+#pragma unroll
+        for (int k = 0; k < NE; ++k) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                asm volatile("" : "+v"(v[k][i]));       // all loads are issued before the first is used
+                if (!(src[k] >= 0 && bg * 8 + i < g.B)) v[k][i] = 0u;
+                acc[k] += __uint_as_float(v[k][i] << 16);
+            }
+            const int ri = threadIdx.x + 256 * k;
+            t[(ri % PT) * LD + ri / PT] = make_uint4(v[k][0] | (v[k][1] << 16), v[k][2] | (v[k][3] << 16), v[k][4] | (v[k][5] << 16), v[k][6] | (v[k][7] << 16));
+        }
+        __syncthreads();
+        // (the buffer written next is not this one, and the barrier of that round comes before this one is written again)
+#pragma unroll
+        for (int k = 0; k < NE; ++k) {
+            const int wi = threadIdx.x + 256 * k, pix = pix0 + wi / CT, c = c0 + wi % CT;
+            if (pix < npix && c < g.Cin) P[(long long)bg * per_img + (long long)pix * g.Cin + c] = t[(wi / CT) * LD + wi % CT];
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < NE; ++k) {
+        const int ri = threadIdx.x + 256 * k, pix = pix0 + ri % PT, c = c0 + ri / PT;
+        if (pix < npix && c < g.Cin) S8[(size_t)chunk * per_img + (size_t)pix * g.Cin + c] = acc[k];
+    }
 }
 
 // internal feature (tap-major, channel-minor) -> offset inside a unit, external index m = (c*kh + ky)*kw + kx
@@ -428,6 +495,144 @@ __global__ __launch_bounds__(256) void cov_bf16_tile_kernel(const uint4* __restr
                 }
             }
         }
+    }
+}
+
+// ---- direct form, all features in one tile (M <= 256)
+// The tile kernel above brings a row panel and a column panel and multiplies the whole square; with a single tile both panels are
+// the same features and half the square is never read.  Here the panel is brought once and only the 32 x 32 MFMA tiles that
+// touch the lower triangle are multiplied: NB (NB + 1) / 2 of them for NB = ceil(M / 32) blocks.  Eight wavefronts: the four
+// wavefronts of a half share the tiles in runs of consecutive tiles (so a wavefront reads few distinct blocks; the lists are
+// compile-time, one copy of the loop per run), the two halves take one half of a chunk's units each and are added through LDS at the end.
+// A chunk is eight units, wavefront w brings unit w.  Ring protocol as above.
+// What bounds it is the loads into LDS (about 23 bytes per cycle and compute unit), which is why the second panel mattered:
+// 147 features, 3.2 M rows (7x7 stride 2 on 256 x 3 x 224 x 224): 208 us before.
+template <int NB>
+__global__ __launch_bounds__(512) void cov_bf16_sym_kernel(const uint4* __restrict__ P, const int* __restrict__ utab, TileCore g,
+                                                           float* __restrict__ part) {
+    constexpr int KS = 8;                          // units per chunk
+    constexpr int NG = (NB + 1) / 2;               // groups of 64 features
+    constexpr int ROW = 64 * NG, TC = 64 * NG;
+    constexpr int NST = NG == 4 ? 5 : 6;
+    constexpr int NT = NB * (NB + 1) / 2, TW = (NT + 3) / 4;
+    __shared__ uint4 pan[NST][KS][ROW];            // 48, 96, 144 or 160 KB
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wh = wave >> 2;
+    const int half = lane >> 5, l32 = lane & 31;
+    const int per_xcd = (g.nsplit + 7) / 8;        // an XCD works on neighbouring ranges
+    const int split = __builtin_amdgcn_readfirstlane(((int)blockIdx.x & 7) * per_xcd + ((int)blockIdx.x >> 3));
+    if (split >= g.nsplit || ((int)blockIdx.x >> 3) >= per_xcd) return;
+    const int c_begin = split * g.chunks_per_split;               // in chunks of KU units, a multiple of KS / KU
+    const int u_begin = c_begin * KU, u_end = min(g.nchunks, c_begin + g.chunks_per_split) * KU;
+    const int nchunks = (u_end - u_begin + KS - 1) / KS;
+
+    int off[NG];
+    unsigned okmask = 0;
+#pragma unroll
+    for (int k = 0; k < NG; ++k) {
+        const int f = 64 * k + lane;
+        const bool ok = f < g.M;
+        int ext_unused;
+        feat_map(ok ? f : 0, g, &off[k], &ext_unused);
+        okmask |= (ok ? 1u : 0u) << k;
+    }
+    int nb = -1;
+    auto fetch_base = [&](int c) { const int u = u_begin + c * KS + wave; nb = u < u_end ? utab[u] : -1; };
+    auto dma_one = [&](int stage, int k) {
+        const int idx = (nb >= 0 && ((okmask >> k) & 1u)) ? nb + off[k] : g.zero_off;
+        dma16(P + idx, &pan[stage][wave][64 * k]);
+    };
+    auto issue = [&](int stage) {
+#pragma unroll
+        for (int k = 0; k < NG; ++k) dma_one(stage, k);
+    };
+    auto run = [&](auto WQ) {
+        constexpr int W = decltype(WQ)::value;
+        constexpr int T0 = W * NT / 4, T1 = (W + 1) * NT / 4, N = T1 - T0;     // this wavefront's tiles, row-major in the triangle
+        auto row_of_tile = [](int t) constexpr { int a = 0; while ((a + 1) * (a + 2) / 2 <= t) ++a; return a; };
+        // blocks these tiles touch: rows A0 .. A1, columns 0 .. A1 at most
+        auto used = [&](int blk) constexpr {
+            for (int t = T0; t < T1; ++t) {
+                int a = 0;
+                while ((a + 1) * (a + 2) / 2 <= t) ++a;
+                if (a == blk || t - a * (a + 1) / 2 == blk) return true;
+            }
+            return false;
+        };
+        floatx16 acc[N > 0 ? N : 1];
+#pragma unroll
+        for (int t = 0; t < N; ++t)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[t][i] = 0.f;
+        bf16x8 fr[2][NB];
+        auto read_blk = [&](int stage, int ks, int set, int blk) {
+            fr[set][blk] = *reinterpret_cast<const bf16x8*>(&pan[stage][2 * (2 * wh + ks) + half][32 * blk + l32]);
+        };
+#pragma unroll
+        for (int i = 0; i < NST - 1; ++i) { fetch_base(i); issue(i); }
+        fetch_base(NST - 1);
+        FW_WAIT_VM((NST - 2) * NG);
+        __builtin_amdgcn_s_barrier();
+        FW_COMPILER_FENCE();
+        issue(NST - 1);
+#pragma unroll
+        for (int k = 0; k < NB; ++k) if (used(k)) read_blk(0, 0, 0, k);
+        int sc = 0;
+        for (int c = 0; c < nchunks; ++c) {
+            const int sn = sc == NST - 1 ? 0 : sc + 1;
+            fetch_base(c + NST);
+#pragma unroll
+            for (int k = 0; k < NB; ++k) if (used(k)) read_blk(sc, 1, 1, k);
+#pragma unroll
+            for (int t = 0; t < N; ++t) {
+                const int a = row_of_tile(T0 + t), b = T0 + t - a * (a + 1) / 2;
+                acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[0][a], fr[0][b], acc[t], 0, 0, 0);
+            }
+            FW_WAIT_LGKM0();
+            FW_WAIT_VM((NST - 2) * NG);
+            __builtin_amdgcn_s_barrier();
+            FW_COMPILER_FENCE();
+#pragma unroll
+            for (int k = 0; k < NB; ++k) if (used(k)) read_blk(sn, 0, 0, k);
+            issue(sc);
+#pragma unroll
+            for (int t = 0; t < N; ++t) {
+                const int a = row_of_tile(T0 + t), b = T0 + t - a * (a + 1) / 2;
+                acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[1][a], fr[1][b], acc[t], 0, 0, 0);
+            }
+            sc = sn;
+        }
+        FW_WAIT_VM(0);
+        FW_WAIT_LGKM0();
+        __syncthreads();
+        // second half of the units into LDS, added by the first half's wavefront with the same tiles
+        float* red = reinterpret_cast<float*>(&pan[0][0][0]) + (size_t)W * TW * 1024;
+        if (wh == 1) {
+#pragma unroll
+            for (int t = 0; t < N; ++t)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) red[(t * 16 + i) * 64 + lane] = acc[t][i];
+        }
+        __syncthreads();
+        if (wh == 0) {
+            float* dst = part + (size_t)split * (TC * TC);
+#pragma unroll
+            for (int t = 0; t < N; ++t) {
+                const int a = row_of_tile(T0 + t), b = T0 + t - a * (a + 1) / 2;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const int row = 32 * a + 8 * (i >> 2) + 4 * half + (i & 3), col = 32 * b + l32;
+                    dst[row * TC + col] = acc[t][i] + red[(t * 16 + i) * 64 + lane];
+                }
+            }
+        }
+    };
+    switch (wave & 3) {
+        case 0: run(std::integral_constant<int, 0>()); break;
+        case 1: run(std::integral_constant<int, 1>()); break;
+        case 2: run(std::integral_constant<int, 2>()); break;
+        default: run(std::integral_constant<int, 3>()); break;
     }
 }
 
@@ -858,9 +1063,23 @@ bool build_tile_geom(const fw_conv_desc* d, fw_layout lay, TileGeom* g) {
                 if (cost < best * 0.999) { best = cost; best_nrt = nrt; best_nct = nct; best_ns = ns; }
             }
         }
+    // All features in one tile: the symmetric kernel.  A chunk of eight units costs the larger of its loads (one panel) and
+    // its MFMAs (two wavefronts per SIMD, each half of the units).
+    g->sym = 0;
+    if (M <= 256) {
+        const int nb = M <= 64 ? 2 : (int)((M + 31) / 32), ng = (nb + 1) / 2, tc = 64 * ng;
+        const long long nch8 = (n_units + 7) / 8;
+        const double t_mfma = 2.0 * 2.0 * ((nb * (nb + 1) / 2 + 3) / 4) * 32.0 + 150.0, t_load = (double)tc * 8.0 * 16.0 / lds_load_rate;
+        const double t_chunk = (t_mfma > t_load ? t_mfma : t_load) / clk;
+        for (int ns = 1; ns <= 256 && ns <= nch8; ++ns) {
+            const double cost = (double)((nch8 + ns - 1) / ns) * t_chunk + (double)ns * tc * tc * 4.0 * 2.0 / bw;
+            if (cost < best * 0.999) { best = cost; best_nrt = best_nct = ng; best_ns = ns; g->sym = nb; }
+        }
+    }
     {
         // stride-1 windows: tap pairs with the same difference share their products (shift-correlation mode)
         TileGeom gs = *g;
+        gs.sym = 0;
         double cs = 0.0;
         if (lay != FW_LAYOUT_ROWS && make_shift_tile_geom(d, &gs, &cs) && (cs < best || d->form == FW_COV_FORM_SHIFT)) {
             const long long per_img = (long long)gs.Hp * gs.Wp * d->Cin;
@@ -877,7 +1096,12 @@ bool build_tile_geom(const fw_conv_desc* d, fw_layout lay, TileGeom* g) {
     g->ncb = (int)((M + g->tc - 1) / g->tc); g->nrb = (int)((M + g->tr - 1) / g->tr);
     g->ntiles = 0;
     for (int I = 0; I < g->nrb; ++I) g->ntiles += cols_of_row(I, g->tr, g->tc, g->ncb);
-    g->chunks_per_split = (g->nchunks + best_ns - 1) / best_ns;
+    if (g->sym) {                                      // whole chunks of eight units
+        g->nchunks = (g->nchunks + 1) / 2 * 2;
+        g->chunks_per_split = (g->nchunks / 2 + best_ns - 1) / best_ns * 2;
+    } else {
+        g->chunks_per_split = (g->nchunks + best_ns - 1) / best_ns;
+    }
     g->nsplit = (g->nchunks + g->chunks_per_split - 1) / g->chunks_per_split;
     // the pre-pass wants about half a million threads: split the image groups when one image gives fewer
     {
@@ -889,7 +1113,7 @@ bool build_tile_geom(const fw_conv_desc* d, fw_layout lay, TileGeom* g) {
         g->bg_chunks = (g->Bg + g->bg_per_chunk - 1) / g->bg_per_chunk;
         g->zero_off = (int)packed;
     }
-    g->direct = (g->nsplit == 1 && ident) ? 1 : 0;
+    g->direct = (g->nsplit == 1 && ident && !g->sym) ? 1 : 0;
     return true;
 }
 
@@ -941,6 +1165,7 @@ bool cov_bf16_plan(const fw_conv_desc* d, fw_layout lay, fw_cov_plan* plan) {
         plan->covered_pixels += (long long)g.B * g.reg[r].rh * g.reg[r].rw * ((g.reg[r].colmask != 0) + (g.gx == 2 && g.reg[r].colmask2 != 0));
     // every tile is multiplied over all chunks of its ranges: 32 reduction entries (4 units of 8 images) per chunk
     plan->mfma_flops_issued = 2.0 * (double)g.ntiles * g.tr * g.tc * 32.0 * (double)g.nchunks;
+    if (g.sym) plan->mfma_flops_issued = 2.0 * (g.sym * (g.sym + 1) / 2) * 1024.0 * 32.0 * (double)g.nchunks;
     if (g.shift) {   // border regions skip the column tiles whose differences they never use
         double chunk_tiles = 0.0;
         for (int r = 0; r < g.nreg; ++r)
@@ -973,7 +1198,24 @@ fw_status cov_bf16_accumulate(const void* X, fw_layout lay, const fw_conv_desc* 
     const int per_img = g.Hp * g.Wp * g.Cin;
     const TileCore& core = g;   // the direct form's kernels take the geometry without the regions
     const dim3 pgrid((per_img + 255) / 256, g.bg_chunks);
-    if (g.shift && split_f32) hipLaunchKernelGGL((pack_images_kernel<true, true>), pgrid, dim3(256), 0, st, X, g, P, S8, utab);
+    if (lay == FW_LAYOUT_NCHW) {        // (a float32 tensor comes here channels-last)
+        if (split_f32) return FW_ERR_UNSUPPORTED;
+        const u16* x = reinterpret_cast<const u16*>(X);
+        const int npix = g.Hp * g.Wp;
+        const dim3 g16(((npix + 63) / 64) * ((g.Cin + 15) / 16), g.bg_chunks), g4(((npix + 255) / 256) * ((g.Cin + 3) / 4), g.bg_chunks);
+        const dim3 g3((npix + 255) / 256, g.bg_chunks);
+        if (g.Cin == 3) {
+            if (g.shift) hipLaunchKernelGGL((pack_nchw_kernel<true, 3>), g3, dim3(256), 0, st, x, g, P, S8, utab);
+            else hipLaunchKernelGGL((pack_nchw_kernel<false, 3>), g3, dim3(256), 0, st, x, core, P, S8, utab);
+        } else if (g.Cin <= 8) {
+            if (g.shift) hipLaunchKernelGGL((pack_nchw_kernel<true, 4>), g4, dim3(256), 0, st, x, g, P, S8, utab);
+            else hipLaunchKernelGGL((pack_nchw_kernel<false, 4>), g4, dim3(256), 0, st, x, core, P, S8, utab);
+        } else {
+            if (g.shift) hipLaunchKernelGGL((pack_nchw_kernel<true, 16>), g16, dim3(256), 0, st, x, g, P, S8, utab);
+            else hipLaunchKernelGGL((pack_nchw_kernel<false, 16>), g16, dim3(256), 0, st, x, core, P, S8, utab);
+        }
+    }
+    else if (g.shift && split_f32) hipLaunchKernelGGL((pack_images_kernel<true, true>), pgrid, dim3(256), 0, st, X, g, P, S8, utab);
     else if (g.shift) hipLaunchKernelGGL((pack_images_kernel<true, false>), pgrid, dim3(256), 0, st, X, g, P, S8, utab);
     else if (split_f32) hipLaunchKernelGGL((pack_images_kernel<false, true>), pgrid, dim3(256), 0, st, X, core, P, S8, utab);
     else hipLaunchKernelGGL((pack_images_kernel<false, false>), pgrid, dim3(256), 0, st, X, core, P, S8, utab);
@@ -984,6 +1226,19 @@ fw_status cov_bf16_accumulate(const void* X, fw_layout lay, const fw_conv_desc* 
         case 4: FW_TILE_LAUNCH(4, 4, true, g); break;
         case 3: FW_TILE_LAUNCH(3, 4, true, g); break;
         default: FW_TILE_LAUNCH(2, 4, true, g); break;
+    }
+    else if (g.sym) {
+#define FW_SYM_LAUNCH(N) hipLaunchKernelGGL(cov_bf16_sym_kernel<N>, dim3((g.nsplit + 7) / 8 * 8), dim3(512), 0, st, P, utab, core, part)
+        switch (g.sym) {
+            case 2: FW_SYM_LAUNCH(2); break;
+            case 3: FW_SYM_LAUNCH(3); break;
+            case 4: FW_SYM_LAUNCH(4); break;
+            case 5: FW_SYM_LAUNCH(5); break;
+            case 6: FW_SYM_LAUNCH(6); break;
+            case 7: FW_SYM_LAUNCH(7); break;
+            default: FW_SYM_LAUNCH(8); break;
+        }
+#undef FW_SYM_LAUNCH
     }
     else switch (g.nrt * 10 + g.nct) {
         case 44: FW_TILE_LAUNCH(4, 4, false, core); break;

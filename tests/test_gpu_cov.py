@@ -153,6 +153,27 @@ def test_few_rows_in_one_launch(n_rows, M, dtype):
         assert np.array_equal(np.triu(A.cpu().numpy(), 1), np.triu(A0, 1))     # nothing above the diagonal is touched
 
 
+@pytest.mark.parametrize("Cin", [1, 3, 4, 5, 8, 9, 16, 17, 40])
+@pytest.mark.parametrize("B,H,W,k,stride,pad", [(9, 7, 11, 3, 1, 1), (17, 9, 8, 2, 3, 0), (8, 23, 19, 7, 2, 3), (3, 5, 5, 3, 2, 1)])
+def test_nchw_tensors_give_the_sums_of_their_channels_last_copies(B, Cin, H, W, k, stride, pad):
+    """bfloat16 NCHW input goes through a packing kernel of its own (tiles of 3, 4 or 16 channels, 64 or 256 pixels); from there
+    on both layouts run the same kernels on the same numbers, so the results are equal bit by bit."""
+    g = torch.Generator().manual_seed(Cin * 100 + H)
+    x = torch.randn(B, Cin, H, W, generator=g).to(torch.bfloat16)
+    d = b.conv_desc(B, Cin, H, W, kh=k, kw=k, stride=stride, pad=pad)
+    M = Cin * k * k
+    ws = workspace(b.fw_workspace_bytes(b.FW_OP_COV_ACCUMULATE, M, 0, d, b.FW_BF16))
+    got = []
+    for lay, X in ((b.FW_LAYOUT_NCHW, x), (b.FW_LAYOUT_NHWC, x.permute(0, 2, 3, 1).contiguous())):
+        A, s = torch.zeros(M, M, device=DEV), torch.zeros(M, device=DEV)
+        b.fw_cov_accumulate(X.to(DEV), b.FW_BF16, lay, d, A, s, ws)
+        torch.cuda.synchronize()
+        got.append((A.cpu().numpy(), s.cpu().numpy()))
+    assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
+    rows = ora.patch_rows(x.permute(0, 2, 3, 1).float().numpy(), B, Cin, H, W, k, k, stride, pad).astype(np.float64)
+    assert relF(np.tril(got[0][0]), np.tril(rows.T @ rows)) < RAW_TOL["bf16"]
+
+
 def test_accumulates_over_batches_and_two_block_recursion():
     """Two batches added into one block equal the block of their union; the second block follows eqs. (vmuxi), (vPhixi)."""
     L0 = wl.small_conv(1, 3, 8, 6, 6, 3, 1, 1, 8)
