@@ -73,6 +73,7 @@ struct TileCore {
     int B, Bg, Cin, H, W, Hp, Wp, kh, kw, stride, pad, Ho, Wo;
     int layout;
     int n_units, nchunks, chunks_per_split, nsplit;
+    int sym;      // all features in one tile: cov_bf16_sym_kernel
     int direct;   // one range per tile and external order == internal order: tiles are added straight into A
     int bg_chunks, bg_per_chunk;   // the pre-pass deals the image groups to this many thread groups
     int zero_off;                  // 16-byte element of P that is always zero (target of masked-off loads)
@@ -494,6 +495,147 @@ __global__ __launch_bounds__(256) void cov_bf16_tile_kernel(const uint4* __restr
                 }
             }
         }
+    }
+}
+
+// ---- direct form, all features in one tile (M <= 224)
+// The tile kernel above brings a row panel and a column panel and multiplies the whole square; with a single tile both panels are
+// the same features and half the square is never read.  Here the panel is brought once and only the 32 x 32 MFMA tiles that
+// touch the lower triangle are multiplied: NB (NB + 1) / 2 of them for NB = ceil(M / 32) blocks.  Eight wavefronts: the four
+// wavefronts of a half share the tiles in runs of consecutive tiles (so a wavefront reads few distinct blocks; the lists are
+// compile-time, one copy of the loop per run), the two halves take one half of a chunk's units each and are added through LDS at the end.
+// A chunk is eight units, wavefront w brings unit w.  Ring protocol as above.
+// What bounds it is the loads into LDS (about 23 bytes per cycle and compute unit), which is why the second panel mattered.
+// Moments of 147 features over 3.2 M rows (7x7 stride 2 on 256 x 3 x 224 x 224, channels-last): 247 us -> 156 us, of which
+// the contraction 204 us -> 120 us; 27 features over 262144 rows: 35 us -> 25 us; 160 features over 200704 rows: 62 us -> 54 us;
+// 224 features: 80 us -> 75 us.  Eight blocks (256 features) lost 1 % (84.0 us against 84.8 us) and keep the general form.
+// block row of tile t of the triangle, in row-major order (t < 36); block column t - a (a + 1) / 2
+__host__ __device__ constexpr int row_of_tile(int t) { return t < 1 ? 0 : t < 3 ? 1 : t < 6 ? 2 : t < 10 ? 3 : t < 15 ? 4 : t < 21 ? 5 : t < 28 ? 6 : 7; }
+// bit per block that tiles t0 .. t1 - 1 touch
+__host__ __device__ constexpr unsigned blocks_of_tiles(int t0, int t1) {
+    unsigned m = 0;
+    for (int t = t0; t < t1; ++t) m |= (1u << row_of_tile(t)) | (1u << (t - row_of_tile(t) * (row_of_tile(t) + 1) / 2));
+    return m;
+}
+
+template <int NB>
+__global__ __launch_bounds__(512) void cov_bf16_sym_kernel(const uint4* __restrict__ P, const int* __restrict__ utab, TileCore g,
+                                                           float* __restrict__ part) {
+    constexpr int KS = 8;                          // units per chunk
+    constexpr int NG = (NB + 1) / 2;               // groups of 64 features
+    constexpr int ROW = 64 * NG, TC = 64 * NG;
+    constexpr int NST = NG == 4 ? 5 : 6;
+    constexpr int NT = NB * (NB + 1) / 2, TW = (NT + 3) / 4;
+    __shared__ uint4 pan[NST][KS][ROW];            // 48, 96, 144 or 160 KB
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wh = wave >> 2;
+    const int half = lane >> 5, l32 = lane & 31;
+    const int per_xcd = (g.nsplit + 7) / 8;        // an XCD works on neighbouring ranges
+    const int split = __builtin_amdgcn_readfirstlane(((int)blockIdx.x & 7) * per_xcd + ((int)blockIdx.x >> 3));
+    if (split >= g.nsplit || ((int)blockIdx.x >> 3) >= per_xcd) return;
+    const int c_begin = split * g.chunks_per_split;               // in chunks of KU units, a multiple of KS / KU
+    const int u_begin = c_begin * KU, u_end = min(g.nchunks, c_begin + g.chunks_per_split) * KU;
+    const int nchunks = (u_end - u_begin + KS - 1) / KS;
+
+    int off[NG];
+    unsigned okmask = 0;
+#pragma unroll
+    for (int k = 0; k < NG; ++k) {
+        const int f = 64 * k + lane;
+        const bool ok = f < g.M;
+        int ext_unused;
+        feat_map(ok ? f : 0, g, &off[k], &ext_unused);
+        okmask |= (ok ? 1u : 0u) << k;
+    }
+    int nb = -1;
+    auto fetch_base = [&](int c) { const int u = u_begin + c * KS + wave; nb = u < u_end ? utab[u] : -1; };
+    auto dma_one = [&](int stage, int k) {
+        const int idx = (nb >= 0 && ((okmask >> k) & 1u)) ? nb + off[k] : g.zero_off;
+        dma16(P + idx, &pan[stage][wave][64 * k]);
+    };
+    auto issue = [&](int stage) {
+#pragma unroll
+        for (int k = 0; k < NG; ++k) dma_one(stage, k);
+    };
+    auto run = [&](auto WQ) {
+        constexpr int W = decltype(WQ)::value;
+        constexpr int T0 = W * NT / 4, T1 = (W + 1) * NT / 4, N = T1 - T0;     // this wavefront's tiles, row-major in the triangle
+        constexpr unsigned USED = blocks_of_tiles(T0, T1);
+        auto used = [](int blk) { return ((USED >> blk) & 1u) != 0; };
+        floatx16 acc[N > 0 ? N : 1];
+#pragma unroll
+        for (int t = 0; t < N; ++t)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[t][i] = 0.f;
+        bf16x8 fr[2][NB];
+        auto read_blk = [&](int stage, int ks, int set, int blk) {
+            fr[set][blk] = *reinterpret_cast<const bf16x8*>(&pan[stage][2 * (2 * wh + ks) + half][32 * blk + l32]);
+        };
+#pragma unroll
+        for (int i = 0; i < NST - 1; ++i) { fetch_base(i); issue(i); }
+        fetch_base(NST - 1);
+        FW_WAIT_VM((NST - 2) * NG);
+        __builtin_amdgcn_s_barrier();
+        FW_COMPILER_FENCE();
+        issue(NST - 1);
+#pragma unroll
+        for (int k = 0; k < NB; ++k) if (used(k)) read_blk(0, 0, 0, k);
+        int sc = 0;
+        for (int c = 0; c < nchunks; ++c) {
+            const int sn = sc == NST - 1 ? 0 : sc + 1;
+            fetch_base(c + NST);
+#pragma unroll
+            for (int k = 0; k < NB; ++k) if (used(k)) read_blk(sc, 1, 1, k);
+#pragma unroll
+            for (int t = 0; t < N; ++t) {
+                const int a = row_of_tile(T0 + t), b = T0 + t - a * (a + 1) / 2;
+                acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[0][a], fr[0][b], acc[t], 0, 0, 0);
+            }
+            FW_WAIT_LGKM0();
+            FW_WAIT_VM((NST - 2) * NG);
+            __builtin_amdgcn_s_barrier();
+            FW_COMPILER_FENCE();
+#pragma unroll
+            for (int k = 0; k < NB; ++k) if (used(k)) read_blk(sn, 0, 0, k);
+            issue(sc);
+#pragma unroll
+            for (int t = 0; t < N; ++t) {
+                const int a = row_of_tile(T0 + t), b = T0 + t - a * (a + 1) / 2;
+                acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[1][a], fr[1][b], acc[t], 0, 0, 0);
+            }
+            sc = sn;
+        }
+        FW_WAIT_VM(0);
+        FW_WAIT_LGKM0();
+        __syncthreads();
+        // second half of the units into LDS, added by the first half's wavefront with the same tiles
+        float* red = reinterpret_cast<float*>(&pan[0][0][0]) + (size_t)W * TW * 1024;
+        if (wh == 1) {
+#pragma unroll
+            for (int t = 0; t < N; ++t)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) red[(t * 16 + i) * 64 + lane] = acc[t][i];
+        }
+        __syncthreads();
+        if (wh == 0) {
+            float* dst = part + (size_t)split * (TC * TC);
+#pragma unroll
+            for (int t = 0; t < N; ++t) {
+                const int a = row_of_tile(T0 + t), b = T0 + t - a * (a + 1) / 2;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const int row = 32 * a + 8 * (i >> 2) + 4 * half + (i & 3), col = 32 * b + l32;
+                    dst[row * TC + col] = acc[t][i] + red[(t * 16 + i) * 64 + lane];
+                }
+            }
+        }
+    };
+    switch (wave & 3) {
+        case 0: run(std::integral_constant<int, 0>()); break;
+        case 1: run(std::integral_constant<int, 1>()); break;
+        case 2: run(std::integral_constant<int, 2>()); break;
+        default: run(std::integral_constant<int, 3>()); break;
     }
 }
 
@@ -924,9 +1066,24 @@ bool build_tile_geom(const fw_conv_desc* d, fw_layout lay, TileGeom* g) {
                 if (cost < best * 0.999) { best = cost; best_nrt = nrt; best_nct = nct; best_ns = ns; }
             }
         }
+    // All features in one tile (up to 224, see the measurements at the kernel): the symmetric kernel.  A chunk of eight units costs the larger of its loads (one panel) and
+    // its MFMAs (two wavefronts per SIMD, each half of the units).
+    g->sym = 0;
+    if (M <= 224) {
+        const int nb = M <= 64 ? 2 : (int)((M + 31) / 32), ng = (nb + 1) / 2, tc = 64 * ng;
+        const long long nch8 = (n_units + 7) / 8;
+        const double t_mfma = 2.0 * 2.0 * ((nb * (nb + 1) / 2 + 3) / 4) * 32.0 + 150.0, t_load = (double)tc * 8.0 * 16.0 / lds_load_rate;
+        const double t_chunk = (t_mfma > t_load ? t_mfma : t_load) / clk;
+        for (int ns = 1; ns <= 256 && ns <= nch8; ++ns) {
+            const double cost = (double)((nch8 + ns - 1) / ns) * t_chunk + (double)ns * tc * tc * 4.0 * 2.0 / bw +
+                                (ident && best_ns == 1 && !g->sym ? 5e-6 : 0.0);   // a launch more than tiles added straight into A
+            if (cost < best * 0.999) { best = cost; best_nrt = best_nct = ng; best_ns = ns; g->sym = nb; }
+        }
+    }
     {
         // stride-1 windows: tap pairs with the same difference share their products (shift-correlation mode)
         TileGeom gs = *g;
+        gs.sym = 0;
         double cs = 0.0;
         if (lay != FW_LAYOUT_ROWS && make_shift_tile_geom(d, &gs, &cs) && (cs < best || d->form == FW_COV_FORM_SHIFT)) {
             const long long per_img = (long long)gs.Hp * gs.Wp * d->Cin;
@@ -943,7 +1100,12 @@ bool build_tile_geom(const fw_conv_desc* d, fw_layout lay, TileGeom* g) {
     g->ncb = (int)((M + g->tc - 1) / g->tc); g->nrb = (int)((M + g->tr - 1) / g->tr);
     g->ntiles = 0;
     for (int I = 0; I < g->nrb; ++I) g->ntiles += cols_of_row(I, g->tr, g->tc, g->ncb);
-    g->chunks_per_split = (g->nchunks + best_ns - 1) / best_ns;
+    if (g->sym) {                                      // whole chunks of eight units
+        g->nchunks = (g->nchunks + 1) / 2 * 2;
+        g->chunks_per_split = (g->nchunks / 2 + best_ns - 1) / best_ns * 2;
+    } else {
+        g->chunks_per_split = (g->nchunks + best_ns - 1) / best_ns;
+    }
     g->nsplit = (g->nchunks + g->chunks_per_split - 1) / g->chunks_per_split;
     // the pre-pass wants about half a million threads: split the image groups when one image gives fewer
     {
@@ -955,7 +1117,7 @@ bool build_tile_geom(const fw_conv_desc* d, fw_layout lay, TileGeom* g) {
         g->bg_chunks = (g->Bg + g->bg_per_chunk - 1) / g->bg_per_chunk;
         g->zero_off = (int)packed;
     }
-    g->direct = (g->nsplit == 1 && ident) ? 1 : 0;
+    g->direct = (g->nsplit == 1 && ident && !g->sym) ? 1 : 0;
     return true;
 }
 
@@ -1007,6 +1169,7 @@ bool cov_bf16_plan(const fw_conv_desc* d, fw_layout lay, fw_cov_plan* plan) {
         plan->covered_pixels += (long long)g.B * g.reg[r].rh * g.reg[r].rw * ((g.reg[r].colmask != 0) + (g.gx == 2 && g.reg[r].colmask2 != 0));
     // every tile is multiplied over all chunks of its ranges: 32 reduction entries (4 units of 8 images) per chunk
     plan->mfma_flops_issued = 2.0 * (double)g.ntiles * g.tr * g.tc * 32.0 * (double)g.nchunks;
+    if (g.sym) plan->mfma_flops_issued = 2.0 * (g.sym * (g.sym + 1) / 2) * 1024.0 * 32.0 * (double)g.nchunks;
     if (g.shift) {   // border regions skip the column tiles whose differences they never use
         double chunk_tiles = 0.0;
         for (int r = 0; r < g.nreg; ++r)
@@ -1067,6 +1230,18 @@ fw_status cov_bf16_accumulate(const void* X, fw_layout lay, const fw_conv_desc* 
         case 4: FW_TILE_LAUNCH(4, 4, true, g); break;
         case 3: FW_TILE_LAUNCH(3, 4, true, g); break;
         default: FW_TILE_LAUNCH(2, 4, true, g); break;
+    }
+    else if (g.sym) {
+#define FW_SYM_LAUNCH(N) hipLaunchKernelGGL(cov_bf16_sym_kernel<N>, dim3((g.nsplit + 7) / 8 * 8), dim3(512), 0, st, P, utab, core, part)
+        switch (g.sym) {
+            case 2: FW_SYM_LAUNCH(2); break;
+            case 3: FW_SYM_LAUNCH(3); break;
+            case 4: FW_SYM_LAUNCH(4); break;
+            case 5: FW_SYM_LAUNCH(5); break;
+            case 6: FW_SYM_LAUNCH(6); break;
+            default: FW_SYM_LAUNCH(7); break;
+        }
+#undef FW_SYM_LAUNCH
     }
     else switch (g.nrt * 10 + g.nct) {
         case 44: FW_TILE_LAUNCH(4, 4, false, core); break;

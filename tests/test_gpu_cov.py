@@ -174,6 +174,29 @@ def test_nchw_tensors_give_the_sums_of_their_channels_last_copies(B, Cin, H, W, 
     assert relF(np.tril(got[0][0]), np.tril(rows.T @ rows)) < RAW_TOL["bf16"]
 
 
+@pytest.mark.parametrize("lay", [b.FW_LAYOUT_NHWC, b.FW_LAYOUT_NHWC_KKC])
+@pytest.mark.parametrize("Cin,kh,kw", [(3, 3, 3), (7, 3, 3), (8, 3, 3), (11, 3, 3), (16, 4, 2), (15, 3, 3), (16, 3, 3), (18, 3, 3), (21, 3, 3), (23, 3, 3),
+                                       (56, 2, 2), (25, 3, 3)])
+@pytest.mark.parametrize("B,H,W", [(9, 6, 5), (40, 33, 31)])
+def test_all_features_in_one_tile(B, H, W, Cin, kh, kw, lay):
+    """Up to 224 features the direct form multiplies the blocks of the triangle only (27 .. 224 features: every count of 32-feature
+    blocks, full and ragged; 225 is the first beyond).  Whole numbers whose sums stay below 2^24: every order of
+    additions gives the same result, so the sums are exact."""
+    g = torch.Generator().manual_seed(Cin)
+    x = torch.randint(-3, 4, (B, H, W, Cin), generator=g).to(torch.bfloat16)
+    d = b.conv_desc(B, Cin, H, W, kh=kh, kw=kw, stride=2, pad=1)
+    M = Cin * kh * kw
+    ws = workspace(b.fw_workspace_bytes(b.FW_OP_COV_ACCUMULATE, M, 0, d, b.FW_BF16))
+    A, s = torch.full((M, M), 5.0, device=DEV), torch.full((M,), 2.0, device=DEV)
+    b.fw_cov_accumulate(x.to(DEV), b.FW_BF16, lay, d, A, s, ws)
+    torch.cuda.synchronize()
+    rows = ora.patch_rows(x.float().numpy(), B, Cin, H, W, kh, kw, 2, 1).astype(np.float64)
+    if lay == b.FW_LAYOUT_NHWC_KKC:
+        rows = rows.reshape(-1, Cin, kh * kw).transpose(0, 2, 1).reshape(-1, M)
+    assert np.array_equal(A.cpu().numpy(), np.tril(rows.T @ rows) + 5.0)           # nothing above the diagonal is touched
+    assert np.array_equal(s.cpu().numpy(), rows.sum(0) + 2.0)
+
+
 def test_accumulates_over_batches_and_two_block_recursion():
     """Two batches added into one block equal the block of their union; the second block follows eqs. (vmuxi), (vPhixi)."""
     L0 = wl.small_conv(1, 3, 8, 6, 6, 3, 1, 1, 8)
