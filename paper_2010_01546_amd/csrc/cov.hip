@@ -24,6 +24,7 @@ constexpr int KT_F32 = 16;     // patch rows per staged chunk, float32 path
 
 struct CovGeom {
     int n_rows, M, nb;
+    int Cr, Mr;               // the caller's channels and features: fewer than Cin and M where the tensor was padded with zero channels
     int B, Cin, H, W, kh, kw, stride, pad, Ho, Wo;
     int layout;
     int rows_per_split, nsplit;
@@ -95,7 +96,7 @@ inline void item_counts(int nb, int* n0, int* n1, int* n2) {
     *n2 = (nb & 1) ? (h + 1 + 3) / 4 : 0;
 }
 
-// internal feature index -> (offset inside a patch, ky, kx, external feature index)
+// internal feature index -> (offset inside a patch, ky, kx, external feature index, -1 for a padded channel)
 struct Feat { int off, ky, kx, ext; };
 __device__ __forceinline__ Feat feat_of(int fi, const CovGeom& g) {
     Feat f;
@@ -109,7 +110,7 @@ __device__ __forceinline__ Feat feat_of(int fi, const CovGeom& g) {
         const int t = fi / g.Cin, c = fi - t * g.Cin;
         f.ky = t / g.kw; f.kx = t - f.ky * g.kw;
         f.off = (f.ky * g.W + f.kx) * g.Cin + c;
-        f.ext = g.layout == FW_LAYOUT_NHWC_KKC ? fi : c * (g.kh * g.kw) + t;
+        f.ext = c >= g.Cr ? -1 : g.layout == FW_LAYOUT_NHWC_KKC ? t * g.Cr + c : c * (g.kh * g.kw) + t;
     }
     return f;
 }
@@ -429,7 +430,7 @@ __global__ __launch_bounds__(256) void cov_reduce_kernel(CovGeom g, const float*
         if (grp == 0 && f < g.M) {
             v = red[0][threadIdx.x] + red[1][threadIdx.x] + red[2][threadIdx.x] + red[3][threadIdx.x];
             const int e = feat_of(f, g).ext;
-            s[e] = (float)((double)s[e] + v);
+            if (e >= 0) s[e] = (float)((double)s[e] + v);
         }
         return;
     }
@@ -444,6 +445,8 @@ __global__ __launch_bounds__(256) void cov_reduce_kernel(CovGeom g, const float*
     const int fi = bi * BLK + row, fj = bj * BLK + col;
     if (fi >= g.M || fj >= g.M) return;
     if (bi == bj && row < col) return;  // diagonal block: its upper half duplicates the lower
+    const int ei = feat_of(fi, g).ext, ej = feat_of(fj, g).ext;
+    if ((ei | ej) < 0) return;          // a padded channel
     const size_t stride = (size_t)g.nitems * 4 * BLK * BLK;
     const float* src = part + (size_t)blk * (BLK * BLK) + e;
     double v = 0.0;
@@ -456,9 +459,8 @@ __global__ __launch_bounds__(256) void cov_reduce_kernel(CovGeom g, const float*
         for (int j = 0; j < 8; ++j) v += (double)x[j];
     }
     for (; sp < g.nsplit; ++sp) v += (double)src[(size_t)sp * stride];
-    const int ei = feat_of(fi, g).ext, ej = feat_of(fj, g).ext;
     const int hi = max(ei, ej), lo = min(ei, ej);
-    float* dst = A + (size_t)hi * g.M + lo;
+    float* dst = A + (size_t)hi * g.Mr + lo;
     *dst = (float)((double)*dst + v);
 }
 
@@ -472,6 +474,7 @@ bool make_geom(const fw_conv_desc* d, fw_dtype dt, fw_layout lay, CovGeom* g) {
     const long long M = (long long)d->Cin * d->kh * d->kw;
     if (n_rows <= 0 || n_rows >= (1ll << 31) || M <= 0 || M > 16384) return false;
     if ((long long)d->B * d->Cin * d->H * d->W >= (1ll << 31)) return false;
+    g->Cr = d->Cin; g->Mr = (int)M;
     g->n_rows = (int)n_rows; g->M = (int)M; g->nb = (int)((M + BLK - 1) / BLK);
     item_counts(g->nb, &g->n0, &g->n1, &g->n2);
     g->nitems = g->n0 + g->n1 + g->n2;
@@ -643,11 +646,11 @@ __global__ __launch_bounds__(256) void mirror_lower_kernel(float* __restrict__ A
 }
 
 // [B][C][HW] -> [B][HW][C] through 32x32 LDS tiles: float32 activations in NCHW order are brought into the
-// channels-last order that the fast accumulation kernel reads with 16-byte loads
-__global__ __launch_bounds__(256) void nchw_to_nhwc_kernel(const float* __restrict__ src, float* __restrict__ dst, int C, int HW) {
+// channels-last order that the fast accumulation kernel reads with 16-byte loads; channels C .. Cp - 1 are zero
+__global__ __launch_bounds__(256) void nchw_to_nhwc_kernel(const float* __restrict__ src, float* __restrict__ dst, int C, int Cp, int HW) {
     __shared__ float t[32][33];
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-    const size_t img = (size_t)blockIdx.z * C * HW;
+    const size_t img = (size_t)blockIdx.z * C * HW, img_dst = (size_t)blockIdx.z * Cp * HW;
     const int p0 = blockIdx.x * 32, c0 = blockIdx.y * 32;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -658,8 +661,30 @@ __global__ __launch_bounds__(256) void nchw_to_nhwc_kernel(const float* __restri
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int p = p0 + ty + 8 * r, c = c0 + tx;
-        if (p < HW && c < C) dst[img + (size_t)p * C + c] = t[tx][ty + 8 * r];
+        if (p < HW && c < Cp) dst[img_dst + (size_t)p * Cp + c] = t[tx][ty + 8 * r];
     }
+}
+
+// The same for few channels (a 32 x 32 tile would be mostly empty) and for channels-last sources: one thread per pixel and four
+// channels of the padded tensor.  Reads run along the pixels of a channel (NCHW) or along the channels.
+template <bool NCHW>
+__global__ __launch_bounds__(256) void pad_channels_kernel(const float* __restrict__ src, float4* __restrict__ dst, int C, int Cq, int HW, int npix) {
+    const long long e = (long long)blockIdx.x * 256 + threadIdx.x;
+    const long long total = (long long)npix * Cq;
+    if (e >= total) return;
+    int pix, q;
+    if (NCHW) { q = (int)(e / npix); pix = (int)(e - (long long)q * npix); }
+    else { pix = (int)(e / Cq); q = (int)(e - (long long)pix * Cq); }
+    float v[4];
+    if (NCHW) {
+        const int b = pix / HW, p = pix - b * HW;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = 4 * q + i < C ? src[((size_t)b * C + 4 * q + i) * HW + p] : 0.f;
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = 4 * q + i < C ? src[(size_t)pix * C + 4 * q + i] : 0.f;
+    }
+    dst[(size_t)pix * Cq + q] = make_float4(v[0], v[1], v[2], v[3]);
 }
 
 __global__ __launch_bounds__(256) void fill_f32_kernel(float* __restrict__ p, size_t n, float v) {
@@ -762,6 +787,39 @@ static bool split_plan(const fw_conv_desc* d, fw_layout lay, SplitPlan* sp) {
     return true;
 }
 
+// float32 layers whose channels are no multiple of four: the 16-byte loads of the fast kernels and the shift form need one, and
+// the kernel without (4-byte gathers) is two to three times slower.  The tensor is copied channels-last with zero channels up to
+// the next multiple and goes through the fast kernels, which drop the padded features when they add into A; all sums stay in
+// float32 as they were.  399 features, 8192 rows: 91 us -> 44 us; 567 features (3x3, stride 2), 8192 rows: 132 us -> 57 us; 525
+// features (5x5), 8177 rows, NCHW: 105 us -> 61 us; 147 features (7x7 stride 2), 3.2 M rows: 5.1 ms -> 2.6 ms; the copy never
+// cost more than the faster kernels gave back, down to 128 rows (27 features, 512 rows: 14.9 us -> 14.5 us).
+// The kernel without stays for tensors beyond the index range of the fast ones.
+// `lay`: the caller's.  Layers that take the split form are not touched (it takes any number of channels).
+// Products of the direct form (whole 64 x 64 blocks, all rows) from which the shift form is the faster one: 270 features, 12544
+// rows (7.7e8) 46 us direct, 47 us shift; 525 features, 8177 rows (1.5e9) 61.4 and 61.0 us; 405 features, 25600 rows (2.9e9)
+// 97 and 62 us; 333 features, 512 rows (4.4e7) 17 and 32 us.
+constexpr double COV_SHIFT_LEAST_WORK = 1.2e9;
+struct PadPlan { fw_conv_desc d; fw_layout lay; };
+static bool pad_plan(const fw_conv_desc* d, fw_layout lay, PadPlan* pp) {
+    if ((d->Cin & 3) == 0) return false;
+    SplitPlan sp;
+    if (split_plan(d, lay, &sp)) return false;
+    const int Cp = (d->Cin + 3) / 4 * 4;
+    const long long kk = (long long)d->kh * d->kw, M = d->Cin * kk, nb = (M + BLK - 1) / BLK;
+    const long long Ho = (d->H + 2 * d->pad - d->kh) / d->stride + 1, Wo = (d->W + 2 * d->pad - d->kw) / d->stride + 1;
+    if (Cp * kk > 16384 || (long long)d->B * d->H * d->W * Cp >= (1ll << 30) || d->B > 65535) return false;   // (limits of the fast kernels)
+    pp->d = *d;
+    pp->d.Cin = Cp;
+    if (d->form == FW_COV_FORM_SPLIT) pp->d.form = FW_COV_FORM_DIRECT;     // (an NCHW tensor that the split form does not take)
+    // The shift form of the padded tensor costs two launches and sums more rows per range: it is taken where both its time and its
+    // error against float64 were no larger than the direct form's.
+    const double work = (double)d->B * (double)(Ho * Wo) * (double)(nb * (nb + 1) / 2 * BLK * BLK);
+    if (d->form == FW_COV_FORM_AUTO && (M <= 256 || M > 2048 || work < COV_SHIFT_LEAST_WORK))
+        pp->d.form = FW_COV_FORM_DIRECT;
+    pp->lay = lay == FW_LAYOUT_NCHW ? FW_LAYOUT_NHWC : lay;
+    return true;
+}
+
 size_t cov_workspace_bytes(int /*M*/, const fw_conv_desc* d, fw_dtype dt, fw_layout lay) {
     if (d && cov_skinny_applies(d, lay)) return cov_skinny_workspace_bytes(d, lay);
     if (dt == FW_BF16) return cov_bf16_workspace_bytes(d, lay);
@@ -771,13 +829,17 @@ size_t cov_workspace_bytes(int /*M*/, const fw_conv_desc* d, fw_dtype dt, fw_lay
         SplitPlan sp;
         if (split_plan(d, copy ? FW_LAYOUT_NHWC : lay, &sp)) return sp.total + (copy ? act_copy_bytes(d) : 0);
     }
-    if (cov_shift_applies(d, copy ? FW_LAYOUT_NHWC : lay))
-        return cov_shift_workspace_bytes(d, copy ? FW_LAYOUT_NHWC : lay) + (copy ? act_copy_bytes(d) : 0);
+    PadPlan pp;
+    const bool pad = pad_plan(d, lay, &pp);
+    if (pad) { d = &pp.d; lay = pp.lay; }
+    else if (copy) lay = FW_LAYOUT_NHWC;
+    const size_t act = copy || pad ? act_copy_bytes(d) : 0;
+    if (cov_shift_applies(d, lay)) return cov_shift_workspace_bytes(d, lay) + act;
     CovGeom g;
-    if (!make_geom(d, dt, copy ? FW_LAYOUT_NHWC : lay, &g)) return 0;
+    if (!make_geom(d, dt, lay, &g)) return 0;
     const size_t part = (size_t)g.nsplit * g.nitems * 4 * BLK * BLK * sizeof(float);
     const size_t sp = (size_t)g.nsplit * g.nb * BLK * sizeof(float);
-    return align_up(part, 256) + align_up(sp, 256) + (copy ? act_copy_bytes(d) : 0);
+    return align_up(part, 256) + align_up(sp, 256) + act;
 }
 
 bool cov_plan(const fw_conv_desc* d, fw_dtype dt, fw_layout lay, fw_cov_plan* plan) {
@@ -793,6 +855,8 @@ bool cov_plan(const fw_conv_desc* d, fw_dtype dt, fw_layout lay, fw_cov_plan* pl
             return true;
         }
     }
+    PadPlan pp;
+    if (pad_plan(d, lay, &pp)) { d = &pp.d; lay = pp.lay; }
     if (cov_shift_plan(d, lay, plan)) return true;
     CovGeom g;
     if (!make_geom(d, dt, lay, &g)) return false;
@@ -821,7 +885,7 @@ fw_status cov_accumulate(const void* X, fw_dtype dt, fw_layout lay, const fw_con
                 float* Xc = reinterpret_cast<float*>(base + sp.total);
                 const int HW = d->H * d->W;
                 hipLaunchKernelGGL(nchw_to_nhwc_kernel, dim3((HW + 31) / 32, (d->Cin + 31) / 32, d->B), dim3(256), 0, st,
-                                   reinterpret_cast<const float*>(X), Xc, d->Cin, HW);
+                                   reinterpret_cast<const float*>(X), Xc, d->Cin, d->Cin, HW);
                 FW_LAUNCH_CHECK();
                 X = Xc;
             }
@@ -838,35 +902,50 @@ fw_status cov_accumulate(const void* X, fw_dtype dt, fw_layout lay, const fw_con
             return FW_OK;
         }
     }
+    const int real_channels = d->Cin;
+    PadPlan pp;
+    const bool pad = pad_plan(d, lay, &pp);
+    const fw_layout src_lay = lay;
+    if (pad) { d = &pp.d; lay = pp.lay; }
+    const size_t act = copy || pad ? act_copy_bytes(d) : 0;
+    // channels-last copy of the activation, with the padded channels, at `at`
+    auto copy_activation = [&](char* at) -> fw_status {
+        float* Xc = reinterpret_cast<float*>(at);
+        const int HW = d->H * d->W, npix = d->B * HW, Cq = d->Cin / 4;
+        const unsigned blocks = (unsigned)(((long long)npix * Cq + 255) / 256);
+        const float* src = reinterpret_cast<const float*>(X);
+        if (copy || (src_lay == FW_LAYOUT_NCHW && d->Cin > 16))
+            hipLaunchKernelGGL(nchw_to_nhwc_kernel, dim3((HW + 31) / 32, (d->Cin + 31) / 32, d->B), dim3(256), 0, st, src, Xc, real_channels, d->Cin, HW);
+        else if (src_lay == FW_LAYOUT_NCHW)
+            hipLaunchKernelGGL(pad_channels_kernel<true>, dim3(blocks), dim3(256), 0, st, src, reinterpret_cast<float4*>(Xc), real_channels, Cq, HW, npix);
+        else
+            hipLaunchKernelGGL(pad_channels_kernel<false>, dim3(blocks), dim3(256), 0, st, src, reinterpret_cast<float4*>(Xc), real_channels, Cq, HW, npix);
+        FW_LAUNCH_CHECK();
+        X = Xc;
+        return FW_OK;
+    };
     if (cov_shift_applies(d, lay)) {
         // stride-1 window: tap pairs with the same offset share their products (cov_shift.hip)
-        const size_t need = cov_shift_workspace_bytes(d, lay) + (copy ? act_copy_bytes(d) : 0);
-        if (!ws || ws_bytes < need) return FW_ERR_WORKSPACE;
-        if (copy) {
-            float* Xc = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + cov_shift_workspace_bytes(d, lay));
-            const int HW = d->H * d->W;
-            hipLaunchKernelGGL(nchw_to_nhwc_kernel, dim3((HW + 31) / 32, (d->Cin + 31) / 32, d->B), dim3(256), 0, st,
-                               reinterpret_cast<const float*>(X), Xc, d->Cin, HW);
-            FW_LAUNCH_CHECK();
-            X = Xc;
+        const size_t own = cov_shift_workspace_bytes(d, lay);
+        if (!ws || ws_bytes < own + act) return FW_ERR_WORKSPACE;
+        if (act) {
+            const fw_status rc = copy_activation(reinterpret_cast<char*>(ws) + own);
+            if (rc != FW_OK) return rc;
         }
-        return cov_shift_accumulate(reinterpret_cast<const float*>(X), lay, d, A, s, ws, ws_bytes, st);
+        return cov_shift_accumulate(reinterpret_cast<const float*>(X), lay, d, A, s, ws, own, st, real_channels);
     }
     CovGeom g;
     if (!make_geom(d, dt, lay, &g)) return FW_ERR_UNSUPPORTED;
+    g.Cr = real_channels;
+    g.Mr = real_channels * d->kh * d->kw;
     const size_t part_bytes = align_up((size_t)g.nsplit * g.nitems * 4 * BLK * BLK * sizeof(float), 256);
     const size_t sp_bytes = align_up((size_t)g.nsplit * g.nb * BLK * sizeof(float), 256);
-    const size_t need = part_bytes + sp_bytes + (copy ? act_copy_bytes(d) : 0);
-    if (!ws || ws_bytes < need) return FW_ERR_WORKSPACE;
+    if (!ws || ws_bytes < part_bytes + sp_bytes + act) return FW_ERR_WORKSPACE;
     float* part = reinterpret_cast<float*>(ws);
     float* spart = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + part_bytes);
-    if (copy) {
-        float* Xc = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + part_bytes + sp_bytes);
-        const int HW = d->H * d->W;
-        hipLaunchKernelGGL(nchw_to_nhwc_kernel, dim3((HW + 31) / 32, (d->Cin + 31) / 32, d->B), dim3(256), 0, st,
-                           reinterpret_cast<const float*>(X), Xc, d->Cin, HW);
-        FW_LAUNCH_CHECK();
-        X = Xc;
+    if (act) {
+        const fw_status rc = copy_activation(reinterpret_cast<char*>(ws) + part_bytes + sp_bytes);
+        if (rc != FW_OK) return rc;
     }
     const dim3 grid(g.nitems, g.nsplit);
     const bool vec4 = dt == FW_F32 && lay != FW_LAYOUT_NCHW && (g.Cin % 4) == 0;

@@ -50,6 +50,7 @@ struct ShiftGeom {
     int nreg, nsplit;
     int rps;                   // pixels per range (multiple of KT); the last range of a region may be shorter
     int kkc;                   // 1: A in (ky, kx, c) feature order, 0: (c, ky, kx)
+    int Cr, Mr;                // the caller's channels and features: fewer than Cin and M where the tensor was padded with zero channels
     ShiftRegion reg[MAXREG];
 };
 
@@ -305,19 +306,19 @@ __global__ __launch_bounds__(256) void shift_region_reduce_kernel(ShiftGeom g, c
 
 __device__ __forceinline__ void tap_channel(int e, const ShiftGeom& g, int* ty, int* tx, int* c) {
     int t;
-    if (g.kkc) { t = e / g.Cin; *c = e - t * g.Cin; }
+    if (g.kkc) { t = e / g.Cr; *c = e - t * g.Cr; }
     else { const int kk = g.kh * g.kw; *c = e / kk; t = e - *c * kk; }
     *ty = t / g.kw;
     *tx = t - *ty * g.kw;
 }
 
 // A[i][j] += sum over the regions that serve the row tap of R_r(d)[c1][c2], one thread per element of the lower
-// triangle in the caller's feature order; workgroups with blockIdx.y == M add the column sums
+// triangle in the caller's feature order; workgroups with blockIdx.y == Mr add the column sums
 __global__ __launch_bounds__(256) void shift_assemble_kernel(ShiftGeom g, const double* __restrict__ Rr, const double* __restrict__ Sr,
                                                              float* __restrict__ A, float* __restrict__ s) {
     const int j = blockIdx.x * 256 + threadIdx.x;
-    if ((int)blockIdx.y == g.M) {
-        if (j >= g.M) return;
+    if ((int)blockIdx.y == g.Mr) {
+        if (j >= g.Mr) return;
         int ty, tx, c;
         tap_channel(j, g, &ty, &tx, &c);
         double v = 0.0;
@@ -345,7 +346,7 @@ __global__ __launch_bounds__(256) void shift_assemble_kernel(ShiftGeom g, const 
     double v = 0.0;
     for (int r = 0; r < g.nreg; ++r)
         if (((g.reg[r].rowmask >> t1y) & 1) && ((g.reg[r].colmask >> t1x) & 1)) v += Rr[(size_t)r * stride + idx];
-    float* dst = A + (size_t)i * g.M + j;
+    float* dst = A + (size_t)i * g.Mr + j;
     *dst = (float)((double)*dst + v);
 }
 
@@ -377,7 +378,8 @@ static bool make_shift_geom(const fw_conv_desc* d, fw_layout lay, ShiftGeom* g) 
     const long long M = (long long)d->Cin * d->kh * d->kw;
     const long long npix = (long long)d->B * d->H * d->W;
     if (g->Ho <= 0 || g->Wo <= 0 || M > 16384 || npix * d->Cin >= (1ll << 30)) return false;   // element indices stay far inside int
-    g->M = (int)M;
+    g->M = g->Mr = (int)M;
+    g->Cr = d->Cin;
     g->nd = d->kw + (d->kh - 1) * (2 * d->kw - 1);
     g->F = g->nd * d->Cin;
     g->nbr = (d->Cin + BLK - 1) / BLK;
@@ -448,9 +450,11 @@ bool cov_shift_plan(const fw_conv_desc* d, fw_layout lay, fw_cov_plan* plan) {
 }
 
 fw_status cov_shift_accumulate(const float* X, fw_layout lay, const fw_conv_desc* d, float* A, float* s, void* ws, size_t ws_bytes,
-                               hipStream_t st) {
+                               hipStream_t st, int real_channels) {
     ShiftGeom g;
     if (!make_shift_geom(d, lay, &g)) return FW_ERR_UNSUPPORTED;
+    g.Cr = real_channels;
+    g.Mr = real_channels * d->kh * d->kw;
     const ShiftWs L = shift_ws_layout(g);
     if (!ws || ws_bytes < L.total) return FW_ERR_WORKSPACE;
     char* base = reinterpret_cast<char*>(ws);
@@ -462,7 +466,7 @@ fw_status cov_shift_accumulate(const float* X, fw_layout lay, const fw_conv_desc
     FW_LAUNCH_CHECK();
     hipLaunchKernelGGL(shift_region_reduce_kernel, dim3(g.nreg * g.nbr * g.nbc * 16 + g.nreg * g.nbr), dim3(256), 0, st, g, part, spart, Rr, Sr);
     FW_LAUNCH_CHECK();
-    hipLaunchKernelGGL(shift_assemble_kernel, dim3((g.M + 255) / 256, g.M + 1), dim3(256), 0, st, g, Rr, Sr, A, s);
+    hipLaunchKernelGGL(shift_assemble_kernel, dim3((g.Mr + 255) / 256, g.Mr + 1), dim3(256), 0, st, g, Rr, Sr, A, s);
     FW_LAUNCH_CHECK();
     return FW_OK;
 }

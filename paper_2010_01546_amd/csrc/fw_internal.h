@@ -121,7 +121,7 @@ inline int shift_bands(int H, int k, int pad, int Ho, ShiftBand* out, int cap) {
 bool cov_shift_applies(const fw_conv_desc* d, fw_layout lay);
 size_t cov_shift_workspace_bytes(const fw_conv_desc* d, fw_layout lay);
 fw_status cov_shift_accumulate(const float* X, fw_layout lay, const fw_conv_desc* d, float* A, float* s, void* ws, size_t ws_bytes,
-                               hipStream_t st);
+                               hipStream_t st, int real_channels);   // channels from real_channels on are padding: not added into A and s
 
 bool cov_shift_plan(const fw_conv_desc* d, fw_layout lay, fw_cov_plan* plan);
 

@@ -197,6 +197,43 @@ def test_all_features_in_one_tile(B, H, W, Cin, kh, kw, lay):
     assert np.array_equal(s.cpu().numpy(), rows.sum(0) + 2.0)
 
 
+@pytest.mark.parametrize("lay", [b.FW_LAYOUT_NHWC, b.FW_LAYOUT_NHWC_KKC, b.FW_LAYOUT_NCHW])
+@pytest.mark.parametrize("form", [b.FW_COV_FORM_AUTO, b.FW_COV_FORM_DIRECT, b.FW_COV_FORM_SHIFT])
+@pytest.mark.parametrize("B,Cin,H,W,k,stride,pad", [(3, 1, 5, 4, 3, 1, 1), (9, 2, 8, 11, 2, 1, 0), (5, 3, 19, 17, 7, 2, 3), (17, 5, 9, 7, 5, 1, 2), (4, 18, 6, 6, 3, 2, 1),
+                                                    (33, 19, 12, 10, 3, 1, 1), (150, 30, 14, 14, 3, 1, 1), (60, 70, 9, 8, 3, 1, 1), (2, 1, 1, 1, 1, 1, 0)])
+def test_float32_channels_that_are_no_multiple_of_four(B, Cin, H, W, k, stride, pad, form, lay):
+    """Such a float32 tensor is padded with zero channels; the padded features must leave no trace.  Whole numbers whose sums stay
+    below 2^24: every order of additions gives the same result, so the sums are exact."""
+    g = torch.Generator().manual_seed(Cin)
+    x = torch.randint(-3, 4, (B, H, W, Cin), generator=g).float()
+    d = b.conv_desc(B, Cin, H, W, kh=k, kw=k, stride=stride, pad=pad, form=form)
+    M = Cin * k * k
+    ws = workspace(b.fw_workspace_bytes(b.FW_OP_COV_ACCUMULATE, M, 0, d, b.FW_F32))
+    A, s = torch.full((M, M), 5.0, device=DEV), torch.full((M,), 2.0, device=DEV)
+    X = x.permute(0, 3, 1, 2).contiguous() if lay == b.FW_LAYOUT_NCHW else x
+    b.fw_cov_accumulate(X.to(DEV), b.FW_F32, lay, d, A, s, ws)
+    torch.cuda.synchronize()
+    rows = ora.patch_rows(x.numpy(), B, Cin, H, W, k, k, stride, pad).astype(np.float64)
+    if lay == b.FW_LAYOUT_NHWC_KKC:
+        rows = rows.reshape(-1, Cin, k * k).transpose(0, 2, 1).reshape(-1, M)
+    assert np.array_equal(A.cpu().numpy(), np.tril(rows.T @ rows) + 5.0)           # nothing above the diagonal is touched
+    assert np.array_equal(s.cpu().numpy(), rows.sum(0) + 2.0)
+
+
+@pytest.mark.parametrize("n_rows,M", [(2049, 129), (2500, 202), (3000, 333)])
+def test_float32_rows_with_features_that_are_no_multiple_of_four(n_rows, M):
+    g = torch.Generator().manual_seed(M)
+    x = torch.randint(-3, 4, (n_rows, M), generator=g).float()
+    d = b.conv_desc(n_rows, M)
+    ws = workspace(b.fw_workspace_bytes(b.FW_OP_COV_ACCUMULATE, M, 0, d, b.FW_F32))
+    A, s = torch.full((M, M), 5.0, device=DEV), torch.full((M,), 2.0, device=DEV)
+    b.fw_cov_accumulate(x.to(DEV), b.FW_F32, b.FW_LAYOUT_ROWS, d, A, s, ws)
+    torch.cuda.synchronize()
+    rows = x.numpy().astype(np.float64)
+    assert np.array_equal(A.cpu().numpy(), np.tril(rows.T @ rows) + 5.0)
+    assert np.array_equal(s.cpu().numpy(), rows.sum(0) + 2.0)
+
+
 def test_accumulates_over_batches_and_two_block_recursion():
     """Two batches added into one block equal the block of their union; the second block follows eqs. (vmuxi), (vPhixi)."""
     L0 = wl.small_conv(1, 3, 8, 6, 6, 3, 1, 1, 8)
