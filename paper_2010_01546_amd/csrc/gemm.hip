@@ -101,16 +101,29 @@ struct StripCfg {
 // With gridDim.z > 1 the contraction index is cut into gridDim.z runs of `kchunks` whole chunks (the last run takes what
 // is left, the ragged end included); workgroup z then writes its partial strip to part[z][S][M] instead of finishing
 // the result, and strip_reduce_kernel adds the runs in a fixed order and applies the epilogue.
+// lower: only the strips that touch the lower triangle of a square result are wanted (what the others would hold is left as it
+// is): row tile r has r / C + 1 of them, listed row by row in gridDim.x.
 template <int MF, int C, bool PLAIN>
 __global__ __launch_bounds__(256) void grad_gemm_f32_strip_kernel(const float* __restrict__ G, const float* __restrict__ Q,
-                                                                  GemmEpilogue Out, int S, int M, int kchunks, float* __restrict__ part) {
+                                                                  GemmEpilogue Out, int S, int M, int kchunks, float* __restrict__ part, int lower) {
     typedef StripCfg<MF, C> K;
     typedef typename Mfma<MF>::acc_t acc_t;
     __shared__ __attribute__((aligned(16))) float sm[K::SMEM];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lr = lane % MF, lk = lane / MF;
-    const int row0 = blockIdx.y * MF, col0 = blockIdx.x * (C * MF);
+    int row_tile = blockIdx.y, strip = blockIdx.x;
+    if (lower) {
+        // group gr = C row tiles with gr + 1 strips each; C gr (gr + 1) / 2 strips come before it
+        const int b = blockIdx.x;
+        int gr = (int)((sqrtf(8.f * (float)b / C + 1.f) - 1.f) * 0.5f);
+        while (C * ((gr + 1) * (gr + 2) / 2) <= b) ++gr;
+        while (C * (gr * (gr + 1) / 2) > b) --gr;
+        const int rem = b - C * (gr * (gr + 1) / 2);
+        row_tile = gr * C + rem / (gr + 1);
+        strip = rem - rem / (gr + 1) * (gr + 1);
+    }
+    const int row0 = row_tile * MF, col0 = strip * (C * MF);
     acc_t acc[C];
 #pragma unroll
     for (int j = 0; j < C; ++j)
@@ -273,25 +286,37 @@ __global__ __launch_bounds__(256) void grad_gemm_f32_strip_kernel(const float* _
 // the end take about as long as ten chunks: measured, a 256 x 2304 x 2304 product got slower when cut in four).
 struct StripChoice { int mf, c, nks, kchunks; };
 constexpr int STRIP_MAX_RUNS = 8;
-inline StripChoice pick_strip(int S, int M, bool plain, bool can_split) {
+// strips of c tiles that touch the lower triangle of a square of t x t tiles
+inline long long lower_strips(long long t, int c) {
+    const long long g = t / c;
+    return c * (g * (g + 1) / 2) + (t - g * c) * (g + 1);
+}
+inline StripChoice pick_strip(int S, int M, bool plain, bool can_split, bool lower) {
     static const int cs[6] = {9, 6, 4, 3, 2, 1};
     StripChoice best = {32, 1, 1, 0};
     double best_cost = 1e300;
     long long best_wgs = 1;
+    auto consider = [&](int mf, int c, bool low) {
+        if (!plain && mf == 32 && c == 9) return;     // the general epilogue does not fit beside 9 x 16 accumulators
+        const int kw = mf == 32 ? 8 : 16, u = strip_u(mf, c), kc = 4 * kw * u;
+        const long long tr = (S + mf - 1) / mf, tc = (M + mf - 1) / mf;
+        const long long wgs = low ? lower_strips(tr, c) : tr * ((tc + c - 1) / c);
+        const double rounds = (double)((wgs + 255) / 256);
+        const double kpad = (double)((M + kc - 1) / kc * kc) / M;
+        // a 16x16 tile is a quarter of the MFMA work of a 32x32 tile and reads twice the operands per flop;
+        // a wider strip reads fewer operands per MFMA
+        const double cost = rounds * c * (mf == 32 ? 1.0 : 0.25 * 1.06) * kpad * (1.0 + 0.02 / c);
+        if (cost < best_cost) { best_cost = cost; best = {mf, c, 1, 0}; best_wgs = wgs; }
+    };
     for (int mf = 32; mf >= 16; mf -= 16)
-        for (int ci = 0; ci < 6; ++ci) {
-            const int c = cs[ci];
-            if (!plain && mf == 32 && c == 9) continue;   // the general epilogue does not fit beside 9 x 16 accumulators
-            const int kw = mf == 32 ? 8 : 16, u = strip_u(mf, c), kc = 4 * kw * u;
-            const long long tr = (S + mf - 1) / mf, tc = (M + mf - 1) / mf;
-            const long long wgs = tr * ((tc + c - 1) / c);
-            const double rounds = (double)((wgs + 255) / 256);
-            const double kpad = (double)((M + kc - 1) / kc * kc) / M;
-            // a 16x16 tile is a quarter of the MFMA work of a 32x32 tile and reads twice the operands per flop;
-            // a wider strip reads fewer operands per MFMA
-            const double cost = rounds * c * (mf == 32 ? 1.0 : 0.25 * 1.06) * kpad * (1.0 + 0.02 / c);
-            if (cost < best_cost) { best_cost = cost; best = {mf, c, 1, 0}; best_wgs = wgs; }
-        }
+        for (int ci = 0; ci < 6; ++ci) consider(mf, cs[ci], false);
+    if (lower) {
+        // Half the strips: narrower ones fit a round.  The tile stays that of the whole product (left free, 800 features went
+        // from tiles of 32 to tiles of 16 and from 51 us to 68 us a refresh).
+        const int mf = best.mf;
+        best_cost = 1e300;
+        for (int ci = 0; ci < 6; ++ci) consider(mf, cs[ci], true);
+    }
     if (can_split && best_wgs <= 64) {
         const int kc = 4 * (best.mf == 32 ? 8 : 16) * strip_u(best.mf, best.c);
         const int nchunks = M / kc;
@@ -324,14 +349,15 @@ __global__ __launch_bounds__(256) void strip_reduce_kernel(const float* __restri
 }
 
 template <int MF>
-void launch_strip(const StripChoice& ch, const float* G, const float* Q, const GemmEpilogue& Out, int S, int M, float* part, hipStream_t st) {
+void launch_strip(const StripChoice& ch, const float* G, const float* Q, const GemmEpilogue& Out, int S, int M, float* part, bool lower, hipStream_t st) {
     const int c = ch.c;
-    const dim3 grid(((M + MF - 1) / MF + c - 1) / c, (S + MF - 1) / MF, ch.nks);
+    const dim3 grid = lower ? dim3((unsigned)lower_strips((S + MF - 1) / MF, c))
+                            : dim3(((M + MF - 1) / MF + c - 1) / c, (S + MF - 1) / MF, ch.nks);
     const bool plain = Out.out && !Out.out_bf16 && Out.taps == 1 && !Out.W;
 #define FW_STRIP_LAUNCH(CC)                                                                                                \
-    if (plain) hipLaunchKernelGGL((grad_gemm_f32_strip_kernel<MF, CC, true>), grid, dim3(256), 0, st, G, Q, Out, S, M, ch.kchunks, part);   \
+    if (plain) hipLaunchKernelGGL((grad_gemm_f32_strip_kernel<MF, CC, true>), grid, dim3(256), 0, st, G, Q, Out, S, M, ch.kchunks, part, lower ? 1 : 0);   \
     else if constexpr (!(MF == 32 && CC == 9))                                                                             \
-        hipLaunchKernelGGL((grad_gemm_f32_strip_kernel<MF, CC, false>), grid, dim3(256), 0, st, G, Q, Out, S, M, ch.kchunks, part)
+        hipLaunchKernelGGL((grad_gemm_f32_strip_kernel<MF, CC, false>), grid, dim3(256), 0, st, G, Q, Out, S, M, ch.kchunks, part, lower ? 1 : 0)
     switch (c) {
         case 9: FW_STRIP_LAUNCH(9); break;
         case 6: FW_STRIP_LAUNCH(6); break;
@@ -353,7 +379,8 @@ void launch_strip(const StripChoice& ch, const float* G, const float* Q, const G
 // wavefronts split the contraction index four ways; operands come straight from global memory / L2 with scalar
 // loads (Q along its rows, like the other kernels), partial tiles are combined through LDS.
 __global__ __launch_bounds__(256) void grad_gemm_f32_small_kernel(const float* __restrict__ G, const float* __restrict__ Q,
-                                                                  GemmEpilogue Out, int S, int M) {
+                                                                  GemmEpilogue Out, int S, int M, int lower) {
+    if (lower && blockIdx.x > blockIdx.y) return;      // a tile above the diagonal
     __shared__ float red[3][32 * 32];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -491,14 +518,16 @@ __global__ __launch_bounds__(256) void taps_to_rows_kernel(const void* __restric
 size_t grad_gemm_partial_bytes(int S, int M) { return align_up((size_t)STRIP_MAX_RUNS * S * M * sizeof(float), 256); }
 
 // part: room for grad_gemm_partial_bytes(S, M) bytes, or null (then the contraction index is not cut into runs)
-fw_status grad_gemm_f32(const float* G, int S, int M, const float* Q, const GemmEpilogue& e, hipStream_t st, float* part) {
+// lower: of a square result only the lower triangle is wanted; what lies above it is undefined afterwards
+fw_status grad_gemm_f32(const float* G, int S, int M, const float* Q, const GemmEpilogue& e, hipStream_t st, float* part, bool lower) {
+    lower = lower && S == M;
     if ((M & 3) != 0)
-        hipLaunchKernelGGL(grad_gemm_f32_small_kernel, dim3((M + 31) / 32, (S + 31) / 32), dim3(256), 0, st, G, Q, e, S, M);
+        hipLaunchKernelGGL(grad_gemm_f32_small_kernel, dim3((M + 31) / 32, (S + 31) / 32), dim3(256), 0, st, G, Q, e, S, M, lower ? 1 : 0);
     else {
         const bool plain = e.out && !e.out_bf16 && e.taps == 1 && !e.W;
-        const StripChoice ch = pick_strip(S, M, plain, part != nullptr);
-        if (ch.mf == 32) launch_strip<32>(ch, G, Q, e, S, M, part, st);
-        else launch_strip<16>(ch, G, Q, e, S, M, part, st);
+        const StripChoice ch = pick_strip(S, M, plain, part != nullptr && !lower, lower);
+        if (ch.mf == 32) launch_strip<32>(ch, G, Q, e, S, M, part, lower, st);
+        else launch_strip<16>(ch, G, Q, e, S, M, part, lower, st);
     }
     FW_LAUNCH_CHECK();
     return FW_OK;

@@ -117,6 +117,27 @@ def test_config1_sixteen_steps():
     assert applied >= 8
 
 
+@pytest.mark.parametrize("M", [147, 160, 242, 255, 256, 404, 512, 516, 525, 576, 580, 764, 900, 1028, 1151, 1152, 1300, 1532, 2044, 2047, 2048, 2052])
+def test_float32_refresh_strips_of_the_lower_triangle(M):
+    """Of Phi_y = Psi T^T only the strips that touch the lower triangle are multiplied, whatever strip width a size takes; the mirror
+    image and the row norms (one launch up to 2048 features) have to fill the rest.  Float32 products (no workspace), tolerance as above."""
+    rng = np.random.default_rng(M)
+    P = rng.standard_normal((M, M)).astype(np.float32) / np.float32(np.sqrt(M))
+    P = ((P + P.T) / 2 + np.eye(M, dtype=np.float32)).astype(np.float32)
+    T = (np.eye(M) + 0.3 * rng.standard_normal((M, M)) / np.sqrt(M)).astype(np.float32)
+    z = lambda *sh: torch.full(sh, float("nan"), device="cuda:0")  # noqa: E731
+    Py, Psi, xi2, lbar = z(M, M), z(M, M), z(M), torch.ones(4, device="cuda:0")
+    Q = dev(np.eye(M))
+    st = b.cond_state(M, dev(P), lbar, dev(T), Q, Q.clone(), Py, Psi, xi2)
+    b.fw_cond_state_refresh(st, None)
+    torch.cuda.synchronize()
+    P64, T64 = P.astype(np.float64), T.astype(np.float64)
+    want = T64 @ P64 @ T64.T
+    assert relF(Psi.cpu().numpy(), T64 @ P64) < 2e-6 and relF(Py.cpu().numpy(), want) < 4e-6
+    assert np.array_equal(Py.cpu().numpy(), Py.cpu().numpy().T)
+    assert relF(xi2.cpu().numpy(), (want ** 2).sum(0)) < 8e-6
+
+
 @pytest.mark.parametrize("split", [False, True])
 @pytest.mark.parametrize("M,leak", [(96, True), (130, True), (64, False), (70, False), (147, True), (1152, True), (1536, True), (1600, False), (2304, True)])
 def test_refresh_for_a_new_block(M, leak, split):
