@@ -173,19 +173,21 @@ __global__ __launch_bounds__(256) void pack_images_kernel(const void* __restrict
     const int Csrc = SPLIT ? g.Cin >> 1 : g.Cin;            // channels of the source tensor
     const int csrc = SPLIT ? (c >= Csrc ? c - Csrc : c) : c;
     const bool lo_plane = SPLIT && c >= Csrc;
-    const long long img_stride = (long long)Csrc * g.H * g.W;
-    const long long src0 = ((long long)y * g.W + x) * Csrc + csrc;
+    // 32-bit element indices (the planner takes tensors below 2^31 elements only): with 64-bit ones the address arithmetic of
+    // eight loads cost this bandwidth-bound pass 5 %
+    const unsigned img_stride = (unsigned)Csrc * g.H * g.W;
+    const unsigned src0 = inside ? ((unsigned)y * g.W + x) * Csrc + csrc : 0u;
     const int dst0 = (yp * g.Wp + xp) * g.Cin + c;
     const int bg0 = chunk * g.bg_per_chunk, bg1 = min(g.Bg, bg0 + g.bg_per_chunk);
     float acc = 0.f;
     for (int bg = bg0; bg < bg1; ++bg) {
-        // eight loads in flight: issued unconditionally (a masked one reads element 0) and masked afterwards; the empty
+        // eight loads in flight: issued unconditionally (a masked one reads an element of the last image, or of the first pixel) and masked afterwards; the empty
         // asm statement keeps the compiler from moving them into branches, where each would be waited for on the spot
         unsigned v[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            const int b = bg * 8 + i;
-            const long long idx = (inside && b < g.B) ? (long long)b * img_stride + src0 : 0;
+            const unsigned b = min(bg * 8 + i, g.B - 1);
+            const unsigned idx = b * img_stride + src0;
             if constexpr (SPLIT) v[i] = __float_as_uint(Xf[idx]);
             else v[i] = X[idx];
         }

@@ -101,11 +101,11 @@ struct StripCfg {
 // With gridDim.z > 1 the contraction index is cut into gridDim.z runs of `kchunks` whole chunks (the last run takes what
 // is left, the ragged end included); workgroup z then writes its partial strip to part[z][S][M] instead of finishing
 // the result, and strip_reduce_kernel adds the runs in a fixed order and applies the epilogue.
-// lower: only the strips that touch the lower triangle of a square result are wanted (what the others would hold is left as it
+// LOWER: only the strips that touch the lower triangle of a square result are wanted (what the others would hold is left as it
 // is): row tile r has r / C + 1 of them, listed row by row in gridDim.x.
-template <int MF, int C, bool PLAIN>
+template <int MF, int C, bool PLAIN, bool LOWER>
 __global__ __launch_bounds__(256) void grad_gemm_f32_strip_kernel(const float* __restrict__ G, const float* __restrict__ Q,
-                                                                  GemmEpilogue Out, int S, int M, int kchunks, float* __restrict__ part, int lower) {
+                                                                  GemmEpilogue Out, int S, int M, int kchunks, float* __restrict__ part) {
     typedef StripCfg<MF, C> K;
     typedef typename Mfma<MF>::acc_t acc_t;
     __shared__ __attribute__((aligned(16))) float sm[K::SMEM];
@@ -113,7 +113,7 @@ __global__ __launch_bounds__(256) void grad_gemm_f32_strip_kernel(const float* _
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lr = lane % MF, lk = lane / MF;
     int row_tile = blockIdx.y, strip = blockIdx.x;
-    if (lower) {
+    if constexpr (LOWER) {
         // group gr = C row tiles with gr + 1 strips each; C gr (gr + 1) / 2 strips come before it
         const int b = blockIdx.x;
         int gr = (int)((sqrtf(8.f * (float)b / C + 1.f) - 1.f) * 0.5f);
@@ -355,9 +355,10 @@ void launch_strip(const StripChoice& ch, const float* G, const float* Q, const G
                             : dim3(((M + MF - 1) / MF + c - 1) / c, (S + MF - 1) / MF, ch.nks);
     const bool plain = Out.out && !Out.out_bf16 && Out.taps == 1 && !Out.W;
 #define FW_STRIP_LAUNCH(CC)                                                                                                \
-    if (plain) hipLaunchKernelGGL((grad_gemm_f32_strip_kernel<MF, CC, true>), grid, dim3(256), 0, st, G, Q, Out, S, M, ch.kchunks, part, lower ? 1 : 0);   \
+    if (plain && lower) hipLaunchKernelGGL((grad_gemm_f32_strip_kernel<MF, CC, true, true>), grid, dim3(256), 0, st, G, Q, Out, S, M, ch.kchunks, part);   \
+    else if (plain) hipLaunchKernelGGL((grad_gemm_f32_strip_kernel<MF, CC, true, false>), grid, dim3(256), 0, st, G, Q, Out, S, M, ch.kchunks, part);   \
     else if constexpr (!(MF == 32 && CC == 9))                                                                             \
-        hipLaunchKernelGGL((grad_gemm_f32_strip_kernel<MF, CC, false>), grid, dim3(256), 0, st, G, Q, Out, S, M, ch.kchunks, part, lower ? 1 : 0)
+        hipLaunchKernelGGL((grad_gemm_f32_strip_kernel<MF, CC, false, false>), grid, dim3(256), 0, st, G, Q, Out, S, M, ch.kchunks, part)
     switch (c) {
         case 9: FW_STRIP_LAUNCH(9); break;
         case 6: FW_STRIP_LAUNCH(6); break;
@@ -520,11 +521,11 @@ size_t grad_gemm_partial_bytes(int S, int M) { return align_up((size_t)STRIP_MAX
 // part: room for grad_gemm_partial_bytes(S, M) bytes, or null (then the contraction index is not cut into runs)
 // lower: of a square result only the lower triangle is wanted; what lies above it is undefined afterwards
 fw_status grad_gemm_f32(const float* G, int S, int M, const float* Q, const GemmEpilogue& e, hipStream_t st, float* part, bool lower) {
-    lower = lower && S == M;
     if ((M & 3) != 0)
-        hipLaunchKernelGGL(grad_gemm_f32_small_kernel, dim3((M + 31) / 32, (S + 31) / 32), dim3(256), 0, st, G, Q, e, S, M, lower ? 1 : 0);
+        hipLaunchKernelGGL(grad_gemm_f32_small_kernel, dim3((M + 31) / 32, (S + 31) / 32), dim3(256), 0, st, G, Q, e, S, M, lower && S == M ? 1 : 0);
     else {
         const bool plain = e.out && !e.out_bf16 && e.taps == 1 && !e.W;
+        lower = lower && plain && S == M;
         const StripChoice ch = pick_strip(S, M, plain, part != nullptr && !lower, lower);
         if (ch.mf == 32) launch_strip<32>(ch, G, Q, e, S, M, part, lower, st);
         else launch_strip<16>(ch, G, Q, e, S, M, part, lower, st);
