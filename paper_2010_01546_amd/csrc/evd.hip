@@ -4,7 +4,9 @@
 // largest gains): reduction to tridiagonal form, divide and conquer, back-transformation (symeig.hip).  The result is then
 // CHECKED against Phi_x itself: W = V Phi_x, and every off-diagonal entry of W V^T must lie below kAccept sqrt(D_i D_j),
 // D_i = sum_k v_ik^2 Phi_kk, i.e. a thousandth of what the storage of Phi_x as float32 leaves undetermined in that entry, or
-// below kAcceptClamp times the eigenvalue at which the gains are clamped.  Where neither holds (diagonals graded over many
+// below kAcceptClamp times the eigenvalue at which the gains are clamped; and V V^T must agree with the identity to kAccept (rows
+// that Phi_x takes to zero carry the largest gain and are seen by nothing else; one more product: 22.70 -> 23.09 ms at M = 2304, 3.60 -> 3.62 at 576).  Where V
+// fails that, it is given up for V = I.  Where neither of the first two holds (diagonals graded over many
 // decades above the clamp), or where the caller asks for a rotation
 // threshold of its own (tol > 0), a one-sided Jacobi iteration goes on from there:
 // orthogonal transformations are applied to the rows of W = V Phi_x and of V until the rows of W are mutually orthogonal;
@@ -44,14 +46,15 @@ inline EvdWs evd_layout(int M) {
     L.nblk_even = (L.nblk + 1) & ~1;
     L.npairs = L.nblk_even / 2;
     L.nslices = (M + JSW - 1) / JSW;
-    // Four float64 matrices: [0] Phi while it is reduced, then vectors of the merges, projections, partial Gram matrices, the
-    // scaled eigenvectors; [1] reflectors, then rotations and packed planes; [2], [3] eigenvectors and their image V Phi.
+    // Four float64 matrices: [0] Phi while it is reduced, then vectors of the merges, projections, a copy of Phi, partial Gram
+    // matrices; [1] reflectors, then rotations, packed planes and the scaled eigenvectors; [2], [3] eigenvectors and their
+    // image V Phi.
     size_t m = sym_eig_matrix_doubles(M);
     const size_t g = (size_t)L.npairs * L.nslices * JP * JP;
     if (g > m) m = g;
     m *= sizeof(double);
-    if (evd_products_split(M) && gemm_split_packed_bytes(M, M) > m) m = gemm_split_packed_bytes(M, M);
-    for (int k = 0; k < 4; ++k) L.mat[k] = take(m);
+    const size_t products = evd_products_split(M) ? gemm_split_packed_bytes(M, M) + (size_t)M * M * sizeof(float) : 0;
+    for (int k = 0; k < 4; ++k) L.mat[k] = take(k == 1 && products > m ? products : m);
     L.small = take(sym_eig_small_bytes(M));
     L.lam = take((size_t)M * sizeof(double));
     L.gq = take((size_t)M * sizeof(double));
@@ -422,15 +425,22 @@ fw_status whiten_evd(const float* Phi_x, int M, const fw_evd_params* p, float* T
     const double floor_rel = p->gain_mode == 1 ? kAcceptClamp / ((double)M * (double)p->g_max) : 0.0;
     rc = sym_eig_check(Phi_x, M, V, W, mat[0], base + L.small, kAccept, floor_abs, floor_rel, lam, cnt, st);
     if (rc != FW_OK) return rc;
-    float* X = reinterpret_cast<float*>(mat[0]);
-    // the outputs are issued before the host looks at the verdict, so that the GPU does not wait for it
+    // the outputs are issued before the host looks at the verdict, so that the GPU does not wait for it; they leave mat[0], the
+    // copy of Phi, alone (T or Q may lie where Phi_x was)
+    float* X = reinterpret_cast<float*>(reinterpret_cast<char*>(mat[1]) + (evd_products_split(M) ? gemm_split_packed_bytes(M, M) : 0));
     rc = evd_outputs(V, M, p, lam, gq, gh, tot, X, mat[1], T, Q, lambda, st);
     if (rc != FW_OK) return rc;
-    int sweeps_needed = 1;
-    FW_HIP_TRY(hipMemcpyAsync(&sweeps_needed, cnt, sizeof(int), hipMemcpyDeviceToHost, st));
+    int verdict[2] = {1, 1};
+    FW_HIP_TRY(hipMemcpyAsync(verdict, cnt, sizeof(verdict), hipMemcpyDeviceToHost, st));
     FW_HIP_TRY(hipStreamSynchronize(st));
-    bool converged = sweeps_needed == 0 && !(p->tol > 0.f);
+    bool converged = verdict[0] == 0 && verdict[1] == 0 && !(p->tol > 0.f);
     if (!converged) {
+        // rotations keep V as orthogonal as it is, so one that is not (a Phi_x with NaN or infinite entries leaves none) is
+        // given up: sweeps from V = I
+        if (verdict[1] != 0) {
+            rc = sym_eig_start_over(mat[0], M, V, W, st);
+            if (rc != FW_OK) return rc;
+        }
         double* Gpart = mat[0];
         double* Rot = mat[1];
         int* flags = reinterpret_cast<int*>(base + L.small);

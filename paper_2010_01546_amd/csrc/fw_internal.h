@@ -195,6 +195,7 @@ size_t sym_eig_matrix_doubles(int M);
 fw_status sym_eig(const float* Phi, int M, double* const buf[4], void* small, double** V, double** free_buf, hipStream_t st);
 fw_status sym_eig_check(const float* Phi, int M, const double* V, double* W, double* copy, void* small, double thr, double floor_abs,
                         double floor_rel, double* lam, int* flag, hipStream_t st);
+fw_status sym_eig_start_over(const double* copy, int M, double* V, double* W, hipStream_t st);
 fw_status sym_eig_spectral_products(const double* V, int M, const double* root_g, float* T, float* Q, hipStream_t st);
 
 // ---- evd.hip

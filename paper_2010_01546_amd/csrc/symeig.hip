@@ -899,7 +899,7 @@ __global__ __launch_bounds__(256) void image_kernel(const double* __restrict__ V
 __global__ __launch_bounds__(256) void row_scale_kernel(const double* __restrict__ V, const float* __restrict__ Phi, int ld, int M,
                                                         double floor_abs, double floor_rel, double* __restrict__ scale, int* __restrict__ flag) {
     const int lane = threadIdx.x & 63, r = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (blockIdx.x == 0 && threadIdx.x == 0) *flag = 0;
+    if (blockIdx.x == 0 && threadIdx.x < 2) flag[threadIdx.x] = 0;
     if (r >= M) return;
     double s = 0.0, tr = 0.0;
     for (int j = lane; j < M; j += 64) {
@@ -914,24 +914,27 @@ __global__ __launch_bounds__(256) void row_scale_kernel(const double* __restrict
         if (r == 0) scale[M] = fmax(floor_abs, floor_rel * tr);
     }
 }
-// S = W V^T on the tiles that touch the lower triangle: its diagonal is lambda; any off-diagonal entry above
-// max(thr scale_i scale_j, scale_M) raises the flag
+// On the tiles that touch the lower triangle: S = W V^T (blockIdx.z = 0), its diagonal is lambda, any off-diagonal entry above
+// max(thr scale_i scale_j, scale_M) raises flag[0]; V V^T (blockIdx.z = 1), any entry further than thr from the identity raises
+// flag[1].  The first alone would pass two equal rows, or a zero one, among the vectors that Phi takes to (nearly) zero.  NaN raises.
 __global__ __launch_bounds__(256) void residual_kernel(const double* __restrict__ W, const double* __restrict__ V, int ld, int M, double thr,
                                                        const double* __restrict__ scale, double* __restrict__ lam, int* __restrict__ flag) {
     const int row0 = blockIdx.y * 64, col0 = blockIdx.x * 64;
     if (col0 > row0) return;
-    const RowsK A = {W, ld, row0, M, M};
+    const bool image = blockIdx.z == 0;
+    const RowsK A = {image ? W : V, ld, row0, M, M};
     const RowsK B = {V, ld, col0, M, M};
     const double floor = scale[M];
     int bad = 0;
     gemm64(A, B, 0, M, [&](int r, int c, double x) {
         const int i = row0 + r, j = col0 + c;
         if (i < M && j < M) {
-            if (i == j) lam[i] = x;
+            if (!image) { if (!(fabs(x - (i == j ? 1.0 : 0.0)) <= thr)) bad = 1; }
+            else if (i == j) lam[i] = x;
             else if (!(fabs(x) <= fmax(thr * scale[i] * scale[j], floor))) bad = 1;
         }
     });
-    if (__any(bad) && (threadIdx.x & 63) == 0) *flag = 1;
+    if (__any(bad) && (threadIdx.x & 63) == 0) flag[blockIdx.z] = 1;
 }
 // T = V^T diag(g) V (z = 0) and Q = V^T diag(g^2) V (z = 1) as float32: lower tiles, mirrored on the way out
 __global__ __launch_bounds__(256) void spectral_product_kernel(const double* __restrict__ V, int ld, int M, const double* __restrict__ g,
@@ -952,6 +955,13 @@ __global__ __launch_bounds__(256) void spectral_product_kernel(const double* __r
 
 __global__ __launch_bounds__(256) void fill64_kernel(double* __restrict__ p, size_t n) {
     for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < n; e += (size_t)gridDim.x * 256) p[e] = 0.0;
+}
+__global__ __launch_bounds__(256) void start_over_kernel(const double* __restrict__ copy, int ld, size_t n, double* __restrict__ V,
+                                                         double* __restrict__ W) {
+    for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < n; e += (size_t)gridDim.x * 256) {
+        W[e] = copy[e];
+        V[e] = e % ld == e / ld ? 1.0 : 0.0;
+    }
 }
 inline int grid_for(size_t n) {
     const size_t b = (n + 255) / 256;
@@ -1085,8 +1095,9 @@ fw_status sym_eig(const float* Phi, int M, double* const buf[4], void* small, do
     return FW_OK;
 }
 
-// W = V Phi, lambda_i = w_i . v_i, and *flag != 0 on the device if some |v_i Phi v_j^T|, i != j, exceeds both
-// thr scale_i scale_j and max(floor_abs, floor_rel trace(Phi)).  `copy`: one more matrix buffer, for the float64 copy of Phi
+// W = V Phi, lambda_i = w_i . v_i, and on the device flag[0] != 0 if some |v_i Phi v_j^T|, i != j, exceeds both thr scale_i scale_j
+// and max(floor_abs, floor_rel trace(Phi)), flag[1] != 0 if some entry of V V^T is further than thr from the identity.
+// `copy`: one more matrix buffer, which gets the symmetric part of Phi in float64
 fw_status sym_eig_check(const float* Phi, int M, const double* V, double* W, double* copy, void* small, double thr, double floor_abs,
                         double floor_rel, double* lam, int* flag, hipStream_t st) {
     const int ld = sym_eig_ld(M), nt = (M + 63) / 64;
@@ -1095,7 +1106,15 @@ fw_status sym_eig_check(const float* Phi, int M, const double* V, double* W, dou
                        flag);
     hipLaunchKernelGGL(sym_load_kernel, dim3((ld + 31) / 32, (M + 31) / 32), dim3(256), 0, st, Phi, M, ld, nullptr, copy);
     hipLaunchKernelGGL(image_kernel, dim3(nt, nt), dim3(256), 0, st, V, copy, ld, M, W);
-    hipLaunchKernelGGL(residual_kernel, dim3(nt, nt), dim3(256), 0, st, W, V, ld, M, thr, scale, lam, flag);
+    hipLaunchKernelGGL(residual_kernel, dim3(nt, nt, 2), dim3(256), 0, st, W, V, ld, M, thr, scale, lam, flag);
+    FW_LAUNCH_CHECK();
+    return FW_OK;
+}
+
+// V = I and W = the symmetric part of Phi that sym_eig_check left in `copy`: where the sweeps start without a decomposition
+fw_status sym_eig_start_over(const double* copy, int M, double* V, double* W, hipStream_t st) {
+    const size_t nn = (size_t)M * sym_eig_ld(M);
+    hipLaunchKernelGGL(start_over_kernel, dim3(grid_for(nn)), dim3(256), 0, st, copy, sym_eig_ld(M), nn, V, W);
     FW_LAUNCH_CHECK();
     return FW_OK;
 }

@@ -1,4 +1,6 @@
 """GPU parity of the EVD / ZCA whitening matrix (Sec. 2, Sec. 3.2) against the CPU oracle."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -128,3 +130,84 @@ def test_special_matrices(kind, M):
     To, Qo, lo_ = ora.whiten_evd(Phi32, eps=1e-5)
     assert relF(T, To) < 1e-5 and relF(Q, Qo) < 1e-5
     assert np.max(np.abs(lam - lo_)) <= 2e-7 * max(lo_[0], 1e-30)
+
+
+@pytest.mark.parametrize("M", [600, 1100, 2300])
+@pytest.mark.parametrize("kind", ["rows", "duplicates", "clusters"])
+def test_deficient_and_clustered_spectra(kind, M):
+    """Fewer rows than features, every feature there twice, three eigenvalues of high multiplicity, over more than four levels of
+    merges: T, Q and the eigenvalues against the oracle, and the space that Phi_x takes to zero (gain 1/eps on all of it).
+    Rounding Phi_x to float32 moves eigenvalues by up to 2^-24 |Phi_x|, the gain 1/sqrt(max(lambda, eps)) of one near eps by
+    2^-25 |Phi_x| / eps of itself: eps is chosen so that this is 3e-6; 16-bit operands from 1536 features on add 5e-6."""
+    rng = np.random.default_rng(M)
+    if kind == "clusters":
+        Phi, _ = reflected_diagonal(M, np.repeat([1.0, 0.25, 0.05], [M // 2, M // 3, M - M // 2 - M // 3]), M)
+        Phi32, eps = Phi.float().cpu().numpy(), 1e-2
+    else:
+        X = rng.standard_normal((M // 4, M))
+        if kind == "duplicates":
+            X = rng.standard_normal((M, M // 2)).repeat(2, axis=1)
+        Phi32, eps = (X.T @ X / len(X)).astype(np.float32), 0.2
+    T, Q, lam = run_evd(Phi32, eps=eps)
+    To, Qo, lo_ = ora.whiten_evd(Phi32, eps=eps)
+    bound = 2e-5 if M >= b.FW_REFRESH_SPLIT_MIN_M else 1e-5
+    assert relF(T, To) < bound and relF(Q, Qo) < bound
+    assert np.max(np.abs(lam - lo_)) <= 2e-7 * lo_[0]
+    if kind == "duplicates":       # (e_2k - e_2k+1) / sqrt 2 spans that space
+        N = T[:, 0::2].astype(np.float64) - T[:, 1::2]
+        want = np.zeros_like(N)
+        want[0::2], want[1::2] = np.eye(M // 2), -np.eye(M // 2)
+        assert relF(N, want / np.sqrt(eps)) < bound
+
+
+@pytest.mark.parametrize("M", [40, 700])
+def test_acceptance_sees_lost_orthogonality(M):
+    """The check behind the direct decomposition, called by itself: exact eigenvectors pass; a null vector that is a copy of
+    another, a zero one or a longer one fails by V V^T (V Phi V^T does not see it); two rows turned towards each other fail
+    by V Phi V^T alone."""
+    lib = b.lib
+    check = lib._ZN2fw13sym_eig_checkEPKfiPKdPdS4_PvdddS4_PiP12ihipStream_t
+    P = C.c_void_p
+    check.argtypes = [P, C.c_int, P, P, P, P, C.c_double, C.c_double, C.c_double, P, P, P]
+    ld, small, n = lib._ZN2fw10sym_eig_ldEi(M), lib._ZN2fw19sym_eig_small_bytesEi(M), lib._ZN2fw22sym_eig_matrix_doublesEi(M)
+    r = M // 4
+    Phi = torch.zeros(M, M, device=DEV)
+    Phi[:r, :r] = torch.diag(torch.linspace(1, 0.5, r, device=DEV))
+    q, _ = torch.linalg.qr(torch.as_tensor(np.random.default_rng(M).standard_normal((M - r, M - r))))
+    good = torch.eye(M, dtype=torch.float64)
+    good[r:, r:] = q               # any basis of the null space
+
+    def verdict(V):
+        Vd = torch.zeros(n, dtype=torch.float64, device=DEV)
+        Vd[:M * ld].view(M, ld)[:, :M] = V.to(DEV)
+        W, copy, lam = torch.zeros_like(Vd), torch.zeros_like(Vd), torch.zeros(M, dtype=torch.float64, device=DEV)
+        flag = torch.zeros(64, dtype=torch.int32, device=DEV)
+        ws = workspace(small)
+        rc = check(Phi.data_ptr(), M, Vd.data_ptr(), W.data_ptr(), copy.data_ptr(), ws.data_ptr(), 2.0 ** -34, 2.0 ** -30 * 1e-5, 0.0,
+                   lam.data_ptr(), flag.data_ptr(), torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert rc == 0
+        return [int(f != 0) for f in flag[:2].tolist()]
+
+    assert verdict(good) == [0, 0]
+    for row in (good[r + 1], 0 * good[r], 1.001 * good[r]):
+        V = good.clone()
+        V[r] = row
+        assert verdict(V) == [0, 1]
+    V = good.clone()
+    c, s = np.cos(1e-6), np.sin(1e-6)
+    V[0], V[r - 1] = c * good[0] + s * good[r - 1], c * good[r - 1] - s * good[0]
+    assert verdict(V) == [1, 0]
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+@pytest.mark.parametrize("M", [48, 200])
+def test_one_feature_not_finite(M, bad):
+    """A feature whose variance is not finite and that is correlated with no other: the direct decomposition leaves nothing, the sweeps
+    that start over from the identity never rotate that feature, so V stays orthogonal and T and Q finite."""
+    Phi32 = wl.spd_matrix(M, M, np.logspace(0, -3, M)).astype(np.float32)
+    Phi32[7, :] = 0
+    Phi32[:, 7] = 0
+    Phi32[7, 7] = bad
+    T, Q, _ = run_evd(Phi32)
+    assert np.isfinite(T).all() and np.isfinite(Q).all()
