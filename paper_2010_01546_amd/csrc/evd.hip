@@ -417,22 +417,41 @@ fw_status whiten_evd(const float* Phi_x, int M, const fw_evd_params* p, float* T
     const double tol = p->tol > 0.f ? (double)p->tol : 1e-12;
     const int max_sweeps = p->max_sweeps > 0 ? p->max_sweeps : 30;
 
-    double *V, *W;
-    fw_status rc = sym_eig(Phi_x, M, mat, base + L.small, &V, &W, st);
-    if (rc != FW_OK) return rc;
+    double *V = mat[2], *W = mat[3];
     // eigenvalues below the clamp all have the clamp's gain: entries far below it cannot move a gain
     const double floor_abs = p->gain_mode == 0 ? kAcceptClamp * (double)p->eps : 0.0;
     const double floor_rel = p->gain_mode == 1 ? kAcceptClamp / ((double)M * (double)p->g_max) : 0.0;
-    rc = sym_eig_check(Phi_x, M, V, W, mat[0], base + L.small, kAccept, floor_abs, floor_rel, lam, cnt, st);
+    // A Phi_x that is diagonal already (features whitened before, a fresh state) needs no decomposition: 1.6 ms -> 0.1 ms at M = 300.
+    // The look costs two launches and a wait, about 20 us; knowing that no feature is dead saves three launches again.
+    int verdict[2] = {1, 1};
+    fw_status rc = sym_eig_check_identity(Phi_x, M, base + L.small, kAccept, floor_abs, floor_rel, cnt, st);
     if (rc != FW_OK) return rc;
+    FW_HIP_TRY(hipMemcpyAsync(verdict, cnt, sizeof(verdict), hipMemcpyDeviceToHost, st));
+    FW_HIP_TRY(hipStreamSynchronize(st));
+    const bool diagonal = verdict[0] == 0;
+    if (diagonal) {
+        rc = sym_eig_load(Phi_x, M, mat[0], st);
+        if (rc != FW_OK) return rc;
+        rc = sym_eig_start_over(mat[0], M, V, W, st);
+        if (rc != FW_OK) return rc;
+        hipLaunchKernelGGL(eig_kernel, dim3((M + 3) / 4), dim3(256), 0, st, W, V, ld, M, lam);
+        FW_LAUNCH_CHECK();
+    } else {
+        rc = sym_eig(Phi_x, M, verdict[1] != 0, mat, base + L.small, &V, &W, st);
+        if (rc != FW_OK) return rc;
+        rc = sym_eig_check(Phi_x, M, V, W, mat[0], base + L.small, kAccept, floor_abs, floor_rel, lam, cnt, st);
+        if (rc != FW_OK) return rc;
+    }
     // the outputs are issued before the host looks at the verdict, so that the GPU does not wait for it; they leave mat[0], the
     // copy of Phi, alone (T or Q may lie where Phi_x was)
     float* X = reinterpret_cast<float*>(reinterpret_cast<char*>(mat[1]) + (evd_products_split(M) ? gemm_split_packed_bytes(M, M) : 0));
     rc = evd_outputs(V, M, p, lam, gq, gh, tot, X, mat[1], T, Q, lambda, st);
     if (rc != FW_OK) return rc;
-    int verdict[2] = {1, 1};
-    FW_HIP_TRY(hipMemcpyAsync(verdict, cnt, sizeof(verdict), hipMemcpyDeviceToHost, st));
-    FW_HIP_TRY(hipStreamSynchronize(st));
+    if (diagonal) verdict[1] = 0;
+    else {
+        FW_HIP_TRY(hipMemcpyAsync(verdict, cnt, sizeof(verdict), hipMemcpyDeviceToHost, st));
+        FW_HIP_TRY(hipStreamSynchronize(st));
+    }
     bool converged = verdict[0] == 0 && verdict[1] == 0 && !(p->tol > 0.f);
     if (!converged) {
         // rotations keep V as orthogonal as it is, so one that is not (a Phi_x with NaN or infinite entries leaves none) is

@@ -87,13 +87,12 @@ __device__ __forceinline__ void reflector(double ss, double alpha, double* tau, 
     *beta = b;
 }
 
-// Features that never vary have a zero row and column.  They are moved behind the others (perm[0 .. M-1] = source of each place,
-// perm[M] = how many of them): eliminated first, their rows give no reflector, so their eigenvectors stay exact unit vectors
+// Features that never vary have a zero row and column.  They are moved behind the others (perm[0 .. M-1] = source of each
+// place): eliminated first, their rows give no reflector, so their eigenvectors stay exact unit vectors
 // and no rounding noise of the others gets into them.  One workgroup.
 __global__ __launch_bounds__(1024) void dead_last_kernel(const float* __restrict__ Phi, int M, int* __restrict__ perm) {
     __shared__ int cnt[16], base_live;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int live_total = 0;
     for (int pass = 0; pass < 2; ++pass) {         // count, then place
         int live = 0;                              // live features before this chunk
         for (int c0 = 0; c0 < M; c0 += 1024) {
@@ -109,11 +108,9 @@ __global__ __launch_bounds__(1024) void dead_last_kernel(const float* __restrict
             live += all;
             __syncthreads();
         }
-        live_total = live;
         if (threadIdx.x == 0) base_live = live;
         __syncthreads();
     }
-    if (threadIdx.x == 0) perm[M] = M - live_total;
 }
 
 // A = symmetric part of Phi in float64, columns beyond M zero; rows and columns in the order of `perm` unless it is null
@@ -136,10 +133,9 @@ __global__ __launch_bounds__(256) void sym_load_kernel(const float* __restrict__
     }
 }
 
-// columns of V back to the caller's order through a second buffer (nothing to do when no feature was moved)
+// columns of V back to the caller's order through a second buffer
 __global__ __launch_bounds__(256) void restore_columns_kernel(const double* __restrict__ V, int M, int ld, const int* __restrict__ perm,
                                                               double* __restrict__ out, int back) {
-    if (perm[M] == 0) return;
     for (int j = blockIdx.x * 256 + threadIdx.x; j < M; j += gridDim.x * 256) {
         const size_t at = (size_t)blockIdx.y * ld;
         if (back) out[at + j] = V[at + j]; else out[at + perm[j]] = V[at + j];
@@ -936,6 +932,38 @@ __global__ __launch_bounds__(256) void residual_kernel(const double* __restrict_
     });
     if (__any(bad) && (threadIdx.x & 63) == 0) flag[blockIdx.z] = 1;
 }
+// The same scale for V = I, flag[0] cleared, flag[1] = is some diagonal entry zero: one workgroup
+__global__ __launch_bounds__(1024) void diagonal_scale_kernel(const float* __restrict__ Phi, int M, double floor_abs, double floor_rel,
+                                                              double* __restrict__ scale, int* __restrict__ flag) {
+    __shared__ double red[16];
+    __shared__ int zeros;
+    if (threadIdx.x == 0) zeros = 0;
+    __syncthreads();
+    double tr = 0.0;
+    bool zero = false;
+    for (int i = threadIdx.x; i < M; i += 1024) {
+        const double d = Phi[(size_t)i * M + i];
+        scale[i] = sqrt(fabs(d));
+        tr += d;
+        zero |= d == 0.0;
+    }
+    if (zero) zeros = 1;
+    tr = block_total<1024>(tr, red);      // its barrier also publishes `zeros`
+    if (threadIdx.x == 0) { scale[M] = fmax(floor_abs, floor_rel * tr); flag[0] = 0; flag[1] = zeros; }
+}
+// Does V = I pass the test of residual_kernel?  Both triangles against the bound, which their mean then meets as well.
+__global__ __launch_bounds__(256) void nearly_diagonal_kernel(const float* __restrict__ Phi, int M, double thr, const double* __restrict__ scale,
+                                                              int* __restrict__ flag) {
+    const double floor = scale[M];
+    int bad = 0;
+    for (int i = blockIdx.x; i < M; i += gridDim.x) {
+        const double si = thr * scale[i];
+        for (int j = threadIdx.x; j < M; j += 256)
+            if (j != i && !(fabs((double)Phi[(size_t)i * M + j]) <= fmax(si * scale[j], floor))) bad = 1;
+        if (__any(bad)) break;
+    }
+    if (__any(bad) && (threadIdx.x & 63) == 0) *flag = 1;
+}
 // T = V^T diag(g) V (z = 0) and Q = V^T diag(g^2) V (z = 1) as float32: lower tiles, mirrored on the way out
 __global__ __launch_bounds__(256) void spectral_product_kernel(const double* __restrict__ V, int ld, int M, const double* __restrict__ g,
                                                                float* __restrict__ o0, float* __restrict__ o1) {
@@ -953,7 +981,9 @@ __global__ __launch_bounds__(256) void spectral_product_kernel(const double* __r
     });
 }
 
-__global__ __launch_bounds__(256) void fill64_kernel(double* __restrict__ p, size_t n) {
+// three matrices, one per blockIdx.y
+__global__ __launch_bounds__(256) void fill64_kernel(double* __restrict__ p0, double* __restrict__ p1, double* __restrict__ p2, size_t n) {
+    double* p = blockIdx.y == 0 ? p0 : blockIdx.y == 1 ? p1 : p2;
     for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < n; e += (size_t)gridDim.x * 256) p[e] = 0.0;
 }
 __global__ __launch_bounds__(256) void start_over_kernel(const double* __restrict__ copy, int ld, size_t n, double* __restrict__ V,
@@ -1022,9 +1052,9 @@ size_t sym_eig_matrix_doubles(int M) {
     return a > b ? a : b;
 }
 
-// Eigenvectors of the symmetric part of Phi as rows, ascending eigenvalues.  buf[0..3]: four matrices of
+// Eigenvectors of the symmetric part of Phi as rows, ascending eigenvalues.  dead: some diagonal entry is zero.  buf[0..3]: four matrices of
 // sym_eig_matrix_doubles(M); on return *V and *free_buf name the buffer with the eigenvectors and one that is free.
-fw_status sym_eig(const float* Phi, int M, double* const buf[4], void* small, double** V, double** free_buf, hipStream_t st) {
+fw_status sym_eig(const float* Phi, int M, bool dead, double* const buf[4], void* small, double** V, double** free_buf, hipStream_t st) {
     const int ld = sym_eig_ld(M);
     const SmallWs L = small_layout(M);
     char* sb = reinterpret_cast<char*>(small);
@@ -1033,11 +1063,9 @@ fw_status sym_eig(const float* Phi, int M, double* const buf[4], void* small, do
     double *d = dbl(L.d), *e = dbl(L.e), *tau = dbl(L.tau), *p[2] = {dbl(L.p0), dbl(L.p1)};
     int* perm = reinterpret_cast<int*>(sb + L.ints) + 8 * ((size_t)M + 64);
     const size_t nn = (size_t)M * ld;
-    hipLaunchKernelGGL(dead_last_kernel, dim3(1), dim3(1024), 0, st, Phi, M, perm);
-    hipLaunchKernelGGL(sym_load_kernel, dim3((ld + 31) / 32, (M + 31) / 32), dim3(256), 0, st, Phi, M, ld, perm, A);
-    hipLaunchKernelGGL(fill64_kernel, dim3(grid_for(nn)), dim3(256), 0, st, Y, nn);
-    hipLaunchKernelGGL(fill64_kernel, dim3(grid_for(nn)), dim3(256), 0, st, Va, nn);
-    hipLaunchKernelGGL(fill64_kernel, dim3(grid_for(nn)), dim3(256), 0, st, Vb, nn);
+    if (dead) hipLaunchKernelGGL(dead_last_kernel, dim3(1), dim3(1024), 0, st, Phi, M, perm);
+    hipLaunchKernelGGL(sym_load_kernel, dim3((ld + 31) / 32, (M + 31) / 32), dim3(256), 0, st, Phi, M, ld, dead ? perm : nullptr, A);
+    hipLaunchKernelGGL(fill64_kernel, dim3(grid_for(nn), 3), dim3(256), 0, st, Y, Va, Vb, nn);
     int c = M - 1, first = 1, cur = 0;
     for (; c >= TAIL; --c, first = 0, cur ^= 1)
         step(A, ld, c, first, Y + (size_t)(c + 1 < M ? c + 1 : c) * ld, p[cur ^ 1], Y + (size_t)c * ld, p[cur], d, e, tau, st);
@@ -1088,8 +1116,10 @@ fw_status sym_eig(const float* Phi, int M, double* const buf[4], void* small, do
         hipLaunchKernelGGL(wy_multiply_kernel, dim3((M + 15) / 16), dim3(256), 0, st, part, slices, F + (size_t)b * NB * NB, M, G);
         hipLaunchKernelGGL(wy_update_kernel, dim3((kmax + 63) / 64, rt), dim3(256), 0, st, G, Y, ld, M, c0, kmax, Va);
     }
-    hipLaunchKernelGGL(restore_columns_kernel, dim3((M + 1023) / 1024, M), dim3(256), 0, st, Va, M, ld, perm, Vb, 0);
-    hipLaunchKernelGGL(restore_columns_kernel, dim3((M + 1023) / 1024, M), dim3(256), 0, st, Vb, M, ld, perm, Va, 1);
+    if (dead) {
+        hipLaunchKernelGGL(restore_columns_kernel, dim3((M + 1023) / 1024, M), dim3(256), 0, st, Va, M, ld, perm, Vb, 0);
+        hipLaunchKernelGGL(restore_columns_kernel, dim3((M + 1023) / 1024, M), dim3(256), 0, st, Vb, M, ld, perm, Va, 1);
+    }
     FW_LAUNCH_CHECK();
     *V = Va; *free_buf = Vb;
     return FW_OK;
@@ -1111,7 +1141,25 @@ fw_status sym_eig_check(const float* Phi, int M, const double* V, double* W, dou
     return FW_OK;
 }
 
-// V = I and W = the symmetric part of Phi that sym_eig_check left in `copy`: where the sweeps start without a decomposition
+// on the device flag[0] != 0 unless V = I passes the test of sym_eig_check, flag[1] != 0 if some diagonal entry is zero
+fw_status sym_eig_check_identity(const float* Phi, int M, void* small, double thr, double floor_abs, double floor_rel, int* flag,
+                                 hipStream_t st) {
+    double* scale = reinterpret_cast<double*>(reinterpret_cast<char*>(small) + small_layout(M).scale);
+    hipLaunchKernelGGL(diagonal_scale_kernel, dim3(1), dim3(1024), 0, st, Phi, M, floor_abs, floor_rel, scale, flag);
+    hipLaunchKernelGGL(nearly_diagonal_kernel, dim3(M < 1024 ? M : 1024), dim3(256), 0, st, Phi, M, thr, scale, flag);
+    FW_LAUNCH_CHECK();
+    return FW_OK;
+}
+
+// the symmetric part of Phi in float64
+fw_status sym_eig_load(const float* Phi, int M, double* copy, hipStream_t st) {
+    const int ld = sym_eig_ld(M);
+    hipLaunchKernelGGL(sym_load_kernel, dim3((ld + 31) / 32, (M + 31) / 32), dim3(256), 0, st, Phi, M, ld, nullptr, copy);
+    FW_LAUNCH_CHECK();
+    return FW_OK;
+}
+
+// V = I and W = the symmetric part of Phi that sym_eig_check or sym_eig_load left in `copy`
 fw_status sym_eig_start_over(const double* copy, int M, double* V, double* W, hipStream_t st) {
     const size_t nn = (size_t)M * sym_eig_ld(M);
     hipLaunchKernelGGL(start_over_kernel, dim3(grid_for(nn)), dim3(256), 0, st, copy, sym_eig_ld(M), nn, V, W);

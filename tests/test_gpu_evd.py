@@ -211,3 +211,31 @@ def test_one_feature_not_finite(M, bad):
     Phi32[7, 7] = bad
     T, Q, _ = run_evd(Phi32)
     assert np.isfinite(T).all() and np.isfinite(Q).all()
+
+
+@pytest.mark.parametrize("M", [1, 2, 63, 300, 1600])
+@pytest.mark.parametrize("kw", [{}, {"gain_mode": 1}, {"tol": 1e-12}])
+def test_diagonal_and_nearly_diagonal(M, kw):
+    """Matrices that need no decomposition (diagonal; off-diagonal entries a tenth of what the acceptance allows), and one whose single
+    off-diagonal entry, in either triangle, is just too large for that: T, Q, eigenvalues and Q_s against the oracle."""
+    rng = np.random.default_rng(M)
+    d = rng.permutation(np.logspace(1, -4, M))
+    d[: M // 8] = 0
+    kind = [np.diag(d)]
+    noise = rng.uniform(-1, 1, (M, M)) * 0.1 * 2.0 ** -34 * np.sqrt(np.outer(d, d))
+    kind.append(np.diag(d) + np.tril(noise, -1) + np.tril(noise, -1).T)
+    if M > 10:
+        i, j = int(np.argsort(d)[-1]), int(np.argsort(d)[-2])
+        for at in ((i, j), (j, i)):
+            P = np.diag(d)
+            P[at] = 0.01 * np.sqrt(d[i] * d[j])
+            kind.append(P)
+    bound = 2e-5 if M >= b.FW_REFRESH_SPLIT_MIN_M else 1e-5
+    for Phi in kind:
+        Phi32 = Phi.astype(np.float32)
+        Qs = dev(np.eye(M, dtype=np.float32))
+        T, Q, lam = run_evd(Phi32, Qs=Qs, eps=1e-3, beta=0.5, **kw)
+        To, Qo, lo_ = ora.whiten_evd(Phi32, eps=1e-3, gain_mode=kw.get("gain_mode", 0))
+        assert relF(T, To) < bound and relF(Q, Qo) < bound
+        assert np.max(np.abs(lam - lo_)) <= 2e-7 * max(lo_[0], 1e-30)
+        assert relF(Qs.cpu().numpy(), ora.smooth_Q(np.eye(M), Qo, 0.5)) < bound
