@@ -364,7 +364,7 @@ def rooflines_of(r, layer, b, cfg_key, layout_name):
     rpeak = PEAK["bf16" if rp.split else "f32"]
     rf = {"bound": "mfma", "export": "fw_cond_state_refresh",
           "kernel": ("3 x split_pack + 2 x gemm_split (bf16 hi/lo operands, 3 MFMA terms per product) + mirror + row norms" if rp.split
-                     else "2 x grad_gemm_f32_strip + mirror + row norms"),
+                     else "2 x grad_gemm_f32_strip (second: lower triangle) + mirror_norm_rows"),
           "achieved": rp.mfma_flops_issued / t4 / 1e12, "peak": rpeak / 1e12, "unit": "TFLOP/s",
           "frac": rp.mfma_flops_issued / t4 / rpeak, "ms": ex["cond_state_refresh"], "mfma_flops_issued": rp.mfma_flops_issued,
           "float32_equivalent_rate_TFLOPs": 4.0 * M ** 3 / t4 / 1e12,

@@ -256,8 +256,9 @@ fw_status fw_cond_state_init(const fw_cond_state* st, void* stream);
 #define FW_REFRESH_SPLIT_MIN_M 1536
 
 /* How fw_cond_state_refresh would run for a given M and workspace size (host arithmetic only): which form the two
- * products take and the flops the matrix cores execute for them (split form: bfloat16 flops, three terms per float32
- * multiplication, whole tiles, lower triangle only for Phi_y; float32 form: 4 M^3). */
+ * products take and the flops the matrix cores execute for them, whole tiles, lower triangle only for Phi_y (split form: bfloat16
+ * flops, three terms per float32 multiplication; float32 form: about 3 M^3 in float32; up to 128 features, 80 where M is no
+ * multiple of 4, both products in full). */
 typedef struct { int split; double mfma_flops_issued; } fw_refresh_plan;
 fw_status fw_cond_refresh_plan_query(int M, size_t ws_bytes, fw_refresh_plan* plan);
 fw_status fw_cond_state_refresh(const fw_cond_state* st, void* ws, size_t ws_bytes, void* stream);

@@ -971,26 +971,32 @@ size_t cond_refresh_workspace_bytes(int M) {
     return align_up((size_t)M * M * sizeof(float), 256) + 3 * gemm_split_packed_bytes(M, M) + refresh_xpart_bytes(M);
 }
 
+static bool refresh_in_rows(int M) { return M <= ((M & 3) == 0 ? REFRESH_ROWS_MAX_M : REFRESH_ROWS_MAX_M_UNALIGNED); }
+
 bool cond_refresh_plan(int M, size_t ws_bytes, fw_refresh_plan* plan) {
     if (M <= 0 || M > 16384) return false;
     plan->split = (ws_bytes >= cond_refresh_workspace_bytes(M) && M >= FW_REFRESH_SPLIT_MIN_M) ? 1 : 0;
     if (plan->split) plan->mfma_flops_issued = gemm_split_flops_issued(M, M, M, 0) + gemm_split_flops_issued(M, M, M, 1);
-    else plan->mfma_flops_issued = 4.0 * (double)M * M * M;
+    else if (refresh_in_rows(M)) {       // two products of every 16 x 16 tile, the contraction index in rounds of 64
+        const double nt = (M + 15) / 16;
+        plan->mfma_flops_issued = 2.0 * nt * nt * 2.0 * 256.0 * ((M + 63) / 64 * 64);
+    } else plan->mfma_flops_issued = grad_gemm_f32_flops_issued(M, M, false) + grad_gemm_f32_flops_issued(M, M, true);
     return true;
 }
 
 // New block, new Phi_x: Psi = T Phi_x and Phi_y = T Phi_x T^T = Psi T^T by two M x M x M products, Phi_y made exactly
-// symmetric from its lower triangle, and the squared row norms for the arg-max.  Both products have the form A B^T with
+// symmetric from its lower triangle, and the squared row norms for the arg-max.  Few features: all of it in one launch
+// (refresh_rows_kernel).  Otherwise both products have the form A B^T with
 // row-major operands: Phi_x is symmetric (its rows stand for its columns), and T is exactly the factor wanted.
 // With the full workspace the operands are split into bfloat16 hi + lo planes and multiplied on the bfloat16 matrix
-// cores (three products per term, float32 accumulation: see gemm_split.hip), only the lower triangle of Phi_y being
-// computed; without it (allowed when the state carries Psi) the products run in plain float32 on the matrix cores.
+// cores (three products per term, float32 accumulation: see gemm_split.hip); without it (allowed when the state carries
+// Psi) the products run in plain float32 on the matrix cores.  Only the lower triangle of Phi_y is computed either way.
 fw_status cond_state_refresh(const fw_cond_state* s, void* ws, size_t ws_bytes, hipStream_t st) {
     const int M = s->M;
     const size_t psi_bytes = align_up((size_t)M * M * sizeof(float), 256);
     char* base = reinterpret_cast<char*>(ws);
     float* Psi = s->Psi ? s->Psi : reinterpret_cast<float*>(base);
-    if (M <= ((M & 3) == 0 ? REFRESH_ROWS_MAX_M : REFRESH_ROWS_MAX_M_UNALIGNED)) {
+    if (refresh_in_rows(M)) {
         const dim3 grid((M + 15) / 16), blk(64 * ((M + 15) / 16));
         if ((M & 3) == 0) hipLaunchKernelGGL(refresh_rows_kernel<true>, grid, blk, 0, st, s->T, s->Phi_x, M, Psi, s->Phi_y, s->xi2);
         else hipLaunchKernelGGL(refresh_rows_kernel<false>, grid, blk, 0, st, s->T, s->Phi_x, M, Psi, s->Phi_y, s->xi2);

@@ -157,6 +157,7 @@ struct GemmEpilogue {
 size_t grad_gemm_partial_bytes(int S, int M);
 fw_status grad_gemm(const void* G, fw_dtype dt, int S, int M, const float* Q, void* G_out, hipStream_t st, float* part = nullptr);
 fw_status grad_gemm_f32(const float* G, int S, int M, const float* Q, const GemmEpilogue& e, hipStream_t st, float* part = nullptr, bool lower = false);
+double grad_gemm_f32_flops_issued(int S, int M, bool lower);
 fw_status grad_stage_rows(const void* G, fw_dtype dt, int S, int M, int taps, float* dst, hipStream_t st);
 fw_status grad_epilogue_from_runs(const float* part, int nks, const GemmEpilogue& e, int S, int M, hipStream_t st);
 

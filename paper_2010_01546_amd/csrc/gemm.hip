@@ -534,6 +534,25 @@ fw_status grad_gemm_f32(const float* G, int S, int M, const float* Q, const Gemm
     return FW_OK;
 }
 
+// what the matrix cores execute in grad_gemm_f32 for a plain result without runs: whole tiles and chunks
+double grad_gemm_f32_flops_issued(int S, int M, bool lower) {
+    lower = lower && S == M;
+    if ((M & 3) != 0) {
+        const double tr = (S + 31) / 32, tiles = lower ? 0.5 * tr * (tr + 1.0) : tr * ((M + 31) / 32);
+        const int kq = ((M + 3) / 4 + 1) & ~1;
+        double k = 0.0;                 // every wavefront's slice in steps of two
+        for (int w = 0; w < 4; ++w) {
+            const int n = (M < (w + 1) * kq ? M : (w + 1) * kq) - w * kq;
+            if (n > 0) k += (n + 1) / 2 * 2;
+        }
+        return 2.0 * tiles * 32.0 * 32.0 * k;
+    }
+    const StripChoice ch = pick_strip(S, M, true, false, lower);
+    const long long tr = (S + ch.mf - 1) / ch.mf, strips = ((M + ch.mf - 1) / ch.mf + ch.c - 1) / ch.c;
+    const int kc = 4 * (ch.mf == 32 ? 8 : 16) * strip_u(ch.mf, ch.c);
+    return 2.0 * (double)(lower ? lower_strips(tr, ch.c) : tr * strips) * ch.c * ch.mf * ch.mf * (double)((M + kc - 1) / kc * kc);
+}
+
 // Epilogue applied to a product that sits in the workspace as `nks` partial results [nks][S][M] (M a multiple of 4): the
 // runs are added in order and every element goes where `e` says (store, per-tap position, rounding, weight update)
 fw_status grad_epilogue_from_runs(const float* part, int nks, const GemmEpilogue& e, int S, int M, hipStream_t st) {

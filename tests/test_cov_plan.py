@@ -136,14 +136,25 @@ def test_plan_invariants_on_random_layers():
 
 def test_refresh_plan():
     """The refresh takes the split form only with the full workspace and from FW_REFRESH_SPLIT_MIN_M features on; its
-    issued flops are three bfloat16 terms per product on whole tiles, the second product on the lower triangle only."""
+    issued flops are three bfloat16 terms per product on whole tiles.  The second product is on the lower triangle only in
+    either form."""
     full = b.fw_workspace_bytes(b.FW_OP_COND_STATE_REFRESH, 4608)
     p = b.fw_cond_refresh_plan_query(4608, full)
     assert p.split == 1
     dense = 2.0 * 4608 ** 3
     assert 3 * dense * 1.5 <= p.mfma_flops_issued <= 3 * dense * 1.7        # one full product + a good half
     assert b.fw_cond_refresh_plan_query(4608, full - 256).split == 0
-    assert b.fw_cond_refresh_plan_query(4608, 0).mfma_flops_issued == 2 * dense
+    # float32 form: the first product in full, of the second only the strips (or 32 x 32 tiles) that touch the lower triangle,
+    # a strip being at most 9 tiles of 32 wide; whole tiles and chunks of up to 256 contraction entries besides
+    for M in (132, 147, 576, 777, 1152, 1532, 4608, 4609):
+        f = b.fw_cond_refresh_plan_query(M, 0).mfma_flops_issued
+        full, tile = 2.0 * M ** 3, -(-M // 32) * 32.0
+        low, high = full + M * M * (M + 1.0), 2.0 * tile * (tile + 0.5 * tile + 288) * (M + 256)
+        assert low <= f <= high, (M, f / full)
+        assert M < 1000 or f < 1.75 * full, (M, f / full)
+    # few features: one launch, both products of every 16 x 16 tile
+    assert b.fw_cond_refresh_plan_query(128, 0).mfma_flops_issued == 4.0 * 128 ** 3
+    assert b.fw_cond_refresh_plan_query(75, 0).mfma_flops_issued == 4.0 * 80 * 80 * 128
     small = b.fw_cond_refresh_plan_query(b.FW_REFRESH_SPLIT_MIN_M - 64, 1 << 40)
     assert small.split == 0
     assert b.fw_cond_refresh_plan_query(b.FW_REFRESH_SPLIT_MIN_M, 1 << 40).split == 1
