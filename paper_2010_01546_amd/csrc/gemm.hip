@@ -302,6 +302,9 @@ inline StripChoice pick_strip(int S, int M, bool plain, bool can_split, bool low
         const long long tr = (S + mf - 1) / mf, tc = (M + mf - 1) / mf;
         const long long wgs = low ? lower_strips(tr, c) : tr * ((tc + c - 1) / c);
         const double rounds = (double)((wgs + 255) / 256);
+        // thousands of strips of a single 16-wide tile lose more to starting up than the count below knows of (1284 .. 1296 features:
+        // 160 us a refresh with the whole product, 191 us with such strips of its triangle)
+        if (low && mf == 16 && c == 1 && rounds > 8.0) return;
         const double kpad = (double)((M + kc - 1) / kc * kc) / M;
         // a 16x16 tile is a quarter of the MFMA work of a 32x32 tile and reads twice the operands per flop;
         // a wider strip reads fewer operands per MFMA

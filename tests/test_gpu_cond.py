@@ -117,7 +117,7 @@ def test_config1_sixteen_steps():
     assert applied >= 8
 
 
-@pytest.mark.parametrize("M", [147, 160, 242, 255, 256, 404, 512, 516, 525, 576, 580, 764, 900, 1028, 1151, 1152, 1300, 1532, 2044, 2047, 2048, 2052])
+@pytest.mark.parametrize("M", [147, 160, 242, 255, 256, 404, 512, 516, 525, 576, 580, 764, 900, 1028, 1151, 1152, 1288, 1300, 1532, 2044, 2047, 2048, 2052])
 def test_float32_refresh_strips_of_the_lower_triangle(M):
     """Of Phi_y = Psi T^T only the strips that touch the lower triangle are multiplied, whatever strip width a size takes; the mirror
     image and the row norms (one launch up to 2048 features) have to fill the rest.  Float32 products (no workspace), tolerance as above."""
