@@ -152,10 +152,11 @@ __device__ __forceinline__ bool pixel_is_covered(const TileCore& g, int yp, int 
 // One thread per (chunk of image groups, padded pixel, channel); it walks its image groups, so the sum it leaves in
 // S8[chunk][yp][xp][c] has a fixed order of additions.
 // The first row of workgroups also writes the unit table.
-// Channels-last sources: a wavefront reads and writes along the channels (NCHW has a kernel of its own below).
+// Channels-last sources: a wavefront reads and writes along the channels.  NCHW: it reads along x and writes with a stride of Cin
+// elements (the kernel below reads and writes along rows; see there where which one is taken).
 // SPLIT: the source is a float32 tensor with g.Cin / 2 channels; packed channel c < Cin / 2 takes hi = bf16(x) of source
 // channel c, packed channel Cin / 2 + c takes lo = bf16(x - hi) (the split form of float32 moments, see cov.hip).
-template <bool SHIFT, bool SPLIT>
+template <bool SHIFT, bool SPLIT, bool NCHW>
 __global__ __launch_bounds__(256) void pack_images_kernel(const void* __restrict__ Xv, std::conditional_t<SHIFT, TileGeom, TileCore> g,
                                                           uint4* __restrict__ P,
                                                           float* __restrict__ S8, int* __restrict__ utab) {
@@ -166,7 +167,7 @@ __global__ __launch_bounds__(256) void pack_images_kernel(const void* __restrict
     const int chunk = blockIdx.y;
     if (chunk == 0) write_unit_table<SHIFT>(g, e, (int)gridDim.x * 256, P, utab);
     if (e >= per_img) return;
-    const int c = e % g.Cin, pix = e / g.Cin, xp = pix % g.Wp, yp = pix / g.Wp;
+    const int pix = NCHW ? e % (g.Hp * g.Wp) : e / g.Cin, c = NCHW ? e / (g.Hp * g.Wp) : e % g.Cin, xp = pix % g.Wp, yp = pix / g.Wp;
     if (!pixel_is_covered(g, yp, xp)) return;            // neither read nor written
     const int y = yp - g.py, x = xp - g.px;
     const bool inside = (unsigned)y < (unsigned)g.H && (unsigned)x < (unsigned)g.W;
@@ -176,7 +177,7 @@ __global__ __launch_bounds__(256) void pack_images_kernel(const void* __restrict
     // 32-bit element indices (the planner takes tensors below 2^31 elements only): with 64-bit ones the address arithmetic of
     // eight loads cost this bandwidth-bound pass 5 %
     const unsigned img_stride = (unsigned)Csrc * g.H * g.W;
-    const unsigned src0 = inside ? ((unsigned)y * g.W + x) * Csrc + csrc : 0u;
+    const unsigned src0 = !inside ? 0u : NCHW ? ((unsigned)csrc * g.H + y) * g.W + x : ((unsigned)y * g.W + x) * Csrc + csrc;
     const int dst0 = (yp * g.Wp + xp) * g.Cin + c;
     const int bg0 = chunk * g.bg_per_chunk, bg1 = min(g.Bg, bg0 + g.bg_per_chunk);
     float acc = 0.f;
@@ -212,7 +213,8 @@ __global__ __launch_bounds__(256) void pack_images_kernel(const void* __restrict
 
 // The same pre-pass for NCHW sources: the reads want to run along x, the writes along the channels.  A workgroup takes
 // PT padded pixels x CT channels (1024 elements, four per thread), reads each channel's pixels along the row, and turns
-// the tile in LDS, so that what it writes is whole runs of CT x 16 bytes (of the full tile where CT covers all channels).
+// the tile in LDS, so that what it writes is whole runs of CT x 16 bytes (of the full tile where CT covers all channels).  Taken
+// for large tensors, see pack_in_tiles.
 // The tile has two buffers: the next image group is read while this one is written.
 // Element by element (reads along x, writes scattered at Cin x 16 bytes) this pass took 59 us for 256 x 3 x 224 x 224 and
 // 58 us for 256 x 128 x 28 x 28, against 27 and 18 us at the rate of a copy.
@@ -226,7 +228,7 @@ __global__ __launch_bounds__(256) void pack_nchw_kernel(const u16* __restrict__ 
     if (chunk == 0) write_unit_table<SHIFT>(g, (int)blockIdx.x * 256 + (int)threadIdx.x, (int)gridDim.x * 256, P, utab);
     const int ncb = (g.Cin + CT - 1) / CT;
     const int pix0 = ((int)blockIdx.x / ncb) * PT, c0 = ((int)blockIdx.x % ncb) * CT;
-    const long long img_stride = (long long)g.Cin * g.H * g.W;
+    const unsigned img_stride = (unsigned)g.Cin * g.H * g.W;     // 32-bit element indices, as above
     // element k of this thread on the reading side: pixel ri % PT, channel ri / PT; on the writing side: channel fastest
     int src[NE];
     float acc[NE];
@@ -245,7 +247,7 @@ __global__ __launch_bounds__(256) void pack_nchw_kernel(const u16* __restrict__ 
 #pragma unroll
         for (int k = 0; k < NE; ++k)
 #pragma unroll
-            for (int i = 0; i < 8; ++i) v[k][i] = X[src[k] >= 0 && bg * 8 + i < g.B ? (long long)(bg * 8 + i) * img_stride + src[k] : 0];
+            for (int i = 0; i < 8; ++i) v[k][i] = X[src[k] >= 0 && bg * 8 + i < g.B ? (unsigned)(bg * 8 + i) * img_stride + (unsigned)src[k] : 0u];
 #pragma unroll
         for (int k = 0; k < NE; ++k) {
 #pragma unroll
@@ -1189,6 +1191,17 @@ size_t cov_bf16_workspace_bytes(const fw_conv_desc* d, fw_layout lay) {
 }
 
 // split_f32: X is a float32 tensor with d->Cin / 2 channels, taken as hi + lo bfloat16 planes (d describes the doubled tensor)
+// Which packing pass an NCHW tensor takes.  The tiles pay from a few MB of packed elements on, and later where the tile is four
+// channels wide; a stride beyond the window leaves pixels that the element-wise pass does not touch.  Whole calls, element-wise
+// first: 0.9 M elements (8 x 100 x 33 x 33 and the like) 28.0 / 29.3 us, 2.4 M about even, 6 M and more 8 to 30 % faster in tiles
+// (256 x 128 x 28 x 28: 58 / 25 us for the pass alone); 4 channels: 1.2 M 25 / 26.5 us, 3.2 M even; 64 x 200 x 64 x 64, 1x1
+// stride 2: 100 / 146 us.
+static bool pack_in_tiles(const TileGeom& g) {
+    if (g.stride > g.kh || g.stride > g.kw) return false;
+    const long long packed = (long long)g.Bg * 8 * g.Hp * g.Wp * g.Cin;
+    return packed >= (g.Cin <= 8 && g.Cin != 3 ? 3100000 : 2100000);
+}
+
 fw_status cov_bf16_accumulate(const void* X, fw_layout lay, const fw_conv_desc* d, float* A, float* s, void* ws, size_t ws_bytes,
                               hipStream_t st, bool split_f32) {
     TileGeom g;
@@ -1204,8 +1217,8 @@ fw_status cov_bf16_accumulate(const void* X, fw_layout lay, const fw_conv_desc* 
     const int per_img = g.Hp * g.Wp * g.Cin;
     const TileCore& core = g;   // the direct form's kernels take the geometry without the regions
     const dim3 pgrid((per_img + 255) / 256, g.bg_chunks);
-    if (lay == FW_LAYOUT_NCHW) {        // (a float32 tensor comes here channels-last)
-        if (split_f32) return FW_ERR_UNSUPPORTED;
+    if (lay == FW_LAYOUT_NCHW && split_f32) return FW_ERR_UNSUPPORTED;     // (a float32 tensor comes here channels-last)
+    if (lay == FW_LAYOUT_NCHW && pack_in_tiles(g)) {
         const u16* x = reinterpret_cast<const u16*>(X);
         const int npix = g.Hp * g.Wp;
         const dim3 g16(((npix + 63) / 64) * ((g.Cin + 15) / 16), g.bg_chunks), g4(((npix + 255) / 256) * ((g.Cin + 3) / 4), g.bg_chunks);
@@ -1221,10 +1234,12 @@ fw_status cov_bf16_accumulate(const void* X, fw_layout lay, const fw_conv_desc* 
             else hipLaunchKernelGGL((pack_nchw_kernel<false, 16>), g16, dim3(256), 0, st, x, core, P, S8, utab);
         }
     }
-    else if (g.shift && split_f32) hipLaunchKernelGGL((pack_images_kernel<true, true>), pgrid, dim3(256), 0, st, X, g, P, S8, utab);
-    else if (g.shift) hipLaunchKernelGGL((pack_images_kernel<true, false>), pgrid, dim3(256), 0, st, X, g, P, S8, utab);
-    else if (split_f32) hipLaunchKernelGGL((pack_images_kernel<false, true>), pgrid, dim3(256), 0, st, X, core, P, S8, utab);
-    else hipLaunchKernelGGL((pack_images_kernel<false, false>), pgrid, dim3(256), 0, st, X, core, P, S8, utab);
+    else if (lay == FW_LAYOUT_NCHW && g.shift) hipLaunchKernelGGL((pack_images_kernel<true, false, true>), pgrid, dim3(256), 0, st, X, g, P, S8, utab);
+    else if (lay == FW_LAYOUT_NCHW) hipLaunchKernelGGL((pack_images_kernel<false, false, true>), pgrid, dim3(256), 0, st, X, core, P, S8, utab);
+    else if (g.shift && split_f32) hipLaunchKernelGGL((pack_images_kernel<true, true, false>), pgrid, dim3(256), 0, st, X, g, P, S8, utab);
+    else if (g.shift) hipLaunchKernelGGL((pack_images_kernel<true, false, false>), pgrid, dim3(256), 0, st, X, g, P, S8, utab);
+    else if (split_f32) hipLaunchKernelGGL((pack_images_kernel<false, true, false>), pgrid, dim3(256), 0, st, X, core, P, S8, utab);
+    else hipLaunchKernelGGL((pack_images_kernel<false, false, false>), pgrid, dim3(256), 0, st, X, core, P, S8, utab);
     FW_LAUNCH_CHECK();
     const dim3 grid(g.shift && !g.spread ? 8 * g.ntiles * ((g.nsplit + 7) / 8) : (g.ntiles * g.nsplit + 7) / 8 * 8);
 #define FW_TILE_LAUNCH(R, C, S, G) hipLaunchKernelGGL((cov_bf16_tile_kernel<R, C, S>), grid, dim3(256), 0, st, P, utab, G, part, A)
