@@ -156,8 +156,20 @@ def test_few_rows_in_one_launch(n_rows, M, dtype):
 @pytest.mark.parametrize("Cin", [1, 3, 4, 5, 8, 9, 16, 17, 40])
 @pytest.mark.parametrize("B,H,W,k,stride,pad", [(9, 7, 11, 3, 1, 1), (17, 9, 8, 2, 3, 0), (8, 23, 19, 7, 2, 3), (3, 5, 5, 3, 2, 1)])
 def test_nchw_tensors_give_the_sums_of_their_channels_last_copies(B, Cin, H, W, k, stride, pad):
-    """bfloat16 NCHW input goes through a packing kernel of its own (tiles of 3, 4 or 16 channels, 64 or 256 pixels); from there
-    on both layouts run the same kernels on the same numbers, so the results are equal bit by bit."""
+    """bfloat16 NCHW input is packed reading along x; from there on both layouts run the same kernels on the same numbers, so the
+    results are equal bit by bit."""
+    nchw_against_channels_last(B, Cin, H, W, k, stride, pad)
+
+
+@pytest.mark.parametrize("B,Cin,H,W,k,stride,pad", [(61, 3, 103, 105, 7, 2, 3), (64, 5, 101, 98, 2, 2, 0), (65, 8, 77, 81, 3, 2, 1), (63, 9, 63, 61, 3, 2, 1),
+                                                    (64, 16, 44, 46, 3, 1, 1), (57, 17, 47, 45, 3, 1, 1), (40, 40, 35, 38, 2, 2, 0), (64, 1, 225, 220, 2, 2, 1)])
+def test_large_nchw_tensors_packed_in_tiles(B, Cin, H, W, k, stride, pad):
+    """The same from the sizes on where the packing turns tiles of 3, 4 or 16 channels x 64 or 256 pixels in LDS: ragged pixel and
+    channel tiles, a ragged last group of images."""
+    nchw_against_channels_last(B, Cin, H, W, k, stride, pad)
+
+
+def nchw_against_channels_last(B, Cin, H, W, k, stride, pad):
     g = torch.Generator().manual_seed(Cin * 100 + H)
     x = torch.randn(B, Cin, H, W, generator=g).to(torch.bfloat16)
     d = b.conv_desc(B, Cin, H, W, kh=k, kw=k, stride=stride, pad=pad)
