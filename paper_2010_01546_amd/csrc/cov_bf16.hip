@@ -1070,11 +1070,15 @@ bool build_tile_geom(const fw_conv_desc* d, fw_layout lay, TileGeom* g) {
                 if (cost < best * 0.999) { best = cost; best_nrt = nrt; best_nct = nct; best_ns = ns; }
             }
         }
-    // All features in one tile (up to 224, see the measurements at the kernel): the symmetric kernel.  A chunk of eight units costs the larger of its loads (one panel) and
-    // its MFMAs (two wavefronts per SIMD, each half of the units).
+    // All features in one tile (up to 224, see the measurements at the kernel): the symmetric kernel.  A chunk of eight units costs
+    // the larger of its loads (one panel) and its MFMAs (two wavefronts per SIMD, each half of the units).
+    // Six blocks (161 .. 192 features) only from 24576 rows on: 162 to 192 features, 200 to 4000 rows 13.4 us in the general form,
+    // 14.4 here (same ratio throughout), even at 20000, 1.03 to 1.1 times as fast here from 32000 on; the other counts are as
+    // fast or faster here at any number of rows.
     g->sym = 0;
-    if (M <= 224) {
-        const int nb = M <= 64 ? 2 : (int)((M + 31) / 32), ng = (nb + 1) / 2, tc = 64 * ng;
+    const int nb = M <= 64 ? 2 : (int)((M + 31) / 32);
+    if (M <= 224 && !(nb == 6 && n_units < 24576 / 8)) {
+        const int ng = (nb + 1) / 2, tc = 64 * ng;
         const long long nch8 = (n_units + 7) / 8;
         const double t_mfma = 2.0 * 2.0 * ((nb * (nb + 1) / 2 + 3) / 4) * 32.0 + 150.0, t_load = (double)tc * 8.0 * 16.0 / lds_load_rate;
         const double t_chunk = (t_mfma > t_load ? t_mfma : t_load) / clk;

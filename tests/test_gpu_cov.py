@@ -189,10 +189,10 @@ def nchw_against_channels_last(B, Cin, H, W, k, stride, pad):
 @pytest.mark.parametrize("lay", [b.FW_LAYOUT_NHWC, b.FW_LAYOUT_NHWC_KKC])
 @pytest.mark.parametrize("Cin,kh,kw", [(3, 3, 3), (7, 3, 3), (8, 3, 3), (11, 3, 3), (16, 4, 2), (15, 3, 3), (16, 3, 3), (18, 3, 3), (21, 3, 3), (23, 3, 3),
                                        (56, 2, 2), (25, 3, 3)])
-@pytest.mark.parametrize("B,H,W", [(9, 6, 5), (40, 33, 31)])
+@pytest.mark.parametrize("B,H,W", [(9, 6, 5), (40, 33, 31), (99, 33, 31)])
 def test_all_features_in_one_tile(B, H, W, Cin, kh, kw, lay):
     """Up to 224 features the direct form multiplies the blocks of the triangle only (27 .. 224 features: every count of 32-feature
-    blocks, full and ragged; 225 is the first beyond).  Whole numbers whose sums stay below 2^24: every order of
+    blocks, full and ragged, six of them only with many rows; 225 is the first beyond).  Whole numbers whose sums stay below 2^24: every order of
     additions gives the same result, so the sums are exact."""
     g = torch.Generator().manual_seed(Cin)
     x = torch.randint(-3, 4, (B, H, W, Cin), generator=g).to(torch.bfloat16)
