@@ -382,9 +382,9 @@ bool cov_few_rows_applies(const fw_conv_desc* d, fw_dtype dt, fw_layout lay) {
     const long long n_rows = (long long)d->B * d->H * d->W, M = d->Cin;
     // Measured against the general forms (us, this form first).  float32: 7 / 15 at 512 rows x 512 features, 31 / 37 at 1108 x 978,
     // 42 / 42 at 1265 x 1041, 52 / 43 at 1591 x 1010, 42 / 39 at 1861 x 819, 46 / 50 at 499 x 1869.  bfloat16, whose general form multiplies sixteen times
-    // faster: 7 / 21 at 512 x 512, 26 / 28 at 1024 x 1024, 29 / 28 at 2048 x 768, 33 / 20 at 64 x 2048.
+    // faster: 7 / 21 at 512 x 512, 24 / 26 at 1405 x 751, 28 / 26 at 1303 x 856, 29 / 28 at 2048 x 768, 33 / 20 at 64 x 2048.
     if (n_rows > 2048 || (n_rows == 2048 && M <= 16)) return false;   // (streamed form from 2048 rows on: 11 features 9.8 us, here 11.5)
-    return dt == FW_BF16 ? M <= 1024 && n_rows * M * M <= (1ll << 30) : M <= 2048 && n_rows * M * M <= (n_rows <= 512 ? 1ll << 31 : 1200000000ll);
+    return dt == FW_BF16 ? M <= 1024 && n_rows * M * M <= 900000000ll : M <= 2048 && n_rows * M * M <= (n_rows <= 512 ? 1ll << 31 : 1200000000ll);
 }
 
 bool cov_few_rows_plan(const fw_conv_desc* d, fw_dtype dt, fw_layout lay, fw_cov_plan* plan) {
