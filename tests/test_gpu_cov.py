@@ -246,6 +246,24 @@ def test_float32_rows_with_features_that_are_no_multiple_of_four(n_rows, M):
     assert np.array_equal(s.cpu().numpy(), rows.sum(0) + 2.0)
 
 
+@pytest.mark.parametrize("n_rows", [64, 100, 448, 512, 576, 832, 1024])
+@pytest.mark.parametrize("M", [1223, 1224])
+def test_float32_direct_form_in_few_ranges(M, n_rows):
+    """The direct form in 1, 2, 7, 8, 9, 13 and 13 row ranges: whole ranges per XCD, or the ones left over dealt out by items.  Whole
+    numbers whose sums stay below 2^24: the sums are exact."""
+    g = torch.Generator().manual_seed(n_rows)
+    x = torch.randint(-3, 4, (n_rows, M), generator=g).float()
+    d = b.conv_desc(n_rows, M, form=b.FW_COV_FORM_DIRECT)
+    assert b.fw_cov_plan_query(b.FW_F32, b.FW_LAYOUT_ROWS, d).ranges == {64: 1, 100: 2, 448: 7, 512: 8, 576: 9}.get(n_rows, 13)
+    ws = workspace(b.fw_workspace_bytes(b.FW_OP_COV_ACCUMULATE, M, 0, d, b.FW_F32))
+    A, s = torch.full((M, M), 5.0, device=DEV), torch.full((M,), 2.0, device=DEV)
+    b.fw_cov_accumulate(x.to(DEV), b.FW_F32, b.FW_LAYOUT_ROWS, d, A, s, ws)
+    torch.cuda.synchronize()
+    rows = x.numpy().astype(np.float64)
+    assert np.array_equal(A.cpu().numpy(), np.tril(rows.T @ rows) + 5.0)
+    assert np.array_equal(s.cpu().numpy(), rows.sum(0) + 2.0)
+
+
 def test_accumulates_over_batches_and_two_block_recursion():
     """Two batches added into one block equal the block of their union; the second block follows eqs. (vmuxi), (vPhixi)."""
     L0 = wl.small_conv(1, 3, 8, 6, 6, 3, 1, 1, 8)
