@@ -808,18 +808,48 @@ static bool split_plan(const fw_conv_desc* d, fw_layout lay, SplitPlan* sp) {
 }
 
 // float32 layers whose channels are no multiple of four: the 16-byte loads of the fast kernels and the shift form need one, and
-// the kernel without (4-byte gathers) is two to three times slower.  The tensor is copied channels-last with zero channels up to
-// the next multiple and goes through the fast kernels, which drop the padded features when they add into A; all sums stay in
-// float32 as they were.  399 features, 8192 rows: 91 us -> 44 us; 567 features (3x3, stride 2), 8192 rows: 132 us -> 57 us; 525
-// features (5x5), 8177 rows, NCHW: 105 us -> 61 us; 147 features (7x7 stride 2), 3.2 M rows: 5.1 ms -> 2.6 ms; the copy never
-// cost more than the faster kernels gave back, down to 128 rows (27 features, 512 rows: 14.9 us -> 14.5 us).
-// The kernel without stays for tensors beyond the index range of the fast ones.
-// `lay`: the caller's.  Layers that take the split form are not touched (it takes any number of channels).
+// the kernel without (4-byte gathers) is two to three times slower per product.  The tensor is copied channels-last with zero
+// channels up to the next multiple and goes through the fast kernels, which drop the padded features when they add into A; all sums
+// stay in float32 as they were.  399 features, 8192 rows: 91 us -> 44 us; 567 features (3x3, stride 2), 8192 rows: 132 us -> 57 us;
+// 525 features (5x5), 8177 rows, NCHW: 105 us -> 61 us; 147 features (7x7 stride 2), 3.2 M rows: 5.1 ms -> 2.6 ms.
+// pad_pays: where the kernel without stays (its time first, then the padded one's).
+//  - up to 32 rows, or 144 rows up to 64 features: the copy is a launch and there is no work to gain it back (81 features, 16 rows:
+//    10.6 / 13.6 us; 5 features, 72 rows: 12.4 / 13.6 us, 144 rows 13.0 / 13.8 us)
+//  - padding that doubles the 64 x 64 blocks (few channels, large window) in the middle of the range, where rows are too few to fill
+//    the ranges and too many for the launches to count: 125 features (200 padded), 12544 rows 30 / 38 us, against 192 rows
+//    17.6 / 15.7 us and 35557 rows 74 / 58 us; 126 features, 24576 rows 48 / 51 us; 245 features, 4352 rows 28.2 / 29.9 us, 17920 rows 72 / 59 us; one block that
+//    becomes three: 54 features, 1813 rows 16.6 / 17.4 us, 32768 rows 50 / 52 us, 50176 rows 72 / 66 us.  More than three times
+//    the blocks do not pay at the other end either: 125 features, 109824 rows 127 / 119 us, 262144 rows 227 / 243 us, 3.2 M
+//    rows 2.0 / 2.6 ms; 49 features (196 padded), 802816 rows 442 / 690 us
+//  - NCHW tensors: the kernel without works in the caller's feature order, the padded one scatters its sums over A, M^2 / 2 single
+//    words kh kw apart: 2597 features, 16 rows 32 / 69 us, 1617 features, 128 rows 33 / 42 us; 3x3, 2745 features, 200 rows
+//    73 / 79 us, 3006 features, 333 rows 145 / 102 us; 5x5, 3825 features, 256 rows 137 / 175 us
+//  - NCHW with a stride beyond the window: the copy brings pixels no window touches (74 channels 1x1 stride 2 of 37 x 56 x 56:
+//    53 / 60 us; 18 channels, 128 x 64 x 20: 69 / 61 us; 255 channels, 37 x 28 x 28: 46 / 38 us)
+static bool pad_pays(const fw_conv_desc* d, fw_layout lay, long long n_rows, long long M, long long Mp) {
+    if (n_rows <= 32 || (M <= 64 && n_rows <= 144)) return false;
+    const long long nb = (M + BLK - 1) / BLK, nbp = (Mp + BLK - 1) / BLK;
+    const bool doubled = 19 * nb * (nb + 1) < 10 * nbp * (nbp + 1), tripled = 32 * nb * (nb + 1) < 10 * nbp * (nbp + 1);
+    if (tripled && (M <= 64 || (n_rows > 4096 && (n_rows <= 32768 || n_rows > 120000)))) return false;
+    if (doubled && M <= 64 && n_rows <= 40960) return false;
+    if (doubled && M <= 256 && n_rows > 4096 && n_rows <= (nb <= 2 ? 28672 : 17408)) return false;
+    if (lay == FW_LAYOUT_NCHW) {
+        if (d->kh * d->kw > 1 && M > 1024 && n_rows < (d->kh * d->kw > 9 ? 512 : 256)) return false;
+        if ((d->stride > d->kh || d->stride > d->kw) && d->Cin > 32 && d->Cin <= 128) return false;
+    }
+    return true;
+}
+// `lay`: the caller's.  Layers that take the split form are not touched (it takes any number of channels), nor are tensors beyond
+// the index range of the fast kernels (or, through the transposing copy, beyond 65535 images: they are its grid's third dimension).
 // Products of the direct form (whole 64 x 64 blocks, all rows) from which the shift form is the faster one: 270 features, 12544
 // rows (7.7e8) 46 us direct, 47 us shift; 525 features, 8177 rows (1.5e9) 61.4 and 61.0 us; 405 features, 25600 rows (2.9e9)
-// 97 and 62 us; 333 features, 512 rows (4.4e7) 17 and 32 us.
+// 97 and 62 us; 333 features, 512 rows (4.4e7) 17 and 32 us.  With few rows it stays the slower one: 1850 features, 925 rows (1.7e9)
+// 83 and 180 us, 62 and 115 us in the (ky, kx, c) order.
 constexpr double COV_SHIFT_LEAST_WORK = 1.2e9;
+constexpr long long COV_SHIFT_LEAST_ROWS = 4096;
 struct PadPlan { fw_conv_desc d; fw_layout lay; };
+// which of the two copies a padded tensor of Cp channels takes: few channels leave a 32 x 32 tile mostly empty
+static bool pad_by_transpose(fw_layout lay, int Cp) { return lay == FW_LAYOUT_NCHW && Cp > 16; }
 static bool pad_plan(const fw_conv_desc* d, fw_layout lay, PadPlan* pp) {
     if ((d->Cin & 3) == 0) return false;
     SplitPlan sp;
@@ -827,14 +857,17 @@ static bool pad_plan(const fw_conv_desc* d, fw_layout lay, PadPlan* pp) {
     const int Cp = (d->Cin + 3) / 4 * 4;
     const long long kk = (long long)d->kh * d->kw, M = d->Cin * kk, nb = (M + BLK - 1) / BLK;
     const long long Ho = (d->H + 2 * d->pad - d->kh) / d->stride + 1, Wo = (d->W + 2 * d->pad - d->kw) / d->stride + 1;
-    if (Cp * kk > 16384 || (long long)d->B * d->H * d->W * Cp >= (1ll << 30) || d->B > 65535) return false;   // (limits of the fast kernels)
+    const long long n_rows = (long long)d->B * Ho * Wo;
+    if (Cp * kk > 16384 || (long long)d->B * d->H * d->W * Cp >= (1ll << 30)) return false;
+    if (pad_by_transpose(lay, Cp) && d->B > 65535) return false;
+    if (!pad_pays(d, lay, n_rows, M, Cp * kk)) return false;
     pp->d = *d;
     pp->d.Cin = Cp;
     if (d->form == FW_COV_FORM_SPLIT) pp->d.form = FW_COV_FORM_DIRECT;     // (an NCHW tensor that the split form does not take)
     // The shift form of the padded tensor costs two launches and sums more rows per range: it is taken where both its time and its
     // error against float64 were no larger than the direct form's.
-    const double work = (double)d->B * (double)(Ho * Wo) * (double)(nb * (nb + 1) / 2 * BLK * BLK);
-    if (d->form == FW_COV_FORM_AUTO && (M <= 256 || M > 2048 || work < COV_SHIFT_LEAST_WORK))
+    const double work = (double)n_rows * (double)(nb * (nb + 1) / 2 * BLK * BLK);
+    if (d->form == FW_COV_FORM_AUTO && (M <= 256 || M > 2048 || n_rows < COV_SHIFT_LEAST_ROWS || work < COV_SHIFT_LEAST_WORK))
         pp->d.form = FW_COV_FORM_DIRECT;
     pp->lay = lay == FW_LAYOUT_NCHW ? FW_LAYOUT_NHWC : lay;
     return true;
@@ -934,7 +967,7 @@ fw_status cov_accumulate(const void* X, fw_dtype dt, fw_layout lay, const fw_con
         const int HW = d->H * d->W, npix = d->B * HW, Cq = d->Cin / 4;
         const unsigned blocks = (unsigned)(((long long)npix * Cq + 255) / 256);
         const float* src = reinterpret_cast<const float*>(X);
-        if (copy || (src_lay == FW_LAYOUT_NCHW && d->Cin > 16))
+        if (copy || pad_by_transpose(src_lay, d->Cin))
             hipLaunchKernelGGL(nchw_to_nhwc_kernel, dim3((HW + 31) / 32, (d->Cin + 31) / 32, d->B), dim3(256), 0, st, src, Xc, real_channels, d->Cin, HW);
         else if (src_lay == FW_LAYOUT_NCHW)
             hipLaunchKernelGGL(pad_channels_kernel<true>, dim3(blocks), dim3(256), 0, st, src, reinterpret_cast<float4*>(Xc), real_channels, Cq, HW, npix);

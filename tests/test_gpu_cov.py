@@ -232,8 +232,9 @@ def test_float32_channels_that_are_no_multiple_of_four(B, Cin, H, W, k, stride, 
     assert np.array_equal(s.cpu().numpy(), rows.sum(0) + 2.0)
 
 
-@pytest.mark.parametrize("n_rows,M", [(2049, 129), (2500, 202), (3000, 333)])
+@pytest.mark.parametrize("n_rows,M", [(2049, 129), (2500, 202), (3000, 333), (65535, 131), (65537, 131)])
 def test_float32_rows_with_features_that_are_no_multiple_of_four(n_rows, M):
+    """(The last two: on either side of the largest third dimension of a grid, which the padding copy of rows does not use.)"""
     g = torch.Generator().manual_seed(M)
     x = torch.randint(-3, 4, (n_rows, M), generator=g).float()
     d = b.conv_desc(n_rows, M)
@@ -260,6 +261,26 @@ def test_float32_direct_form_in_few_ranges(M, n_rows):
     b.fw_cov_accumulate(x.to(DEV), b.FW_F32, b.FW_LAYOUT_ROWS, d, A, s, ws)
     torch.cuda.synchronize()
     rows = x.numpy().astype(np.float64)
+    assert np.array_equal(A.cpu().numpy(), np.tril(rows.T @ rows) + 5.0)
+    assert np.array_equal(s.cpu().numpy(), rows.sum(0) + 2.0)
+
+
+@pytest.mark.parametrize("lay", [b.FW_LAYOUT_NHWC, b.FW_LAYOUT_NCHW])
+@pytest.mark.parametrize("B,Cin,H,W,k,stride", [(32, 7, 1, 1, 3, 1), (33, 7, 1, 1, 3, 1), (144, 7, 1, 1, 3, 1), (145, 7, 1, 1, 3, 1), (16, 5, 16, 16, 5, 1),
+                                                (17, 5, 16, 16, 5, 1), (70, 5, 16, 16, 5, 1), (24, 129, 4, 4, 3, 2), (47, 129, 4, 4, 3, 2), (48, 129, 4, 4, 3, 2),
+                                                (9, 33, 16, 16, 1, 2), (9, 129, 16, 16, 1, 2), (100, 1, 3, 3, 7, 1), (50, 53, 2, 2, 7, 2)])
+def test_float32_channels_padded_or_not(B, Cin, H, W, k, stride, lay):
+    """Either side of the lines between the padded copy and the kernel that reads such channels as they are; exact as above."""
+    g = torch.Generator().manual_seed(Cin)
+    x = torch.randint(-3, 4, (B, H, W, Cin), generator=g).float()
+    d = b.conv_desc(B, Cin, H, W, kh=k, kw=k, stride=stride, pad=k // 2)
+    M = Cin * k * k
+    ws = workspace(b.fw_workspace_bytes(b.FW_OP_COV_ACCUMULATE, M, 0, d, b.FW_F32))
+    A, s = torch.full((M, M), 5.0, device=DEV), torch.full((M,), 2.0, device=DEV)
+    X = x.permute(0, 3, 1, 2).contiguous() if lay == b.FW_LAYOUT_NCHW else x
+    b.fw_cov_accumulate(X.to(DEV), b.FW_F32, lay, d, A, s, ws)
+    torch.cuda.synchronize()
+    rows = ora.patch_rows(x.numpy(), B, Cin, H, W, k, k, stride, k // 2).astype(np.float64)
     assert np.array_equal(A.cpu().numpy(), np.tril(rows.T @ rows) + 5.0)
     assert np.array_equal(s.cpu().numpy(), rows.sum(0) + 2.0)
 
