@@ -171,7 +171,7 @@ __global__ __launch_bounds__(256) void probe_matvec_kernel(const float* __restri
 // 16 wavefronts takes a whole basis vector (or, while there are fewer than 16, a run of its 64-wide strips): one shuffle
 // reduction per wavefront and pass instead of one per basis vector and wavefront.  The partial coefficients of a vector
 // are added in the order of the strips.
-// M = 525, 16 steps: 7 us a step instead of 26.
+// M = 525, 16 steps: 10 us a step instead of 26.
 __global__ __launch_bounds__(1024) void probe_orth_kernel(int j, int M, size_t ld, double* __restrict__ Qb, const double* __restrict__ w,
                                                           double* __restrict__ alpha, double* __restrict__ beta, double breakdown,
                                                           ProbeState* __restrict__ st) {
@@ -361,13 +361,16 @@ __device__ int tridiag_count_below(const double* a, const double* b, int n, doub
     return cnt;
 }
 
-// One workgroup, eight wavefronts per eigenvalue; every round cuts the bracket of its eigenvalue into 513 parts, one trial
-// point per thread.  The rounds follow one another and each is one serial chain of n float64 divisions, so the two
-// eigenvalues run side by side and wider cuts save rounds: 7 in all (one wavefront: 24), 12 us instead of 37 at n = 16.
-__global__ __launch_bounds__(1024) void probe_final_kernel(const double* __restrict__ alpha, const double* __restrict__ beta,
+// One workgroup, PROBE_CUTS / 64 wavefronts per eigenvalue; every round cuts the bracket of its eigenvalue into PROBE_CUTS + 1 parts, one
+// trial point per thread.  The rounds follow one another and each is one serial chain of n float64 divisions, so the two
+// eigenvalues run side by side; more points a round would save rounds, but the divisions of the wavefronts of a SIMD queue up.
+// 129^11 = 2^77 of the bracket: a smallest eigenvalue far below the resolution of the largest is still told from zero.
+// n = 16: 17.5 us (7 rounds of 512 points each, 2^63 of the bracket: 24.2 us; one wavefront for both, 24 rounds: 37 us).
+constexpr int PROBE_CUTS = 128, PROBE_ROUNDS = 11;
+__global__ __launch_bounds__(2 * PROBE_CUTS) void probe_final_kernel(const double* __restrict__ alpha, const double* __restrict__ beta,
                                                            const ProbeState* __restrict__ st, float* __restrict__ out) {
     __shared__ double al[PROBE_MAX_K], be[PROBE_MAX_K];
-    __shared__ int first_s[2][16];
+    __shared__ int first_s[2][2][PROBE_CUTS / 64];
     __shared__ double res[2];
     const int n = st->steps;
     if (n <= 0) { if (threadIdx.x < 4) out[threadIdx.x] = 0.f; return; }
@@ -382,22 +385,23 @@ __global__ __launch_bounds__(1024) void probe_final_kernel(const double* __restr
     // largest: the smallest x with count_below(x) = n;  smallest: the smallest x with count_below(x) >= 1.
     // count_below grows with x, so the threads that reach the count form a suffix: the bracket becomes the part between
     // the last thread that does not and the first that does.
-    const int which = threadIdx.x >> 9, t = threadIdx.x & 511, lane = t & 63;
+    constexpr int NW = PROBE_CUTS / 64;
+    const int which = threadIdx.x / PROBE_CUTS, t = threadIdx.x % PROBE_CUTS, lane = t & 63;
     const int need = which == 0 ? n : 1;
     double a = lo, b = hi;
-    for (int it = 0; it < 7; ++it) {   // 513^7 > 2^63: the bracket shrinks below float64 resolution
-        const double h = (b - a) / 513.0;
+    for (int it = 0; it < PROBE_ROUNDS; ++it) {
+        const double h = (b - a) / (double)(PROBE_CUTS + 1);
         const double x = a + h * (double)(t + 1);
         const bool ok = tridiag_count_below(al, be, n, x) >= need;
         const unsigned long long mask = __ballot(ok);
-        // the first trial point of this wavefront that reaches the count, 512 when none does
-        int* fs = &first_s[which][(it & 1) * 8];
-        if (lane == 0) fs[t >> 6] = mask ? (t & ~63) + __ffsll((long long)mask) - 1 : 512;
+        // the first trial point of this wavefront that reaches the count, PROBE_CUTS when none does
+        int* fs = first_s[which][it & 1];
+        if (lane == 0) fs[t >> 6] = mask ? (t & ~63) + __ffsll((long long)mask) - 1 : PROBE_CUTS;
         __syncthreads();
-        int first = 512;
+        int first = PROBE_CUTS;
 #pragma unroll
-        for (int g = 0; g < 8; ++g) first = min(first, fs[g]);
-        const double na = a + h * (double)first, nb = first < 512 ? a + h * (double)(first + 1) : b;
+        for (int g = 0; g < NW; ++g) first = min(first, fs[g]);
+        const double na = a + h * (double)first, nb = first < PROBE_CUTS ? a + h * (double)(first + 1) : b;
         a = na; b = nb;
     }
     if (t == 0) res[which] = 0.5 * (a + b);
@@ -456,7 +460,7 @@ fw_status cond_probe(const float* Phi_y, int M, const float* b0, int k, float* o
         }
         else hipLaunchKernelGGL(probe_orth_kernel, dim3(1), dim3(1024), 0, st, j, M, L.ld, Qb, w, alpha, beta, 1e-7, ps);
     }
-    hipLaunchKernelGGL(probe_final_kernel, dim3(1), dim3(1024), 0, st, alpha, beta, ps, out);
+    hipLaunchKernelGGL(probe_final_kernel, dim3(1), dim3(2 * PROBE_CUTS), 0, st, alpha, beta, ps, out);
     FW_LAUNCH_CHECK();
     return FW_OK;
 }

@@ -248,3 +248,16 @@ def test_matrix_core_rate_probe():
     assert float(sink.abs().sum()) == 0.0                      # the sink is never written
     assert 0.3e15 < rates[0] < 2.6e15 and rates[1] > 0.9 * rates[0]
 
+
+
+def test_condition_probe_resolves_a_tiny_smallest_value():
+    """[[1, b], [b, b^2 + 2^-63]] with b = 2^-20: every step of the iteration from the first unit vector is exact in float64, and so is
+    the smaller eigenvalue, 2^-63 to within 2^-40 of itself.  Twelve cuts into 65 parts (the bisection's least) leave 2^-72 of a
+    bracket of length one: 2^-9 of that value."""
+    P = np.array([[1, 2.0 ** -20], [2.0 ** -20, 2.0 ** -40 + 2.0 ** -63]], dtype=np.float32)
+    assert float(P[1, 1]) == 2.0 ** -40 + 2.0 ** -63
+    out = torch.zeros(4, device=DEV)
+    b.fw_cond_probe(dev(P), 2, dev(np.array([1, 0], dtype=np.float32)), 2, out, workspace(b.fw_workspace_bytes(b.FW_OP_COND_PROBE, 2, 2)))
+    top, bottom, ratio, steps = host(out)
+    assert steps == 2 and abs(top - 1) < 1e-6
+    assert abs(bottom - 2.0 ** -63) < 2.0 ** -72 + 2.0 ** -87 and abs(ratio * 2.0 ** -63 - 1) < 2.0 ** -8
