@@ -212,7 +212,7 @@ __global__ __launch_bounds__(256) void pack_images_kernel(const void* __restrict
 }
 
 // The same pre-pass for NCHW sources: the reads want to run along x, the writes along the channels.  A workgroup takes
-// PT padded pixels x CT channels (1024 elements, four per thread), reads each channel's pixels along the row, and turns
+// PT padded pixels x CT channels (1024 elements, four per thread; 768, three per thread, for three channels), reads each channel's pixels along the row, and turns
 // the tile in LDS, so that what it writes is whole runs of CT x 16 bytes (of the full tile where CT covers all channels).  Taken
 // for large tensors, see pack_in_tiles.
 // The tile has two buffers: the next image group is read while this one is written.

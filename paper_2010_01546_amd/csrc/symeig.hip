@@ -8,8 +8,8 @@
 // The vectors w, x (the row to eliminate) and v are worked out by every workgroup for itself (M entries each, two sums over
 // the workgroup), so a step has no second launch and no grid-wide barrier; a thread owns fixed columns and keeps its entries
 // of v_prev, w and v in registers while the rows of the workgroup stream past.  The whole matrix is stored (both triangles)
-// so that rows are contiguous.  Bound: the launch and the two dependent sums (about 5 us a step) up to M = 2000, the
-// traffic of 16 M^3/3 bytes beyond.  The last 128 rows are finished by one workgroup with the block in its registers.
+// so that rows are contiguous.  Bound: the launch and the two dependent sums (3.4 to 5.7 us a step) up to about 1000 rows, from
+// there on the traffic of 16 M^3/3 bytes (7.3 us a step at 1025 to 1536 rows, 10.2 up to 2048, 14.6 up to 2560).  The last 128 rows are finished by one workgroup with the block in its registers.
 //
 // Divide and conquer (J. J. M. Cuppen 1981).  T is torn at equidistant places into leaves of at most 16 rows (Jacobi, one
 // wavefront each); a merge of two neighbours is a rank-one update D + rho z z^T.  Deflation as in the paper by Gu and
