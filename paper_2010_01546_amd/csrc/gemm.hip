@@ -382,14 +382,25 @@ void launch_strip(const StripChoice& ch, const float* G, const float* Q, const G
 // M not a multiple of 4 (rows of G and Q not 16-byte aligned): a workgroup owns a 32x32 tile of G_out and its four
 // wavefronts split the contraction index four ways; operands come straight from global memory / L2 with scalar
 // loads (Q along its rows, like the other kernels), partial tiles are combined through LDS.
+// LOWER: only the tiles that touch the lower triangle of a square result, listed row by row in gridDim.x (as a square grid whose upper
+// half leaves at once, the work of the XCDs came out uneven: 1137 features 356 us a refresh with the whole product, 386 us that
+// way, 300 us like this).
+template <bool LOWER>
 __global__ __launch_bounds__(256) void grad_gemm_f32_small_kernel(const float* __restrict__ G, const float* __restrict__ Q,
-                                                                  GemmEpilogue Out, int S, int M, int lower) {
-    if (lower && blockIdx.x > blockIdx.y) return;      // a tile above the diagonal
+                                                                  GemmEpilogue Out, int S, int M) {
+    int tile_row = blockIdx.y, tile_col = blockIdx.x;
+    if constexpr (LOWER) {
+        const int b = blockIdx.x;
+        tile_row = (int)((sqrtf(8.f * (float)b + 1.f) - 1.f) * 0.5f);
+        while ((tile_row + 1) * (tile_row + 2) / 2 <= b) ++tile_row;
+        while (tile_row * (tile_row + 1) / 2 > b) --tile_row;
+        tile_col = b - tile_row * (tile_row + 1) / 2;
+    }
     __shared__ float red[3][32 * 32];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = lane >> 5, l32 = lane & 31;
-    const int row0 = blockIdx.y * 32, col0 = blockIdx.x * 32;
+    const int row0 = tile_row * 32, col0 = tile_col * 32;
     int kq = ((M + 3) / 4 + 1) & ~1;             // even slice length per wavefront
     const int kb = wave * kq, ke = min(M, kb + kq);
     const int r = row0 + l32, c = col0 + l32;
@@ -524,8 +535,11 @@ size_t grad_gemm_partial_bytes(int S, int M) { return align_up((size_t)STRIP_MAX
 // part: room for grad_gemm_partial_bytes(S, M) bytes, or null (then the contraction index is not cut into runs)
 // lower: of a square result only the lower triangle is wanted; what lies above it is undefined afterwards
 fw_status grad_gemm_f32(const float* G, int S, int M, const float* Q, const GemmEpilogue& e, hipStream_t st, float* part, bool lower) {
-    if ((M & 3) != 0)
-        hipLaunchKernelGGL(grad_gemm_f32_small_kernel, dim3((M + 31) / 32, (S + 31) / 32), dim3(256), 0, st, G, Q, e, S, M, lower && S == M ? 1 : 0);
+    const unsigned tc = (M + 31) / 32;
+    if ((M & 3) != 0 && lower && S == M)
+        hipLaunchKernelGGL(grad_gemm_f32_small_kernel<true>, dim3(tc * (tc + 1) / 2), dim3(256), 0, st, G, Q, e, S, M);
+    else if ((M & 3) != 0)
+        hipLaunchKernelGGL(grad_gemm_f32_small_kernel<false>, dim3(tc, (S + 31) / 32), dim3(256), 0, st, G, Q, e, S, M);
     else {
         const bool plain = e.out && !e.out_bf16 && e.taps == 1 && !e.W;
         lower = lower && plain && S == M;
