@@ -393,14 +393,14 @@ static bool make_shift_geom(const fw_conv_desc* d, fw_layout lay, ShiftGeom* g) 
     const double shifted = (double)g->nbr * (double)g->nbc;
     if (shifted * 1.1 >= direct && d->form != FW_COV_FORM_SHIFT) return false;
     // Small layers: the form costs one launch more, and its one round of workgroups leaves each a long chain of chunks.  Measured
-    // for 3x3 and 5x5 windows, direct against this form: 36 features, 12544 rows 26 and 31 us; 25600 rows 39.5 and 37.7 us;
+    // for 3x3 and 5x5 windows, direct against this form: 144 features, 16384 rows 35 and 33 us; 36 features, 12544 rows 26 and 31 us; 25600 rows 39.5 and 37.7 us;
     // 252 features, 3136 rows 21 and 31 us; 12544 rows (5.1e8) 43.6 and 45.1 us; 200 features, 16384 rows (6.7e8) 44 and
     // 51 us; 576 features, 3136 rows (5.8e8) 40 and 44 us; 288 features, 25600 rows (1.6e9) 63 and 58 us.  Not where the window is
     // larger than the image (most of the direct form's products are with padding) and not beyond 2048 features (in the (c, ky, kx)
     // order its sums are scattered over A): 5x5 over 1 x 1, 1900 features, 8 rows 45 and 35 us, 4100 features, 64 rows 162 and 70 us;
     // 5x5 over 1 x 9, 2300 features, 72 rows 65 and 52 us.
     const long long n_rows = (long long)d->B * g->Ho * g->Wo;
-    if (d->form == FW_COV_FORM_AUTO && M <= 2048 && (M <= 1024 || (d->H >= d->kh && d->W >= d->kw)) && n_rows <= 16384 &&
+    if (d->form == FW_COV_FORM_AUTO && M <= 2048 && (M <= 1024 || (d->H >= d->kh && d->W >= d->kw)) && n_rows <= (M <= 128 ? 16384 : 12288) &&
         direct * (double)(BLK * BLK) * (double)n_rows <= 7.5e8) return false;
     ShiftBand rows[8 * 2], cols[8 * 2];
     const int nr = shift_bands(d->H, d->kh, d->pad, g->Ho, rows, 16), nc = shift_bands(d->W, d->kw, d->pad, g->Wo, cols, 16);
