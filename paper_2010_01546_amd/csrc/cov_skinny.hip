@@ -327,13 +327,16 @@ __global__ __launch_bounds__(512) void cov_few_rows_kernel(const void* __restric
     const int J = (int)blockIdx.x - I * (I + 1) / 2;
     const int fa = 16 * I + c, fb = 16 * J + c;
     const bool a_ok = fa < M, b_ok = fb < M;
-    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-    float cs = 0.f;
+    // float32 sums of 32 rows per wavefront, float64 from there on: over 1500 rows of positive values the error of one float32 chain per
+    // wavefront had been two to three times that of the general forms (8e-8 against 3e-8)
+    double sum[4] = {0.0, 0.0, 0.0, 0.0}, csum = 0.0;
     auto value = [&](size_t e) {
         return BF16 ? __uint_as_float((unsigned)reinterpret_cast<const unsigned short*>(Xv)[e] << 16) : reinterpret_cast<const float*>(Xv)[e];
     };
     for (int r0 = 4 * wave; r0 < n_rows; r0 += 32 * U) {
         float a[U], b[U];
+        floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+        float cs = 0.f;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int r = r0 + 32 * u + kq;
@@ -348,10 +351,13 @@ __global__ __launch_bounds__(512) void cov_few_rows_kernel(const void* __restric
             cs += x;
             acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x, y, acc, 0, 0, 0);
         }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sum[i] += (double)acc[i];
+        csum += (double)cs;
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) red[wave][(4 * kq + i) * 16 + c] = acc[i];
-    sred[wave][lane] = cs;
+    for (int i = 0; i < 4; ++i) red[wave][(4 * kq + i) * 16 + c] = (float)sum[i];
+    sred[wave][lane] = (float)csum;
     __syncthreads();
     const int t = threadIdx.x;
     if (t < 256) {
@@ -383,6 +389,7 @@ bool cov_few_rows_applies(const fw_conv_desc* d, fw_dtype dt, fw_layout lay) {
     // Measured against the general forms (us, this form first).  float32: 7 / 15 at 512 rows x 512 features, 31 / 37 at 1108 x 978,
     // 42 / 42 at 1265 x 1041, 52 / 43 at 1591 x 1010, 42 / 39 at 1861 x 819, 46 / 50 at 499 x 1869.  bfloat16, whose general form multiplies sixteen times
     // faster: 7 / 21 at 512 x 512, 24 / 26 at 1405 x 751, 28 / 26 at 1303 x 856, 29 / 28 at 2048 x 768, 33 / 20 at 64 x 2048.
+    if (n_rows < 32 && M > 1408) return false;                         // thousands of tiles for a single batch: 1650 features, 26 rows 23 us, here 25
     if (n_rows > 2048 || (n_rows == 2048 && M <= 16)) return false;   // (streamed form from 2048 rows on: 11 features 9.8 us, here 11.5)
     return dt == FW_BF16 ? M <= 1024 && n_rows * M * M <= 900000000ll : M <= 2048 && n_rows * M * M <= (n_rows <= 512 ? 1ll << 31 : 1200000000ll);
 }

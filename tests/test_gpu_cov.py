@@ -153,6 +153,23 @@ def test_few_rows_in_one_launch(n_rows, M, dtype):
         assert np.array_equal(np.triu(A.cpu().numpy(), 1), np.triu(A0, 1))     # nothing above the diagonal is touched
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("n_rows,M", [(1250, 19), (1533, 23), (1940, 50), (2047, 129), (1472, 221), (1100, 860)])
+def test_few_rows_error_of_positive_sums(n_rows, M, dtype):
+    """Sums of positive values over more than a thousand rows: storing them as float32 leaves 2^-25 per entry, and the float32 chains of
+    32 rows behind them less than that again, so the whole stays below 2^-24 (one chain per wavefront: 6e-8 to 9e-8)."""
+    rng = np.random.default_rng(M)
+    X = dev(np.abs(rng.standard_normal((n_rows, M))).astype(np.float32), torch.bfloat16 if dtype == "bf16" else torch.float32)
+    x64 = X.double().cpu().numpy()
+    dt = b.FW_BF16 if dtype == "bf16" else b.FW_F32
+    d = b.conv_desc(n_rows, M)
+    A, s = torch.zeros(M, M, device=DEV), torch.zeros(M, device=DEV)
+    b.fw_cov_accumulate(X, dt, b.FW_LAYOUT_ROWS, d, A, s, workspace(b.fw_workspace_bytes(b.FW_OP_COV_ACCUMULATE, M, 0, d, dt)))
+    torch.cuda.synchronize()
+    assert relF(np.tril(A.cpu().numpy()), np.tril(x64.T @ x64)) < 2.0 ** -24
+    assert relF(s.cpu().numpy(), x64.sum(0)) < 2.0 ** -24
+
+
 @pytest.mark.parametrize("Cin", [1, 3, 4, 5, 8, 9, 16, 17, 40])
 @pytest.mark.parametrize("B,H,W,k,stride,pad", [(9, 7, 11, 3, 1, 1), (17, 9, 8, 2, 3, 0), (8, 23, 19, 7, 2, 3), (3, 5, 5, 3, 2, 1)])
 def test_nchw_tensors_give_the_sums_of_their_channels_last_copies(B, Cin, H, W, k, stride, pad):
