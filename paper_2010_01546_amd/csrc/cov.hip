@@ -97,8 +97,8 @@ inline void item_counts(int nb, int* n0, int* n1, int* n2) {
     *n2 = (nb & 1) ? (h + 1 + 3) / 4 : 0;
 }
 
-// internal feature index -> (offset inside a patch, ky, kx, external feature index, -1 for a padded channel)
-struct Feat { int off, ky, kx, ext; };
+// internal feature index -> offset inside a patch, ky, kx
+struct Feat { int off, ky, kx; };
 __device__ __forceinline__ Feat feat_of(int fi, const CovGeom& g) {
     Feat f;
     if (g.layout == FW_LAYOUT_NCHW) {
@@ -106,14 +106,19 @@ __device__ __forceinline__ Feat feat_of(int fi, const CovGeom& g) {
         const int c = fi / kk, t = fi - c * kk;
         f.ky = t / g.kw; f.kx = t - f.ky * g.kw;
         f.off = (c * g.H + f.ky) * g.W + f.kx;
-        f.ext = fi;
     } else {  // NHWC and ROWS: tap-major, channel-minor
         const int t = fi / g.Cin, c = fi - t * g.Cin;
         f.ky = t / g.kw; f.kx = t - f.ky * g.kw;
         f.off = (f.ky * g.W + f.kx) * g.Cin + c;
-        f.ext = c >= g.Cr ? -1 : g.layout == FW_LAYOUT_NHWC_KKC ? t * g.Cr + c : c * (g.kh * g.kw) + t;
     }
     return f;
+}
+// internal feature index -> the caller's, -1 for a padded channel (divisions only where the two orders differ)
+__device__ __forceinline__ int external_of(int fi, const CovGeom& g) {
+    const bool kkc = g.layout == FW_LAYOUT_NHWC_KKC;
+    if (g.layout == FW_LAYOUT_NCHW || (g.Cr == g.Cin && (kkc || g.Cin == g.M))) return fi;
+    const int t = fi / g.Cin, c = fi - t * g.Cin;
+    return c >= g.Cr ? -1 : kkc ? t * g.Cr + c : c * (g.kh * g.kw) + t;
 }
 
 struct RowInfo { long long base; int iy0, ix0; };
@@ -439,7 +444,7 @@ __global__ __launch_bounds__(256) void cov_reduce_kernel(CovGeom g, const float*
         __syncthreads();
         if (grp == 0 && f < g.M) {
             v = red[0][threadIdx.x] + red[1][threadIdx.x] + red[2][threadIdx.x] + red[3][threadIdx.x];
-            const int e = feat_of(f, g).ext;
+            const int e = external_of(f, g);
             if (e >= 0) s[e] = (float)((double)s[e] + v);
         }
         return;
@@ -469,6 +474,8 @@ __global__ __launch_bounds__(256) void cov_reduce_kernel(CovGeom g, const float*
         for (int j = 0; j < 8; ++j) v += (double)x[j];
     }
     for (; sp < g.nsplit; ++sp) v += (double)src[(size_t)sp * stride];
+    const int ei = external_of(fi, g), ej = external_of(fj, g);
+    if ((ei | ej) < 0) return;          // a padded channel (looked at here: the divisions would hold up the loads)
     const int hi = max(ei, ej), lo = min(ei, ej);
     float* dst = A + (size_t)hi * g.Mr + lo;
     *dst = (float)((double)*dst + v);
