@@ -398,9 +398,11 @@ static bool make_shift_geom(const fw_conv_desc* d, fw_layout lay, ShiftGeom* g) 
     // 51 us; 576 features, 3136 rows (5.8e8) 40 and 44 us; 288 features, 25600 rows (1.6e9) 63 and 58 us.  Not where the window is
     // larger than the image (most of the direct form's products are with padding) and not beyond 2048 features (in the (c, ky, kx)
     // order its sums are scattered over A): 5x5 over 1 x 1, 1900 features, 8 rows 45 and 35 us, 4100 features, 64 rows 162 and 70 us;
-    // 5x5 over 1 x 9, 2300 features, 72 rows 65 and 52 us.
-    const long long n_rows = (long long)d->B * g->Ho * g->Wo;
-    if (d->form == FW_COV_FORM_AUTO && M <= 2048 && (M <= 1024 || (d->H >= d->kh && d->W >= d->kw)) && n_rows <= (M <= 128 ? 16384 : 12288) &&
+    // 5x5 over 1 x 9, 2300 features, 72 rows 65 and 52 us; nor up to 64 rows, or 256 rows
+    // of more than 1024 features, whose ranges are longer float32 chains than the regions here (32 rows: error 7.4e-8 against 3.2e-8).
+    const long long n_rows = (long long)d->B * g->Ho * g->Wo, most_rows = M <= 128 ? 16384 : 12288, least_rows = M <= 1024 ? 65 : 257;
+    const bool roomy = M <= 1024 || (d->H >= d->kh && d->W >= d->kw);
+    if (d->form == FW_COV_FORM_AUTO && M <= 2048 && roomy && n_rows >= least_rows && n_rows <= most_rows &&
         direct * (double)(BLK * BLK) * (double)n_rows <= 7.5e8) return false;
     ShiftBand rows[8 * 2], cols[8 * 2];
     const int nr = shift_bands(d->H, d->kh, d->pad, g->Ho, rows, 16), nc = shift_bands(d->W, d->kw, d->pad, g->Wo, cols, 16);

@@ -170,6 +170,24 @@ def test_few_rows_error_of_positive_sums(n_rows, M, dtype):
     assert relF(s.cpu().numpy(), x64.sum(0)) < 2.0 ** -24
 
 
+@pytest.mark.parametrize("layout", [b.FW_LAYOUT_NHWC, b.FW_LAYOUT_NHWC_KKC])
+@pytest.mark.parametrize("B,Cin,k", [(8, 8, 3), (8, 12, 5), (8, 40, 3), (2, 8, 3), (2, 28, 5), (8, 188, 3)])
+def test_small_convolutions_error_of_positive_sums(B, Cin, k, layout):
+    """32 and 128 rows of positive values (4 x 4 images): chains of 32 rows, or the shift form's regions, leave 3e-8 to 4.7e-8 of A;
+    chains of 64 rows, and of 32 where they are the only one, 6.5e-8 to 7.4e-8."""
+    g = torch.Generator().manual_seed(Cin)
+    x = torch.randn(B, 4, 4, Cin, generator=g).abs()
+    d = b.conv_desc(B, Cin, 4, 4, kh=k, kw=k, stride=1, pad=k // 2)
+    M = Cin * k * k
+    A, s = torch.zeros(M, M, device=DEV), torch.zeros(M, device=DEV)
+    b.fw_cov_accumulate(x.to(DEV), b.FW_F32, layout, d, A, s, workspace(b.fw_workspace_bytes(b.FW_OP_COV_ACCUMULATE, M, 0, d, b.FW_F32)))
+    torch.cuda.synchronize()
+    rows = ora.patch_rows(x.numpy(), B, Cin, 4, 4, k, k, 1, k // 2).astype(np.float64)
+    if layout == b.FW_LAYOUT_NHWC_KKC:
+        rows = rows.reshape(-1, Cin, k * k).transpose(0, 2, 1).reshape(-1, M)
+    assert relF(np.tril(A.cpu().numpy()), np.tril(rows.T @ rows)) < 5.6e-8
+
+
 @pytest.mark.parametrize("Cin", [1, 3, 4, 5, 8, 9, 16, 17, 40])
 @pytest.mark.parametrize("B,H,W,k,stride,pad", [(9, 7, 11, 3, 1, 1), (17, 9, 8, 2, 3, 0), (8, 23, 19, 7, 2, 3), (3, 5, 5, 3, 2, 1)])
 def test_nchw_tensors_give_the_sums_of_their_channels_last_copies(B, Cin, H, W, k, stride, pad):
