@@ -874,9 +874,14 @@ __global__ __launch_bounds__(1024) void mirror_norm_rows_kernel(float* __restric
 // launches: 7.0 / 15.6 us at 64 features, 10.2 / 15.6 at 128, 16.5 / 15.4 at 160; with rows that are not 16-byte aligned
 // (single loads) 11.0 / 14.9 at 75 and 26.9 / 18.5 at 147.
 constexpr int REFRESH_ROWS_MAX_M = 128, REFRESH_ROWS_MAX_M_UNALIGNED = 80;
+// Four accumulators, added pairwise: a single float32 chain over the whole contraction index had 1.2 times (up to 1.8 times) the
+// error of the general form, whose wavefronts take a quarter of it each.
 template <bool V4>
-__device__ __forceinline__ void refresh_tile(const float* a_row, const float* __restrict__ b_row, int K, int kq, floatx4& acc) {
+__device__ __forceinline__ floatx4 refresh_tile(const float* a_row, const float* __restrict__ b_row, int K, int kq) {
     constexpr int U = 4;
+    floatx4 acc[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc[i] = floatx4{0.f, 0.f, 0.f, 0.f};
     for (int k0 = 0; k0 < K; k0 += 16 * U) {
         float a[U][4], b[U][4];
 #pragma unroll
@@ -899,10 +904,11 @@ __device__ __forceinline__ void refresh_tile(const float* a_row, const float* __
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const bool ok = k + q < K;
-                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(ok ? a[u][q] : 0.f, ok ? b[u][q] : 0.f, acc, 0, 0, 0);
+                acc[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(ok ? a[u][q] : 0.f, ok ? b[u][q] : 0.f, acc[q], 0, 0, 0);
             }
         }
     }
+    return (acc[0] + acc[1]) + (acc[2] + acc[3]);
 }
 template <bool V4>
 __global__ __launch_bounds__(512) void refresh_rows_kernel(const float* __restrict__ T, const float* __restrict__ Phi_x, int M,
@@ -915,17 +921,15 @@ __global__ __launch_bounds__(512) void refresh_rows_kernel(const float* __restri
     const int row0 = blockIdx.x * 16, col = tile * 16 + r;
     const float* Trow = T + (size_t)min(row0 + r, M - 1) * M;    // rows past the end feed results that are not stored
     const size_t coff = (size_t)min(col, M - 1) * M;
-    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-    refresh_tile<V4>(Trow, Phi_x + coff, M, kq, acc);     // Phi_x is symmetric: its rows stand for its columns
+    floatx4 acc = refresh_tile<V4>(Trow, Phi_x + coff, M, kq);     // Phi_x is symmetric: its rows stand for its columns
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int row = row0 + 4 * kq + i;
         Ps[4 * kq + i][col] = acc[i];
         if (row < M && col < M) Psi[(size_t)row * M + col] = acc[i];
-        acc[i] = 0.f;
     }
     __syncthreads();
-    refresh_tile<V4>(Ps[r], T + coff, M, kq, acc);
+    acc = refresh_tile<V4>(Ps[r], T + coff, M, kq);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int row = row0 + 4 * kq + i;
@@ -941,9 +945,9 @@ __global__ __launch_bounds__(512) void refresh_rows_kernel(const float* __restri
     }
     __syncthreads();
     if (threadIdx.x < 16 && row0 + (int)threadIdx.x < M) {
-        float q = 0.f;
-        for (int k = 0; k < ntiles; ++k) q += red[k][threadIdx.x];
-        xi2[row0 + threadIdx.x] = q;
+        double q = 0.0;
+        for (int k = 0; k < ntiles; ++k) q += (double)red[k][threadIdx.x];
+        xi2[row0 + threadIdx.x] = (float)q;
     }
 }
 

@@ -218,3 +218,25 @@ def test_refresh_at_the_largest_config_size():
     print(f"M={M}: rel-F(Psi) = {e_psi:.2e}, rel-F(Phi_y) = {e_py:.2e}")
     assert e_psi < 2e-5 and e_py < 2e-5 and np.array_equal(Py, Py.T)
     assert relF(run.host("xi2"), np.sum(want ** 2, axis=0)) < 4e-5
+
+
+@pytest.mark.parametrize("M", [60, 63, 75, 79, 100, 128])
+def test_one_launch_refresh_error(M):
+    """Sums of M products of a positive covariance: the rounding errors of a float32 chain add up like a random walk, sqrt(M) 2^-24 times
+    a factor that is 0.44 for both products in one chain each, and 0.25 in four chains of M / 4, as the kernel has them (measured over
+    these inputs, 60 to 128 features); the bound lies between."""
+    worst = 0.0
+    for seed in range(4):
+        g = torch.Generator().manual_seed(10 * M + seed)
+        x = torch.randn(2 * M, M, generator=g).abs()
+        P = x.T @ x / (2 * M)
+        P = ((P + P.T) / 2).to("cuda:0")
+        T = (torch.eye(M) + 0.3 * torch.randn(M, M, generator=g) / M ** 0.5).to("cuda:0")
+        z = lambda *sh: torch.zeros(*sh, device="cuda:0")  # noqa: E731
+        Py, Psi, xi2, lbar, Q = z(M, M), z(M, M), z(M), torch.ones(4, device="cuda:0"), torch.eye(M, device="cuda:0")
+        b.fw_cond_state_refresh(b.cond_state(M, P, lbar, T, Q, Q.clone(), Py, Psi, xi2),
+                                workspace(b.fw_workspace_bytes(b.FW_OP_COND_STATE_REFRESH, M)))
+        torch.cuda.synchronize()
+        want = T.double() @ P.double() @ T.double().T
+        worst = max(worst, relF(Psi.cpu().numpy(), (T.double() @ P.double()).cpu().numpy()), relF(Py.cpu().numpy(), want.cpu().numpy()))
+    assert worst < np.sqrt(M) * 2.0 ** -24 / 3, worst * 2.0 ** 24 / np.sqrt(M)
