@@ -305,13 +305,14 @@ typedef struct {
  *   Qs      i/o  [M, M] or NULL: Qs <- beta Qs + (1-beta) Q
  *   lambda  out  [M] eigenvalues, decreasing
  *   ws      scratch, fw_workspace_bytes(FW_OP_WHITEN_EVD, M, 0, NULL, FW_F32) bytes
- * The decomposition runs in float64 inside the workspace: V = I where that passes the check below already, otherwise reduction to
- * tridiagonal form, divide and conquer, back-transformation, then a check of every off-diagonal entry of V Phi_x V^T and of V V^T.  The result stands when all of the
- * first are below 2^-34 sqrt(D_i D_j), D_i = sum_k v_ik^2 Phi_kk (a thousandth of the float32 rounding of Phi_x), or below 2^-30
- * times the eigenvalue at which the gains are clamped, and all of the second are within 2^-34 of the identity; otherwise, or when
- * tol > 0 asks for it, one-sided Jacobi sweeps continue from there (from V = I where V V^T failed, as it does when Phi_x has NaN
- * or infinite entries) in float64 until no pair of rows exceeds the rotation threshold.  The call blocks for the verdict on I,
- * for that on V, and once per sweep where there are any.
+ * The decomposition runs in float64 inside the workspace: V = I where that passes the check below already, otherwise
+ * reduction to tridiagonal form, divide and conquer, back-transformation, then a check of every off-diagonal entry of V
+ * Phi_x V^T and of V V^T.  The result stands when all of the first are below 2^-34 sqrt(D_i D_j), D_i = sum_k v_ik^2 Phi_kk
+ * (a thousandth of the float32 rounding of Phi_x), or below 2^-30 times the eigenvalue at which the gains are clamped, and
+ * the second agrees with the identity to 2^-34 (entry by entry up to 1024 features, against eight vectors beyond);
+ * otherwise, or when tol > 0 asks for it, one-sided Jacobi sweeps continue from there (from V = I where V V^T failed, as it
+ * does when Phi_x has NaN or infinite entries) in float64 until no pair of rows exceeds the rotation threshold.  The call
+ * blocks for the verdict on I, for that on V, and once per sweep where there are any.
  */
 fw_status fw_whiten_evd(const float* Phi_x, int M, const fw_evd_params* p, float* T, float* Q, float* Qs,
                         float* lambda, void* ws, size_t ws_bytes, void* stream);

@@ -2,23 +2,22 @@
 //
 // Phi_x = V^T Lambda V with the eigenvectors as rows of V, in float64 inside the workspace (small eigenvalues carry the
 // largest gains): reduction to tridiagonal form, divide and conquer, back-transformation (symeig.hip).  The result is then
-// CHECKED against Phi_x itself: W = V Phi_x, and every off-diagonal entry of W V^T must lie below kAccept sqrt(D_i D_j),
-// D_i = sum_k v_ik^2 Phi_kk, i.e. a thousandth of what the storage of Phi_x as float32 leaves undetermined in that entry, or
-// below kAcceptClamp times the eigenvalue at which the gains are clamped; and V V^T must agree with the identity to kAccept (rows
-// that Phi_x takes to zero carry the largest gain and are seen by nothing else; one more product: 22.70 -> 23.09 ms at M = 2304, 3.60 -> 3.62 at 576).  Where V
-// fails that, it is given up for V = I.  Where neither of the first two holds (diagonals graded over many
-// decades above the clamp), or where the caller asks for a rotation
-// threshold of its own (tol > 0), a one-sided Jacobi iteration goes on from there:
-// orthogonal transformations are applied to the rows of W = V Phi_x and of V until the rows of W are mutually orthogonal;
-// then W = Lambda V and lambda_k = w_k . v_k.  The iteration is blocked: rows are cut into blocks of 32, a round of the
-// round-robin schedule takes disjoint pairs of blocks, and for every pair (64 rows) three kernels run: the 64x64 Gram matrix
-// of the rows (partial sums over column slices), its diagonalisation by a cyclic two-sided Jacobi iteration in LDS, which
-// yields the 64x64 rotation that makes the 64 rows orthogonal to each other, and the application of that rotation to the
-// rows of W and V.  T = V^T diag(sqrt g) V and Q = V^T diag(g) V: in float64, or for many features as split products on the
-// bfloat16 matrix cores (gemm_split.hip).
+// CHECKED against Phi_x itself: W = V Phi_x, and every off-diagonal entry of W V^T must lie below kAccept sqrt(D_i D_j), D_i
+// = sum_k v_ik^2 Phi_kk, i.e. a thousandth of what the storage of Phi_x as float32 leaves undetermined in that entry, or
+// below kAcceptClamp times the eigenvalue at which the gains are clamped; and V V^T must agree with the identity to kAccept
+// (rows that Phi_x takes to zero carry the largest gain and are seen by nothing else; by eight products with vectors where M
+// is large).  Where V fails that, it is given up for V = I.  Where neither of the first two holds (diagonals graded over
+// many decades above the clamp), or where the caller asks for a rotation threshold of its own (tol > 0), a one-sided Jacobi
+// iteration goes on from there: orthogonal transformations are applied to the rows of W = V Phi_x and of V until the rows of
+// W are mutually orthogonal; then W = Lambda V and lambda_k = w_k . v_k.  The iteration is blocked: rows are cut into blocks
+// of 32, a round of the round-robin schedule takes disjoint pairs of blocks, and for every pair (64 rows) three kernels run:
+// the 64x64 Gram matrix of the rows (partial sums over column slices), its diagonalisation by a cyclic two-sided Jacobi
+// iteration in LDS, which yields the 64x64 rotation that makes the 64 rows orthogonal to each other, and the application of
+// that rotation to the rows of W and V.  T = V^T diag(sqrt g) V and Q = V^T diag(g) V: in float64, or for many features as
+// split products on the bfloat16 matrix cores (gemm_split.hip).
 //
 // Why not Jacobi alone: from V = I it needs 13 to 19 sweeps that each stream W and V once per round.  One call took
-// 31 ms at M = 576, 175 ms at 2304 and 0.86 s at 4608; this way 3.6, 22.7 and 119 ms.
+// 31 ms at M = 576, 175 ms at 2304 and 0.86 s at 4608; this way 3.6, 22.7 and 121 ms.
 #include "fw_internal.h"
 
 namespace fw {
@@ -439,7 +438,7 @@ fw_status whiten_evd(const float* Phi_x, int M, const fw_evd_params* p, float* T
     } else {
         rc = sym_eig(Phi_x, M, verdict[1] != 0, mat, base + L.small, &V, &W, st);
         if (rc != FW_OK) return rc;
-        rc = sym_eig_check(Phi_x, M, V, W, mat[0], base + L.small, kAccept, floor_abs, floor_rel, lam, cnt, st);
+        rc = sym_eig_check(Phi_x, M, V, W, mat[0], mat[1], base + L.small, kAccept, floor_abs, floor_rel, lam, cnt, st);
         if (rc != FW_OK) return rc;
     }
     // the outputs are issued before the host looks at the verdict, so that the GPU does not wait for it; they leave mat[0], the

@@ -194,7 +194,7 @@ int sym_eig_ld(int M);
 size_t sym_eig_small_bytes(int M);
 size_t sym_eig_matrix_doubles(int M);
 fw_status sym_eig(const float* Phi, int M, bool dead, double* const buf[4], void* small, double** V, double** free_buf, hipStream_t st);
-fw_status sym_eig_check(const float* Phi, int M, const double* V, double* W, double* copy, void* small, double thr, double floor_abs,
+fw_status sym_eig_check(const float* Phi, int M, const double* V, double* W, double* copy, double* scratch, void* small, double thr, double floor_abs,
                         double floor_rel, double* lam, int* flag, hipStream_t st);
 fw_status sym_eig_check_identity(const float* Phi, int M, void* small, double thr, double floor_abs, double floor_rel, int* flag,
                                  hipStream_t st);

@@ -160,15 +160,16 @@ def test_deficient_and_clustered_spectra(kind, M):
         assert relF(N, want / np.sqrt(eps)) < bound
 
 
-@pytest.mark.parametrize("M", [40, 700])
+@pytest.mark.parametrize("M", [40, 700, 1024, 1025, 1601])
 def test_acceptance_sees_lost_orthogonality(M):
     """The check behind the direct decomposition, called by itself: exact eigenvectors pass; a null vector that is a copy of
-    another, a zero one or a longer one fails by V V^T (V Phi V^T does not see it); two rows turned towards each other fail
+    another, a zero one or a longer one fails by V V^T, entry by entry or (from 1025 rows on) against vectors (V Phi V^T does not see
+    it), wherever it stands, and so does a row that leans on another by 1e-9; two rows turned towards each other fail
     by V Phi V^T alone."""
     lib = b.lib
-    check = lib._ZN2fw13sym_eig_checkEPKfiPKdPdS4_PvdddS4_PiP12ihipStream_t
+    check = lib._ZN2fw13sym_eig_checkEPKfiPKdPdS4_S4_PvdddS4_PiP12ihipStream_t
     P = C.c_void_p
-    check.argtypes = [P, C.c_int, P, P, P, P, C.c_double, C.c_double, C.c_double, P, P, P]
+    check.argtypes = [P, C.c_int, P, P, P, P, P, C.c_double, C.c_double, C.c_double, P, P, P]
     ld, small, n = lib._ZN2fw10sym_eig_ldEi(M), lib._ZN2fw19sym_eig_small_bytesEi(M), lib._ZN2fw22sym_eig_matrix_doublesEi(M)
     r = M // 4
     Phi = torch.zeros(M, M, device=DEV)
@@ -180,20 +181,22 @@ def test_acceptance_sees_lost_orthogonality(M):
     def verdict(V):
         Vd = torch.zeros(n, dtype=torch.float64, device=DEV)
         Vd[:M * ld].view(M, ld)[:, :M] = V.to(DEV)
-        W, copy, lam = torch.zeros_like(Vd), torch.zeros_like(Vd), torch.zeros(M, dtype=torch.float64, device=DEV)
+        W, copy, scratch, lam = torch.zeros_like(Vd), torch.zeros_like(Vd), torch.zeros_like(Vd), torch.zeros(M, dtype=torch.float64, device=DEV)
         flag = torch.zeros(64, dtype=torch.int32, device=DEV)
         ws = workspace(small)
-        rc = check(Phi.data_ptr(), M, Vd.data_ptr(), W.data_ptr(), copy.data_ptr(), ws.data_ptr(), 2.0 ** -34, 2.0 ** -30 * 1e-5, 0.0,
+        rc = check(Phi.data_ptr(), M, Vd.data_ptr(), W.data_ptr(), copy.data_ptr(), scratch.data_ptr(), ws.data_ptr(), 2.0 ** -34, 2.0 ** -30 * 1e-5, 0.0,
                    lam.data_ptr(), flag.data_ptr(), torch.cuda.current_stream().cuda_stream)
         torch.cuda.synchronize()
         assert rc == 0
         return [int(f != 0) for f in flag[:2].tolist()]
 
     assert verdict(good) == [0, 0]
-    for row in (good[r + 1], 0 * good[r], 1.001 * good[r]):
-        V = good.clone()
-        V[r] = row
-        assert verdict(V) == [0, 1]
+    for at in (r, (r + M) // 2, M - 1):
+        other = good[r + 1]
+        for row in (other, 0 * good[at], 1.001 * good[at], good[at] + 1e-9 * other):
+            V = good.clone()
+            V[at] = row
+            assert verdict(V) == [0, 1]
     V = good.clone()
     c, s = np.cos(1e-6), np.sin(1e-6)
     V[0], V[r - 1] = c * good[0] + s * good[r - 1], c * good[r - 1] - s * good[0]
