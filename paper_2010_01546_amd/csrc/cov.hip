@@ -828,6 +828,10 @@ static bool split_plan(const fw_conv_desc* d, fw_layout lay, SplitPlan* sp) {
 //    becomes three: 54 features, 1813 rows 16.6 / 17.4 us, 32768 rows 50 / 52 us, 50176 rows 72 / 66 us.  More than three times
 //    the blocks do not pay at the other end either: 125 features, 109824 rows 127 / 119 us, 262144 rows 227 / 243 us, 3.2 M
 //    rows 2.0 / 2.6 ms; 49 features (196 padded), 802816 rows 442 / 690 us
+//    Beyond 256 features the line follows rows times padded pairs of blocks: 405 features (2.36 times the pairs), 2072 rows 27 / 35 us,
+//    3600 rows 37 / 43 us, but 784 rows 25 / 22 us and 5328 rows 54 / 50 us; 605 features (2.47 times), 980 rows 28 / 36 us; with 1.8
+//    times the pairs and more, 441 features, 2072 rows 28.4 / 31.4 us, 1152 rows 26.3 / 23.5 us, 5328 rows 57 / 47 us; 486 features,
+//    2072 rows 32.5 / 35.2 us, 3600 rows 51 / 44 us
 //  - NCHW tensors: the kernel without works in the caller's feature order, the padded one scatters its sums over A, M^2 / 2 single
 //    words kh kw apart: 2597 features, 16 rows 32 / 69 us, 1617 features, 128 rows 33 / 42 us; 3x3, 2745 features, 200 rows
 //    73 / 79 us, 3006 features, 333 rows 145 / 102 us; 5x5, 3825 features, 256 rows 137 / 175 us
@@ -840,6 +844,11 @@ static bool pad_pays(const fw_conv_desc* d, fw_layout lay, long long n_rows, lon
     if (tripled && (M <= 64 || (n_rows > 4096 && (n_rows <= 32768 || n_rows > 120000)))) return false;
     if (doubled && M <= 64 && n_rows <= 40960) return false;
     if (doubled && M <= 256 && n_rows > 4096 && n_rows <= (nb <= 2 ? 28672 : 17408)) return false;
+    if (M > 256) {
+        const long long pairs = nb * (nb + 1) / 2, padded = nbp * (nbp + 1) / 2;
+        if (5 * padded >= 11 * pairs && n_rows * padded > 64000 && n_rows * padded <= 330000) return false;
+        if (5 * padded >= 9 * pairs && n_rows * padded > 76000 && n_rows * padded <= 230000) return false;
+    }
     if (lay == FW_LAYOUT_NCHW) {
         if (d->kh * d->kw > 1 && M > 1024 && n_rows < (d->kh * d->kw > 9 ? 512 : 256)) return false;
         if ((d->stride > d->kh || d->stride > d->kw) && d->Cin > 32 && d->Cin <= 128) return false;

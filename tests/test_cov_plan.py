@@ -182,3 +182,11 @@ def test_grad_plan():
     with pytest.raises(b.FwError):
         b.fw_grad_plan_query(b.FW_F32, 0, M, 0)
 
+
+@pytest.mark.parametrize("Cin,k,lo,hi,items", [(9, 7, 28, 85, 7), (5, 9, 19, 102, 7)])
+def test_float32_padding_that_doubles_the_blocks_is_left_out_in_the_middle(Cin, k, lo, hi, items):
+    """441 features (588 padded) and 405 (648): images of 49 rows at either side of the lines; `items` work items per range without
+    the padded copy."""
+    for B, padded in ((lo, True), (lo + 1, False), (hi, False), (hi + 1, True)):
+        p = b.fw_cov_plan_query(b.FW_F32, b.FW_LAYOUT_NHWC, b.conv_desc(B, Cin, 7, 7, k, k, 1, k // 2))
+        assert (p.workgroups > items * p.ranges) == padded, B
