@@ -835,6 +835,8 @@ static bool split_plan(const fw_conv_desc* d, fw_layout lay, SplitPlan* sp) {
 //  - NCHW tensors: the kernel without works in the caller's feature order, the padded one scatters its sums over A, M^2 / 2 single
 //    words kh kw apart: 2597 features, 16 rows 32 / 69 us, 1617 features, 128 rows 33 / 42 us; 3x3, 2745 features, 200 rows
 //    73 / 79 us, 3006 features, 333 rows 145 / 102 us; 5x5, 3825 features, 256 rows 137 / 175 us
+//    and from 768 features in the middle of the range: 7x7, 882 features, 288 rows 27.4 / 25.1 us, 512 rows 28.0 / 31.4 us, 784 rows
+//    34.0 / 36.5 us, 1332 rows 52 / 43 us; 5x5, 925 features, 512 rows 29.0 / 31.7 us
 //  - NCHW with a stride beyond the window: the copy brings pixels no window touches (74 channels 1x1 stride 2 of 37 x 56 x 56:
 //    53 / 60 us; 18 channels, 128 x 64 x 20: 69 / 61 us; 255 channels, 37 x 28 x 28: 46 / 38 us)
 static bool pad_pays(const fw_conv_desc* d, fw_layout lay, long long n_rows, long long M, long long Mp) {
@@ -851,6 +853,7 @@ static bool pad_pays(const fw_conv_desc* d, fw_layout lay, long long n_rows, lon
     }
     if (lay == FW_LAYOUT_NCHW) {
         if (d->kh * d->kw > 1 && M > 1024 && n_rows < (d->kh * d->kw > 9 ? 512 : 256)) return false;
+        if (d->kh * d->kw > 9 && M > 768 && n_rows > 384 && n_rows <= 800) return false;
         if ((d->stride > d->kh || d->stride > d->kw) && d->Cin > 32 && d->Cin <= 128) return false;
     }
     return true;

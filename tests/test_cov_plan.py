@@ -190,3 +190,10 @@ def test_float32_padding_that_doubles_the_blocks_is_left_out_in_the_middle(Cin, 
     for B, padded in ((lo, True), (lo + 1, False), (hi, False), (hi + 1, True)):
         p = b.fw_cov_plan_query(b.FW_F32, b.FW_LAYOUT_NHWC, b.conv_desc(B, Cin, 7, 7, k, k, 1, k // 2))
         assert (p.workgroups > items * p.ranges) == padded, B
+
+
+def test_float32_nchw_padding_left_out_in_the_middle():
+    """7x7 on 18 channels (882 features, 980 padded): images of 9 rows at either side of the lines."""
+    for B, padded in ((42, True), (43, False), (88, False), (89, True)):
+        p = b.fw_cov_plan_query(b.FW_F32, b.FW_LAYOUT_NCHW, b.conv_desc(B, 18, 3, 3, 7, 7, 1, 3))
+        assert (p.workgroups > 28 * p.ranges) == padded, (B, p.workgroups, p.ranges)

@@ -303,7 +303,8 @@ def test_float32_direct_form_in_few_ranges(M, n_rows):
 @pytest.mark.parametrize("lay", [b.FW_LAYOUT_NHWC, b.FW_LAYOUT_NCHW])
 @pytest.mark.parametrize("B,Cin,H,W,k,stride", [(32, 7, 1, 1, 3, 1), (33, 7, 1, 1, 3, 1), (144, 7, 1, 1, 3, 1), (145, 7, 1, 1, 3, 1), (16, 5, 16, 16, 5, 1),
                                                 (17, 5, 16, 16, 5, 1), (70, 5, 16, 16, 5, 1), (24, 129, 4, 4, 3, 2), (47, 129, 4, 4, 3, 2), (48, 129, 4, 4, 3, 2),
-                                                (9, 33, 16, 16, 1, 2), (9, 129, 16, 16, 1, 2), (100, 1, 3, 3, 7, 1), (50, 53, 2, 2, 7, 2), (28, 9, 7, 7, 7, 1), (29, 9, 7, 7, 7, 1), (19, 5, 7, 7, 9, 1), (20, 5, 7, 7, 9, 1)])
+                                                (9, 33, 16, 16, 1, 2), (9, 129, 16, 16, 1, 2), (100, 1, 3, 3, 7, 1), (50, 53, 2, 2, 7, 2), (28, 9, 7, 7, 7, 1), (29, 9, 7, 7, 7, 1), (19, 5, 7, 7, 9, 1), (20, 5, 7, 7, 9, 1),
+                                                (42, 18, 3, 3, 7, 1), (43, 18, 3, 3, 7, 1), (88, 18, 3, 3, 7, 1), (89, 18, 3, 3, 7, 1)])
 def test_float32_channels_padded_or_not(B, Cin, H, W, k, stride, lay):
     """Either side of the lines between the padded copy and the kernel that reads such channels as they are; exact as above."""
     g = torch.Generator().manual_seed(Cin)
