@@ -10,6 +10,8 @@
 // of v_prev, w and v in registers while the rows of the workgroup stream past.  The whole matrix is stored (both triangles)
 // so that rows are contiguous.  Bound: the launch and the two dependent sums (3.4 to 5.7 us a step) up to about 1000 rows, from
 // there on the traffic of 16 M^3/3 bytes (7.3 us a step at 1025 to 1536 rows, 10.2 up to 2048, 14.6 up to 2560).  The last 128 rows are finished by one workgroup with the block in its registers.
+// From 129 rows on, and for the last 2560 of more, tri_rows_kernel does all of it in one launch (see there); the steps are for what lies
+// beyond and for a device that does not hold its workgroups at a time.
 //
 // Divide and conquer (J. J. M. Cuppen 1981).  T is torn at equidistant places into leaves of at most 16 rows (Jacobi, one
 // wavefront each); a merge of two neighbours is a rank-one update D + rho z z^T.  Deflation as in the paper by Gu and
@@ -240,6 +242,236 @@ __global__ __launch_bounds__(T) void tri_step_kernel(double* __restrict__ A, int
 #pragma unroll
         for (int k = 0; k < T / 64; ++k) s += rowred[r * (T / 64) + k];
         pnew[blockIdx.x + G * r] = s;
+    }
+}
+
+// ---- the reduction in one launch, the matrix in registers
+// A step of the chain above costs a launch and a pass over the active block in memory, yet 2560 x 2560 doubles fit the registers of
+// the chip.  Here every workgroup keeps blocks of 8 rows in registers (block-cyclic; a thread owns fixed columns, as above) and what
+// a step exchanges is its product p = A v and the next row to eliminate, n entries each.  They go through memory into places written
+// once (a row of two buffers for each step, filled with SENTINEL before the launch): the owners store them past the caches, every
+// workgroup polls the entries of its own columns until none is SENTINEL any more.  So the value is its own signal, and nothing is ever reset; 8
+// rows in a row are 64 bytes of one owner (rows dealt out one by one, their lines written by sixteen owners: 2 to 3 us more a step).
+// All workgroups have to be resident at a time (cooperative launch).  A poll gives up after POLL_LIMIT rounds (seconds); the
+// workgroups that wait for this one then do so too, and d[0] = NaN makes the caller's acceptance fail.  Rows per workgroup: eight, ten where
+// eight would need more than 256 workgroups.
+// Bound by the round trip through the last-level cache (about 1.7 us a step, 2.5 at 2304 rows, where 230 workgroups read 37 KB each) and two
+// sums over the workgroup.  Whole call, launches per step -> this: 576 features 3.55 -> 2.85 ms, 2304 features 22.8 -> 14.2 ms.  Polls at
+// once instead of after POLL_DELAY: 15.0 ms; after twice the delay: 14.8 ms.  Up to 128 rows the single workgroup is as fast.
+constexpr unsigned long long SENTINEL = ~0ull;    // a NaN that no arithmetic on widened float32 produces; publish() keeps it out for good
+constexpr int POLL_LIMIT = 1 << 21;
+constexpr int ROWS_MAX_M = 2560;
+constexpr int POLL_DELAY = 12;                    // of 64 clocks before the first poll: an early one only gets in the way of the stores
+
+__device__ __forceinline__ void publish(double* p, double x) {
+    unsigned long long b = (unsigned long long)__double_as_longlong(x);
+    if (b == SENTINEL) b = 0x7ff8000000000000ull;
+    __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ unsigned long long peek(const double* p) {
+    return __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// x' + y' of the pair after lanes 32..63 of x changed places with lanes 0..31 of y: lanes below 32 hold the sum of x's halves, the others y's
+__device__ __forceinline__ double fold32(double x, double y) {
+    union { double d; unsigned i[2]; } a, b;
+    a.d = x; b.d = y;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const auto r = __builtin_amdgcn_permlane32_swap(a.i[k], b.i[k], false, false);
+        a.i[k] = r[0]; b.i[k] = r[1];
+    }
+    return a.d + b.d;
+}
+// the same for the odd rows of 16 lanes of x and the even ones of y
+__device__ __forceinline__ double fold16(double x, double y) {
+    union { double d; unsigned i[2]; } a, b;
+    a.d = x; b.d = y;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const auto r = __builtin_amdgcn_permlane16_swap(a.i[k], b.i[k], false, false);
+        a.i[k] = r[0]; b.i[k] = r[1];
+    }
+    return a.d + b.d;
+}
+// sum over the 16 lanes of a row, in every one of them
+__device__ __forceinline__ double sum16(double v) {
+    union { double d; int i[2]; } a, b;
+    a.d = v;
+#define FW_SUM16(c) b.i[0] = __builtin_amdgcn_update_dpp(0, a.i[0], c, 0xf, 0xf, true); b.i[1] = __builtin_amdgcn_update_dpp(0, a.i[1], c, 0xf, 0xf, true); a.d += b.d
+    FW_SUM16(0xB1);      // lanes 1,0,3,2
+    FW_SUM16(0x4E);      // lanes 2,3,0,1
+    FW_SUM16(0x141);     // half of 16 mirrored
+    FW_SUM16(0x140);     // 16 mirrored
+#undef FW_SUM16
+    return a.d;
+}
+
+// sums of RB (8 or 10) values over the wavefront; row 0 .. RB - 1 to out[0 .. RB - 1]
+template <int RB>
+__device__ __forceinline__ void row_sums(const double (&acc)[RB], int lane, double* out) {
+    const double s0 = fold32(acc[0], acc[4]), s1 = fold32(acc[1], acc[5]), s2 = fold32(acc[2], acc[6]), s3 = fold32(acc[3], acc[7]);
+    const double u0 = sum16(fold16(s0, s2)), u1 = sum16(fold16(s1, s3));    // rows 2 g and 2 g + 1 in lanes 16 g .. 16 g + 15
+    double u2 = 0.0;
+    if constexpr (RB == 10) {
+        const double s4 = fold32(acc[RB - 2], acc[RB - 1]);
+        u2 = sum16(fold16(s4, s4));                                         // row 8 below lane 32, row 9 from there on
+    }
+    if ((lane & 15) == 0) {
+        out[lane >> 3] = u0; out[(lane >> 3) + 1] = u1;
+        if constexpr (RB == 10) out[8 + (lane >> 5)] = u2;
+    }
+}
+
+// T threads of C columns each, RB rows b RB .. b RB + RB - 1 per workgroup b.  Eliminates rows c0, c0 - 1, ..., 1 of the leading
+// (c0 + 1) x (c0 + 1) block; c0 < C T, c0 < RB gridDim.x.  Pslot, Xslot: row c holds what step c leaves.
+// The reflector's scale is not waited for: the rows are multiplied with x as it is (x_{c-1} left out), and the sum of squares that
+// gives the scale crosses the workgroup together with the products.
+template <int T, int C, int RB>
+__global__ __launch_bounds__(T) void tri_rows_kernel(const double* __restrict__ A, int ld, int c0, int first, const double* __restrict__ vprev,
+                                                     const double* __restrict__ pprev, double* __restrict__ Pslot, double* __restrict__ Xslot,
+                                                     double* __restrict__ Vh, double* __restrict__ d, double* __restrict__ e,
+                                                     double* __restrict__ tau) {
+    constexpr int NW = T / 64;
+    __shared__ double vl[C * T + RB];             // reflector of the step before
+    __shared__ double rowred[NW][RB], rowp[RB], col[RB], red[2][NW];
+    __shared__ double s_pc, s_alpha, s_d;
+    __shared__ int s_bad;
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int b = blockIdx.x, i0 = b * RB;
+    double a[RB][C], v[C];
+#pragma unroll
+    for (int r = 0; r < RB; ++r)
+#pragma unroll
+        for (int q = 0; q < C; ++q) {
+            const int i = i0 + r, j = t + T * q;
+            a[r][q] = (i <= c0 && j <= c0) ? A[(size_t)i * ld + j] : 0.0;
+        }
+#pragma unroll
+    for (int q = 0; q < C; ++q) {
+        const int j = t + T * q;
+        v[q] = (j <= c0 && !first) ? vprev[j] : 0.0;
+        vl[j] = v[q];
+    }
+    if (t < RB) {
+        rowp[t] = (i0 + t <= c0 && !first) ? pprev[i0 + t] : 0.0;
+        vl[C * T + t] = 0.0;
+    }
+    if (t == 0) { s_bad = 0; s_pc = 0.0; }
+    double tp = first ? 0.0 : tau[c0 + 1];
+    for (int c = c0; c >= 1; --c) {
+        if (i0 >= c) return;                      // no row of this workgroup is left (workgroup 0 stays to the end)
+        double w[C], x[C];
+        if (c == c0) {
+#pragma unroll
+            for (int q = 0; q < C; ++q) {
+                const int j = t + T * q;
+                w[q] = (j <= c && !first) ? pprev[j] : 0.0;
+                x[q] = j <= c ? A[(size_t)c * ld + j] : 0.0;
+            }
+        } else {
+            const double* ps = Pslot + (size_t)(c + 1) * ld;
+            const double* xs = Xslot + (size_t)(c + 1) * ld;
+            unsigned long long pb[C], xb[C];
+            bool have_x = false;                  // the row comes first: its owner stored it before the products of the same step
+            __builtin_amdgcn_s_sleep(POLL_DELAY);
+            for (int spin = 0;; ++spin) {
+                bool there = true, there_x = true;
+#pragma unroll
+                for (int q = 0; q < C; ++q) pb[q] = t + T * q <= c ? peek(ps + t + T * q) : 0;
+                if (!have_x) {
+#pragma unroll
+                    for (int q = 0; q < C; ++q) xb[q] = t + T * q <= c ? peek(xs + t + T * q) : 0;
+                }
+#pragma unroll
+                for (int q = 0; q < C; ++q) { there &= pb[q] != SENTINEL; there_x &= xb[q] != SENTINEL; }
+                have_x = __all(there_x);
+                if (have_x && __all(there)) break;
+                if (spin >= POLL_LIMIT) { s_bad = 1; break; }
+            }
+#pragma unroll
+            for (int q = 0; q < C; ++q) { w[q] = __longlong_as_double((long long)pb[q]); x[q] = __longlong_as_double((long long)xb[q]); }
+        }
+        double dot = 0.0;
+#pragma unroll
+        for (int q = 0; q < C; ++q) {
+            dot += v[q] * w[q];
+            if (t + T * q == c) s_pc = w[q];
+        }
+        dot = block_total<T>(dot, red[0]);
+        if (s_bad) {
+            if (t == 0) d[0] = __longlong_as_double(0x7ff8000000000000ll);
+            return;
+        }
+        const double h = 0.5 * tp * tp * dot, vc = vl[c], wc = tp * s_pc - h * vc;
+        double ss = 0.0;
+#pragma unroll
+        for (int q = 0; q < C; ++q) {
+            const int j = t + T * q;
+            w[q] = tp * w[q] - h * v[q];
+            x[q] -= vc * w[q] + wc * v[q];
+            if (j == c - 1) s_alpha = x[q];
+            if (j == c) s_d = x[q];
+            if (j >= c - 1) x[q] = 0.0;
+            ss += x[q] * x[q];
+        }
+        double acc[RB];
+#pragma unroll
+        for (int r = 0; r < RB; ++r) {
+            // rows from c on are updated with what lies there and never looked at again
+            const double vi = -vl[i0 + r], wi = -(tp * rowp[r] + h * vi);
+            acc[r] = 0.0;
+#pragma unroll
+            for (int q = 0; q < C; ++q) {
+                if (T * q >= c) break;
+                a[r][q] = fma(vi, w[q], fma(wi, v[q], a[r][q]));
+                acc[r] = fma(a[r][q], x[q], acc[r]);
+            }
+        }
+        if (c - 1 - i0 < RB) {                    // the row to eliminate next
+#pragma unroll
+            for (int r = 0; r < RB; ++r)
+                if (i0 + r == c - 1) {
+#pragma unroll
+                    for (int q = 0; q < C; ++q)
+                        if (t + T * q < c) publish(Xslot + (size_t)c * ld + t + T * q, a[r][q]);
+                }
+        }
+#pragma unroll
+        for (int q = 0; q < C; ++q)
+            if (t + T * q == c - 1) {
+#pragma unroll
+                for (int r = 0; r < RB; ++r) col[r] = a[r][q];
+            }
+        row_sums<RB>(acc, lane, rowred[wave]);
+        ss = block_total<T>(ss, red[1]);
+        double tn, beta, scale;
+        reflector(ss, s_alpha, &tn, &beta, &scale);
+        if (t < RB) {
+            double s = 0.0;
+#pragma unroll
+            for (int k = 0; k < NW; ++k) s += rowred[k][t];
+            s = scale * s + col[t];
+            if (i0 + t < c) publish(Pslot + (size_t)c * ld + i0 + t, s);
+            rowp[t] = s;
+        }
+#pragma unroll
+        for (int q = 0; q < C; ++q) {
+            const int j = t + T * q;
+            v[q] = j == c - 1 ? 1.0 : x[q] * scale;
+            vl[j] = v[q];
+        }
+        // what the later stages read: nothing in this launch waits for it
+        if (b == 0) {
+#pragma unroll
+            for (int q = 0; q < C; ++q)
+                if (t + T * q < c) Vh[(size_t)c * ld + t + T * q] = v[q];
+            if (t == 0) {
+                tau[c] = tn; e[c - 1] = beta; d[c] = s_d;
+                if (c == 1) { d[0] = a[0][0]; tau[0] = 0.0; }
+            }
+        }
+        tp = tn;
     }
 }
 
@@ -1054,10 +1286,12 @@ __global__ __launch_bounds__(256) void spectral_product_kernel(const double* __r
     });
 }
 
-// three matrices, one per blockIdx.y
-__global__ __launch_bounds__(256) void fill64_kernel(double* __restrict__ p0, double* __restrict__ p1, double* __restrict__ p2, size_t n) {
+// three matrices, one per blockIdx.y: zero, and a bit pattern in the other two
+__global__ __launch_bounds__(256) void fill64_kernel(double* __restrict__ p0, double* __restrict__ p1, double* __restrict__ p2, size_t n,
+                                                     unsigned long long bits) {
     double* p = blockIdx.y == 0 ? p0 : blockIdx.y == 1 ? p1 : p2;
-    for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < n; e += (size_t)gridDim.x * 256) p[e] = 0.0;
+    const double x = blockIdx.y == 0 ? 0.0 : __longlong_as_double((long long)bits);
+    for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < n; e += (size_t)gridDim.x * 256) p[e] = x;
 }
 __global__ __launch_bounds__(256) void start_over_kernel(const double* __restrict__ copy, int ld, size_t n, double* __restrict__ V,
                                                          double* __restrict__ W) {
@@ -1100,6 +1334,31 @@ void step(double* A, int ld, int c, int first, const double* vp, const double* p
 #undef FW_STEP
 }
 
+// The reduction of the leading (c + 1) x (c + 1) block in one launch; false: not possible (too many rows, or the device does not hold
+// the workgroups at a time), nothing was launched.
+template <int T, int C, int RB>
+bool launch_rows(const double* A, int ld, int c, int first, const double* vp, const double* pp, double* Pslot, double* Xslot, double* Y, double* d,
+                 double* e, double* tau, hipStream_t st) {
+    void* args[] = {&A, &ld, &c, &first, &vp, &pp, &Pslot, &Xslot, &Y, &d, &e, &tau};
+    if (hipLaunchCooperativeKernel(reinterpret_cast<const void*>(tri_rows_kernel<T, C, RB>), dim3(c / RB + 1), dim3(T), args, 0, st) == hipSuccess) return true;
+    (void)hipGetLastError();
+    return false;
+}
+bool rows(const double* A, int ld, int c, int first, const double* vp, const double* pp, double* Pslot, double* Xslot, double* Y, double* d,
+          double* e, double* tau, hipStream_t st) {
+    const int n = c + 1;
+#define FW_ROWS(T, C, RB) return launch_rows<T, C, RB>(A, ld, c, first, vp, pp, Pslot, Xslot, Y, d, e, tau, st)
+    if (n <= 256) FW_ROWS(256, 1, 8);
+    if (n <= 512) FW_ROWS(256, 2, 8);
+    if (n <= 768) FW_ROWS(256, 3, 8);
+    if (n <= 1024) FW_ROWS(512, 2, 8);
+    if (n <= 1536) FW_ROWS(512, 3, 8);
+    if (n <= 2048) FW_ROWS(512, 4, 8);
+    if (n <= ROWS_MAX_M) FW_ROWS(512, 5, 10);
+#undef FW_ROWS
+    return false;
+}
+
 struct SmallWs { size_t d, e, tau, p0, p1, dn, sd, sz, kd, kz, zh, rtau, dd, rc, rs, scale, F, ints, flag, total; };
 inline SmallWs small_layout(int M) {
     SmallWs L;
@@ -1138,12 +1397,22 @@ fw_status sym_eig(const float* Phi, int M, bool dead, double* const buf[4], void
     const size_t nn = (size_t)M * ld;
     if (dead) hipLaunchKernelGGL(dead_last_kernel, dim3(1), dim3(1024), 0, st, Phi, M, perm);
     hipLaunchKernelGGL(sym_load_kernel, dim3((ld + 31) / 32, (M + 31) / 32), dim3(256), 0, st, Phi, M, ld, dead ? perm : nullptr, A);
-    hipLaunchKernelGGL(fill64_kernel, dim3(grid_for(nn), 3), dim3(256), 0, st, Y, Va, Vb, nn);
     int c = M - 1, first = 1, cur = 0;
-    for (; c >= TAIL; --c, first = 0, cur ^= 1)
-        step(A, ld, c, first, Y + (size_t)(c + 1 < M ? c + 1 : c) * ld, p[cur ^ 1], Y + (size_t)c * ld, p[cur], d, e, tau, st);
-    hipLaunchKernelGGL(tri_tail_kernel, dim3(1), dim3(1024), 0, st, A, ld, c, first, Y + (size_t)(c + 1 < M ? c + 1 : c) * ld, p[cur ^ 1], Y, d, e,
-                       tau);
+    auto vp = [&] { return Y + (size_t)(c + 1 < M ? c + 1 : c) * ld; };
+    auto one_step = [&] {
+        step(A, ld, c, first, vp(), p[cur ^ 1], Y + (size_t)c * ld, p[cur], d, e, tau, st);
+        --c; first = 0; cur ^= 1;
+    };
+    hipLaunchKernelGGL(fill64_kernel, dim3(grid_for(nn), 3), dim3(256), 0, st, Y, Va, Vb, nn, M > TAIL ? SENTINEL : 0ull);
+    bool reduced = false;
+    if (M > TAIL) {
+        while (c >= ROWS_MAX_M) one_step();
+        reduced = rows(A, ld, c, first, vp(), p[cur ^ 1], Va, Vb, Y, d, e, tau, st);
+        if (!reduced)
+            while (c >= TAIL) one_step();
+    }
+    if (!reduced) hipLaunchKernelGGL(tri_tail_kernel, dim3(1), dim3(1024), 0, st, A, ld, c, first, vp(), p[cur ^ 1], Y, d, e, tau);
+    if (M > TAIL) hipLaunchKernelGGL(fill64_kernel, dim3(grid_for(nn), 2), dim3(256), 0, st, Va, Vb, Vb, nn, 0ull);
     FW_LAUNCH_CHECK();
 
     int leaves = 1;

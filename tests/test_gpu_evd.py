@@ -99,6 +99,44 @@ def test_direct_decomposition_sizes(M):
     assert torch.equal(T, T.T) and torch.equal(Q, Q.T)
 
 
+# The reduction in one launch: workgroups of 8 rows (10 beyond 2048), the last one whole, with one row and with one row missing,
+# the largest and smallest of its range.  Same bounds as above.
+@pytest.mark.parametrize("M", [135, 136, 137, 256, 512, 768, 1024, 1536, 2047, 2048, 2050, 2051, 2559, 2560])
+def test_reduction_in_one_launch_sizes(M):
+    test_direct_decomposition_sizes(M)
+
+
+def test_decompositions_on_two_streams():
+    """Two threads with a stream each: every one gets what it gets alone, bit for bit."""
+    import threading
+    sizes, alone, got, errors = [300, 900], {}, {}, []
+
+    def call(M, where, stream):
+        try:
+            with torch.cuda.stream(stream):
+                T = torch.empty(M, M, device=DEV); Q = torch.empty(M, M, device=DEV); out = torch.empty(M, device=DEV)
+                ws = workspace(b.fw_workspace_bytes(b.FW_OP_WHITEN_EVD, M))
+                for _ in range(3):
+                    b.fw_whiten_evd(Phi[M], M, b.evd_params(), T, Q, None, out, ws)
+                stream.synchronize()
+                where[M] = (T, Q, out)
+        except Exception as ex:  # noqa: BLE001
+            errors.append(ex)
+
+    Phi = {M: dev(wl.spd_matrix(M, M, np.logspace(0, -3, M)).astype(np.float32)) for M in sizes}
+    torch.cuda.synchronize()
+    for M in sizes:
+        call(M, alone, torch.cuda.Stream())
+    threads = [threading.Thread(target=call, args=(M, got, torch.cuda.Stream())) for M in sizes]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors
+    for M in sizes:
+        assert all(torch.equal(x, y) for x, y in zip(alone[M], got[M]))
+
+
 @pytest.mark.parametrize("kind", ["dead", "duplicate", "identity", "zero", "graded", "tol"])
 @pytest.mark.parametrize("M", [33, 200])
 def test_special_matrices(kind, M):
