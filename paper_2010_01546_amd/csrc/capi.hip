@@ -123,14 +123,16 @@ fw_status fw_grad_transform(const void* G, fw_dtype dt, int S, int M, const floa
     float* part = (ws && ws_bytes >= fixed + grad_gemm_partial_bytes(S, M))
                       ? reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + fixed) : nullptr;
     if (dt == FW_BF16 && ws && ws_bytes >= grad_ws_bytes(M) + grad_wide_bytes(S, M)) {
+        GemmEpilogue e = {};
+        e.out = G_out; e.out_bf16 = 1; e.taps = 1;
+        const bool split = grad_split_applies(S, M) && (M & 3) == 0 && ws_bytes >= fixed + grad_gemm_partial_bytes(S, M) + grad_split_bytes(S, M);
+        if (!split && grad_takes_bf16(S, M, false)) return gemm_planes(G, true, S, M, M, Q, e, false, st);
         // widened to float32 in the workspace, multiplied in float32, rounded to bfloat16 as the results are stored
         float* G32 = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + grad_ws_bytes(M));
         const fw_status rc = grad_stage_rows(G, FW_BF16, S, M, 1, G32, st);
         if (rc != FW_OK) return rc;
-        GemmEpilogue e = {};
-        e.out = G_out; e.out_bf16 = 1; e.taps = 1;
         // a large product takes the split form from the widened copy, its runs summed and rounded by the epilogue pass
-        if (grad_split_applies(S, M) && (M & 3) == 0 && ws_bytes >= fixed + grad_gemm_partial_bytes(S, M) + grad_split_bytes(S, M))
+        if (split)
             return split_rows_apply(G32, S, M, Q, e, reinterpret_cast<char*>(ws) + fixed + grad_gemm_partial_bytes(S, M), st);
         return grad_gemm_f32(G32, S, M, Q, e, st, part);
     }
@@ -177,18 +179,19 @@ fw_status fw_sgd_update(const void* G, fw_dtype dt, int S, int M, int taps, cons
     if (!aligned16(G) || !aligned16(Q) || !aligned16(W) || (V && !aligned16(V)) || (ws && !aligned16(ws))) return FW_ERR_ALIGNMENT;
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     const float* rows = reinterpret_cast<const float*>(G);
-    if (dt == FW_BF16 || taps > 1) {
-        if (!ws || ws_bytes < grad_wide_bytes((long long)S * taps, M)) return FW_ERR_WORKSPACE;
-        const fw_status rc = grad_stage_rows(G, dt, S, M, taps, reinterpret_cast<float*>(ws), st);
-        if (rc != FW_OK) return rc;
-        rows = reinterpret_cast<const float*>(ws);
-    }
     GemmEpilogue e = {};
     e.taps = taps; e.W = W; e.V = p->momentum > 0.f ? V : nullptr;
     e.lr = p->lr; e.momentum = p->momentum; e.wd = p->weight_decay;
     const size_t wide = grad_wide_bytes((long long)S * taps, M);
-    if (grad_split_applies(S * taps, M) && (M & 3) == 0 && ws && ws_bytes >= wide + grad_split_bytes(S * taps, M))
-        return split_rows_apply(rows, S * taps, M, Q, e, reinterpret_cast<char*>(ws) + wide, st);
+    const bool split = grad_split_applies(S * taps, M) && (M & 3) == 0 && ws && ws_bytes >= wide + grad_split_bytes(S * taps, M);
+    if (dt == FW_BF16 || taps > 1) {
+        if (!ws || ws_bytes < wide) return FW_ERR_WORKSPACE;
+        if (taps == 1 && !split && grad_takes_bf16(S, M, false)) return gemm_planes(G, true, S, M, M, Q, e, false, st);
+        const fw_status rc = grad_stage_rows(G, dt, S, M, taps, reinterpret_cast<float*>(ws), st);
+        if (rc != FW_OK) return rc;
+        rows = reinterpret_cast<const float*>(ws);
+    }
+    if (split) return split_rows_apply(rows, S * taps, M, Q, e, reinterpret_cast<char*>(ws) + wide, st);
     return grad_gemm_f32(rows, S * taps, M, Q, e, st);
 }
 

@@ -158,8 +158,13 @@ size_t grad_gemm_partial_bytes(int S, int M);
 fw_status grad_gemm(const void* G, fw_dtype dt, int S, int M, const float* Q, void* G_out, hipStream_t st, float* part = nullptr);
 fw_status grad_gemm_f32(const float* G, int S, int M, const float* Q, const GemmEpilogue& e, hipStream_t st, float* part = nullptr, bool lower = false);
 double grad_gemm_f32_flops_issued(int S, int M, bool lower);
+bool grad_takes_bf16(int S, int M, bool plain);
 fw_status grad_stage_rows(const void* G, fw_dtype dt, int S, int M, int taps, float* dst, hipStream_t st);
 fw_status grad_epilogue_from_runs(const float* part, int nks, const GemmEpilogue& e, int S, int M, hipStream_t st);
+
+// ---- gemm_planes.hip: C = A B^T, float32 accuracy on the bfloat16 matrix cores (operands split in three), any K
+fw_status gemm_planes(const void* A, bool a_bf16, int S, int N, int K, const float* B, const GemmEpilogue& e, bool lower, hipStream_t st);
+double gemm_planes_flops(int S, int N, int K, bool lower);
 
 // ---- gemm_split.hip: C = A B^T in float32-grade accuracy on the bfloat16 matrix cores (operands split in hi + lo)
 size_t gemm_split_packed_bytes(int rows, int K);

@@ -4,6 +4,7 @@
 //   float32: v_mfma_f32_32x32x2_f32 or v_mfma_f32_16x16x4_f32, strips of output tiles per workgroup (see below).
 //   bfloat16: v_mfma_f32_32x32x16_bf16, 64 x 128 tile per workgroup, Q rounded to bfloat16 while it is staged.
 #include "fw_internal.h"
+#include "gemm_emit.h"
 #include <type_traits>
 
 namespace fw {
@@ -41,34 +42,6 @@ struct Mfma<16> {
     // register i of lane (lr, lk) holds row 4*lk + i, column lr
     static __device__ __forceinline__ int row(int i, int lk) { return 4 * lk + i; }
 };
-
-// What the float32 kernels do with a finished element (row, col) of G Q, value v:
-//   taps == 1: element index row * M + col.  taps > 1 (per-tap form): the product ran on rows (s, tap) of the permuted
-//   gradient, and the element belongs at [s][col][tap] of an [S, M, taps] array (the layout of a convolution weight).
-//   out (float32, or bfloat16 bits when out_bf16): the transformed gradient, written when non-null.
-//   W (and V): the update  d = v + wd W;  V = momentum V + d (if V);  W -= lr (V or d)   (eq. (vtWrn_SGD)).
-__device__ __forceinline__ void emit(const GemmEpilogue& e, int row, int col, int M, float v) {
-    size_t idx;
-    if (e.taps > 1) {
-        const int s = row / e.taps, t = row - s * e.taps;
-        idx = ((size_t)s * M + col) * e.taps + t;
-    } else {
-        idx = (size_t)row * M + col;
-    }
-    if (e.out) {
-        if (e.out_bf16) reinterpret_cast<unsigned short*>(e.out)[idx] = f32_to_bf16_rne(v);
-        else reinterpret_cast<float*>(e.out)[idx] = v;
-    }
-    if (e.W) {
-        const float w = e.W[idx];
-        float d = v + e.wd * w;
-        if (e.V) {
-            d = e.momentum * e.V[idx] + d;
-            e.V[idx] = d;
-        }
-        e.W[idx] = w - e.lr * d;
-    }
-}
 
 // float4 per lane, panel and chunk: enough for about 2000 cycles of MFMAs per chunk and wavefront, within an LDS stage
 // of at most 80 KB
@@ -284,7 +257,7 @@ __global__ __launch_bounds__(256) void grad_gemm_f32_strip_kernel(const float* _
 // workspace for partial strips is at hand, the contraction index is cut into up to STRIP_MAX_RUNS runs of whole chunks;
 // a run shorter than about 16 chunks is not worth it (filling the LDS ring and summing the four wavefronts' strips at
 // the end take about as long as ten chunks: measured, a 256 x 2304 x 2304 product got slower when cut in four).
-struct StripChoice { int mf, c, nks, kchunks; };
+struct StripChoice { int mf, c, nks, kchunks; double us; };   // us: estimated time
 constexpr int STRIP_MAX_RUNS = 8;
 // strips of c tiles that touch the lower triangle of a square of t x t tiles
 inline long long lower_strips(long long t, int c) {
@@ -293,7 +266,7 @@ inline long long lower_strips(long long t, int c) {
 }
 inline StripChoice pick_strip(int S, int M, bool plain, bool can_split, bool lower) {
     static const int cs[6] = {9, 6, 4, 3, 2, 1};
-    StripChoice best = {32, 1, 1, 0};
+    StripChoice best = {32, 1, 1, 0, 0.0};
     double best_cost = 1e300;
     long long best_wgs = 1;
     auto consider = [&](int mf, int c, bool low) {
@@ -309,7 +282,7 @@ inline StripChoice pick_strip(int S, int M, bool plain, bool can_split, bool low
         // a 16x16 tile is a quarter of the MFMA work of a 32x32 tile and reads twice the operands per flop;
         // a wider strip reads fewer operands per MFMA
         const double cost = rounds * c * (mf == 32 ? 1.0 : 0.25 * 1.06) * kpad * (1.0 + 0.02 / c);
-        if (cost < best_cost) { best_cost = cost; best = {mf, c, 1, 0}; best_wgs = wgs; }
+        if (cost < best_cost) { best_cost = cost; best = {mf, c, 1, 0, 0.0}; best_wgs = wgs; }
     };
     for (int mf = 32; mf >= 16; mf -= 16)
         for (int ci = 0; ci < 6; ++ci) consider(mf, cs[ci], false);
@@ -328,7 +301,28 @@ inline StripChoice pick_strip(int S, int M, bool plain, bool can_split, bool low
         while (nks > 1 && nchunks / nks < 16) --nks;
         if (nks > 1) { best.nks = nks; best.kchunks = (nchunks + nks - 1) / nks; }
     }
+    // filling and draining the ring costs every round about 1.5 us (2.5 us with strips of one tile), an entry of the contraction
+    // index and unit of cost 4.3 to 5 ns
+    best.us = 2.0 + (double)((best_wgs + 255) / 256) * (best.c == 1 ? 2.5 : 1.5) + 0.0048 * best_cost * M;
     return best;
+}
+
+// Is the three-plane form (gemm_planes.hip) the faster one?  Its time: chunks of 32 entries, for each about 0.45 us (a bfloat16 A: 0.25)
+// per tile of 64 x 64 that a compute unit holds.  Measured against the strips, us: 896^3 18.6 / 71, its lower triangle 17.3 / 48,
+// 1280^3 40.6 / 74, lower 27.1 / 43, 1472^3 66.7 / 79, lower 42.5 / 76, 384 x 2304 x 2304 46 / 60; the strips stay where they fill one
+// round: 512^3 11.3 / 6.5, 576^3 12.4 / 10.2, 1152^3 34.9 / 34.9, lower 24.2 / 20.0, 256 x 2304 x 2304 45 / 32.
+// Where M is no multiple of 4 it stands against grad_gemm_f32_small_kernel: 777^3 17.4 / 74, lower 16.4 / 48, 1137^3 38 / 170, 50 x 525 x 525
+// 12.1 / 14.4, 147 x 199 x 199 7.4 / 7.8, 147 x 147 x 147 6.8 / 6.5, 16 x 2047 x 2047 33 / 30.
+// A bfloat16 G needs no float32 copy there (2.3 us and more): 1000 x 512 x 512 9.5 / 13.7, 1000 x 1152 x 1152 22 / 39; 256 x 512 x 512
+// 9.3 / 7.1, 256 x 2304 x 2304 38 / 34.
+bool planes_pay(int S, int M, bool a_bf16, bool plain, bool can_split, bool lower) {
+    if ((M & 3) != 0) return a_bf16 ? M >= 96 : M >= 192 && S > 16;
+    const double chunks = (double)((M + 31) / 32), tr = (double)((S + 63) / 64);
+    const double tiles = lower ? 0.5 * tr * (tr + 1.0) : tr * ((M + 63) / 64);
+    const double held = (double)(((long long)tiles + 255) / 256);
+    const double planes = 3.5 + chunks * (a_bf16 ? 0.1 + 0.25 * held : 0.07 + 0.45 * held);
+    const double strips = pick_strip(S, M, plain, can_split && !lower, lower).us + (a_bf16 ? 3.0 : 0.0);
+    return planes < 0.95 * strips;
 }
 
 // sum of the partial strips of the runs, in run order, then the epilogue
@@ -536,13 +530,14 @@ size_t grad_gemm_partial_bytes(int S, int M) { return align_up((size_t)STRIP_MAX
 // lower: of a square result only the lower triangle is wanted; what lies above it is undefined afterwards
 fw_status grad_gemm_f32(const float* G, int S, int M, const float* Q, const GemmEpilogue& e, hipStream_t st, float* part, bool lower) {
     const unsigned tc = (M + 31) / 32;
-    if ((M & 3) != 0 && lower && S == M)
+    const bool plain = e.out && !e.out_bf16 && e.taps == 1 && !e.W;
+    lower = lower && plain && S == M;
+    if (planes_pay(S, M, false, plain, part != nullptr, lower)) return gemm_planes(G, false, S, M, M, Q, e, lower, st);
+    if ((M & 3) != 0 && lower)
         hipLaunchKernelGGL(grad_gemm_f32_small_kernel<true>, dim3(tc * (tc + 1) / 2), dim3(256), 0, st, G, Q, e, S, M);
     else if ((M & 3) != 0)
         hipLaunchKernelGGL(grad_gemm_f32_small_kernel<false>, dim3(tc, (S + 31) / 32), dim3(256), 0, st, G, Q, e, S, M);
     else {
-        const bool plain = e.out && !e.out_bf16 && e.taps == 1 && !e.W;
-        lower = lower && plain && S == M;
         const StripChoice ch = pick_strip(S, M, plain, part != nullptr && !lower, lower);
         if (ch.mf == 32) launch_strip<32>(ch, G, Q, e, S, M, part, lower, st);
         else launch_strip<16>(ch, G, Q, e, S, M, part, lower, st);
@@ -551,9 +546,14 @@ fw_status grad_gemm_f32(const float* G, int S, int M, const float* Q, const Gemm
     return FW_OK;
 }
 
-// what the matrix cores execute in grad_gemm_f32 for a plain result without runs: whole tiles and chunks
+// Does a bfloat16 G go into the product as it is (instead of widened to float32 first)?
+bool grad_takes_bf16(int S, int M, bool plain) { return planes_pay(S, M, true, plain, true, false); }
+
+// what the matrix cores execute in grad_gemm_f32 for a plain result without runs: whole tiles and chunks (the three-plane form: the
+// float32 products it stands for)
 double grad_gemm_f32_flops_issued(int S, int M, bool lower) {
     lower = lower && S == M;
+    if (planes_pay(S, M, false, true, false, lower)) return gemm_planes_flops(S, M, M, lower);
     if ((M & 3) != 0) {
         const double tr = (S + 31) / 32, tiles = lower ? 0.5 * tr * (tr + 1.0) : tr * ((M + 31) / 32);
         const int kq = ((M + 3) / 4 + 1) & ~1;

@@ -207,3 +207,41 @@ def test_largest_feature_count():
     assert (num / den) ** 0.5 < 1e-5
     with pytest.raises(b.FwError):
         b.fw_grad_transform(dev(G[:, :64]), b.FW_F32, S, M + 4, None, Q, out)
+
+
+# The three-plane form: tiles of 64 x 64 and chunks of 32 entries with one row, column or entry too many and too few, contraction
+# shorter than a chunk, sizes that are no multiple of 4 (from 192 features and 17 rows on; bfloat16 from 96 on) and multiples of 4 where it
+# takes over from the strips.  Operands carry 24 bits and the chain of a result has M / 32 links: 2^-24 sqrt(M / 32) and the final
+# additions stay below 1e-6; bfloat16 results (8 significant bits) are rounded once, at most 2^-8 relative.
+@pytest.mark.parametrize("S,M", [(17, 193), (64, 223), (65, 225), (63, 255), (130, 321), (50, 525), (200, 1023), (900, 896), (2304, 256), (384, 2304)])
+def test_three_planes_f32(S, M):
+    T32, Q64 = sym_Q(M, M + 9)
+    Q32 = Q64.astype(np.float32)
+    G = (rng.standard_normal((S, M)) * np.exp(rng.uniform(-8, 8, (S, 1)))).astype(np.float32)
+    out = torch.full((S, M), float("nan"), device=DEV)
+    b.fw_grad_transform(dev(G), b.FW_F32, S, M, None, dev(Q32), out)
+    torch.cuda.synchronize()
+    want = G.astype(np.float64) @ Q32.astype(np.float64)
+    err = np.linalg.norm(out.cpu().numpy() - want, axis=1) / np.linalg.norm(want, axis=1)
+    assert err.max() < 1e-6                   # every row against its own size
+
+
+@pytest.mark.parametrize("S,M", [(3, 97), (64, 99), (65, 129), (50, 525), (1000, 256), (384, 512), (1000, 1156)])
+def test_three_planes_bf16(S, M):
+    T32, Q64 = sym_Q(M, M + 11)
+    Q32 = Q64.astype(np.float32)
+    G = wl.round_to_bf16((rng.standard_normal((S, M)) * 0.1).astype(np.float32))
+    want = G.astype(np.float64) @ Q32.astype(np.float64)
+    ws = workspace(b.fw_workspace_bytes(b.FW_OP_GRAD_TRANSFORM, M, S, None, b.FW_BF16))
+    out = torch.zeros(S, M, device=DEV, dtype=torch.bfloat16)
+    b.fw_grad_transform(dev(G, torch.bfloat16), b.FW_BF16, S, M, None, dev(Q32), out, ws)
+    torch.cuda.synchronize()
+    got = out.float().cpu().numpy()
+    assert np.max(np.abs(got - want) / np.maximum(np.abs(want), 1e-3 * np.abs(want).max())) < 1.001 * 2.0 ** -8
+    W0 = rng.standard_normal((S, M)).astype(np.float32)
+    W, V = dev(W0.copy()), torch.zeros(S, M, device=DEV)
+    wsu = workspace(b.fw_workspace_bytes(b.FW_OP_SGD_UPDATE, M, S, None, b.FW_BF16))
+    b.fw_sgd_update(dev(G, torch.bfloat16), b.FW_BF16, S, M, 1, dev(Q32), b.sgd_params(0.1, 0.9, 5e-4), W, V, wsu)
+    torch.cuda.synchronize()
+    d = want + 5e-4 * W0
+    assert relF(V.cpu().numpy(), d) < 1e-6 and relF(W.cpu().numpy(), W0 - 0.1 * d) < 1e-6
