@@ -1,6 +1,7 @@
 // Companions of the hot path: bias compensation when the tracked mean moves (Sec. 3.1, eq. (vtb_corr)) and the two
 // monitoring figures of Sec. 6, whiteness rho (eq. (rho)) and normalised rank kappa (Sec. 3.2, eq. (hMs)).
 #include "fw_internal.h"
+#include "lane_sums.h"
 
 namespace fw {
 namespace {
@@ -109,7 +110,9 @@ __global__ __launch_bounds__(1024) void diagnostics_final_kernel(const double* _
 // image already lies in the space built so far) is recorded in `st` on the device and the remaining launches return at once.
 struct ProbeState { int steps, done; double prev_beta; };
 constexpr int PROBE_MAX_K = 32;
-constexpr int PROBE_SPREAD_MIN_M = 2048;   // above this the orthogonalisation of a step runs on many workgroups
+// above this, and with more than 16 basis vectors above half of it, the orthogonalisation of a step runs on many workgroups (a thread of
+// the single one would need more registers than it has)
+constexpr int PROBE_SPREAD_MIN_M = 2048;
 
 // q_0 = b0 / |b0| (b0 = all ones when absent)
 __global__ __launch_bounds__(1024) void probe_init_kernel(const float* __restrict__ b0, int M, double* __restrict__ q0, ProbeState* __restrict__ st) {
@@ -167,92 +170,95 @@ __global__ __launch_bounds__(256) void probe_matvec_kernel(const float* __restri
 
 // Step j of the recurrence, one workgroup: alpha_j = q_j . w, w made orthogonal to q_0 .. q_j (twice, all coefficients of
 // a pass taken from the same w), beta_j = |w|, q_(j+1) = w / beta_j -- or the breakdown flag when nothing is left of w.
-// w stays in LDS (16 KB at the largest M that comes here).  The step is a chain of latencies, not of bytes, so each of the
-// 16 wavefronts takes a whole basis vector (or, while there are fewer than 16, a run of its 64-wide strips): one shuffle
-// reduction per wavefront and pass instead of one per basis vector and wavefront.  The partial coefficients of a vector
-// are added in the order of the strips.
-// M = 525, 16 steps: 10 us a step instead of 26.
+// A thread owns E entries and keeps them, and those of the up to NB > j basis vectors, in registers: one round of loads, all in flight
+// together.  The coefficients of a pass are summed over the wavefront NB at a time, cross the workgroup through LDS and are added
+// by every wavefront for itself in the order of the wavefronts, so a pass has one barrier.
+// M = 525, 16 steps: 3.5 us a step (the basis read again for every product and subtraction, three barriers a pass: 10.3 us).
+template <int E, int NB>
 __global__ __launch_bounds__(1024) void probe_orth_kernel(int j, int M, size_t ld, double* __restrict__ Qb, const double* __restrict__ w,
                                                           double* __restrict__ alpha, double* __restrict__ beta, double breakdown,
                                                           ProbeState* __restrict__ st) {
-    __shared__ double wl[PROBE_SPREAD_MIN_M];
-    __shared__ double red[16];
-    __shared__ double part[PROBE_MAX_K + 1][16];
-    __shared__ double coef[PROBE_MAX_K + 1];
+    __shared__ double part[3][16][NB + 1];
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    double x[E], q[NB][E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int m = t + 1024 * e;
+        x[e] = m < M ? w[m] : 0.0;
+#pragma unroll
+        for (int i = 0; i < NB; ++i) q[i][e] = (i <= j && m < M) ? Qb[(size_t)i * ld + m] : 0.0;
+    }
     if (st->done) return;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    double s0 = 0.0;
-    for (int m = threadIdx.x; m < M; m += 1024) {
-        const double x = w[m];
-        wl[m] = x;
-        s0 += x * x;
-    }
-    const double n0 = sqrt(block_sum_1024(s0, red));     // has the barriers that publish wl
-    const int runs = j < 16 ? 16 / (j + 1) : 1;          // wavefronts per basis vector
+    // NB values per lane -> their sums over the wavefront in part[..][wave][0 .. NB - 1]
+    auto sums_to = [&](const double (&v)[NB], double* out) {
+        double h[NB / 2];
+#pragma unroll
+        for (int i = 0; i < NB / 2; ++i) h[i] = fold32(v[i], v[i + NB / 2]);
+#pragma unroll
+        for (int i = 0; i < NB / 4; ++i) {
+            const double s = sum16(fold16(h[i], h[i + NB / 4]));     // value i + g NB / 4 in lanes 16 g .. 16 g + 15
+            if ((lane & 15) == 0) out[i + (lane >> 4) * (NB / 4)] = s;
+        }
+    };
+    auto square = [&] {
+        double s = 0.0;
+#pragma unroll
+        for (int e = 0; e < E; ++e) s += x[e] * x[e];
+        return sum16(fold16(fold32(s, s), fold32(s, s)));            // over the wavefront, in every lane
+    };
+    double n0 = 0.0, al = 0.0;
+#pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
-        for (int vr = wave; vr < (j + 1) * runs; vr += 16) {
-            const int i = vr / runs, run = vr - i * runs;
-            const double* q = Qb + (size_t)i * ld;
-            const int step = 64 * runs;
-            double d = 0.0;
-            int m = 64 * run + lane;
-            for (; m + 7 * step < M; m += 8 * step) {
-                double x[8];
+        double v[NB];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) x[u] = q[m + u * step];
+        for (int i = 0; i < NB; ++i) {
+            v[i] = 0.0;
 #pragma unroll
-                for (int u = 0; u < 8; ++u) d += x[u] * wl[m + u * step];
-            }
-            {
-                // the rest, one batch as well: entries beyond M read entry 0 and count with weight zero
-                double x[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) x[u] = q[m + u * step < M ? m + u * step : 0];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) d += m + u * step < M ? x[u] * wl[m + u * step] : 0.0;
-            }
-            d = wave_sum(d);
-            if (lane == 0) part[i][run] = d;
+            for (int e = 0; e < E; ++e) v[i] += q[i][e] * x[e];
+        }
+        sums_to(v, part[pass][wave]);
+        if (pass == 0) {
+            const double s = square();
+            if (lane == 0) part[0][wave][NB] = s;
         }
         __syncthreads();
-        if ((int)threadIdx.x <= j) {
-            double c = 0.0;
-            for (int r = 0; r < runs; ++r) c += part[threadIdx.x][r];
-            coef[threadIdx.x] = c;
-            if (pass == 0 && (int)threadIdx.x == j) alpha[j] = c;
+        // coefficient `lane` (and behind the last one the square of the first pass)
+        double c = 0.0;
+        if (lane < NB + (pass == 0 ? 1 : 0)) {
+#pragma unroll
+            for (int g = 0; g < 16; ++g) c += part[pass][g][lane];
         }
-        __syncthreads();
-        for (int m = threadIdx.x; m < M; m += 1024) {
-            double x = wl[m];
-            int i = 0;
-            for (; i + 8 <= j + 1; i += 8) {
-                double q[8];
+        auto from_lane = [&](int i) {
+            const long long b = __double_as_longlong(c);
+            const unsigned lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffll), i), hi = __builtin_amdgcn_readlane((int)(b >> 32), i);
+            return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+        };
+        if (pass == 0) { n0 = sqrt(from_lane(NB)); al = from_lane(j); }
 #pragma unroll
-                for (int u = 0; u < 8; ++u) q[u] = Qb[(size_t)(i + u) * ld + m];
+        for (int i = 0; i < NB; ++i) {
+            const double ci = from_lane(i);
 #pragma unroll
-                for (int u = 0; u < 8; ++u) x -= coef[i + u] * q[u];
-            }
-            if (i <= j) {
-                double q[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) q[u] = Qb[(size_t)(i + u <= j ? i + u : 0) * ld + m];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) x -= i + u <= j ? coef[i + u] * q[u] : 0.0;
-            }
-            wl[m] = x;
+            for (int e = 0; e < E; ++e) x[e] -= ci * q[i][e];
         }
-        __syncthreads();
     }
+    const double s = square();
+    if (lane == 0) part[2][wave][0] = s;
+    __syncthreads();
     double s1 = 0.0;
-    for (int m = threadIdx.x; m < M; m += 1024) s1 += wl[m] * wl[m];
-    const double nw = sqrt(block_sum_1024(s1, red));
+#pragma unroll
+    for (int g = 0; g < 16; ++g) s1 += part[2][g][0];
+    const double nw = sqrt(s1);
     const bool stop = !(nw > breakdown * n0);
     if (!stop) {
         const double inv = 1.0 / nw;
-        double* qn = Qb + (size_t)(j + 1) * ld;
-        for (int m = threadIdx.x; m < M; m += 1024) qn[m] = wl[m] * inv;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int m = t + 1024 * e;
+            if (m < M) Qb[(size_t)(j + 1) * ld + m] = x[e] * inv;
+        }
     }
-    if (threadIdx.x == 0) {
+    if (t == 0) {
+        alpha[j] = al;
         beta[j] = nw;
         st->steps = j + 1;
         if (stop) st->done = 1;
@@ -450,7 +456,8 @@ fw_status cond_probe(const float* Phi_y, int M, const float* b0, int k, float* o
     hipLaunchKernelGGL(probe_init_kernel, dim3(1), dim3(1024), 0, st, b0, M, Qb, ps);
     for (int j = 0; j < k; ++j) {
         hipLaunchKernelGGL(probe_matvec_kernel, dim3((M + 3) / 4), dim3(256), 0, st, Phi_y, Qb + (size_t)j * L.ld, M, w, ps);
-        if (M > PROBE_SPREAD_MIN_M) {
+        const bool two = M > PROBE_SPREAD_MIN_M / 2;
+        if (M > PROBE_SPREAD_MIN_M || (two && j >= 16)) {
             // many features: the step spread over ceil(M / 256) workgroups, four launches
             const dim3 g((M + PROBE_WG - 1) / PROBE_WG), blk(PROBE_WG);
             hipLaunchKernelGGL(probe_orth_phase_kernel<1>, g, blk, 0, st, j, M, L.ld, Qb, w, part, alpha, beta, 1e-7, ps);
@@ -458,7 +465,12 @@ fw_status cond_probe(const float* Phi_y, int M, const float* b0, int k, float* o
             hipLaunchKernelGGL(probe_orth_phase_kernel<3>, g, blk, 0, st, j, M, L.ld, Qb, w, part, alpha, beta, 1e-7, ps);
             hipLaunchKernelGGL(probe_orth_phase_kernel<4>, g, blk, 0, st, j, M, L.ld, Qb, w, part, alpha, beta, 1e-7, ps);
         }
-        else hipLaunchKernelGGL(probe_orth_kernel, dim3(1), dim3(1024), 0, st, j, M, L.ld, Qb, w, alpha, beta, 1e-7, ps);
+#define FW_PROBE_ORTH(E, NB) hipLaunchKernelGGL((probe_orth_kernel<E, NB>), dim3(1), dim3(1024), 0, st, j, M, L.ld, Qb, w, alpha, beta, 1e-7, ps)
+        else if (two) { if (j < 8) FW_PROBE_ORTH(2, 8); else FW_PROBE_ORTH(2, 16); }
+        else if (j < 8) FW_PROBE_ORTH(1, 8);
+        else if (j < 16) FW_PROBE_ORTH(1, 16);
+        else FW_PROBE_ORTH(1, 32);
+#undef FW_PROBE_ORTH
     }
     hipLaunchKernelGGL(probe_final_kernel, dim3(1), dim3(2 * PROBE_CUTS), 0, st, alpha, beta, ps, out);
     FW_LAUNCH_CHECK();
