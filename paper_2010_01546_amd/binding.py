@@ -113,8 +113,16 @@ def _ptr(t):
     return t.data_ptr()
 
 
+# The handle of the current stream without a Stream object around it: 0.2 us instead of 2.8 us a call, of which a block boundary
+# makes five to ten (128 x 64 features: 45 us of host time a pass -> 32 us, the kernels take 38 us).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream):
     if stream is None:
+        if _raw_stream is not None and _device is not None and torch.cuda.is_initialized():
+            return _raw_stream(_device())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream
