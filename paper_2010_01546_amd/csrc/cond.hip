@@ -726,7 +726,9 @@ __global__ __launch_bounds__(256) void state_init_kernel(fw_cond_state s) {
 // (I, J), I >= J (M a multiple of 4): the tile (I,J) is read once with 16-byte loads, written transposed as (J,I) through
 // LDS, and leaves two sets of partial sums of squares: over its columns for the rows of block I, over its rows for the
 // rows of block J (the mirrored tile's rows).  xpart[colblock][row], summed by partial_sum_kernel.
-__global__ __launch_bounds__(256) void mirror_rownorm_kernel(float* __restrict__ P, int M, int Mp, float* __restrict__ xpart) {
+// With nks > 0 the lower triangle is the sum of the runs part[nks][M][M], added in order, and is written as well.
+__global__ __launch_bounds__(256) void mirror_rownorm_kernel(float* __restrict__ P, int M, int Mp, float* __restrict__ xpart,
+                                                             const float* __restrict__ part, int nks) {
     __shared__ float t[64][65];
     int I = (int)((sqrtf(8.f * (float)blockIdx.x + 1.f) - 1.f) * 0.5f);
     while ((I + 1) * (I + 2) / 2 <= (int)blockIdx.x) ++I;
@@ -739,7 +741,17 @@ __global__ __launch_bounds__(256) void mirror_rownorm_kernel(float* __restrict__
         const int rr = r0 + 16 * pass, i = I * 64 + rr;
         float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
         if (i < M && j < M) {
-            v = *reinterpret_cast<const float4*>(P + (size_t)i * M + j);
+            const size_t e = (size_t)i * M + j;
+            if (nks > 0) {
+                v = *reinterpret_cast<const float4*>(part + e);
+                for (int z = 1; z < nks; ++z) {
+                    const float4 w = *reinterpret_cast<const float4*>(part + (size_t)z * M * M + e);
+                    v.x += w.x; v.y += w.y; v.z += w.z; v.w += w.w;
+                }
+                if (I != J) *reinterpret_cast<float4*>(P + e) = v;
+            } else {
+                v = *reinterpret_cast<const float4*>(P + e);
+            }
             if (I == J) {            // diagonal tile: what lies above the diagonal is taken from below it, after the barrier
                 if (j > i) v.x = 0.f;
                 if (j + 1 > i) v.y = 0.f;
@@ -971,16 +983,27 @@ static size_t refresh_xpart_bytes(int M) {
     const size_t nt = (size_t)(M + 63) / 64, Mp = (size_t)(M + 63) / 64 * 64;
     return align_up(nt * Mp * sizeof(float), 256);
 }
-size_t cond_refresh_workspace_bytes(int M) {
+static size_t refresh_split_bytes(int M) {
     return align_up((size_t)M * M * sizeof(float), 256) + 3 * gemm_split_packed_bytes(M, M) + refresh_xpart_bytes(M);
 }
+// Few 256-wide tiles leave compute units idle: both products then cut their contraction index into runs, which the passes behind
+// them (packing of Psi, mirror image of Phi_y) add up on the way.
+static int refresh_runs(int M, int lower) {
+    return M >= FW_REFRESH_SPLIT_MIN_M && (M & 3) == 0 ? gemm_split_caller_runs(M, M, M, lower) : 1;
+}
+static size_t refresh_runs_bytes(int M) {
+    const int a = refresh_runs(M, 0), b = refresh_runs(M, 1), n = a > b ? a : b;
+    return n > 1 ? align_up((size_t)n * M * M * sizeof(float), 256) : 0;
+}
+size_t cond_refresh_workspace_bytes(int M) { return refresh_split_bytes(M) + refresh_runs_bytes(M); }
 
 static bool refresh_in_rows(int M) { return M <= ((M & 3) == 0 ? REFRESH_ROWS_MAX_M : REFRESH_ROWS_MAX_M_UNALIGNED); }
 
 bool cond_refresh_plan(int M, size_t ws_bytes, fw_refresh_plan* plan) {
     if (M <= 0 || M > 16384) return false;
-    plan->split = (ws_bytes >= cond_refresh_workspace_bytes(M) && M >= FW_REFRESH_SPLIT_MIN_M) ? 1 : 0;
-    if (plan->split) plan->mfma_flops_issued = gemm_split_flops_issued(M, M, M, 0) + gemm_split_flops_issued(M, M, M, 1);
+    plan->split = (ws_bytes >= refresh_split_bytes(M) && M >= FW_REFRESH_SPLIT_MIN_M) ? 1 : 0;
+    const bool runs = refresh_runs_bytes(M) > 0 && ws_bytes >= cond_refresh_workspace_bytes(M);
+    if (plan->split) plan->mfma_flops_issued = gemm_split_flops_issued(M, M, M, 0, false, runs) + gemm_split_flops_issued(M, M, M, 1, false, runs);
     else if (refresh_in_rows(M)) {       // two products of every 16 x 16 tile, the contraction index in rounds of 64
         const double nt = (M + 15) / 16;
         plan->mfma_flops_issued = 2.0 * nt * nt * 2.0 * 256.0 * ((M + 63) / 64 * 64);
@@ -1010,21 +1033,34 @@ fw_status cond_state_refresh(const fw_cond_state* s, void* ws, size_t ws_bytes, 
     fw_status rc;
     // Below about 1500 features the float32 kernel is as fast (too few 256-wide tiles for 256 compute units, and the
     // three packing passes cost as much as a product); FW_REFRESH_SPLIT_MIN_M is where the split form starts.
-    if (ws && ws_bytes >= cond_refresh_workspace_bytes(M) && M >= FW_REFRESH_SPLIT_MIN_M) {
+    if (ws && ws_bytes >= refresh_split_bytes(M) && M >= FW_REFRESH_SPLIT_MIN_M) {
         const size_t pb = gemm_split_packed_bytes(M, M);
         void* Tp = base + psi_bytes;
         void* Xp = base + psi_bytes + pb;
         void* Pp = base + psi_bytes + 2 * pb;
         if ((rc = gemm_split_pack(s->T, M, M, Tp, st)) != FW_OK) return rc;
         if ((rc = gemm_split_pack(s->Phi_x, M, M, Xp, st)) != FW_OK) return rc;
-        if ((rc = gemm_split_run(Tp, Xp, M, M, M, 0, Psi, st)) != FW_OK) return rc;
-        if ((rc = gemm_split_pack(Psi, M, M, Pp, st)) != FW_OK) return rc;
-        if ((rc = gemm_split_run(Pp, Tp, M, M, M, 1, s->Phi_y, st)) != FW_OK) return rc;
+        float* part = refresh_runs_bytes(M) > 0 && ws_bytes >= cond_refresh_workspace_bytes(M)
+                          ? reinterpret_cast<float*>(base + refresh_split_bytes(M)) : nullptr;
+        int runs = 1;
+        if (part && refresh_runs(M, 0) > 1) {
+            if ((rc = gemm_split_run(Tp, Xp, M, M, M, 0, part, st, part, &runs, true)) != FW_OK) return rc;
+            if ((rc = gemm_split_sum_pack(part, runs, M, M, Psi, Pp, st)) != FW_OK) return rc;
+        } else {
+            if ((rc = gemm_split_run(Tp, Xp, M, M, M, 0, Psi, st)) != FW_OK) return rc;
+            if ((rc = gemm_split_pack(Psi, M, M, Pp, st)) != FW_OK) return rc;
+        }
+        int lower_runs = 0;
+        if (part && refresh_runs(M, 1) > 1) {
+            if ((rc = gemm_split_run(Pp, Tp, M, M, M, 1, part, st, part, &lower_runs, true)) != FW_OK) return rc;
+        } else {
+            if ((rc = gemm_split_run(Pp, Tp, M, M, M, 1, s->Phi_y, st)) != FW_OK) return rc;
+        }
         if ((M & 3) == 0) {
             // mirror and squared row norms in one pass
             float* xpart = reinterpret_cast<float*>(base + psi_bytes + 3 * pb);
             const int nt = (M + 63) / 64, Mp = nt * 64;
-            hipLaunchKernelGGL(mirror_rownorm_kernel, dim3(nt * (nt + 1) / 2), dim3(256), 0, st, s->Phi_y, M, Mp, xpart);
+            hipLaunchKernelGGL(mirror_rownorm_kernel, dim3(nt * (nt + 1) / 2), dim3(256), 0, st, s->Phi_y, M, Mp, xpart, part, lower_runs);
             hipLaunchKernelGGL(partial_sum_kernel, dim3((M + 15) / 16), dim3(256), 0, st, xpart, nt, M, Mp, s->xi2);
             FW_LAUNCH_CHECK();
             return FW_OK;

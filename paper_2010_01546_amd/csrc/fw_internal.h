@@ -170,11 +170,13 @@ double gemm_planes_flops(int S, int N, int K, bool lower);
 size_t gemm_split_packed_bytes(int rows, int K);
 fw_status gemm_split_pack(const float* X, int rows, int K, void* Xp, hipStream_t st);
 fw_status gemm_split_pack_transposed(const float* X, int K, int rows, void* Xp, hipStream_t st);
-double gemm_split_flops_issued(int R, int N, int K, int lower, bool with_runs = false);
+double gemm_split_flops_issued(int R, int N, int K, int lower, bool with_runs = false, bool caller_runs = false);
+int gemm_split_caller_runs(int R, int N, int K, int lower);
+fw_status gemm_split_sum_pack(const float* part, int runs, int rows, int K, float* X, void* Xp, hipStream_t st);
 int gemm_split_runs(int R, int N, int K);
 size_t gemm_split_partial_bytes(int R, int N, int K);
 fw_status gemm_split_run(const void* Ap, const void* Bp, int R, int N, int K, int lower, float* C, hipStream_t st,
-                         float* part = nullptr, int* runs_out = nullptr);
+                         float* part = nullptr, int* runs_out = nullptr, bool caller_runs = false);
 
 // ---- extras.hip
 fw_status mfma_rate_probe(int zero_operands, int iters, float* sink, double* flops, hipStream_t st);

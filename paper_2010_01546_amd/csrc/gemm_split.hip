@@ -47,7 +47,10 @@ __host__ __device__ inline int sp_cols_of_row(int I, int tr, int ncb, int lower)
 
 // ---- pre-pass: float32 [R, K] -> packed hi / lo planes.  A workgroup takes 64 rows x 64 contraction entries: coalesced
 // reads along k into LDS, then thread (r, kb) forms the two 16-byte elements; consecutive threads write consecutive rows.
-__global__ __launch_bounds__(256) void split_pack_kernel(const float* __restrict__ X, int R, int K, int Rp, int KB, uint4* __restrict__ Xp) {
+// SUM: X holds nks partial results [nks][R][K] (K a multiple of 4); they are added in order, the sum also goes to C.
+template <bool SUM>
+__global__ __launch_bounds__(256) void split_pack_kernel(const float* __restrict__ X, int R, int K, int Rp, int KB, uint4* __restrict__ Xp, int nks,
+                                                         float* __restrict__ C) {
     __shared__ float tile[64][65];
     const int r0 = blockIdx.y * 64, k0 = blockIdx.x * 64;
     const bool vec = (K & 3) == 0;
@@ -56,7 +59,17 @@ __global__ __launch_bounds__(256) void split_pack_kernel(const float* __restrict
         const int r = r0 + rr, k = k0 + 4 * q;
         float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
         if (r < R) {
-            if (vec) {
+            if (SUM) {
+                if (k < K) {
+                    const size_t at = (size_t)r * K + k;
+                    v = *reinterpret_cast<const float4*>(X + at);
+                    for (int z = 1; z < nks; ++z) {
+                        const float4 w = *reinterpret_cast<const float4*>(X + (size_t)z * R * K + at);
+                        v.x += w.x; v.y += w.y; v.z += w.z; v.w += w.w;
+                    }
+                    *reinterpret_cast<float4*>(C + at) = v;
+                }
+            } else if (vec) {
                 if (k < K) v = *reinterpret_cast<const float4*>(X + (size_t)r * K + k);
             } else {
                 const float* p = X + (size_t)r * K;
@@ -270,7 +283,7 @@ __global__ __launch_bounds__(256) void gemm_split_kernel(const uint4* __restrict
 
 struct SplitWs { size_t a, b, total; };
 
-inline bool make_split_geom(int R, int N, int K, int lower, SplitGeom* g, int max_runs = 1) {
+inline bool make_split_geom(int R, int N, int K, int lower, SplitGeom* g, int max_runs = 1, bool summed_by_caller = false) {
     if (R <= 0 || N <= 0 || K <= 0 || R > 16384 || N > 16384 || K > 16384) return false;
     g->R = R; g->N = N; g->K = K; g->lower = lower;
     g->Rp = (R + 63) / 64 * 64; g->Np = (N + 63) / 64 * 64;
@@ -280,7 +293,9 @@ inline bool make_split_geom(int R, int N, int K, int lower, SplitGeom* g, int ma
     // Tile height (64 nrt) and, when partial results may be used (max_runs > 1) and the tiles are few, the number of runs
     // the contraction index is cut into: least estimated time = rounds of 256 workgroups x (stages of a run + ring fill) x
     // time of a stage (its MFMAs, or its loads into LDS at about 23 bytes per cycle and compute unit), plus the pass that
-    // adds runs + 1 copies of the result.  A run keeps at least 32 stages.
+    // adds runs + 1 copies of the result.  A run keeps at least 32 stages.  A caller that adds them in a pass it needs anyway
+    // (summed_by_caller) pays for reading them only, and 24 stages are enough.
+    const int min_stages = summed_by_caller ? 24 : 32;
     const int nst = (g->KB) >> 1;
     double best = 1e300;
     for (int nrt = 4; nrt >= 2; --nrt) {
@@ -293,14 +308,15 @@ inline bool make_split_geom(int R, int N, int K, int lower, SplitGeom* g, int ma
         if (max_runs > 1 && nt <= 128) {
             kmax = (int)(256 / nt);
             if (kmax > max_runs) kmax = max_runs;
-            while (kmax > 1 && nst / kmax < 32) --kmax;
+            while (kmax > 1 && nst / kmax < min_stages) --kmax;
         }
         for (int nks = 1; nks <= kmax; ++nks) {
             const int spk = (nst + nks - 1) / nks;
             const int runs = (nst + spk - 1) / spk;
             const double rounds = (double)((nt * runs + 255) / 256);
             double cost = rounds * (spk + 5.0) * t_stage;
-            if (runs > 1) cost += (runs + 1.0) * R * (double)N * 4.0 / 4.0e12 * 2.0e9 + 4000.0;
+            if (runs > 1 && summed_by_caller) cost += (double)runs * nt * tr * SP_TC * 4.0 / 5.0e12 * 2.0e9;
+            else if (runs > 1) cost += (runs + 1.0) * R * (double)N * 4.0 / 4.0e12 * 2.0e9 + 4000.0;
             if (cost < best * 0.999) {
                 best = cost;
                 g->nrt = nrt; g->tr = tr; g->nrb = nrb; g->ncb = ncb; g->ntiles = (int)nt; g->nks = runs; g->spk = spk;
@@ -339,8 +355,18 @@ size_t gemm_split_packed_bytes(int rows, int K) {
 // Xp = packed hi / lo planes of X [rows, K]
 fw_status gemm_split_pack(const float* X, int rows, int K, void* Xp, hipStream_t st) {
     const int Rp = (rows + 63) / 64 * 64, KB = (K + 15) / 16 * 2;
-    hipLaunchKernelGGL(split_pack_kernel, dim3((8 * KB + 63) / 64, Rp / 64), dim3(256), 0, st, X, rows, K, Rp, KB,
-                       reinterpret_cast<uint4*>(Xp));
+    hipLaunchKernelGGL(split_pack_kernel<false>, dim3((8 * KB + 63) / 64, Rp / 64), dim3(256), 0, st, X, rows, K, Rp, KB,
+                       reinterpret_cast<uint4*>(Xp), 1, nullptr);
+    FW_LAUNCH_CHECK();
+    return FW_OK;
+}
+
+// X [rows, K] = the sum of the runs part[runs][rows][K] (K a multiple of 4), and Xp = its packed planes
+fw_status gemm_split_sum_pack(const float* part, int runs, int rows, int K, float* X, void* Xp, hipStream_t st) {
+    if ((K & 3) != 0 || runs < 1) return FW_ERR_UNSUPPORTED;
+    const int Rp = (rows + 63) / 64 * 64, KB = (K + 15) / 16 * 2;
+    hipLaunchKernelGGL(split_pack_kernel<true>, dim3((8 * KB + 63) / 64, Rp / 64), dim3(256), 0, st, part, rows, K, Rp, KB,
+                       reinterpret_cast<uint4*>(Xp), runs, X);
     FW_LAUNCH_CHECK();
     return FW_OK;
 }
@@ -361,15 +387,22 @@ int gemm_split_runs(int R, int N, int K) {
     if (!make_split_geom(R, N, K, 0, &g, GEMM_SPLIT_MAX_RUNS)) return 1;
     return g.nks;
 }
+// runs of a product whose caller adds them itself (lower: of a symmetric result, whose upper tiles are left out of every run)
+int gemm_split_caller_runs(int R, int N, int K, int lower) {
+    SplitGeom g;
+    if (!make_split_geom(R, N, K, lower, &g, GEMM_SPLIT_MAX_RUNS, true)) return 1;
+    return g.nks;
+}
 // room for those runs (for one result at least: a caller that sums the runs itself gets a single run there too)
 size_t gemm_split_partial_bytes(int R, int N, int K) {
     return align_up((size_t)gemm_split_runs(R, N, K) * R * N * sizeof(float), 256);
 }
 
 // with_runs: as gemm_split_run chooses the tiles when it is given room for partial results
-double gemm_split_flops_issued(int R, int N, int K, int lower, bool with_runs) {
+// caller_runs: as with gemm_split_caller_runs
+double gemm_split_flops_issued(int R, int N, int K, int lower, bool with_runs, bool caller_runs) {
     SplitGeom g;
-    if (!make_split_geom(R, N, K, lower, &g, (with_runs && !lower) ? GEMM_SPLIT_MAX_RUNS : 1)) return 0.0;
+    if (!make_split_geom(R, N, K, lower, &g, ((with_runs && !lower) || caller_runs) ? GEMM_SPLIT_MAX_RUNS : 1, caller_runs)) return 0.0;
     return 3.0 * 2.0 * (double)g.ntiles * g.tr * SP_TC * (8.0 * g.KB);
 }
 
@@ -378,11 +411,12 @@ double gemm_split_flops_issued(int R, int N, int K, int lower, bool with_runs) {
 // part: room for gemm_split_partial_bytes(R, N, K) bytes, or null (then the contraction index is never cut into runs)
 // runs_out: when given (with part, and C == part), the runs are left unsummed in part[run][R][N] (a single run: part[0]) and
 //   their number is returned, for a caller that adds them in an epilogue of its own
+// caller_runs: with runs_out, as many runs as gemm_split_caller_runs says
 fw_status gemm_split_run(const void* Ap, const void* Bp, int R, int N, int K, int lower, float* C, hipStream_t st, float* part,
-                         int* runs_out) {
-    if (runs_out && (!part || C != part || lower)) return FW_ERR_INVALID_ARG;
+                         int* runs_out, bool caller_runs) {
+    if (runs_out && (!part || C != part || (lower && !caller_runs))) return FW_ERR_INVALID_ARG;
     SplitGeom g;
-    if (!make_split_geom(R, N, K, lower, &g, (part && !lower) ? GEMM_SPLIT_MAX_RUNS : 1)) return FW_ERR_UNSUPPORTED;
+    if (!make_split_geom(R, N, K, lower, &g, (part && (!lower || caller_runs)) ? GEMM_SPLIT_MAX_RUNS : 1, caller_runs)) return FW_ERR_UNSUPPORTED;
     const dim3 grid((g.ntiles * g.nks + 7) / 8 * 8);
     const uint4* a = reinterpret_cast<const uint4*>(Ap);
     const uint4* b = reinterpret_cast<const uint4*>(Bp);
