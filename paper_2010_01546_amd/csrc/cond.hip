@@ -541,8 +541,9 @@ __global__ __launch_bounds__(256) void update_kernel(fw_cond_state s, const floa
 // ---- the whole step in one launch, for few features
 // Up to 64 features the six launches of the general form do next to nothing each: their time is the time between
 // launches (about 4.4 us apiece).  Here one workgroup of 1024 threads brings all six matrices to LDS, their loads in
-// flight together, and does the step from there; what remains is a chain of about 15 barriers.  A wavefront owns the
-// rows wave, wave + 16, ..., a lane is a column.  64 features: 13.7 us instead of 24 us.
+// flight together, and does the step from there.  The chain of five products runs in single wavefronts with a matrix in the
+// registers of each, two barriers in all; the update is spread over all 16: a wavefront owns the rows wave, wave + 16, ..., a lane is a
+// column.  64 features: 24 us with six launches, 13 us with every product spread over 16 wavefronts and 15 barriers, 10.5 us like this.
 // The line lies where six matrices fill the LDS: with one matrix at a time in LDS and the others read behind one another
 // from memory, one compute unit needed 77 us at 147 features against 31 us of the six launches.
 constexpr int COND_SMALL_MAX_M = 64;
@@ -560,14 +561,22 @@ __device__ __forceinline__ float wave_sum_dpp(float v) {
     return (r0 + r1) + (r2 + r3);
 }
 
+__device__ __forceinline__ float wave_max_dpp(float v) {
+#define FW_DPP_MAX(ctrl) v = fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xf, 0xf, true)))
+    FW_DPP_MAX(0xB1); FW_DPP_MAX(0x4E); FW_DPP_MAX(0x141); FW_DPP_MAX(0x140);     // the moves of wave_sum_dpp
+#undef FW_DPP_MAX
+    const float r0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 0)), r1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 16));
+    const float r2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 32)), r3 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 48));
+    return fmaxf(fmaxf(r0, r1), fmaxf(r2, r3));
+}
+
 __global__ __launch_bounds__(1024) void cond_small_kernel(fw_cond_state s, fw_cond_params prm, fw_cond_info* __restrict__ info) {
-    constexpr int PER = COND_SMALL_MAX_M / 16, G = 16;
+    constexpr int PER = COND_SMALL_MAX_M / 16;
     constexpr int MAT = COND_SMALL_MAX_M * (COND_SMALL_MAX_M + 1);
     __shared__ float Py[MAT], Tm[MAT], Qm[MAT], Sm[MAT], Pm[MAT], Xm[MAT];
-    __shared__ float wl[64], vt[64], v[64], u[64], t[64], p[64];
-    __shared__ float part[3][1024];
-    __shared__ float bv[16];
-    __shared__ int bi[16];
+    __shared__ float x0[64], v[64], u[64], t[64], p[64];
+    __shared__ float out_a, out_lam;
+    __shared__ Scal sc;
     const int M = s.M, ld = M | 1;      // odd row pitch: rows and columns are both read without conflicts
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -582,6 +591,8 @@ __global__ __launch_bounds__(1024) void cond_small_kernel(fw_cond_state s, fw_co
     auto put = [&](float* dst, const float (&x)[PER]) {
         FW_EACH(k, i, j) dst[i * ld + j] = x[k];
     };
+    const float x2_raw = (wave == 0 && lane < M) ? s.xi2[lane] : -1.f, lambda_bar = *s.lambda_bar;
+    const float x2 = x2_raw > -1.f ? x2_raw : -1.f;
     {
         float x[PER], y0[PER], y1[PER], y2[PER], y3[PER], y4[PER];
         load(s.Phi_y, x); load(s.T, y0); load(s.Q, y1); load(s.Qs, y2);
@@ -589,92 +600,79 @@ __global__ __launch_bounds__(1024) void cond_small_kernel(fw_cond_state s, fw_co
         put(Py, x); put(Tm, y0); put(Qm, y1); put(Sm, y2);
         if (leak) { put(Pm, y3); put(Xm, y4); }
     }
-    float best; int mp;
-    block_argmax(s.xi2, M, bv, bi, &best, &mp);     // its barrier publishes the matrices
-    const float xi_mp = sqrtf(fmaxf(best, 0.f));
-    int flags = 0;
+    __syncthreads();
 
-    // y = scale * (P^T x), a column per lane and every 16th row per wavefront: partial sums through LDS, added in order.  Up to
-    // three products run side by side (a null pointer is left out).  x must be published; y is published on return.
-    auto products = [&](const float* P0, const float* P1, const float* P2, const float* x, float scale, float* y0, float* y1, float* y2) {
-        if (lane < M) {
-            float a0 = 0.f, a1 = 0.f, a2 = 0.f;
+    // The chain of products: a wavefront holds a whole matrix, a column per lane, and takes the entries of x from its own lanes, so a
+    // product needs no barrier.  Wavefront 0 has Phi_y and goes from the arg-max to v and u alone; 1 and 2 have T and Psi.
+    if (wave < 3) {
+        float col[COND_SMALL_MAX_M];
+        {
+            const float* src = wave == 0 ? Py : wave == 1 ? Tm : Pm;
+            const bool mine = lane < M && (wave < 2 || leak);
 #pragma unroll
-            for (int k = 0; k < PER; ++k) {
-                const int i = wave + G * k;
-                if (i >= M) break;
-                const float xi = x[i];
-                a0 += P0[i * ld + lane] * xi;
-                if (P1) a1 += P1[i * ld + lane] * xi;
-                if (P2) a2 += P2[i * ld + lane] * xi;
+            for (int i = 0; i < COND_SMALL_MAX_M; ++i) col[i] = (mine && i < M) ? src[i * ld + lane] : 0.f;
+        }
+        // column `lane` of the matrix times x (zero in the lanes from M on)
+        auto product = [&](float x) {
+            float y0 = 0.f, y1 = 0.f, y2 = 0.f, y3 = 0.f;
+#pragma unroll
+            for (int i = 0; i < COND_SMALL_MAX_M; i += 4) {
+                auto at = [&](int k) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), k)); };
+                y0 += col[i] * at(i); y1 += col[i + 1] * at(i + 1); y2 += col[i + 2] * at(i + 2); y3 += col[i + 3] * at(i + 3);
             }
-            part[0][tid] = a0;
-            if (P1) part[1][tid] = a1;
-            if (P2) part[2][tid] = a2;
+            return (y0 + y1) + (y2 + y3);
+        };
+        if (wave == 0) {
+            // m', eq. (mt): norms that are NaN do not count, the lowest index on ties
+            const float best = wave_max_dpp(x2);
+            const unsigned long long ties = __ballot(lane < M && x2 == best);
+            const int mp = ties ? __ffsll((long long)ties) - 1 : 0;
+            const float xi_mp = sqrtf(fmaxf(best, 0.f));
+            const float c = product(lane < M ? Py[mp * ld + lane] : 0.f);                                  // eq. (vc)
+            // coherence set and weights (rule after eq. (vc))
+            const bool in = lane < M && fabsf(c) >= fmaxf(prm.c_rel * xi_mp * sqrtf(fmaxf(x2, 0.f)), prm.c_abs);
+            const int total = __popcll(__ballot(in));
+            int flags = total == 0 ? 1 : 0;
+            float cur = product(in && c != 0.f ? 1.f / ((float)total * c) : 0.f);                          // v~, first line of eq. (tve)
+            float nrm, inv;
+            for (int it = 0;; ++it) {
+                nrm = sqrtf(wave_sum_dpp(cur * cur));
+                inv = (nrm > 0.f && (flags & 1) == 0) ? 1.f / nrm : 0.f;
+                if (it == prm.n_power_iters) break;
+                cur = product(cur) * inv;                                                                  // refinement
+            }
+            if (!(nrm == nrm) || nrm > 3.0e38f) flags |= 4;
+            x0[lane] = cur; v[lane] = cur * inv;
+            if (lane == 0) { sc.vnorm = nrm; sc.m_prime = mp; sc.set_size = total; sc.flags = flags; sc.lambda_e = inv; }
         }
         __syncthreads();
-        if (tid < M) {
-            float a0 = 0.f, a1 = 0.f, a2 = 0.f;
-#pragma unroll
-            for (int g = 0; g < G; ++g) {
-                a0 += part[0][g * 64 + tid];
-                if (P1) a1 += part[1][g * 64 + tid];
-                if (P2) a2 += part[2][g * 64 + tid];
+        const float cur = x0[lane], inv = sc.lambda_e;
+        const float y = product(cur) * inv;                     // u = Phi_y v, t = T^T v, p = Psi^T v
+        (wave == 0 ? u : wave == 1 ? t : p)[lane] = y;
+        if (wave == 0) {
+            const float lam_e = wave_sum_dpp(cur * inv * y);                                               // eq. (lambda)
+            int flags = sc.flags, applied = 0;
+            float g_e = 1.f, a = 0.f;
+            if ((flags & 1) == 0) {                             // eqs. (ge), (xi) and the guard
+                g_e = prm.delta * lambda_bar / fmaxf(lam_e, prm.eps);
+                if (prm.guard && g_e >= 1.f) flags |= 2;
+                else if (!(g_e == g_e) || g_e > 3.0e38f) flags |= 4;
+                else { a = sqrtf(g_e) - 1.f; applied = 1; }
             }
-            y0[tid] = a0 * scale;
-            if (P1) y1[tid] = a1 * scale;
-            if (P2) y2[tid] = a2 * scale;
+            const float lam = (flags & 1) ? 0.f : lam_e;
+            if (lane == 0) {
+                out_a = a; out_lam = lam;
+                if (info) {
+                    info->lambda_e = lam; info->g_e = g_e; info->a_e = a; info->v_norm = sc.vnorm;
+                    info->m_prime = sc.m_prime; info->set_size = sc.set_size; info->applied = applied; info->flags = flags;
+                }
+            }
         }
+    } else {
         __syncthreads();
-    };
-    // sum over m of f(m), by every wavefront for itself
-    auto total_of = [&](auto f) {
-        float x = 0.f;
-        if (lane < M) x = f(lane);
-        return wave_sum_dpp(x);
-    };
-    products(Py, nullptr, nullptr, Py + mp * ld, 1.f, vt, nullptr, nullptr);   // c, eq. (vc)
-    // coherence set and weights (rule after eq. (vc))
-    auto member = [&](int m) {
-        const float thr = fmaxf(prm.c_rel * xi_mp * sqrtf(fmaxf(s.xi2[m], 0.f)), prm.c_abs);
-        return fabsf(vt[m]) >= thr;
-    };
-    const float total = total_of([&](int m) { return member(m) ? 1.f : 0.f; });
-    if (total == 0.f) flags |= 1;
-    if (tid < M) {
-        const float cm = vt[tid];
-        wl[tid] = cm != 0.f && member(tid) ? 1.f / (total * cm) : 0.f;
     }
     __syncthreads();
-    products(Py, nullptr, nullptr, wl, 1.f, vt, nullptr, nullptr);             // v~, first line of eq. (tve)
-    float* cur = vt;
-    float* other = wl;
-    float nrm = 0.f, inv = 0.f;
-    for (int it = 0;; ++it) {
-        nrm = sqrtf(total_of([&](int m) { return cur[m] * cur[m]; }));
-        inv = (nrm > 0.f && (flags & 1) == 0) ? 1.f / nrm : 0.f;
-        if (it == prm.n_power_iters) break;
-        products(Py, nullptr, nullptr, cur, inv, other, nullptr, nullptr);     // refinement
-        float* tmp = cur; cur = other; other = tmp;
-    }
-    if (!(nrm == nrm) || nrm > 3.0e38f) flags |= 4;
-    if (tid < M) v[tid] = cur[tid] * inv;
-    // u = Phi_y v, t = T^T v, p = Psi^T v
-    products(Py, Tm, leak ? Pm : nullptr, cur, inv, u, t, p);
-    const float lam_e = total_of([&](int m) { return v[m] * u[m]; });                    // eq. (lambda)
-    float g_e = 1.f, a = 0.f;
-    int applied = 0;
-    if ((flags & 1) == 0) {                         // eqs. (ge), (xi) and the guard
-        g_e = prm.delta * (*s.lambda_bar) / fmaxf(lam_e, prm.eps);
-        if (prm.guard && g_e >= 1.f) flags |= 2;
-        else if (!(g_e == g_e) || g_e > 3.0e38f) flags |= 4;
-        else { a = sqrtf(g_e) - 1.f; applied = 1; }
-    }
-    const float lam = (flags & 1) ? 0.f : lam_e;
-    if (tid == 0 && info) {
-        info->lambda_e = lam; info->g_e = g_e; info->a_e = a; info->v_norm = nrm;
-        info->m_prime = mp; info->set_size = (int)total; info->applied = applied; info->flags = flags;
-    }
+    const float a = out_a, lam = out_lam;
 
     // update: the formulas of update_kernel.  Old values of a symmetric matrix come from its lower triangle (hi, lo), and the
     // terms of a symmetric result are taken in that order, so both positions get the same value.
