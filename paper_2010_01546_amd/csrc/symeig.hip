@@ -703,6 +703,113 @@ __global__ __launch_bounds__(512) void dc_deflate_kernel(DcArrays D, const doubl
     }
 }
 
+// The same for merges of up to DEFLATE_MAX entries, all in LDS, one thread only where something is rotated.  Which entries have a
+// negligible component of z is known at once, and so is for which neighbours among the others the rotation is due, as long as neither
+// has been rotated: the serial part starts at those pairs and ends where a rotated entry and its next neighbour part, which
+// leaves most merges without any.  (One thread through all entries took 195 ns each: 0.93 of 14.2 ms at 2304 rows, 0.23 of 2.8 at 576.)
+constexpr int DEFLATE_MAX = 4096;
+__global__ __launch_bounds__(512) void dc_deflate_lds_kernel(DcArrays D, const double* __restrict__ e, int M, int ld, int P, const double* __restrict__ V) {
+    __shared__ double cd[DEFLATE_MAX], cz[DEFLATE_MAX];
+    __shared__ unsigned short ci[DEFLATE_MAX];            // place in the merged order
+    __shared__ unsigned long long due[DEFLATE_MAX / 64], gone[DEFLATE_MAX / 64];
+    __shared__ int cnt[8];
+    const int m = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int off = part_begin(m, P, M), mid = part_begin(2 * m + 1, 2 * P, M), end = part_begin(m + 1, P, M);
+    const int n = end - off, n1 = mid - off;
+    const double rho = fabs(e[mid - 1]);
+    const double sgn = e[mid - 1] >= 0.0 ? 1.0 : -1.0;
+    const double r = 2.0 * rho;
+    const double* d = D.d + off;
+    double* sd = D.sd + off; double* sz = D.sz + off; int* srow = D.srow + off;
+    for (int i = tid; i < n; i += 512) { sd[i] = d[i]; sz[i] = 0.0; srow[i] = off + i; }   // every place has a value (NaN)
+    if (tid < DEFLATE_MAX / 64) { due[tid] = 0; gone[tid] = 0; }
+    __syncthreads();
+    // place in the merged order: entries of the first part come first on ties
+    for (int i = tid; i < n; i += 512) {
+        const double x = d[i];
+        int lo = i < n1 ? n1 : 0, hi = i < n1 ? n : n1;
+        const int base = lo;
+        while (lo < hi) {
+            const int k = (lo + hi) >> 1;
+            if (i < n1 ? d[k] < x : d[k] <= x) lo = k + 1; else hi = k;
+        }
+        const int pos = (i < n1 ? i : i - n1) + (lo - base);
+        sd[pos] = x;
+        sz[pos] = (i < n1 ? V[(size_t)(off + i) * ld + mid - 1] : sgn * V[(size_t)(off + i) * ld + mid]) * 0.70710678118654752440;
+        srow[pos] = off + i;
+    }
+    __syncthreads();
+    const double big = fmax(fmax(fabs(sd[0]), fabs(sd[n - 1])), r);
+    const double tol = 8.0 * EPS * big;
+    // places of the true ones of `yes` in order, behind those of earlier calls (`base`, updated)
+    auto place = [&](bool yes, int& base) {
+        const unsigned long long mask = __ballot(yes);
+        if (lane == 0) cnt[wave] = __popcll(mask);
+        __syncthreads();
+        int before = base, all = 0;
+#pragma unroll
+        for (int w = 0; w < 8; ++w) { if (w < wave) before += cnt[w]; all += cnt[w]; }
+        __syncthreads();
+        base += all;
+        return before + __popcll(mask & ((1ull << lane) - 1ull));
+    };
+    int ns = 0;                                           // entries with a component of z, moved together
+    for (int c0 = 0; c0 < n; c0 += 512) {
+        const int i = c0 + tid;
+        const double x = i < n ? sd[i] : 0.0, z = i < n ? sz[i] : 0.0;
+        const bool none = i < n && r * fabs(z) <= tol;
+        const int first = ns, at = place(i < n && !none, ns);
+        if (i < n && !none) { cd[at] = x; cz[at] = z; ci[at] = (unsigned short)i; }
+        if (none) {
+            const int k = c0 - first + (tid - (at - first));      // entries without one before this one
+            D.dd[off + k] = x; D.drow[off + k] = i;
+        }
+    }
+    __syncthreads();
+    auto rotates = [&](double pd, double pz, double jd, double jz) { return fabs((jd - pd) * (pz * jz)) <= tol * (pz * pz + jz * jz); };
+    for (int c0 = 0; c0 < ns; c0 += 512) {
+        const int i = c0 + tid;
+        const unsigned long long mask = __ballot(i + 1 < ns && rotates(cd[i], cz[i], cd[i + 1], cz[i + 1]));
+        if (lane == 0 && i < ns) due[i >> 6] = mask;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        int nd = n - ns, nr = 0, t = 0;
+        for (;;) {
+            // the next pair (t, t + 1) that is due
+            int w = t >> 6;
+            unsigned long long mask = w < DEFLATE_MAX / 64 ? due[w] & (~0ull << (t & 63)) : 0;
+            while (!mask && ++w < DEFLATE_MAX / 64) mask = due[w];
+            if (!mask) break;
+            int p = 64 * w + __ffsll((long long)mask) - 1, j = p + 1;
+            double pd = cd[p], pz = cz[p];
+            while (j < ns) {
+                double jd = cd[j], jz = cz[j];
+                if (!rotates(pd, pz, jd, jz)) break;
+                const double rr = sqrt(pz * pz + jz * jz), c = jz / rr, s = pz / rr;
+                D.ri[off + nr] = ci[p]; D.rj[off + nr] = ci[j]; D.rc[off + nr] = c; D.rs[off + nr] = s; ++nr;
+                D.dd[off + nd] = c * c * pd + s * s * jd; D.drow[off + nd] = ci[p]; ++nd;
+                gone[p >> 6] |= 1ull << (p & 63);
+                jd = s * s * pd + c * c * jd;
+                jz = rr;
+                p = j; pd = jd; pz = jz; ++j;
+            }
+            cd[p] = pd; cz[p] = pz;
+            t = j;
+        }
+        D.cnt[4 * m + 1] = nd; D.cnt[4 * m + 2] = nr;
+    }
+    __syncthreads();
+    int nk = 0;
+    for (int c0 = 0; c0 < ns; c0 += 512) {
+        const int i = c0 + tid;
+        const bool keep = i < ns && !((gone[i >> 6] >> (i & 63)) & 1);
+        const int at = place(keep, nk);
+        if (keep) { D.kd[off + at] = cd[i]; D.kz[off + at] = cz[i]; D.krow[off + at] = ci[i]; }
+    }
+    if (tid == 0) D.cnt[4 * m] = nk;
+}
+
 // plane rotations of the deflation on rows of V, one thread per column; the chain prev -> next stays in a register
 __global__ __launch_bounds__(64) void dc_rotate_kernel(DcArrays D, int M, int ld, int P, double* __restrict__ V) {
     const int m = blockIdx.y;
@@ -1009,29 +1116,58 @@ __global__ __launch_bounds__(256) void dc_product_kernel(DcArrays D, int M, int 
     });
 }
 
-// F of a block of reflectors (rows c0 .. c0 + 63 of Y): H_c0 H_c0+1 ... = I - Y^T F Y, upper triangular,
-// F[:k][k] = -tau_k F[:k][:k] (Y y_k), F[k][k] = tau_k
-__global__ __launch_bounds__(256) void wy_factor_kernel(const double* __restrict__ Y, int ld, int M, const double* __restrict__ tau,
-                                                        double* __restrict__ F) {
-    __shared__ double Gm[NB][NB + 1], Fs[NB][NB + 1];
+// gram[block][slice] = Y Y^T of a block of reflectors (rows c0 .. c0 + 63 of Y) over a slice of the columns
+constexpr int WY_SLICES = 4;
+__global__ __launch_bounds__(256) void wy_gram_kernel(const double* __restrict__ Y, int ld, int M, double* __restrict__ gram) {
+    const int c0 = blockIdx.x * NB, kmax = min(c0 + NB, M);
+    const int ks = ((kmax + WY_SLICES - 1) / WY_SLICES + 15) / 16 * 16;
+    const int kb = min(kmax, (int)blockIdx.y * ks), ke = min(kmax, kb + ks);
+    double* dst = gram + ((size_t)blockIdx.x * WY_SLICES + blockIdx.y) * NB * NB;
+    const RowsK A = {Y, ld, c0, M, ke};
+    gemm64(A, A, kb, ke, [&](int r, int c, double x) { dst[r * NB + c] = x; });
+}
+// F of a block: H_c0 H_c0+1 ... = I - Y^T F Y, upper triangular, F[:k][k] = -tau_k F[:k][:k] (Y y_k), F[k][k] = tau_k.  A row of F needs
+// nothing of the other rows: one lane each, no barrier in the recurrence.
+__global__ __launch_bounds__(256) void wy_factor_kernel(const double* __restrict__ gram, int M, const double* __restrict__ tau, double* __restrict__ F) {
+    __shared__ double Gm[NB][NB + 2], Ft[NB][NB];        // Ft[column][row]
     const int c0 = blockIdx.x * NB;
-    const int kmax = min(c0 + NB, M);
-    const RowsK A = {Y, ld, c0, M, kmax};
-    gemm64(A, A, 0, kmax, [&](int r, int c, double x) { Gm[r][c] = x; });
-    for (int e = threadIdx.x; e < NB * NB; e += 256) Fs[e >> 6][e & 63] = 0.0;
-    __syncthreads();
-    for (int k = 0; k < NB; ++k) {
-        const double tk = c0 + k < M ? tau[c0 + k] : 0.0;
-        if (threadIdx.x < NB) {
-            const int i = threadIdx.x;
-            double s = 0.0;
-            for (int q = i; q < k; ++q) s += Fs[i][q] * Gm[q][k];
-            if (i < k) Fs[i][k] = -tk * s;
-            if (i == k) Fs[k][k] = tk;
-        }
-        __syncthreads();
+    const double* src = gram + (size_t)blockIdx.x * WY_SLICES * NB * NB;
+    for (int e = threadIdx.x; e < NB * NB; e += 256) {
+        double s = 0.0;
+#pragma unroll
+        for (int k = 0; k < WY_SLICES; ++k) s += src[(size_t)k * NB * NB + e];
+        Gm[e & 63][e >> 6] = s;                          // symmetric; [column][row] so that a column of it lies along a row here
+        Ft[e >> 6][e & 63] = 0.0;
     }
-    for (int e = threadIdx.x; e < NB * NB; e += 256) F[(size_t)blockIdx.x * NB * NB + e] = Fs[e >> 6][e & 63];
+    __syncthreads();
+    if (threadIdx.x < NB) {
+        const int i = threadIdx.x;
+        const double ti = c0 + i < M ? tau[c0 + i] : 0.0;
+        for (int k = 0; k < NB; ++k) {
+            const double tk = lane_value(ti, k);
+            double s0 = 0.0, s1 = 0.0;
+            int q = 0;
+            for (; q + 8 <= k; q += 8) {
+#pragma unroll
+                for (int u = 0; u < 8; u += 2) { s0 += Ft[q + u][i] * Gm[k][q + u]; s1 += Ft[q + u + 1][i] * Gm[k][q + u + 1]; }
+            }
+            for (; q < k; ++q) s0 += Ft[q][i] * Gm[k][q];
+            Ft[k][i] = i < k ? -tk * (s0 + s1) : i == k ? tk : 0.0;
+        }
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < NB * NB; e += 256) F[(size_t)blockIdx.x * NB * NB + e] = Ft[e & 63][e >> 6];
+}
+// Z = F Y, all blocks: the reflections are then V -= (V Y^T) Z
+__global__ __launch_bounds__(256) void wy_form_kernel(const double* __restrict__ F, const double* __restrict__ Y, int ld, int M, double* __restrict__ Z) {
+    const int c0 = blockIdx.y * NB, nb = min(NB, M - c0), kmax = c0 + nb;
+    const int col0 = blockIdx.x * 64;
+    if (col0 >= kmax) return;
+    const RowsK A = {F + (size_t)blockIdx.y * NB * NB, NB, 0, NB, NB};
+    const ColsK B = {Y + (size_t)c0 * ld, ld, col0, kmax, nb, nullptr, nullptr};
+    gemm64(A, B, 0, NB, [&](int r, int c, double x) {
+        if (r < nb && col0 + c < kmax) Z[(size_t)(c0 + r) * ld + col0 + c] = x;
+    });
 }
 
 // part[slice] = V Y^T restricted to a slice of the contraction index
@@ -1046,28 +1182,18 @@ __global__ __launch_bounds__(256) void wy_project_kernel(const double* __restric
         if (row0 + r < M) dst[(size_t)(row0 + r) * NB + c] = x;
     });
 }
-// out = (sum of the slices) F
-__global__ __launch_bounds__(256) void wy_multiply_kernel(const double* __restrict__ part, int slices, const double* __restrict__ F, int M,
-                                                          double* __restrict__ out) {
-    __shared__ double Fs[NB][NB + 1], Gs[16][NB + 1];
-    const int row0 = blockIdx.x * 16;
-    for (int e = threadIdx.x; e < NB * NB; e += 256) Fs[e >> 6][e & 63] = F[e];
-    for (int e = threadIdx.x; e < 16 * NB; e += 256) {
-        const int r = row0 + (e >> 6);
-        double s = 0.0;
-        if (r < M)
-            for (int k = 0; k < slices; ++k) s += part[((size_t)k * M + r) * NB + (e & 63)];
-        Gs[e >> 6][e & 63] = s;
-    }
-    __syncthreads();
-    for (int e = threadIdx.x; e < 16 * NB; e += 256) {
-        const int r = e >> 6, c = e & 63;
-        double s = 0.0;
-        for (int q = 0; q <= c; ++q) s += Gs[r][q] * Fs[q][c];
-        if (row0 + r < M) out[(size_t)(row0 + r) * NB + c] = s;
-    }
+// out = sum of the slices
+__global__ __launch_bounds__(256) void wy_sum_kernel(const double* __restrict__ part, int slices, int n, double* __restrict__ out) {
+    const int e = blockIdx.x * 256 + threadIdx.x;
+    if (e >= n) return;
+    double x[8], s = 0.0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) x[k] = k < slices ? part[(size_t)k * n + e] : 0.0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) s += x[k];
+    out[e] = s;
 }
-// V -= G Y
+// V -= G Z, Z the rows of a block
 __global__ __launch_bounds__(256) void wy_update_kernel(const double* __restrict__ Gm, const double* __restrict__ Y, int ld, int M, int c0,
                                                         int kmax, double* __restrict__ V) {
     const int row0 = blockIdx.y * 64, col0 = blockIdx.x * 64;
@@ -1344,10 +1470,10 @@ inline SmallWs small_layout(int M) {
 
 int sym_eig_ld(int M) { return (M + 15) / 16 * 16; }
 size_t sym_eig_small_bytes(int M) { return small_layout(M).total; }
-// doubles the first matrix buffer must hold besides the matrix: projections of the back-transformation
+// doubles the first matrix buffer must hold besides the matrix: products of reflectors and projections of the back-transformation
 size_t sym_eig_matrix_doubles(int M) {
-    const size_t a = (size_t)M * sym_eig_ld(M), b = (size_t)M * NB * 9;
-    return a > b ? a : b;
+    const size_t a = (size_t)M * sym_eig_ld(M), b = (size_t)M * NB * 9, c = (size_t)((M + NB - 1) / NB) * WY_SLICES * NB * NB;
+    return a > b ? (a > c ? a : c) : (b > c ? b : c);
 }
 
 // Eigenvectors of the symmetric part of Phi as rows, ascending eigenvalues.  dead: some diagonal entry is zero.  buf[0..3]: four matrices of
@@ -1395,7 +1521,8 @@ fw_status sym_eig(const float* Phi, int M, bool dead, double* const buf[4], void
     for (int P = leaves / 2; P >= 1; P /= 2) {
         const int nmax = (M + P - 1) / P + 1;
         const dim3 waves((nmax + 3) / 4, P);
-        hipLaunchKernelGGL(dc_deflate_kernel, dim3(P), dim3(512), 0, st, D, e, M, ld, P, Va);
+        if (nmax <= DEFLATE_MAX) hipLaunchKernelGGL(dc_deflate_lds_kernel, dim3(P), dim3(512), 0, st, D, e, M, ld, P, Va);
+        else hipLaunchKernelGGL(dc_deflate_kernel, dim3(P), dim3(512), 0, st, D, e, M, ld, P, Va);
         hipLaunchKernelGGL(dc_rotate_kernel, dim3((nmax + 63) / 64, P), dim3(64), 0, st, D, M, ld, P, Va);
         hipLaunchKernelGGL(dc_secular_kernel, waves, dim3(256), 0, st, D, e, M, P);
         hipLaunchKernelGGL(dc_zhat_kernel, waves, dim3(256), 0, st, D, M, ld, P, Va, Vb);
@@ -1409,7 +1536,10 @@ fw_status sym_eig(const float* Phi, int M, bool dead, double* const buf[4], void
     // back-transformation: blocks of reflectors in ascending order
     const int nblk = (M + NB - 1) / NB, rt = (M + 63) / 64;
     double* F = dbl(L.F);
-    hipLaunchKernelGGL(wy_factor_kernel, dim3(nblk), dim3(256), 0, st, Y, ld, M, tau, F);
+    double* Z = Vb;                                       // free until the end
+    hipLaunchKernelGGL(wy_gram_kernel, dim3(nblk, WY_SLICES), dim3(256), 0, st, Y, ld, M, A);
+    hipLaunchKernelGGL(wy_factor_kernel, dim3(nblk), dim3(256), 0, st, A, M, tau, F);
+    hipLaunchKernelGGL(wy_form_kernel, dim3((M + 63) / 64, nblk), dim3(256), 0, st, F, Y, ld, M, Z);
     double* part = A;
     double* G = A + (size_t)8 * M * NB;
     for (int b = 0; b < nblk; ++b) {
@@ -1421,8 +1551,8 @@ fw_status sym_eig(const float* Phi, int M, bool dead, double* const buf[4], void
         const int kslice = ((kmax + slices - 1) / slices + 15) / 16 * 16;
         slices = (kmax + kslice - 1) / kslice;
         hipLaunchKernelGGL(wy_project_kernel, dim3(rt, slices), dim3(256), 0, st, Va, Y, ld, M, c0, kmax, kslice, part);
-        hipLaunchKernelGGL(wy_multiply_kernel, dim3((M + 15) / 16), dim3(256), 0, st, part, slices, F + (size_t)b * NB * NB, M, G);
-        hipLaunchKernelGGL(wy_update_kernel, dim3((kmax + 63) / 64, rt), dim3(256), 0, st, G, Y, ld, M, c0, kmax, Va);
+        if (slices > 1) hipLaunchKernelGGL(wy_sum_kernel, dim3((M * NB + 255) / 256), dim3(256), 0, st, part, slices, M * NB, G);
+        hipLaunchKernelGGL(wy_update_kernel, dim3((kmax + 63) / 64, rt), dim3(256), 0, st, slices > 1 ? G : part, Z, ld, M, c0, kmax, Va);
     }
     if (dead) {
         hipLaunchKernelGGL(restore_columns_kernel, dim3((M + 1023) / 1024, M), dim3(256), 0, st, Va, M, ld, perm, Vb, 0);
