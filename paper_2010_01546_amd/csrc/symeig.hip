@@ -986,7 +986,7 @@ __global__ __launch_bounds__(256) void dc_vectors_kernel(DcArrays D, int M, int 
 // contraction entries in LDS as [k][row], the next chunk's loads in registers while the matrix cores work.  A 16x16x4
 // product takes 64 cycles of a SIMD for 1 KB of fragments, so nothing but the matrix cores is near its limit.
 // Operands are functors: load(k0, buf) fetches this thread's four entries of a chunk, KC tells how they lie (four along k
-// of one row, or four along the rows of one k).
+// of one row, or four along the rows of one k); k_end must not lie beyond any operand's nk.
 constexpr int GLD = 80;     // LDS row of 64 entries: 80 * 8 bytes put the two k of a half-wavefront 32 banks apart
 
 template <bool KC>
@@ -1009,17 +1009,15 @@ struct RowsK {
         const int r = row0 + s.r, k = k0 + s.k;
         const double* q = p + (size_t)r * ld + k;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) b[i] = 0.0;
-        if (r < nr) {
-            if (k + 4 <= nk) {
-                const doublex2 x = *reinterpret_cast<const doublex2*>(q), y = *reinterpret_cast<const doublex2*>(q + 2);
-                b[0] = x[0]; b[1] = x[1]; b[2] = y[0]; b[3] = y[1];
-            } else {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) if (k + i < nk) b[i] = q[i];
-            }
-        }
+        for (int i = 0; i < 4; ++i) b[i] = (r < nr && k + i < nk) ? q[i] : 0.0;
     }
+    // entries k0 .. k0 + 15 all lie below nk: loads without a branch (a row beyond the end reads the last one; keep() makes it zero)
+    __device__ __forceinline__ void load_whole(int k0, const Slot<true>& s, double (&b)[4]) const {
+        const double* q = p + (size_t)min(row0 + s.r, nr - 1) * ld + k0 + s.k;
+        const doublex2 x = *reinterpret_cast<const doublex2*>(q), y = *reinterpret_cast<const doublex2*>(q + 2);
+        b[0] = x[0]; b[1] = x[1]; b[2] = y[0]; b[3] = y[1];
+    }
+    __device__ __forceinline__ double keep(const Slot<true>& s, int, double x) const { return row0 + s.r < nr ? x : 0.0; }
 };
 // row-major matrix p[k][col]; optional list of rows
 struct ColsK {
@@ -1036,6 +1034,13 @@ struct ColsK {
             for (int i = 0; i < 4; ++i) if (c + i < nc) b[i] = q[i];
         }
     }
+    __device__ __forceinline__ void load_whole(int k0, const Slot<false>& s, double (&b)[4]) const {
+        const int k = k0 + s.k, c = col0 + s.r;
+        const double* q = p + (size_t)(list ? list2[list[k]] : k) * ld;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) b[i] = q[min(c + i, nc - 1)];
+    }
+    __device__ __forceinline__ double keep(const Slot<false>& s, int i, double x) const { return col0 + s.r + i < nc ? x : 0.0; }
 };
 // the same with a factor per k, or its square
 struct ColsKScaled {
@@ -1051,6 +1056,13 @@ struct ColsKScaled {
             for (int i = 0; i < 4; ++i) if (c + i < nc) b[i] = f * p[(size_t)k * ld + c + i];
         }
     }
+    __device__ __forceinline__ void load_whole(int k0, const Slot<false>& s, double (&b)[4]) const {
+        const int k = k0 + s.k, c = col0 + s.r;
+        const double f = square ? g[k] * g[k] : g[k];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) b[i] = f * p[(size_t)k * ld + min(c + i, nc - 1)];
+    }
+    __device__ __forceinline__ double keep(const Slot<false>& s, int i, double x) const { return col0 + s.r + i < nc ? x : 0.0; }
 };
 template <class OA, class OB, class Epi>
 __device__ __forceinline__ void gemm64(const OA& A, const OB& B, int k_begin, int k_end, const Epi& epi) {
@@ -1065,30 +1077,65 @@ __device__ __forceinline__ void gemm64(const OA& A, const OB& B, int k_begin, in
     for (int a = 0; a < 2; ++a)
 #pragma unroll
         for (int b = 0; b < 2; ++b) acc[a][b] = doublex4{0.0, 0.0, 0.0, 0.0};
-    double ra[4], rb[4];
-    A.load(k_begin, sa, ra);
-    B.load(k_begin, sb, rb);
-    int cur = 0;
-    for (int k0 = k_begin; k0 < k_end; k0 += 16, cur ^= 1) {
-        sa.store(As[cur], ra);
-        sb.store(Bs[cur], rb);
-        __syncthreads();
-        if (k0 + 16 < k_end) { A.load(k0 + 16, sa, ra); B.load(k0 + 16, sb, rb); }
+    // chunk c in LDS, c + 1 and c + 2 in registers or on their way, one barrier a chunk.  Past the last whole chunk it is loaded again,
+    // unread, so that no branch stands between a load and its use.
+    double ra[2][4], rb[2][4];
+    auto load = [&](int c, int set) { A.load_whole(k_begin + 16 * c, sa, ra[set]); B.load_whole(k_begin + 16 * c, sb, rb[set]); };
+    auto stage = [&](int c, int set) {
+        double x[4], y[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) { x[q] = A.keep(sa, q, ra[set][q]); y[q] = B.keep(sb, q, rb[set][q]); }
+        sa.store(As[c & 1], x);
+        sb.store(Bs[c & 1], y);
+    };
+    auto multiply = [&](int c) {
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) {
             double fa[2], fb[2];
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
-                fa[t] = As[cur][(4 * ks + lq) * GLD + wr + 16 * t + lr];
-                fb[t] = Bs[cur][(4 * ks + lq) * GLD + wc + 16 * t + lr];
+                fa[t] = As[c & 1][(4 * ks + lq) * GLD + wr + 16 * t + lr];
+                fb[t] = Bs[c & 1][(4 * ks + lq) * GLD + wc + 16 * t + lr];
             }
 #pragma unroll
             for (int a = 0; a < 2; ++a)
 #pragma unroll
                 for (int b = 0; b < 2; ++b) acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[a], fb[b], acc[a][b], 0, 0, 0);
         }
-        // the other buffer is written next: everybody has left it, because a wavefront gets here only after the barrier
-        // that followed the stores into this one
+    };
+    auto barrier = [] {
+        FW_WAIT_LGKM0();
+        __builtin_amdgcn_s_barrier();
+        FW_COMPILER_FENCE();
+    };
+    const int len = k_end - k_begin, nfull = len > 0 ? len / 16 : 0;
+    if (nfull > 0) {
+        const int last = nfull - 1;
+        load(0, 0);
+        load(min(1, last), 1);
+        stage(0, 0);
+        load(min(2, last), 0);
+        barrier();
+        int c = 0;
+        for (; c + 1 < nfull; c += 2) {
+            stage(c + 1, 1);
+            load(min(c + 3, last), 1);
+            multiply(c);
+            barrier();
+            stage(c + 2, 0);
+            load(min(c + 4, last), 0);
+            multiply(c + 1);
+            barrier();
+        }
+        if (c < nfull) { multiply(c); barrier(); }
+    }
+    if (nfull * 16 < len) {
+        A.load(k_begin + 16 * nfull, sa, ra[0]);
+        B.load(k_begin + 16 * nfull, sb, rb[0]);
+        sa.store(As[0], ra[0]);
+        sb.store(Bs[0], rb[0]);
+        barrier();
+        multiply(0);
     }
 #pragma unroll
     for (int a = 0; a < 2; ++a)
@@ -1165,7 +1212,7 @@ __global__ __launch_bounds__(256) void wy_form_kernel(const double* __restrict__
     if (col0 >= kmax) return;
     const RowsK A = {F + (size_t)blockIdx.y * NB * NB, NB, 0, NB, NB};
     const ColsK B = {Y + (size_t)c0 * ld, ld, col0, kmax, nb, nullptr, nullptr};
-    gemm64(A, B, 0, NB, [&](int r, int c, double x) {
+    gemm64(A, B, 0, nb, [&](int r, int c, double x) {
         if (r < nb && col0 + c < kmax) Z[(size_t)(c0 + r) * ld + col0 + c] = x;
     });
 }
@@ -1198,8 +1245,9 @@ __global__ __launch_bounds__(256) void wy_update_kernel(const double* __restrict
                                                         int kmax, double* __restrict__ V) {
     const int row0 = blockIdx.y * 64, col0 = blockIdx.x * 64;
     const RowsK A = {Gm, NB, row0, M, NB};
-    const ColsK B = {Y + (size_t)c0 * ld, ld, col0, kmax, min(NB, M - c0), nullptr, nullptr};
-    gemm64(A, B, 0, NB, [&](int r, int c, double x) {
+    const int nb = min(NB, M - c0);
+    const ColsK B = {Y + (size_t)c0 * ld, ld, col0, kmax, nb, nullptr, nullptr};
+    gemm64(A, B, 0, nb, [&](int r, int c, double x) {
         if (row0 + r < M && col0 + c < kmax) V[(size_t)(row0 + r) * ld + col0 + c] -= x;
     });
 }
