@@ -80,14 +80,31 @@ __device__ __forceinline__ double block_total(double v, double* red) {
 }
 
 // reflector for (x_0 .. x_{n-1}) -> beta e_{n-1} from the sum of squares of the entries before the last and the last one:
-// v = scale x with v_{n-1} = 1, H = I - tau v v^T
+// v = scale x with v_{n-1} = 1, H = I - tau v v^T.  It stands in every step's chain of dependent operations, so both reciprocals
+// come from the hardware's estimate and two Newton steps each (the norm with a last correction from its residual) instead of a square
+// root and two divisions behind it: 35 of 2270 us at 576 rows.
 __device__ __forceinline__ void reflector(double ss, double alpha, double* tau, double* beta, double* scale) {
     if (ss == 0.0) { *tau = 0.0; *beta = alpha; *scale = 0.0; return; }
-    const double nrm = sqrt(alpha * alpha + ss);
-    const double b = alpha >= 0.0 ? -nrm : nrm;
-    *tau = (b - alpha) / b;
-    *scale = 1.0 / (alpha - b);
-    *beta = b;
+    const double n2 = alpha * alpha + ss;
+    if (!(n2 > 1e-280 && n2 < 1e280)) {      // beyond the range where the estimates and their squares are normal numbers
+        const double nrm = sqrt(n2), b = alpha >= 0.0 ? -nrm : nrm;
+        *tau = (b - alpha) / b;
+        *scale = 1.0 / (alpha - b);
+        *beta = b;
+        return;
+    }
+    double y = __builtin_amdgcn_rsq(n2);     // 1 / |x|
+#pragma unroll
+    for (int i = 0; i < 2; ++i) y = fma(0.5 * y, fma(-n2 * y, y, 1.0), y);
+    double nrm = n2 * y;
+    nrm = fma(0.5 * y, fma(-nrm, nrm, n2), nrm);
+    const double den = fabs(alpha) + nrm;
+    double r = __builtin_amdgcn_rcp(den);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) r = fma(r, fma(-den, r, 1.0), r);
+    *tau = fma(fabs(alpha), y, 1.0);
+    *scale = alpha >= 0.0 ? r : -r;
+    *beta = alpha >= 0.0 ? -nrm : nrm;
 }
 
 // Features that never vary have a zero row and column.  They are moved behind the others (perm[0 .. M-1] = source of each
@@ -257,12 +274,13 @@ __global__ __launch_bounds__(T) void tri_step_kernel(double* __restrict__ A, int
 // workgroups that wait for this one then do so too, and d[0] = NaN makes the caller's acceptance fail.  Rows per workgroup: eight, ten where
 // eight would need more than 256 workgroups.
 // Bound by the round trip through the last-level cache (about 1.7 us a step, 2.5 at 2304 rows, where 230 workgroups read 37 KB each) and two
-// sums over the workgroup.  Whole call, launches per step -> this: 576 features 3.55 -> 2.85 ms, 2304 features 22.8 -> 14.2 ms.  Polls at
-// once instead of after POLL_DELAY: 15.0 ms; after twice the delay: 14.8 ms.  Up to 128 rows the single workgroup is as fast.
+// sums over the workgroup.  Whole call, launches per step -> this, the rest as it then was: 576 features 3.55 -> 2.85 ms, 2304 features
+// 22.8 -> 14.2 ms (polls at once instead of after POLL_DELAY: 15.0 ms; after twice the delay: 14.8 ms).  Up to 128 rows the single
+// workgroup is as fast.
 constexpr unsigned long long SENTINEL = ~0ull;    // a NaN that no arithmetic on widened float32 produces; publish() keeps it out for good
 constexpr int POLL_LIMIT = 1 << 21;
 constexpr int ROWS_MAX_M = 2560;
-constexpr int POLL_DELAY = 12;                    // of 64 clocks before the first poll: an early one only gets in the way of the stores
+constexpr int POLL_DELAY = 10;                    // of 64 clocks before the first poll: an early one only gets in the way of the stores
 
 __device__ __forceinline__ void publish(double* p, double x) {
     unsigned long long b = (unsigned long long)__double_as_longlong(x);
@@ -1484,13 +1502,17 @@ bool launch_rows(const double* A, int ld, int c, int first, const double* vp, co
     (void)hipGetLastError();
     return false;
 }
+// Threads and columns per thread: few columns shorten the chain of a step, many wavefronts lengthen its sums.  Whole calls, us: 512 features
+// 1811 (256 threads of two 1833), 576 features 2203 (256 of three 2274, 640 of one 2178), 768 features 2873 (256 of three 2977, 768 of one
+// 2921), 1024 features 3770 (1024 of one 4179), 1536 features 6261 (768 of two 6519), 2048 features 9285 (1024 of two 10466).
 bool rows(const double* A, int ld, int c, int first, const double* vp, const double* pp, double* Pslot, double* Xslot, double* Y, double* d,
           double* e, double* tau, hipStream_t st) {
     const int n = c + 1;
 #define FW_ROWS(T, C, RB) return launch_rows<T, C, RB>(A, ld, c, first, vp, pp, Pslot, Xslot, Y, d, e, tau, st)
     if (n <= 256) FW_ROWS(256, 1, 8);
-    if (n <= 512) FW_ROWS(256, 2, 8);
-    if (n <= 768) FW_ROWS(256, 3, 8);
+    if (n <= 512) FW_ROWS(512, 1, 8);
+    if (n <= 640) FW_ROWS(320, 2, 8);
+    if (n <= 768) FW_ROWS(384, 2, 8);
     if (n <= 1024) FW_ROWS(512, 2, 8);
     if (n <= 1536) FW_ROWS(512, 3, 8);
     if (n <= 2048) FW_ROWS(512, 4, 8);
