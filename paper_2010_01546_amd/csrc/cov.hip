@@ -964,10 +964,7 @@ fw_status cov_accumulate(const void* X, fw_dtype dt, fw_layout lay, const fw_con
             float* A2 = reinterpret_cast<float*>(base + sp.a2);
             float* s2 = reinterpret_cast<float*>(base + sp.s2);
             const int M = d->Cin * d->kh * d->kw;
-            // A2 and s2 lie next to each other (a2 then s2): one fill
-            fw_status rc = fill_f32(A2, (sp.s2 - sp.a2) / sizeof(float) + 2 * (size_t)M, 0.f, st);
-            if (rc != FW_OK) return rc;
-            rc = cov_bf16_accumulate(X, sp.lay2, &sp.d2, A2, s2, base + sp.inner, sp.total - sp.inner, st, true);
+            const fw_status rc = cov_bf16_accumulate(X, sp.lay2, &sp.d2, A2, s2, base + sp.inner, sp.total - sp.inner, st, true);
             if (rc != FW_OK) return rc;
             hipLaunchKernelGGL(split_fold_kernel, dim3((M + 255) / 256, M + 1), dim3(256), 0, st, A2, s2, M, d->Cin, d->kh * d->kw, sp.ckk, A, s);
             FW_LAUNCH_CHECK();

@@ -74,6 +74,7 @@ struct TileCore {
     int layout;
     int n_units, nchunks, chunks_per_split, nsplit;
     int sym;      // all features in one tile: cov_bf16_sym_kernel
+    int fresh;    // A and s hold nothing yet: their lower triangle and entries are written, not added to
     int direct;   // one range per tile and external order == internal order: tiles are added straight into A
     int bg_chunks, bg_per_chunk;   // the pre-pass deals the image groups to this many thread groups
     int zero_off;                  // 16-byte element of P that is always zero (target of masked-off loads)
@@ -687,12 +688,12 @@ __global__ __launch_bounds__(1024) void column_sums_kernel(TileCore g, const flo
         double t = 0.0;
 #pragma unroll
         for (int q = 0; q < 16; ++q) t += red[q][fl];
-        if (gridDim.y == 1) s[ext] = (float)((double)s[ext] + t);   // few positions: one slice, no second step
+        if (gridDim.y == 1) s[ext] = (float)((g.fresh ? 0.0 : (double)s[ext]) + t);   // few positions: one slice, no second step
         else cpart[(size_t)blockIdx.y * g.M + ext] = t;
     }
 }
 
-__global__ __launch_bounds__(256) void column_sums_final_kernel(int M, int nslices, const double* __restrict__ cpart, float* __restrict__ s) {
+__global__ __launch_bounds__(256) void column_sums_final_kernel(int M, int nslices, int fresh, const double* __restrict__ cpart, float* __restrict__ s) {
     const int m = blockIdx.x * 16 + (threadIdx.x & 15), part = threadIdx.x >> 4;   // 16 features x 16 lanes
     double t = 0.0;
     if (m < M)
@@ -704,7 +705,7 @@ __global__ __launch_bounds__(256) void column_sums_final_kernel(int M, int nslic
         double v = 0.0;
 #pragma unroll
         for (int q = 0; q < 16; ++q) v += red[q][threadIdx.x];
-        s[m] = (float)((double)s[m] + v);
+        s[m] = (float)((fresh ? 0.0 : (double)s[m]) + v);
     }
 }
 
@@ -751,7 +752,7 @@ __global__ __launch_bounds__(256) void tile_reduce_kernel(TileCore g, const floa
     feat_map(fi, g, &o, &ei);
     feat_map(fj, g, &o, &ej);
     float* dst = A + (size_t)max(ei, ej) * g.M + min(ei, ej);
-    *dst = (float)((double)*dst + v);
+    *dst = (float)((g.fresh ? 0.0 : (double)*dst) + v);
 }
 
 // Shift-correlation mode: the block of A that pairs row tap t1 with column tap t2 <= t1 (in tap order) is the sum, over
@@ -824,7 +825,7 @@ __global__ __launch_bounds__(256) void shift_tile_assemble_kernel(TileGeom g, co
         if (kkc && (t1 != t2 || c2 + 3 <= c1)) {
             // channels-last order: the four columns are contiguous in A (16-byte aligned: Cin and c2 are multiples of 4)
             float4* dst = reinterpret_cast<float4*>(A + (size_t)(t1 * g.Cin + c1) * g.M + (size_t)t2 * g.Cin + c2);
-            float4 o = *dst;
+            float4 o = g.fresh ? make_float4(0.f, 0.f, 0.f, 0.f) : *dst;
             o.x = (float)((double)o.x + v0); o.y = (float)((double)o.y + v1);
             o.z = (float)((double)o.z + v2); o.w = (float)((double)o.w + v3);
             *dst = o;
@@ -841,7 +842,7 @@ __global__ __launch_bounds__(256) void shift_tile_assemble_kernel(TileGeom g, co
             const int ei = kkc ? t1 * g.Cin + c1 : c1 * kk + t1;
             const int ej = kkc ? t2 * g.Cin + cc : cc * kk + t2;
             dst[q] = A + (keep[q] ? (size_t)max(ei, ej) * g.M + min(ei, ej) : 0);
-            old[q] = *dst[q];
+            old[q] = g.fresh ? 0.f : *dst[q];
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q)
@@ -1212,6 +1213,11 @@ fw_status cov_bf16_accumulate(const void* X, fw_layout lay, const fw_conv_desc* 
     if (!make_tile_geom(d, lay, &g)) return FW_ERR_UNSUPPORTED;
     const Bf16Ws L = ws_layout(g);
     if (!ws || ws_bytes < L.total) return FW_ERR_WORKSPACE;
+    g.fresh = split_f32 ? 1 : 0;          // the doubled moments live for this call only
+    if (g.fresh && g.direct) {            // tiles added straight into A
+        const fw_status rc = fill_f32(A, (size_t)g.M * g.M, 0.f, st);
+        if (rc != FW_OK) return rc;
+    }
     char* base = reinterpret_cast<char*>(ws);
     uint4* P = reinterpret_cast<uint4*>(base + L.packed);
     int* utab = reinterpret_cast<int*>(base + L.utab);
@@ -1301,7 +1307,7 @@ fw_status cov_bf16_accumulate(const void* X, fw_layout lay, const fw_conv_desc* 
         if (ns > CS_SLICES) ns = CS_SLICES;
         if (ns < 1) ns = 1;
         hipLaunchKernelGGL(column_sums_kernel, dim3(nfb, ns), dim3(1024), 0, st, g, S8, cpart, s);
-        if (ns > 1) hipLaunchKernelGGL(column_sums_final_kernel, dim3((g.M + 15) / 16), dim3(256), 0, st, g.M, ns, cpart, s);
+        if (ns > 1) hipLaunchKernelGGL(column_sums_final_kernel, dim3((g.M + 15) / 16), dim3(256), 0, st, g.M, ns, g.fresh, cpart, s);
     }
     FW_LAUNCH_CHECK();
     return FW_OK;
