@@ -32,8 +32,8 @@ namespace fw {
 namespace {
 
 struct Scal {
-    int m_prime, set_size, applied, flags;
-    float xi_mp, lambda_e, g_e, a_e, vnorm;
+    int m_prime, set_size, flags;
+    float xi_mp, lambda_e, a_e, vnorm;
 };
 
 constexpr int TILE = 32;
@@ -377,6 +377,33 @@ __global__ __launch_bounds__(256) void partial_sum_kernel(const float* __restric
     partial_sum_block(part, nparts, M, Mp, blockIdx.x, out, red);
 }
 
+// lambda_e = v^T u (eq. (lambda)), g_e, a_e (eqs. (ge), (xi)), the guard and, where `record`, the diagnostics, by a whole workgroup: the
+// same in every workgroup that calls it
+__device__ __forceinline__ void step_scalars(const float* __restrict__ v, const float* __restrict__ u, int M, float* red,
+                                             const float* __restrict__ lambda_bar, const fw_cond_params& prm, Scal* __restrict__ sc,
+                                             fw_cond_info* __restrict__ info, bool record, float* a_out, float* lam_out) {
+    float dot = 0.f;
+    for (int m = threadIdx.x; m < M; m += blockDim.x) dot += v[m] * u[m];
+    const float lam_e = block_sum(dot, red);
+    int flags = sc->flags;
+    float g_e = 1.f, a_e = 0.f;
+    int applied = 0;
+    if ((flags & 1) == 0) {
+        g_e = prm.delta * (*lambda_bar) / fmaxf(lam_e, prm.eps);
+        if (prm.guard && g_e >= 1.f) flags |= 2;
+        else if (!(g_e == g_e) || g_e > 3.0e38f) flags |= 4;
+        else { a_e = sqrtf(g_e) - 1.f; applied = 1; }
+    }
+    const float lam = (flags & 1) ? 0.f : lam_e;
+    if (a_out) { *a_out = a_e; *lam_out = lam; }
+    if (!record || threadIdx.x != 0) return;
+    if (!a_out) { sc->lambda_e = lam; sc->a_e = a_e; }          // for the launch that follows
+    if (info) {
+        info->lambda_e = lam; info->g_e = g_e; info->a_e = a_e; info->v_norm = sc->vnorm;
+        info->m_prime = sc->m_prime; info->set_size = sc->set_size; info->applied = applied; info->flags = flags;
+    }
+}
+
 // t = T^T v (workgroups below nred) and p = Psi^T v (the next nred, with leak) from their partial products, and in the
 // last workgroup lambda_e = v^T u (eq. (lambda)), g_e, a_e (eqs. (ge), (xi)), the guard and the diagnostics
 __global__ __launch_bounds__(256) void t_reduce_scalars_kernel(const float* __restrict__ tpart, const float* __restrict__ ppart,
@@ -393,26 +420,7 @@ __global__ __launch_bounds__(256) void t_reduce_scalars_kernel(const float* __re
         partial_sum_block(ppart, nparts, M, Mp, blockIdx.x - nred, pv, red);
         return;
     }
-    float dot = 0.f;
-    for (int m = threadIdx.x; m < M; m += blockDim.x) dot += v[m] * u[m];
-    const float lam_e = block_sum(dot, &red[0][0]);
-    if (threadIdx.x == 0) {
-        int flags = sc->flags;
-        float g_e = 1.f, a_e = 0.f;
-        int applied = 0;
-        if ((flags & 1) == 0) {
-            g_e = prm.delta * (*lambda_bar) / fmaxf(lam_e, prm.eps);
-            if (prm.guard && g_e >= 1.f) flags |= 2;
-            else if (!(g_e == g_e) || g_e > 3.0e38f) flags |= 4;
-            else { a_e = sqrtf(g_e) - 1.f; applied = 1; }
-        }
-        sc->lambda_e = (flags & 1) ? 0.f : lam_e;
-        sc->g_e = g_e; sc->a_e = a_e; sc->applied = applied; sc->flags = flags;
-        if (info) {
-            info->lambda_e = sc->lambda_e; info->g_e = g_e; info->a_e = a_e; info->v_norm = sc->vnorm;
-            info->m_prime = sc->m_prime; info->set_size = sc->set_size; info->applied = applied; info->flags = flags;
-        }
-    }
+    step_scalars(v, u, M, &red[0][0], lambda_bar, prm, sc, info, true, nullptr, nullptr);
 }
 
 // Fused update over the pair of mirrored tiles (I,J) and (J,I), I >= J, one workgroup per pair (pairs enumerated along a
@@ -420,9 +428,14 @@ __global__ __launch_bounds__(256) void t_reduce_scalars_kernel(const float* __re
 // mirrored position takes its old values from that tile transposed through LDS, so the pass reads 4 of the 16 M^2 words
 // of a step only half (9 M^2 words move instead of 11).  T and Psi are not symmetric: both of their tiles are read, each
 // position needs its own element and, for the terms T + T^T and Psi + Psi^T, the other tile's transposed one.
+// FUSED: t and p are the partial products tpart and ppart still ([nparts][Mp]); a workgroup adds up the 64 entries its tiles need and
+// works out the scalars for itself, all behind its own loads, which saves t_reduce_scalars_kernel.
+template <bool FUSED>
 __global__ __launch_bounds__(256) void update_kernel(fw_cond_state s, const float* __restrict__ v, const float* __restrict__ u,
-                                                     const float* __restrict__ t, const float* __restrict__ p, const Scal* __restrict__ sc,
-                                                     float gamma, float beta, int Mp, float* __restrict__ xpart) {
+                                                     const float* __restrict__ t, const float* __restrict__ p, Scal* __restrict__ sc,
+                                                     fw_cond_params prm, int nparts, fw_cond_info* __restrict__ info, int Mp,
+                                                     float* __restrict__ xpart) {
+    const float gamma = prm.gamma, beta = prm.beta;
     // pair index -> (I, J), I >= J: I (I + 1) / 2 + J
     int I = (int)((sqrtf(8.f * (float)blockIdx.x + 1.f) - 1.f) * 0.5f);
     while ((I + 1) * (I + 2) / 2 <= (int)blockIdx.x) ++I;
@@ -433,10 +446,9 @@ __global__ __launch_bounds__(256) void update_kernel(fw_cond_state s, const floa
     // four LDS tiles, used twice: first for the transposed elements of T and Psi, then for those of the symmetric
     // matrices (a workgroup's LDS decides how many of them a compute unit holds, and with them the loads in flight)
     __shared__ float L0[TILE][TILE + 1], L1[TILE][TILE + 1], L2[TILE][TILE + 1], L3[TILE][TILE + 1];
+    __shared__ float tp[2][64], tsum[FUSED ? 2 : 1][4][64], red[4];     // t, p of the rows of blocks I (0 .. 31) and J (32 .. 63)
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-    const float a = sc->a_e, lam = sc->lambda_e;
     const float g1 = 1.f - gamma, g2 = gamma * gamma, gg1 = gamma * g1, g1sq = g1 * g1, b1 = 1.f - beta;
-    const float aa2 = a * (a + 2.f), a2lam = a * a * lam;
 
     // Everything this workgroup reads is asked for before anything is stored (the state pointers may not be told apart
     // by the compiler, so a load behind a store would wait for it: a chain of round trips that dominates small M).
@@ -468,6 +480,40 @@ __global__ __launch_bounds__(256) void update_kernel(fw_cond_state s, const floa
             if (!ok) { Tv[pos][r] = 0.f; Pv[pos][r] = 0.f; }
         }
     }
+    float a, lam;
+    if constexpr (FUSED) {
+        const int e = threadIdx.x & 63, grp = threadIdx.x >> 6;
+        const int m = (e < 32 ? I : J) * TILE + (e & 31);
+        float st = 0.f, sp = 0.f;
+        if (m < M)
+            for (int b0 = grp; b0 < nparts; b0 += 16) {
+                float xt[4], xp[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const size_t at = (size_t)(b0 + 4 * q < nparts ? b0 + 4 * q : b0) * Mp + m;
+                    xt[q] = t[at];
+                    xp[q] = leak ? p[at] : 0.f;
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if (b0 + 4 * q < nparts) { st += xt[q]; sp += xp[q]; }
+            }
+        tsum[0][grp][e] = st; tsum[FUSED ? 1 : 0][grp][e] = sp;
+        step_scalars(v, u, M, red, s.lambda_bar, prm, sc, info, blockIdx.x == 0, &a, &lam);     // has the barriers that publish tsum
+        if (threadIdx.x < 128) {
+            const int k = threadIdx.x >> 6;
+            tp[k][e] = (tsum[k][0][e] + tsum[k][1][e]) + (tsum[k][2][e] + tsum[k][3][e]);
+        }
+    } else {
+        a = sc->a_e; lam = sc->lambda_e;
+        if (threadIdx.x < 64) {
+            const int m = (threadIdx.x < 32 ? I : J) * TILE + (threadIdx.x & 31);
+            tp[0][threadIdx.x] = m < M ? t[m] : 0.f;
+            tp[1][threadIdx.x] = leak && m < M ? p[m] : 0.f;
+        }
+    }
+    __syncthreads();
+    const float aa2 = a * (a + 2.f), a2lam = a * a * lam;
     if (leak) {
         // transposed elements of T and Psi: position a reads tile b transposed and the other way round (the diagonal
         // tile reads itself)
@@ -501,8 +547,8 @@ __global__ __launch_bounds__(256) void update_kernel(fw_cond_state s, const floa
         if (pos >= npos) break;
         const int rowblk = pos == 0 ? I : J, colblk = pos == 0 ? J : I;
         const int j = colblk * TILE + tx;
-        const float vj = j < M ? v[j] : 0.f, uj = j < M ? u[j] : 0.f, tj = j < M ? t[j] : 0.f;
-        const float pj = (leak && j < M) ? p[j] : 0.f;
+        const int ro = 32 * pos, co = 32 - ro;                 // where the row block's and the column block's entries lie in tp
+        const float vj = j < M ? v[j] : 0.f, uj = j < M ? u[j] : 0.f, tj = tp[0][co + tx], pj = tp[1][co + tx];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int yy = ty + 8 * r;
@@ -510,7 +556,7 @@ __global__ __launch_bounds__(256) void update_kernel(fw_cond_state s, const floa
             float sq = 0.f;
             if (i < M && j < M) {
                 const size_t e = (size_t)i * M + j;
-                const float vi = v[i], ui = u[i], ti = t[i];
+                const float vi = v[i], ui = u[i], ti = tp[0][ro + yy];
                 const float dij = (i == j) ? 1.f : 0.f;
                 const float Told = Tv[pos][r];
                 const float Qold = pos == 0 ? Qv[r] : L0[tx][yy], Yold = pos == 0 ? Yv[r] : L1[tx][yy];
@@ -519,7 +565,7 @@ __global__ __launch_bounds__(256) void update_kernel(fw_cond_state s, const floa
                 float Qn = g2 * (Qold + aa2 * (ti * tj)) + g1sq * dij;
                 float Yn = g2 * (Yold + a * (vi * uj + ui * vj) + a2lam * (vi * vj));
                 if (leak) {
-                    const float Psiold = Pv[pos][r], phix = pos == 0 ? Xv[r] : L3[tx][yy], pi = p[i];
+                    const float Psiold = Pv[pos][r], phix = pos == 0 ? Xv[r] : L3[tx][yy], pi = tp[1][ro + yy];
                     Qn += gg1 * (a * (vi * tj + ti * vj) + Told + Tt[pos][r]);
                     Yn += gg1 * (Psiold + Pt[pos][r] + a * (vi * pj + pi * vj)) + g1sq * phix;
                     s.Psi[e] = gamma * (Psiold + a * vi * pj) + g1 * phix;
@@ -537,6 +583,10 @@ __global__ __launch_bounds__(256) void update_kernel(fw_cond_state s, const floa
         }
     }
 }
+
+// Up to here the sums ride along with the loads of the update; beyond it every workgroup's share of them costs more than the launch.  A
+// step, fused / not: 72 features 21.2 / 22.7 us, 288 23.1 / 24.4, 576 26.2 / 27.1, 800 30.2 / 30.3, 1152 34.7 / 34.4, 1800 68 / 60.
+constexpr int UPDATE_FUSED_MAX_M = 640;
 
 // ---- the whole step in one launch, for few features
 // Up to 64 features the six launches of the general form do next to nothing each: their time is the time between
@@ -1140,9 +1190,14 @@ fw_status cond_reduce_step(const fw_cond_state* s, const fw_cond_params* p, fw_c
     const int nvm = ncol * L.nrb, last = nred * (leak ? 2 : 1);
     hipLaunchKernelGGL(matvec_u_vecmat_kernel, dim3(nmv + nvm * (leak ? 2 : 1)), mv_blk, 0, st, s->Phi_y, s->T, s->Psi, cur, M, L.Mp,
                        L.vm_rows, nmv, nvm, sc, v, u, tpart, ppart);
-    hipLaunchKernelGGL(t_reduce_scalars_kernel, dim3(last + 1), mv_blk, 0, st, tpart, ppart, L.nrb, M, L.Mp, nred, last, t, pv, v, u,
-                       s->lambda_bar, *p, sc, info);
-    hipLaunchKernelGGL(update_kernel, dim3(L.nt * (L.nt + 1) / 2), dim3(256), 0, st, *s, v, u, t, pv, sc, p->gamma, p->beta, L.Mp, xpart);
+    const dim3 pairs(L.nt * (L.nt + 1) / 2);
+    if (M <= UPDATE_FUSED_MAX_M) {
+        hipLaunchKernelGGL(update_kernel<true>, pairs, dim3(256), 0, st, *s, v, u, tpart, ppart, sc, *p, L.nrb, info, L.Mp, xpart);
+    } else {
+        hipLaunchKernelGGL(t_reduce_scalars_kernel, dim3(last + 1), mv_blk, 0, st, tpart, ppart, L.nrb, M, L.Mp, nred, last, t, pv, v, u,
+                           s->lambda_bar, *p, sc, info);
+        hipLaunchKernelGGL(update_kernel<false>, pairs, dim3(256), 0, st, *s, v, u, t, pv, sc, *p, 0, info, L.Mp, xpart);
+    }
     hipLaunchKernelGGL(partial_sum_kernel, dim3(nred), dim3(256), 0, st, xpart, L.nt, M, L.Mp, s->xi2);
     FW_LAUNCH_CHECK();
     return FW_OK;

@@ -618,21 +618,32 @@ __global__ __launch_bounds__(256) void finalize_phi64_kernel(const float* __rest
         a[r] = *reinterpret_cast<const float4*>(A + e);
         ph[r] = first ? make_float4(0.f, 0.f, 0.f, 0.f) : *reinterpret_cast<const float4*>(Phi + e);
     }
+    // the sums and means of the rows and columns are asked for in the same round (inside the loop over the rows they were a round trip each)
+    float si[4], mui[4], sj[4], muj[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int i = I * 64 + ty + 16 * r, j = j0 + r;
+        si[r] = s[col_ok && i < M ? i : 0];
+        mui[r] = first ? 0.f : mu_old[col_ok && i < M ? i : 0];
+        sj[r] = s[j < M ? j : 0];
+        muj[r] = first ? 0.f : mu_old[j < M ? j : 0];
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) asm volatile("" : "+v"(si[r]), "+v"(mui[r]), "+v"(sj[r]), "+v"(muj[r]));
     double mhj[4], mj[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const int j = j0 + q;
-        mhj[q] = j < M ? (double)s[j] * inv_n : 0.0;
-        mj[q] = j < M ? (first ? mhj[q] : (double)alpha * (double)mu_old[j] + (1.0 - (double)alpha) * mhj[q]) : 0.0;
+        mhj[q] = j < M ? (double)sj[q] * inv_n : 0.0;
+        mj[q] = j < M ? (first ? mhj[q] : (double)alpha * (double)muj[q] + (1.0 - (double)alpha) * mhj[q]) : 0.0;
     }
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int yy = ty + 16 * r;
         const int i = I * 64 + yy;
-        asm volatile("" : "+v"(a[r].x), "+v"(a[r].y), "+v"(a[r].z), "+v"(a[r].w));
         const bool row_ok = col_ok && i < M;
-        const double mhi = row_ok ? (double)s[i] * inv_n : 0.0;
-        const double mi = first ? mhi : (double)alpha * (double)(row_ok ? mu_old[i] : 0.f) + (1.0 - (double)alpha) * mhi;
+        const double mhi = row_ok ? (double)si[r] * inv_n : 0.0;
+        const double mi = first ? mhi : (double)alpha * (double)(row_ok ? mui[r] : 0.f) + (1.0 - (double)alpha) * mhi;
         const float av[4] = {a[r].x, a[r].y, a[r].z, a[r].w}, pv[4] = {ph[r].x, ph[r].y, ph[r].z, ph[r].w};
         float o[4];
 #pragma unroll
