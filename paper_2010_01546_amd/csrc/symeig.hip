@@ -24,6 +24,7 @@
 // Back-transformation: blocks of 64 reflectors in compact form I - Y^T F Y (rows of Y = reflectors, F upper triangular).
 #include "fw_internal.h"
 #include "lane_sums.h"
+#include <type_traits>
 
 namespace fw {
 namespace {
@@ -1270,6 +1271,112 @@ __global__ __launch_bounds__(256) void wy_update_kernel(const double* __restrict
     });
 }
 
+// All blocks of reflectors on 16 rows of V in one launch: V -= (V Y^T) Z, block after block.  The rows stay in registers as the transposed
+// accumulators of v_mfma_f64_16x16x4_f64 -- a lane holds row lr, columns 16 tile + 4 lq .. + 3 -- which is at once the layout of
+// the second operand of Y V^T and of the result of Z^T P^T: nothing of V moves between the blocks, and no workgroup waits for another.  Eight
+// wavefronts share the column tiles (tile = wavefront + 8 slot); Y and Z come from the caches, the next tile's on their way while this one's are
+// multiplied; the eight shares of P = V Y^T are added through LDS.  NS: slots per wavefront.
+// Bound: the matrix cores of M / 16 compute units, and the reads of Y and Z by each of them.
+constexpr int STRIP_MAX_M = 2560;
+// f(0), f(1), .. f(N - 1) with compile-time constants
+template <int N, class F>
+__device__ __forceinline__ void each(const F& f) {
+    if constexpr (N > 0) {
+        each<N - 1>(f);
+        f(std::integral_constant<int, N - 1>());
+    }
+}
+template <int NS>
+__global__ __launch_bounds__(512) void wy_strip_kernel(const double* __restrict__ Y, const double* __restrict__ Z, int ld, int M, double* __restrict__ V) {
+    __shared__ double part[8][16][64], sum[16][64];
+    const int lane = threadIdx.x & 63, lr = lane & 15, lq = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int row = blockIdx.x * 16 + lr;
+    const int zc = 4 * (lr & 3) + (lr >> 2);        // column of a tile that row lr of the result of Z^T P^T stands for
+    double* vrow = V + (size_t)min(row, M - 1) * ld + 4 * lq;
+    doublex4 acc[NS];
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+        const int tl = wave + 8 * i;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[i][v] = 16 * tl < ld ? vrow[16 * tl + v] : 0.0;
+    }
+    for (int c0 = 0; c0 < M; c0 += NB) {
+        const int nb = min(NB, M - c0), ntl = (c0 + nb + 15) / 16;
+        const int act = wave < ntl ? (ntl - wave + 7) / 8 : 0;      // slots of this wavefront that hold columns below c0 + nb
+        // P^T = Y V^T, 32 of the 64 reflectors at a time
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf) {
+            doublex4 pt[2] = {doublex4{0.0, 0.0, 0.0, 0.0}, doublex4{0.0, 0.0, 0.0, 0.0}};
+            const double* y0 = Y + (size_t)min(c0 + 32 * hf + lr, M - 1) * ld + 4 * lq;
+            const double* y1 = Y + (size_t)min(c0 + 32 * hf + 16 + lr, M - 1) * ld + 4 * lq;
+            doublex2 ya[2][4];
+            auto load = [&](int i, doublex2 (&b)[4]) {
+                const int at = 16 * min(wave + 8 * i, ntl - 1);
+                b[0] = *reinterpret_cast<const doublex2*>(y0 + at); b[1] = *reinterpret_cast<const doublex2*>(y0 + at + 2);
+                b[2] = *reinterpret_cast<const doublex2*>(y1 + at); b[3] = *reinterpret_cast<const doublex2*>(y1 + at + 2);
+            };
+            load(0, ya[0]);
+            each<NS>([&](auto slot) {
+                constexpr int i = decltype(slot)::value;
+                if (i >= act) return;
+                load(i + 1, ya[(i + 1) & 1]);
+                const doublex2 (&b)[4] = ya[i & 1];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    pt[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(b[v >> 1][v & 1], acc[i][v], pt[0], 0, 0, 0);
+                    pt[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(b[2 + (v >> 1)][v & 1], acc[i][v], pt[1], 0, 0, 0);
+                }
+            });
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) part[wave][8 * hf + 4 * m + v][lane] = pt[m][v];     // reflector 32 hf + 16 m + 4 v + lq
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const int s = 2 * wave + k;
+            double x = 0.0;
+#pragma unroll
+            for (int w = 0; w < 8; ++w) x += part[w][s][lane];
+            sum[s][lane] = 4 * s + lq < nb ? -x : 0.0;              // reflector 4 s + lq
+        }
+        __syncthreads();
+        // V^T -= Z^T P^T, 32 reflectors at a time
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf) {
+            double p[8], za[2][8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) p[k] = sum[8 * hf + k][lane];
+            const double* zr[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) zr[k] = Z + (size_t)min(c0 + 32 * hf + 4 * k + lq, M - 1) * ld + zc;
+            auto load = [&](int i, double (&b)[8]) {
+                const int at = 16 * min(wave + 8 * i, ntl - 1);
+#pragma unroll
+                for (int k = 0; k < 8; ++k) b[k] = zr[k][at];
+            };
+            load(0, za[0]);
+            each<NS>([&](auto slot) {
+                constexpr int i = decltype(slot)::value;
+                if (i >= act) return;
+                load(i + 1, za[(i + 1) & 1]);
+#pragma unroll
+                for (int k = 0; k < 8; ++k) acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(za[i & 1][k], p[k], acc[i], 0, 0, 0);
+            });
+        }
+    }
+    if (row >= M) return;
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+        const int tl = wave + 8 * i;
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            if (16 * tl + 4 * lq + v < M) vrow[16 * tl + v] = acc[i][v];
+    }
+}
+
 // ------------------------------------------------------------------------------------------- acceptance, T and Q
 // W = V Phi
 __global__ __launch_bounds__(256) void image_kernel(const double* __restrict__ V, const double* __restrict__ Phi, int ld, int M,
@@ -1610,19 +1717,30 @@ fw_status sym_eig(const float* Phi, int M, bool dead, double* const buf[4], void
     hipLaunchKernelGGL(wy_gram_kernel, dim3(nblk, WY_SLICES), dim3(256), 0, st, Y, ld, M, A);
     hipLaunchKernelGGL(wy_factor_kernel, dim3(nblk), dim3(256), 0, st, A, M, tau, F);
     hipLaunchKernelGGL(wy_form_kernel, dim3((M + 63) / 64, nblk), dim3(256), 0, st, F, Y, ld, M, Z);
-    double* part = A;
-    double* G = A + (size_t)8 * M * NB;
-    for (int b = 0; b < nblk; ++b) {
-        const int c0 = b * NB, kmax = c0 + NB < M ? c0 + NB : M;
-        int slices = 256 / rt;
-        if (slices > 8) slices = 8;
-        if (slices < 1) slices = 1;
-        while (slices > 1 && kmax / slices < 64) --slices;
-        const int kslice = ((kmax + slices - 1) / slices + 15) / 16 * 16;
-        slices = (kmax + kslice - 1) / kslice;
-        hipLaunchKernelGGL(wy_project_kernel, dim3(rt, slices), dim3(256), 0, st, Va, Y, ld, M, c0, kmax, kslice, part);
-        if (slices > 1) hipLaunchKernelGGL(wy_sum_kernel, dim3((M * NB + 255) / 256), dim3(256), 0, st, part, slices, M * NB, G);
-        hipLaunchKernelGGL(wy_update_kernel, dim3((kmax + 63) / 64, rt), dim3(256), 0, st, slices > 1 ? G : part, Z, ld, M, c0, kmax, Va);
+    if (M <= STRIP_MAX_M) {
+        const int slots = ((M + 15) / 16 + 7) / 8;
+#define FW_STRIPS(NS) hipLaunchKernelGGL(wy_strip_kernel<NS>, dim3((M + 15) / 16), dim3(512), 0, st, Y, Z, ld, M, Va)
+        if (slots <= 2) FW_STRIPS(2);
+        else if (slots <= 5) FW_STRIPS(5);
+        else if (slots <= 10) FW_STRIPS(10);
+        else if (slots <= 15) FW_STRIPS(15);
+        else FW_STRIPS(20);
+#undef FW_STRIPS
+    } else {
+        double* part = A;
+        double* G = A + (size_t)8 * M * NB;
+        for (int b = 0; b < nblk; ++b) {
+            const int c0 = b * NB, kmax = c0 + NB < M ? c0 + NB : M;
+            int slices = 256 / rt;
+            if (slices > 8) slices = 8;
+            if (slices < 1) slices = 1;
+            while (slices > 1 && kmax / slices < 64) --slices;
+            const int kslice = ((kmax + slices - 1) / slices + 15) / 16 * 16;
+            slices = (kmax + kslice - 1) / kslice;
+            hipLaunchKernelGGL(wy_project_kernel, dim3(rt, slices), dim3(256), 0, st, Va, Y, ld, M, c0, kmax, kslice, part);
+            if (slices > 1) hipLaunchKernelGGL(wy_sum_kernel, dim3((M * NB + 255) / 256), dim3(256), 0, st, part, slices, M * NB, G);
+            hipLaunchKernelGGL(wy_update_kernel, dim3((kmax + 63) / 64, rt), dim3(256), 0, st, slices > 1 ? G : part, Z, ld, M, c0, kmax, Va);
+        }
     }
     if (dead) {
         hipLaunchKernelGGL(restore_columns_kernel, dim3((M + 1023) / 1024, M), dim3(256), 0, st, Va, M, ld, perm, Vb, 0);
