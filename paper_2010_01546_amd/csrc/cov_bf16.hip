@@ -693,32 +693,38 @@ __global__ __launch_bounds__(1024) void column_sums_kernel(TileCore g, const flo
     }
 }
 
-__global__ __launch_bounds__(256) void column_sums_final_kernel(int M, int nslices, int fresh, const double* __restrict__ cpart, float* __restrict__ s) {
-    const int m = blockIdx.x * 16 + (threadIdx.x & 15), part = threadIdx.x >> 4;   // 16 features x 16 lanes
-    double t = 0.0;
-    if (m < M)
-        for (int q = part; q < nslices; q += 16) t += cpart[(size_t)q * M + m];
+// Second step, 16 features by 256 threads.  It rides along with the pass that adds up the partial tiles, in workgroups of its own (a launch of
+// its own took 4.7 us).
+struct SumsFinal { int nblocks, nslices; const double* cpart; float* s; };    // nblocks = 0: nothing to do
+__device__ __forceinline__ void column_sums_final(const TileCore& g, const SumsFinal& f, int blk) {
     __shared__ double red[16][17];
+    const int m = blk * 16 + (threadIdx.x & 15), part = threadIdx.x >> 4;   // 16 features x 16 lanes
+    double t = 0.0;
+    if (m < g.M)
+        for (int q = part; q < f.nslices; q += 16) t += f.cpart[(size_t)q * g.M + m];
     red[part][threadIdx.x & 15] = t;
     __syncthreads();
-    if (part == 0 && m < M) {
+    if (part == 0 && m < g.M) {
         double v = 0.0;
 #pragma unroll
         for (int q = 0; q < 16; ++q) v += red[q][threadIdx.x];
-        s[m] = (float)((fresh ? 0.0 : (double)s[m]) + v);
+        f.s[m] = (float)((g.fresh ? 0.0 : (double)f.s[m]) + v);
     }
 }
+__global__ __launch_bounds__(256) void column_sums_final_kernel(TileCore g, SumsFinal f) { column_sums_final(g, f, blockIdx.x); }
 
 // partial tiles -> A (float64 sum over the ranges).  A workgroup takes 256 / NG consecutive tile elements; its NG groups
 // of threads share the ranges (group q takes the ranges q, q + NG, ..., eight loads in flight) and are added in a fixed
 // order, so that many ranges do not become a long chain of loads in few threads.
 template <int NG>
-__global__ __launch_bounds__(256) void tile_reduce_kernel(TileCore g, const float* __restrict__ part, float* __restrict__ A) {
+__global__ __launch_bounds__(256) void tile_reduce_kernel(TileCore g, const float* __restrict__ part, float* __restrict__ A, SumsFinal f) {
+    if ((int)blockIdx.x < f.nblocks) { column_sums_final(g, f, blockIdx.x); return; }
     constexpr int EPB = 256 / NG;                  // elements per workgroup
     const int bpt = g.tr * g.tc / EPB;             // workgroups per tile of tr x tc
-    const int tile = blockIdx.x / bpt;
+    const int blk = (int)blockIdx.x - f.nblocks;
+    const int tile = blk / bpt;
     const int le = threadIdx.x % EPB, grp = threadIdx.x / EPB;
-    const int e = (blockIdx.x - tile * bpt) * EPB + le;
+    const int e = (blk - tile * bpt) * EPB + le;
     int I, J;
     tile_coords(tile, g, &I, &J);
     const int row = e / g.tc, col = e - row * g.tc;
@@ -761,11 +767,16 @@ __global__ __launch_bounds__(256) void tile_reduce_kernel(TileCore g, const floa
 // and the loads (16 bytes per lane along c2, four in flight) and the writes run along rows; its NG groups of threads
 // share the ranges and are added in a fixed order; float64 sums.
 template <int NG>
-__global__ __launch_bounds__(256) void shift_tile_assemble_kernel(TileGeom g, const float* __restrict__ part, float* __restrict__ A) {
+__global__ __launch_bounds__(256) void shift_tile_assemble_kernel(TileGeom g, const float* __restrict__ part, float* __restrict__ A, SumsFinal f, int zf) {
+    if ((int)blockIdx.z < zf) {                       // the first zf layers of the grid: column sums
+        const int blk = (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
+        if (blk < f.nblocks) column_sums_final(g, f, blk);
+        return;
+    }
     const int kk = g.kh * g.kw;
     int t1 = 0;
     {
-        int pr = blockIdx.z;                          // pair index: t1 (t1 + 1) / 2 + t2
+        int pr = (int)blockIdx.z - zf;                // pair index: t1 (t1 + 1) / 2 + t2
         while ((t1 + 1) * (t1 + 2) / 2 <= pr) ++t1;
         pr -= t1 * (t1 + 1) / 2;
         const int t2 = pr;
@@ -1280,24 +1291,7 @@ fw_status cov_bf16_accumulate(const void* X, fw_layout lay, const fw_conv_desc* 
     }
 #undef FW_TILE_LAUNCH
     FW_LAUNCH_CHECK();
-    if (g.shift) {
-        // few channels: too few workgroups of 16 x 64 entries to hide the chain of loads over the ranges; share them
-        const int pairs = g.kh * g.kw * (g.kh * g.kw + 1) / 2, cb = (g.Cin + 63) / 64;
-        if ((long long)cb * ((g.Cin + 15) / 16) * pairs < 512)
-            hipLaunchKernelGGL(shift_tile_assemble_kernel<4>, dim3(cb, (g.Cin + 3) / 4, pairs), dim3(256), 0, st, g, part, A);
-        else
-            hipLaunchKernelGGL(shift_tile_assemble_kernel<1>, dim3(cb, (g.Cin + 15) / 16, pairs), dim3(256), 0, st, g, part, A);
-    }
-    else if (!g.direct) {
-        // many ranges and few tiles: share the ranges inside a workgroup
-        const int elems = g.ntiles * g.tr * g.tc;
-        if (g.nsplit >= 64 && elems / 16 <= 65536 * 4)
-            hipLaunchKernelGGL(tile_reduce_kernel<16>, dim3(elems / 16), dim3(256), 0, st, g, part, A);
-        else if (g.nsplit >= 24)
-            hipLaunchKernelGGL(tile_reduce_kernel<4>, dim3(elems / 64), dim3(256), 0, st, g, part, A);
-        else
-            hipLaunchKernelGGL(tile_reduce_kernel<1>, dim3(elems / 256), dim3(256), 0, st, g, part, A);
-    }
+    SumsFinal f = {0, 0, cpart, s};
     {
         // slices of the positions: enough workgroups to fill the chip, none when a workgroup per 64 features already does
         const long long total = (long long)g.Ho * g.bg_chunks * ((g.Wo + 7) / 8);   // runs of eight positions
@@ -1307,8 +1301,29 @@ fw_status cov_bf16_accumulate(const void* X, fw_layout lay, const fw_conv_desc* 
         if (ns > CS_SLICES) ns = CS_SLICES;
         if (ns < 1) ns = 1;
         hipLaunchKernelGGL(column_sums_kernel, dim3(nfb, ns), dim3(1024), 0, st, g, S8, cpart, s);
-        if (ns > 1) hipLaunchKernelGGL(column_sums_final_kernel, dim3((g.M + 15) / 16), dim3(256), 0, st, g.M, ns, g.fresh, cpart, s);
+        if (ns > 1) { f.nblocks = (g.M + 15) / 16; f.nslices = ns; }
     }
+    if (g.shift) {
+        // few channels: too few workgroups of 16 x 64 entries to hide the chain of loads over the ranges; share them
+        const int pairs = g.kh * g.kw * (g.kh * g.kw + 1) / 2, cb = (g.Cin + 63) / 64;
+        const bool few = (long long)cb * ((g.Cin + 15) / 16) * pairs < 512;
+        const int cy = few ? (g.Cin + 3) / 4 : (g.Cin + 15) / 16;
+        const int zf = (f.nblocks + cb * cy - 1) / (cb * cy);
+        const dim3 agrid(cb, cy, pairs + zf);
+        if (few) hipLaunchKernelGGL(shift_tile_assemble_kernel<4>, agrid, dim3(256), 0, st, g, part, A, f, zf);
+        else hipLaunchKernelGGL(shift_tile_assemble_kernel<1>, agrid, dim3(256), 0, st, g, part, A, f, zf);
+    }
+    else if (!g.direct) {
+        // many ranges and few tiles: share the ranges inside a workgroup
+        const int elems = g.ntiles * g.tr * g.tc;
+        if (g.nsplit >= 64 && elems / 16 <= 65536 * 4)
+            hipLaunchKernelGGL(tile_reduce_kernel<16>, dim3(elems / 16 + f.nblocks), dim3(256), 0, st, g, part, A, f);
+        else if (g.nsplit >= 24)
+            hipLaunchKernelGGL(tile_reduce_kernel<4>, dim3(elems / 64 + f.nblocks), dim3(256), 0, st, g, part, A, f);
+        else
+            hipLaunchKernelGGL(tile_reduce_kernel<1>, dim3(elems / 256 + f.nblocks), dim3(256), 0, st, g, part, A, f);
+    }
+    else if (f.nblocks > 0) hipLaunchKernelGGL(column_sums_final_kernel, dim3(f.nblocks), dim3(256), 0, st, g, f);
     FW_LAUNCH_CHECK();
     return FW_OK;
 }
