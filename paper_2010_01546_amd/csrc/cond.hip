@@ -66,9 +66,38 @@ inline WsLayout ws_layout(int M) {
     return L;
 }
 
+// sum over the wavefront, the same value in every lane, on the vector pipe alone (no LDS permutes: a tenth of their latency)
+__device__ __forceinline__ float wave_sum_dpp(float v) {
+#define FW_DPP_ADD(ctrl) v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xf, 0xf, true))
+    FW_DPP_ADD(0xB1);     // lanes 1,0,3,2
+    FW_DPP_ADD(0x4E);     // lanes 2,3,0,1
+    FW_DPP_ADD(0x141);    // half of 16 mirrored
+    FW_DPP_ADD(0x140);    // 16 mirrored: every lane has the sum of its 16
+#undef FW_DPP_ADD
+    const float r0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 0)), r1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 16));
+    const float r2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 32)), r3 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 48));
+    return (r0 + r1) + (r2 + r3);
+}
+
+__device__ __forceinline__ float wave_max_dpp(float v) {
+#define FW_DPP_MAX(ctrl) v = fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xf, 0xf, true)))
+    FW_DPP_MAX(0xB1); FW_DPP_MAX(0x4E); FW_DPP_MAX(0x141); FW_DPP_MAX(0x140);     // the moves of wave_sum_dpp
+#undef FW_DPP_MAX
+    const float r0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 0)), r1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 16));
+    const float r2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 32)), r3 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 48));
+    return fmaxf(fmaxf(r0, r1), fmaxf(r2, r3));
+}
+
+__device__ __forceinline__ int wave_min_dpp(int v) {
+#define FW_DPP_MIN(ctrl) v = min(v, __builtin_amdgcn_update_dpp(0, v, ctrl, 0xf, 0xf, true))
+    FW_DPP_MIN(0xB1); FW_DPP_MIN(0x4E); FW_DPP_MIN(0x141); FW_DPP_MIN(0x140);
+#undef FW_DPP_MIN
+    return min(min(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)), min(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
+}
+
 // sum over the workgroup, the same value in every thread
 __device__ __forceinline__ float block_sum(float v, float* red) {
-    v = wave_sum(v);
+    v = wave_sum_dpp(v);
     __syncthreads();
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
@@ -105,12 +134,9 @@ __device__ __forceinline__ void block_argmax(const float* __restrict__ xi2, int 
             if (v > best) { best = v; idx = m; }
         }
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const float ov = __shfl_xor(best, o, 64);
-        const int oi = __shfl_xor(idx, o, 64);
-        if (ov > best || (ov == best && oi < idx)) { best = ov; idx = oi; }
-    }
+    const float top = wave_max_dpp(best);
+    idx = wave_min_dpp(best == top ? idx : 0x7fffffff);
+    best = top;
     if ((threadIdx.x & 63) == 0) { bv[threadIdx.x >> 6] = best; bi[threadIdx.x >> 6] = idx; }
     __syncthreads();
     best = bv[0]; idx = bi[0];
@@ -142,7 +168,7 @@ __device__ __forceinline__ float row_dot(const float* __restrict__ row, const fl
     } else {
         for (int k = lane; k < M; k += 64) acc += row[k] * x[k];
     }
-    return wave_sum(acc);
+    return wave_sum_dpp(acc);
 }
 
 // The first four 16-byte loads of a row, issued before a workgroup's preparation (arg-max, weights, norm) so that the
@@ -181,7 +207,7 @@ __device__ __forceinline__ float row_dot_pref(const float* __restrict__ row, con
         const float4 a = r4[k], b = x4[k];
         acc += a.x * b.x + a.y * b.y + a.z * b.z + a.w * b.w;
     }
-    return wave_sum(acc);
+    return wave_sum_dpp(acc);
 }
 
 // c = Phi_y (Phi_y e_m') (eq. (vc)) with the arg-max of eq. (mt) found by every workgroup for itself; four rows per
@@ -597,28 +623,6 @@ constexpr int UPDATE_FUSED_MAX_M = 640;
 // The line lies where six matrices fill the LDS: with one matrix at a time in LDS and the others read behind one another
 // from memory, one compute unit needed 77 us at 147 features against 31 us of the six launches.
 constexpr int COND_SMALL_MAX_M = 64;
-
-// sum over the wavefront, the same value in every lane, on the vector pipe alone (no LDS permutes: a tenth of their latency)
-__device__ __forceinline__ float wave_sum_dpp(float v) {
-#define FW_DPP_ADD(ctrl) v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xf, 0xf, true))
-    FW_DPP_ADD(0xB1);     // lanes 1,0,3,2
-    FW_DPP_ADD(0x4E);     // lanes 2,3,0,1
-    FW_DPP_ADD(0x141);    // half of 16 mirrored
-    FW_DPP_ADD(0x140);    // 16 mirrored: every lane has the sum of its 16
-#undef FW_DPP_ADD
-    const float r0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 0)), r1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 16));
-    const float r2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 32)), r3 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 48));
-    return (r0 + r1) + (r2 + r3);
-}
-
-__device__ __forceinline__ float wave_max_dpp(float v) {
-#define FW_DPP_MAX(ctrl) v = fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xf, 0xf, true)))
-    FW_DPP_MAX(0xB1); FW_DPP_MAX(0x4E); FW_DPP_MAX(0x141); FW_DPP_MAX(0x140);     // the moves of wave_sum_dpp
-#undef FW_DPP_MAX
-    const float r0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 0)), r1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 16));
-    const float r2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 32)), r3 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 48));
-    return fmaxf(fmaxf(r0, r1), fmaxf(r2, r3));
-}
 
 __global__ __launch_bounds__(1024) void cond_small_kernel(fw_cond_state s, fw_cond_params prm, fw_cond_info* __restrict__ info) {
     constexpr int PER = COND_SMALL_MAX_M / 16;

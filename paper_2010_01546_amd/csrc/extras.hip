@@ -357,12 +357,14 @@ __global__ __launch_bounds__(PROBE_WG) void probe_orth_phase_kernel(int j, int M
 // number of eigenvalues below x (sign changes of the pivots of T - x I)
 __device__ int tridiag_count_below(const double* a, const double* b, int n, double x) {
     int cnt = 0;
-    double d = 1.0;
+    double r = 0.0;       // 1 / pivot before: the hardware's estimate and two Newton steps, about an ulp (a division has twice the chain)
     for (int i = 0; i < n; ++i) {
         const double off = i > 0 ? b[i - 1] * b[i - 1] : 0.0;
-        d = a[i] - x - (i > 0 ? off / d : 0.0);
-        if (d == 0.0) d = -1e-300;
+        double d = a[i] - x - off * r;
+        if (fabs(d) < 1e-300) d = d > 0.0 ? 1e-300 : -1e-300;
         if (d < 0.0) ++cnt;
+        const double y = __builtin_amdgcn_rcp(d), z = fma(y, fma(-d, y, 1.0), y);
+        r = fabs(d) < 1e290 ? fma(z, fma(-d, z, 1.0), z) : 0.0;
     }
     return cnt;
 }
