@@ -565,7 +565,8 @@ struct DcArrays {                 // [M] each; a merge works on its own range
     int *krow, *org, *kpos;       // kept entries: row; pole next to the root; place of the root in the new order
     double *dd; int *drow;        // deflated entries
     int *ri, *rj; double *rc, *rs;   // plane rotations of the deflation, in order
-    int *cnt;                     // per merge: kept, deflated, rotations, unused
+    int *ucol, *urow;             // kept entries: column of U (those of the first child, those a rotation mixed, those of the second); row of V by column of U
+    int *cnt;                     // per merge: kept, deflated, rotations, first mixed column of U + 65536 x first column of the second child
 };
 
 // tears T at the leaf boundaries: both diagonal neighbours lose |e|
@@ -716,10 +717,15 @@ __global__ __launch_bounds__(512) void dc_deflate_kernel(DcArrays D, const doubl
             }
         }
     }
+    __shared__ int s_nk;
     if (threadIdx.x == 0) {
         if (prow >= 0) { D.kd[off + nk] = pd; D.kz[off + nk] = pz; D.krow[off + nk] = prow; ++nk; }
         D.cnt[4 * m] = nk; D.cnt[4 * m + 1] = nd; D.cnt[4 * m + 2] = nr;
+        D.cnt[4 * m + 3] = nk << 16;              // every column counts as mixed
+        s_nk = nk;
     }
+    __syncthreads();
+    for (int i = threadIdx.x; i < s_nk; i += blockDim.x) { D.ucol[off + i] = i; D.urow[off + i] = srow[D.krow[off + i]]; }
 }
 
 // The same for merges of up to DEFLATE_MAX entries, all in LDS, one thread only where something is rotated.  Which entries have a
@@ -730,7 +736,7 @@ constexpr int DEFLATE_MAX = 4096;
 __global__ __launch_bounds__(512) void dc_deflate_lds_kernel(DcArrays D, const double* __restrict__ e, int M, int ld, int P, const double* __restrict__ V) {
     __shared__ double cd[DEFLATE_MAX], cz[DEFLATE_MAX];
     __shared__ unsigned short ci[DEFLATE_MAX];            // place in the merged order
-    __shared__ unsigned long long due[DEFLATE_MAX / 64], gone[DEFLATE_MAX / 64];
+    __shared__ unsigned long long due[DEFLATE_MAX / 64], gone[DEFLATE_MAX / 64], mixed[DEFLATE_MAX / 64];
     __shared__ int cnt[8];
     const int m = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int off = part_begin(m, P, M), mid = part_begin(2 * m + 1, 2 * P, M), end = part_begin(m + 1, P, M);
@@ -741,7 +747,7 @@ __global__ __launch_bounds__(512) void dc_deflate_lds_kernel(DcArrays D, const d
     const double* d = D.d + off;
     double* sd = D.sd + off; double* sz = D.sz + off; int* srow = D.srow + off;
     for (int i = tid; i < n; i += 512) { sd[i] = d[i]; sz[i] = 0.0; srow[i] = off + i; }   // every place has a value (NaN)
-    if (tid < DEFLATE_MAX / 64) { due[tid] = 0; gone[tid] = 0; }
+    if (tid < DEFLATE_MAX / 64) { due[tid] = 0; gone[tid] = 0; mixed[tid] = 0; }
     __syncthreads();
     // place in the merged order: entries of the first part come first on ties
     for (int i = tid; i < n; i += 512) {
@@ -814,19 +820,41 @@ __global__ __launch_bounds__(512) void dc_deflate_lds_kernel(DcArrays D, const d
                 p = j; pd = jd; pz = jz; ++j;
             }
             cd[p] = pd; cz[p] = pz;
+            mixed[p >> 6] |= 1ull << (p & 63);
             t = j;
         }
         D.cnt[4 * m + 1] = nd; D.cnt[4 * m + 2] = nr;
     }
     __syncthreads();
-    int nk = 0;
+    // kept entries in order, and for the product with the children's vectors by the columns these have: 0 first child, 1 both, 2 second
+    auto kind = [&](int i) {
+        if (i >= ns || ((gone[i >> 6] >> (i & 63)) & 1)) return 3;
+        if ((mixed[i >> 6] >> (i & 63)) & 1) return 1;
+        return srow[ci[i]] < off + n1 ? 0 : 2;
+    };
+    int nk = 0, count[3] = {0, 0, 0};
     for (int c0 = 0; c0 < ns; c0 += 512) {
-        const int i = c0 + tid;
-        const bool keep = i < ns && !((gone[i >> 6] >> (i & 63)) & 1);
-        const int at = place(keep, nk);
-        if (keep) { D.kd[off + at] = cd[i]; D.kz[off + at] = cz[i]; D.krow[off + at] = ci[i]; }
+        const int i = c0 + tid, what = kind(i);
+        const int at = place(what < 3, nk);
+        if (what < 3) { D.kd[off + at] = cd[i]; D.kz[off + at] = cz[i]; D.krow[off + at] = ci[i]; }
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const int c = place(what == k, count[k]);
+            if (what == k) D.ucol[off + at] = c;          // inside its kind
+        }
     }
-    if (tid == 0) D.cnt[4 * m] = nk;
+    const int base[3] = {0, count[0], count[0] + count[1]};
+    nk = 0;
+    for (int c0 = 0; c0 < ns; c0 += 512) {
+        const int i = c0 + tid, what = kind(i);
+        const int at = place(what < 3, nk);
+        if (what < 3) {
+            const int c = D.ucol[off + at] + (what == 0 ? base[0] : what == 1 ? base[1] : base[2]);
+            D.ucol[off + at] = c;
+            D.urow[off + c] = srow[ci[i]];
+        }
+    }
+    if (tid == 0) { D.cnt[4 * m] = nk; D.cnt[4 * m + 3] = base[1] | (base[2] << 16); }
 }
 
 // plane rotations of the deflation on rows of V, one thread per column; the chain prev -> next stays in a register
@@ -993,11 +1021,14 @@ __global__ __launch_bounds__(256) void dc_vectors_kernel(DcArrays D, int M, int 
     double ss = 0.0;
     for (int i = lane; i < k; i += 64) {
         const double u = zh[i] / ((kd[i] - dorg) - tau);
-        row[i] = u;
+        row[D.ucol[off + i]] = u;
         ss += u * u;
     }
     const double inv = 1.0 / sqrt(wave_total(ss));
-    for (int i = lane; i < k; i += 64) row[i] *= inv;
+    for (int i = lane; i < k; i += 64) {                  // as above: a lane meets its own entries again
+        const int c = D.ucol[off + i];
+        row[c] *= inv;
+    }
 }
 
 // ------------------------------------------------------------------------------------------- float64 matrix products
@@ -1042,20 +1073,20 @@ struct RowsK {
 struct ColsK {
     static constexpr bool kc = false;
     const double* p; int ld, col0, nc, nk;
-    const int* list; const int* list2;     // row of entry k: list2[list[k]] if given
+    const int* list;                       // row of entry k: list[k] if given
     __device__ __forceinline__ void load(int k0, const Slot<false>& s, double (&b)[4]) const {
         const int k = k0 + s.k, c = col0 + s.r;
 #pragma unroll
         for (int i = 0; i < 4; ++i) b[i] = 0.0;
         if (k < nk) {
-            const double* q = p + (size_t)(list ? list2[list[k]] : k) * ld + c;
+            const double* q = p + (size_t)(list ? list[k] : k) * ld + c;
 #pragma unroll
             for (int i = 0; i < 4; ++i) if (c + i < nc) b[i] = q[i];
         }
     }
     __device__ __forceinline__ void load_whole(int k0, const Slot<false>& s, double (&b)[4]) const {
         const int k = k0 + s.k, c = col0 + s.r;
-        const double* q = p + (size_t)(list ? list2[list[k]] : k) * ld;
+        const double* q = p + (size_t)(list ? list[k] : k) * ld;
 #pragma unroll
         for (int i = 0; i < 4; ++i) b[i] = q[min(c + i, nc - 1)];
     }
@@ -1174,10 +1205,13 @@ __global__ __launch_bounds__(256) void dc_product_kernel(DcArrays D, int M, int 
     const int off = part_begin(m, P, M), n = part_begin(m + 1, P, M) - off;
     const int col0 = blockIdx.x * 64;
     if (col0 >= n) return;
+    // a child's vectors have nothing in the columns of the other: only the entries that reach into this tile's columns are summed over
+    const int n1 = part_begin(2 * m + 1, 2 * P, M) - off, b1 = D.cnt[4 * m + 3] & 0xffff, b2 = D.cnt[4 * m + 3] >> 16;
+    const int kb = col0 >= n1 ? b1 : 0, ke = col0 + 64 <= n1 ? b2 : k;
     const RowsK A = {U + (size_t)off * ld + off, ld, row0, k, k};
-    const ColsK B = {V + off, ld, col0, n, k, D.krow + off, D.srow + off};
+    const ColsK B = {V + off, ld, col0, n, k, D.urow + off};
     const int* kpos = D.kpos + off;
-    gemm64(A, B, 0, k, [&](int r, int c, double x) {
+    gemm64(A, B, kb, ke, [&](int r, int c, double x) {
         if (row0 + r < k && col0 + c < n) Vout[(size_t)kpos[row0 + r] * ld + off + col0 + c] = x;
     });
 }
@@ -1230,7 +1264,7 @@ __global__ __launch_bounds__(256) void wy_form_kernel(const double* __restrict__
     const int col0 = blockIdx.x * 64;
     if (col0 >= kmax) return;
     const RowsK A = {F + (size_t)blockIdx.y * NB * NB, NB, 0, NB, NB};
-    const ColsK B = {Y + (size_t)c0 * ld, ld, col0, kmax, nb, nullptr, nullptr};
+    const ColsK B = {Y + (size_t)c0 * ld, ld, col0, kmax, nb, nullptr};
     gemm64(A, B, 0, nb, [&](int r, int c, double x) {
         if (r < nb && col0 + c < kmax) Z[(size_t)(c0 + r) * ld + col0 + c] = x;
     });
@@ -1265,7 +1299,7 @@ __global__ __launch_bounds__(256) void wy_update_kernel(const double* __restrict
     const int row0 = blockIdx.y * 64, col0 = blockIdx.x * 64;
     const RowsK A = {Gm, NB, row0, M, NB};
     const int nb = min(NB, M - c0);
-    const ColsK B = {Y + (size_t)c0 * ld, ld, col0, kmax, nb, nullptr, nullptr};
+    const ColsK B = {Y + (size_t)c0 * ld, ld, col0, kmax, nb, nullptr};
     gemm64(A, B, 0, nb, [&](int r, int c, double x) {
         if (row0 + r < M && col0 + c < kmax) V[(size_t)(row0 + r) * ld + col0 + c] -= x;
     });
@@ -1383,7 +1417,7 @@ __global__ __launch_bounds__(256) void image_kernel(const double* __restrict__ V
                                                     double* __restrict__ W) {
     const int row0 = blockIdx.y * 64, col0 = blockIdx.x * 64;
     const RowsK A = {V, ld, row0, M, M};
-    const ColsK B = {Phi, ld, col0, M, M, nullptr, nullptr};
+    const ColsK B = {Phi, ld, col0, M, M, nullptr};
     gemm64(A, B, 0, M, [&](int r, int c, double x) {
         if (row0 + r < M && col0 + c < M) W[(size_t)(row0 + r) * ld + col0 + c] = x;
     });
@@ -1541,7 +1575,7 @@ __global__ __launch_bounds__(256) void spectral_product_kernel(const double* __r
     if (col0 > row0) return;
     float* out = blockIdx.z == 0 ? o0 : o1;
     const ColsKScaled A = {V, ld, row0, M, M, g, blockIdx.z == 1};
-    const ColsK B = {V, ld, col0, M, M, nullptr, nullptr};
+    const ColsK B = {V, ld, col0, M, M, nullptr};
     gemm64(A, B, 0, M, [&](int r, int c, double x) {
         const int i = row0 + r, j = col0 + c;
         if (i < M && j <= i) {
@@ -1637,7 +1671,7 @@ inline SmallWs small_layout(int M) {
     L.d = take(v); L.e = take(v); L.tau = take(v); L.p0 = take(v); L.p1 = take(v); L.dn = take(v); L.sd = take(v); L.sz = take(v); L.kd = take(v);
     L.kz = take(v); L.zh = take(v); L.rtau = take(v); L.dd = take(v); L.rc = take(v); L.rs = take(v); L.scale = take(v);
     L.F = take((size_t)((M + NB - 1) / NB) * NB * NB * sizeof(double));
-    L.ints = take((size_t)(M + 64) * 9 * sizeof(int));
+    L.ints = take((size_t)(M + 64) * 11 * sizeof(int));
     L.flag = take(256);
     L.total = o;
     return L;
@@ -1692,6 +1726,7 @@ fw_status sym_eig(const float* Phi, int M, bool dead, double* const buf[4], void
     int* ib = reinterpret_cast<int*>(sb + L.ints);
     const size_t mi = (size_t)M + 64;
     D.srow = ib; D.krow = ib + mi; D.org = ib + 2 * mi; D.kpos = ib + 3 * mi; D.drow = ib + 4 * mi; D.ri = ib + 5 * mi; D.rj = ib + 6 * mi;
+    D.ucol = ib + 9 * mi; D.urow = ib + 10 * mi;
     D.cnt = ib + 7 * mi;         // four per merge; a level has at most M / 16 of them
     if (leaves > 1) hipLaunchKernelGGL(dc_tear_kernel, dim3((leaves + 255) / 256), dim3(256), 0, st, d, e, M, leaves);
     hipLaunchKernelGGL(dc_leaf_kernel, dim3(leaves), dim3(64), 0, st, d, e, M, ld, leaves, Va);
