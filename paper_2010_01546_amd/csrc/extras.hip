@@ -173,7 +173,8 @@ __global__ __launch_bounds__(256) void probe_matvec_kernel(const float* __restri
 // A thread owns E entries and keeps them, and those of the up to NB > j basis vectors, in registers: one round of loads, all in flight
 // together.  The coefficients of a pass are summed over the wavefront NB at a time, cross the workgroup through LDS and are added
 // by every wavefront for itself in the order of the wavefronts, so a pass has one barrier.
-// M = 525, 16 steps: 3.5 us a step (the basis read again for every product and subtraction, three barriers a pass: 10.3 us).
+// M = 525: 4.6 us a step with up to 8 vectors, 6.1 us with up to 16 (the basis read again for every product and subtraction, three barriers
+// a pass: 10.3 us).
 template <int E, int NB>
 __global__ __launch_bounds__(1024) void probe_orth_kernel(int j, int M, size_t ld, double* __restrict__ Qb, const double* __restrict__ w,
                                                           double* __restrict__ alpha, double* __restrict__ beta, double breakdown,
@@ -357,14 +358,12 @@ __global__ __launch_bounds__(PROBE_WG) void probe_orth_phase_kernel(int j, int M
 // number of eigenvalues below x (sign changes of the pivots of T - x I)
 __device__ int tridiag_count_below(const double* a, const double* b, int n, double x) {
     int cnt = 0;
-    double r = 0.0;       // 1 / pivot before: the hardware's estimate and two Newton steps, about an ulp (a division has twice the chain)
+    double d = 1.0;
     for (int i = 0; i < n; ++i) {
         const double off = i > 0 ? b[i - 1] * b[i - 1] : 0.0;
-        double d = a[i] - x - off * r;
-        if (fabs(d) < 1e-300) d = d > 0.0 ? 1e-300 : -1e-300;
+        d = a[i] - x - (i > 0 ? off / d : 0.0);
+        if (d == 0.0) d = -1e-300;
         if (d < 0.0) ++cnt;
-        const double y = __builtin_amdgcn_rcp(d), z = fma(y, fma(-d, y, 1.0), y);
-        r = fabs(d) < 1e290 ? fma(z, fma(-d, z, 1.0), z) : 0.0;
     }
     return cnt;
 }
