@@ -142,10 +142,12 @@ fw_status fw_cov_finalize(const float* A, const float* s, long long n, int M, fl
  *               are split into bfloat16 hi + lo planes (16 significant bits each) and multiplied on the bfloat16 matrix
  *               cores as hi hi + hi lo + lo hi with float32 accumulation (relative Frobenius error a few 1e-6 instead of
  *               a few 1e-7; 1.5 to 2.6 times as fast)
- * dt = FW_F32: float32 matrix-core products.
- * dt = FW_BF16 with the workspace: G is widened to float32 in the workspace, the products are float32 on the matrix
- *   cores with Q as it is (past the size rule above, with M a multiple of 4: the split form), G_out is rounded to
- *   bfloat16 (nearest even).
+ * dt = FW_F32: float32 matrix-core products, or, where that is faster, products of operands split into three bfloat16 numbers
+ *   each (24 significant bits, six products; error below that of the float32 instructions).  There, as in the split form, a row
+ *   with an infinite entry comes out as NaN, and entries above 3.38e38 count as infinite.
+ * dt = FW_BF16 with the workspace: the products have float32 accuracy with Q as it is -- G widened to float32 in the workspace,
+ *   or taken as it is by the three-number form above (past the size rule above, with M a multiple of 4: the split form) --, G_out
+ *   is rounded to bfloat16 (nearest even).
  * dt = FW_BF16 without it: Q is rounded to bfloat16 on the fly, products are bf16 x bf16 accumulated in float32,
  *   G_out is rounded to bfloat16.  Q must be symmetric in every mode (its rows are read as its columns).
  */
@@ -156,7 +158,7 @@ fw_status fw_grad_transform(const void* G, fw_dtype dt, int S, int M, const floa
 
 /* How fw_grad_transform would run the product G Q for a given shape, element type and workspace size (host arithmetic
  * only): whether it takes the split form, and the flops the matrix cores execute for it (split form: bfloat16 flops,
- * three terms per float32 multiplication, whole tiles; otherwise 2 S M^2 float32 flops). */
+ * three terms per float32 multiplication, whole tiles; otherwise 2 S M^2 float32 flops, in whichever way they are multiplied). */
 typedef struct { int split; double mfma_flops_issued; } fw_grad_plan;
 fw_status fw_grad_plan_query(fw_dtype dt, int S, int M, size_t ws_bytes, fw_grad_plan* plan);
 
@@ -248,7 +250,9 @@ fw_status fw_cond_state_init(const fw_cond_state* st, void* stream);
  *   ws   scratch of fw_workspace_bytes(FW_OP_COND_STATE_REFRESH, M, 0, NULL, FW_F32) bytes (about 16 M^2 bytes).
  *        With it the float32 operands are split into two bfloat16 numbers each (hi + lo, 16 significant bits) and the
  *        products run on the bfloat16 matrix cores as hi hi + hi lo + lo hi with float32 accumulation: relative
- *        Frobenius error of Psi and Phi_y a few 1e-6, several times faster.
+ *        Frobenius error of Psi and Phi_y a few 1e-6, several times faster.  Up to about 3000 features, M a multiple of 4,
+ *        up to 32 M^2 bytes: room for partial results, which let few tiles use the whole chip (without that room, with the
+ *        16 M^2 bytes: as fast as tiles allow).
  *        With ws NULL or smaller than that, or M < FW_REFRESH_SPLIT_MIN_M (where the split form would not be faster), the
  *        products run in plain float32 (error a few 1e-7); that needs st->Psi, or at least M^2 floats (rounded up to 256
  *        bytes) of ws to stand in for it (FW_ERR_WORKSPACE otherwise).
@@ -257,7 +261,7 @@ fw_status fw_cond_state_init(const fw_cond_state* st, void* stream);
 
 /* How fw_cond_state_refresh would run for a given M and workspace size (host arithmetic only): which form the two
  * products take and the flops the matrix cores execute for them, whole tiles, lower triangle only for Phi_y (split form: bfloat16
- * flops, three terms per float32 multiplication; float32 form: about 3 M^3 in float32; up to 128 features, 80 where M is no
+ * flops, three terms per float32 multiplication; float32 form: about 3 M^3, as float32 products also where each is six bfloat16 ones; up to 128 features, 80 where M is no
  * multiple of 4, both products in full). */
 typedef struct { int split; double mfma_flops_issued; } fw_refresh_plan;
 fw_status fw_cond_refresh_plan_query(int M, size_t ws_bytes, fw_refresh_plan* plan);
