@@ -143,8 +143,9 @@ fw_status fw_cov_finalize(const float* A, const float* s, long long n, int M, fl
  *               cores as hi hi + hi lo + lo hi with float32 accumulation (relative Frobenius error a few 1e-6 instead of
  *               a few 1e-7; 1.5 to 2.6 times as fast)
  * dt = FW_F32: float32 matrix-core products, or, where that is faster, products of operands split into three bfloat16 numbers
- *   each (24 significant bits, six products; error below that of the float32 instructions).  There, as in the split form, a row
- *   with an infinite entry comes out as NaN, and entries above 3.38e38 count as infinite.
+ *   each (24 significant bits at any exponent, six products; error below that of the float32 instructions; results that an
+ *   infinite entry or one above 2^119 enters are multiplied in float32 and so are what they are there).  In the split form a row with
+ *   an infinite entry comes out as NaN, entries above 3.38e38 count as infinite, and those below 2^-118 lose their 16 bits one by one.
  * dt = FW_BF16 with the workspace: the products have float32 accuracy with Q as it is -- G widened to float32 in the workspace,
  *   or taken as it is by the three-number form above (past the size rule above, with M a multiple of 4: the split form) --, G_out
  *   is rounded to bfloat16 (nearest even).
@@ -170,7 +171,8 @@ fw_status fw_grad_plan_query(fw_dtype dt, int S, int M, size_t ws_bytes, fw_grad
  *              must not overlap.  A channels-last weight [S, kh, kw, Cin] is plain [S taps, M] rows: use fw_grad_transform.
  *   Q          [M, M] float32, symmetric
  *   ws         scratch, fw_workspace_bytes(FW_OP_GRAD_TRANSFORM_TAPS, M, S * taps, NULL, dt) bytes (the gradient as rows)
- * Products are float32 on the matrix cores for both element types; bfloat16 results are rounded to nearest even.
+ * Products have float32 accuracy for both element types (float32, or three bfloat16 numbers per operand, as in
+ * fw_grad_transform); bfloat16 results are rounded to nearest even.
  * When M is a multiple of 4 and the S * taps rows meet fw_grad_transform's size rule for the split form, the product takes
  * that form (bfloat16 hi + lo planes, relative error a few 1e-6).
  */
@@ -187,7 +189,8 @@ fw_status fw_grad_transform_taps(const void* G, fw_dtype dt, int S, int M, int t
  *          With it, M a multiple of 4 and S * taps rows that meet fw_grad_transform's size rule for the split form, the
  *          product takes that form (about 1.7 times faster at S = 512, M = 4608); its runs of the contraction index are
  *          then kept in the workspace and added by the pass that updates W and V.
- * Without the split form the transformed gradient is not written anywhere.
+ * Without the split form the transformed gradient is not written anywhere and the product has float32 accuracy (the forms of
+ * fw_grad_transform); infinite entries then reach the entries of W and V that they enter, in the split form the whole row.
  */
 typedef struct { float lr, momentum, weight_decay; } fw_sgd_params;
 fw_status fw_sgd_update(const void* G, fw_dtype dt, int S, int M, int taps, const float* Q, const fw_sgd_params* p,
@@ -254,7 +257,7 @@ fw_status fw_cond_state_init(const fw_cond_state* st, void* stream);
  *        up to 32 M^2 bytes: room for partial results, which let few tiles use the whole chip (without that room, with the
  *        16 M^2 bytes: as fast as tiles allow).
  *        With ws NULL or smaller than that, or M < FW_REFRESH_SPLIT_MIN_M (where the split form would not be faster), the
- *        products run in plain float32 (error a few 1e-7); that needs st->Psi, or at least M^2 floats (rounded up to 256
+ *        products have float32 accuracy (error a few 1e-7; the forms of fw_grad_transform); that needs st->Psi, or at least M^2 floats (rounded up to 256
  *        bytes) of ws to stand in for it (FW_ERR_WORKSPACE otherwise).
  */
 #define FW_REFRESH_SPLIT_MIN_M 1536

@@ -1,10 +1,17 @@
 // Float32 products on the bfloat16 matrix cores:  C = A B^T  for row-major float32 (or bfloat16) A [S, K] and float32 B [N, K].
 //
-// A float32 number is the sum of three bfloat16 numbers: h = bf16(x), m = bf16(x - h), l = bf16(x - h - m), each difference exact, so
-// 24 significant bits are kept over the whole range of exponents.  Of the nine products of two such sums the six above 2^-24 are
-// taken, h h, h m, m h, m m, h l, l h, on v_mfma_f32_32x32x16_bf16 (sixteen times the rate of the float32 instruction).  A
-// bfloat16 gradient is its own h: three products.  The large products h h have accumulators of their own, one for each half of a
-// chunk, so that a rounding of a partial sum happens K / 32 times in a chain and the five small ones do not add to it.
+// A float32 number is x = h + 2^-16 (m + l) with three bfloat16 numbers h = bf16(x), m = bf16(2^16 (x - h)), l = bf16(2^16 (x - h) - m),
+// each difference exact (splitting into three bfloat16 numbers: G. Henry, P. T. P. Tang, A. Heinecke 2019).  bfloat16 has the
+// exponents of float32 but ends 16 bits earlier, at 2^-133: without the factor the last part of a number below 2^-110 is lost (4e-6 of
+// it at 2^-116, 1e-3 at 2^-124), with it all 24 bits are kept down to the smallest one.
+// Of the nine products of two such sums the six above 2^-24 are taken, h h, h m, m h, m m, h l, l h, on v_mfma_f32_32x32x16_bf16
+// (sixteen times the rate of the float32 instruction).  A bfloat16 gradient is its own h: three products.  Products with the same
+// factor share accumulators, one set for each half of a chunk, so that a rounding of a partial sum of the large products h h
+// happens K / 32 times in a chain and the five small ones do not add to it.
+//
+// Infinite entries, and those above 2^119, have no such sum, and sums of products above 2^112 overflow with it: the result is infinite or
+// NaN then.  A wavefront that sees such a result multiplies its 32 x 32 results once more in float32, so that they are what the
+// float32 instruction gives.
 //
 // The operands are read as they lie in memory and split on the way into LDS: no packing pass and no workspace.
 #include "fw_internal.h"
@@ -31,7 +38,7 @@ __device__ __forceinline__ void split8(const float (&x)[8], uint4& h, uint4& m, 
         union { bf2 v; unsigned u; } p;
         p.v[0] = (__bf16)x0; p.v[1] = (__bf16)x1;
         hp[k] = p.u;
-        const float r0 = x0 - __uint_as_float(p.u << 16), r1 = x1 - __uint_as_float(p.u & 0xffff0000u);
+        const float r0 = 65536.f * (x0 - __uint_as_float(p.u << 16)), r1 = 65536.f * (x1 - __uint_as_float(p.u & 0xffff0000u));
         p.v[0] = (__bf16)r0; p.v[1] = (__bf16)r1;
         mp[k] = p.u;
         const float s0 = r0 - __uint_as_float(p.u << 16), s1 = r1 - __uint_as_float(p.u & 0xffff0000u);
@@ -116,9 +123,9 @@ __global__ __launch_bounds__(NT) void gemm_planes_kernel(const void* __restrict_
         at[8 * PITCH] = l;
     };
 
-    floatx16 big, small;
+    floatx16 big, small, mm;                          // results times 1, 2^16, 2^32
 #pragma unroll
-    for (int i = 0; i < 16; ++i) big[i] = small[i] = 0.f;
+    for (int i = 0; i < 16; ++i) big[i] = small[i] = mm[i] = 0.f;
     auto multiply = [&](int c) {
         const uint4* at = lds[c & 1] + (2 * part + half) * PITCH + l32;
         auto a = [&](int pl) { return *reinterpret_cast<const bf16x8*>(at + pl * 4 * PITCH + 32 * wr); };
@@ -128,7 +135,7 @@ __global__ __launch_bounds__(NT) void gemm_planes_kernel(const void* __restrict_
         if constexpr (!ABF16) {
             const bf16x8 am = a(1), al = a(2);
             small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, bh, small, 0, 0, 0);
-            small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(am, bm, small, 0, 0, 0);
+            mm = __builtin_amdgcn_mfma_f32_32x32x16_bf16(am, bm, mm, 0, 0, 0);
             small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(am, bh, small, 0, 0, 0);
         }
         small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bl, small, 0, 0, 0);
@@ -171,24 +178,43 @@ __global__ __launch_bounds__(NT) void gemm_planes_kernel(const void* __restrict_
         barrier();
     }
 
-    small += big;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) big[i] += 0x1p-16f * (ABF16 ? small[i] : small[i] + 0x1p-16f * mm[i]);
     float* red = reinterpret_cast<float*>(lds);       // the two sets' halves of the sum: [wavefront of the set][register][lane]
     static_assert(TR * TC * 4 <= (int)sizeof(lds), "room for the partial tile");
     if (part == 1) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) red[((wave & 3) * 16 + i) * 64 + lane] = small[i];
+        for (int i = 0; i < 16; ++i) red[((wave & 3) * 16 + i) * 64 + lane] = big[i];
     }
     __syncthreads();
     if (part == 1) return;
-    const bool plain = Out.out && !Out.out_bf16 && Out.taps == 1 && !Out.W;
     const int col = col0 + 32 * wc + l32;
+    bool finite = true;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        big[i] += red[((wave & 3) * 16 + i) * 64 + lane];
+        finite &= fabsf(big[i]) <= 3.402823466e38f;
+    }
+    if (__any(!finite)) {
+        const size_t arow = (size_t)min(row0 + 32 * wr + l32, S - 1) * K;
+        const float* a32 = reinterpret_cast<const float*>(Av) + arow;
+        const unsigned short* a16 = reinterpret_cast<const unsigned short*>(Av) + arow;
+        const float* b32 = B + (size_t)min(col, N - 1) * K;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) big[i] = 0.f;
+        for (int k0 = 0; k0 < K; k0 += 2) {           // lanes below 32 have entry k0, the others k0 + 1
+            const int k = k0 + half;
+            const float x = k < K ? (ABF16 ? bf16_to_f32(a16[k]) : a32[k]) : 0.f, y = k < K ? b32[k] : 0.f;
+            big = __builtin_amdgcn_mfma_f32_32x32x2f32(x, y, big, 0, 0, 0);
+        }
+    }
+    const bool plain = Out.out && !Out.out_bf16 && Out.taps == 1 && !Out.W;
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
         const int row = row0 + 32 * wr + 8 * (i >> 2) + 4 * half + (i & 3);
-        const float v = small[i] + red[((wave & 3) * 16 + i) * 64 + lane];
         if (row < S && col < N) {
-            if (plain) reinterpret_cast<float*>(Out.out)[(size_t)row * N + col] = v;
-            else emit(Out, row, col, N, v);
+            if (plain) reinterpret_cast<float*>(Out.out)[(size_t)row * N + col] = big[i];
+            else emit(Out, row, col, N, big[i]);
         }
     }
 }

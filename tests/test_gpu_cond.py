@@ -80,6 +80,34 @@ def test_refresh_around_the_one_launch_form(M):
     assert relF(xi2.cpu().numpy(), (want ** 2).sum(0)) < 8e-6
 
 
+@pytest.mark.parametrize("M", [525, 1280])
+@pytest.mark.parametrize("scale", [-116, -122])
+def test_refresh_of_a_small_covariance(M, scale):
+    """Entries of Phi_x down to subnormal numbers, in the products of three bfloat16 numbers per operand: as exact as of any other size
+    (subnormal results add their rounding of 2^-150, 2^-28 of an entry of 2^-122)."""
+    rng = np.random.default_rng(M)
+    P = (spd(M, M, 1.0, -1.0) * 2.0 ** scale).astype(np.float32)
+    P = np.tril(P) + np.tril(P, -1).T
+    T = (np.eye(M) + 0.3 * rng.standard_normal((M, M)) / np.sqrt(M)).astype(np.float32)
+    z = lambda *sh: torch.full(sh, float("nan"), device="cuda:0")  # noqa: E731
+    Py, Psi, xi2, lbar = z(M, M), z(M, M), z(M), torch.ones(4, device="cuda:0")
+    Q = dev(np.eye(M))
+
+    def refresh():
+        st = b.cond_state(M, dev(P), lbar, dev(T), Q, Q.clone(), Py, Psi, xi2)
+        b.fw_cond_state_refresh(st, workspace(b.fw_workspace_bytes(b.FW_OP_COND_STATE_REFRESH, M)))
+        torch.cuda.synchronize()
+        return Psi.cpu().numpy(), Py.cpu().numpy()
+    P64, T64 = P.astype(np.float64), T.astype(np.float64)
+    psi, py = refresh()
+    assert relF(psi, T64 @ P64) < 2e-6 and relF(py, T64 @ P64 @ T64.T) < 4e-6
+    P[5, 5] = np.inf                       # a feature without a finite variance: its column of Psi, and nothing else of Psi
+    psi, _ = refresh()
+    assert np.array_equal(psi[:, 5], np.sign(T[:, 5]) * np.float32(np.inf))
+    rest = np.arange(M) != 5
+    assert relF(psi[:, rest], (T64 @ np.where(np.isinf(P64), 0, P64))[:, rest]) < 2e-6
+
+
 def test_invariants_free_running():
     """After many free-running steps Q = T^T T and Phi_y = T Phi_x T^T still hold, and the condition number has dropped."""
     M = 96

@@ -245,3 +245,72 @@ def test_three_planes_bf16(S, M):
     torch.cuda.synchronize()
     d = want + 5e-4 * W0
     assert relF(V.cpu().numpy(), d) < 1e-6 and relF(W.cpu().numpy(), W0 - 0.1 * d) < 1e-6
+
+
+# Numbers of any size in the three-plane form.  Rows of G (or all of Q) at 2^-k, up to where a tile is multiplied in float32 and down to where entries are subnormal: 24 bits of
+# an operand and float32 sums leave the 1e-6 of above; a subnormal result is rounded to 2^-150, 2^-26 of a row at 2^-124.
+@pytest.mark.parametrize("S,M", [(50, 525), (900, 896)])
+@pytest.mark.parametrize("gdt", [b.FW_F32, b.FW_BF16])
+def test_three_planes_numbers_of_any_size(S, M, gdt):
+    T32, Q64 = sym_Q(M, M + 13)
+    k = np.array([0, 60, -100, -118, 112, 116, 120, 124])
+    tdt = torch.bfloat16 if gdt == b.FW_BF16 else torch.float32
+    for gk, qk in ((k[np.arange(S) % 8][:, None], 0), (0, 116), (0, 124)):
+        Q32 = (Q64 * 2.0 ** -float(qk)).astype(np.float32)
+        G = (rng.standard_normal((S, M)) * 2.0 ** -gk.astype(float) if qk == 0 else rng.standard_normal((S, M))).astype(np.float32)
+        if gdt == b.FW_BF16:
+            G = wl.round_to_bf16(G)
+        want = G.astype(np.float64) @ Q32.astype(np.float64)
+        W, V = torch.zeros(S, M, device=DEV), torch.zeros(S, M, device=DEV)
+        ws = workspace(b.fw_workspace_bytes(b.FW_OP_SGD_UPDATE, M, S, None, gdt))
+        b.fw_sgd_update(dev(G, tdt), gdt, S, M, 1, dev(Q32), b.sgd_params(0.5, 0.9, 0.0), W, V, ws)
+        got = {"V": V.cpu().numpy(), "W": -2.0 * W.cpu().numpy().astype(np.float64)}
+        if gdt == b.FW_F32:
+            out = torch.full((S, M), float("nan"), device=DEV)
+            b.fw_grad_transform(dev(G), gdt, S, M, None, dev(Q32), out)
+            got["out"] = out.cpu().numpy()
+        for name, x in got.items():
+            err = np.linalg.norm(x - want, axis=1) / np.linalg.norm(want, axis=1)
+            assert err.max() < 1e-6, (name, int(err.argmax()))
+
+
+# Infinite entries, NaN, and finite ones above the largest bfloat16 number: what float32 arithmetic gives, and only in the rows (of G) and
+# columns (of Q) that they enter.
+@pytest.mark.parametrize("S,M", [(50, 525), (130, 193), (900, 896)])
+@pytest.mark.parametrize("gdt", [b.FW_F32, b.FW_BF16])
+def test_three_planes_infinite_and_huge(S, M, gdt):
+    T32, Q64 = sym_Q(M, M + 17)
+    Q32 = (0.25 * Q64).astype(np.float32)
+    Q32[7, 11] = Q32[11, 7] = 0.0
+    tdt = torch.bfloat16 if gdt == b.FW_BF16 else torch.float32
+    ws = workspace(b.fw_workspace_bytes(b.FW_OP_SGD_UPDATE, M, S, None, gdt))
+    wst = workspace(b.fw_workspace_bytes(b.FW_OP_GRAD_TRANSFORM, M, S, None, gdt))
+    for kind in ("G", "Q"):
+        G = rng.standard_normal((S, M)).astype(np.float32)
+        Q = Q32.copy()
+        if kind == "G":
+            G[3, 7], G[33, M - 1], G[S - 1, 0], G[5, 2] = np.inf, -np.inf, np.nan, 3.4e38 if gdt == b.FW_F32 else 3.3e38
+        else:
+            Q[9, 40] = Q[40, 9] = -np.inf
+            Q[M - 1, M - 1] = 3.4e38
+            G[:, M - 1] *= 0.1
+        if gdt == b.FW_BF16:
+            G = np.where(np.isfinite(G), wl.round_to_bf16(np.where(np.isfinite(G), G, 0).astype(np.float32)), G)
+        with np.errstate(invalid="ignore"):
+            want = G.astype(np.float64) @ Q.astype(np.float64)
+        want = np.where(np.isnan(G).any(1)[:, None], np.nan, want)
+        V, W = torch.zeros(S, M, device=DEV), torch.zeros(S, M, device=DEV)
+        b.fw_sgd_update(dev(G, tdt), gdt, S, M, 1, dev(Q), b.sgd_params(0.0, 0.9, 0.0), W, V, ws)
+        out = torch.zeros(S, M, device=DEV, dtype=tdt)
+        b.fw_grad_transform(dev(G, tdt), gdt, S, M, None, dev(Q), out, wst)
+        for got, bound in ((V.cpu().numpy(), 1e-6), (out.float().cpu().numpy(), 1e-6 if gdt == b.FW_F32 else 2.0 ** -8)):
+            assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isposinf(got), np.isposinf(want))
+            assert np.array_equal(np.isneginf(got), np.isneginf(want))
+            ok = np.isfinite(want)
+            # every row (and every huge column) against its own size
+            for x, y in ((got, want), (got.T, want.T)):
+                f = np.isfinite(y)
+                for r in range(len(y)):
+                    if f[r].any():
+                        assert relF(x[r][f[r]].astype(np.float64), y[r][f[r]]) < bound
+            assert ok.any()
