@@ -401,7 +401,7 @@ static fw_status evd_outputs(const double* V, int M, const fw_evd_params* p, dou
 size_t evd_workspace_bytes(int M) { return evd_layout(M).total; }
 
 fw_status whiten_evd(const float* Phi_x, int M, const fw_evd_params* p, float* T, float* Q, float* Qs, float* lambda, void* ws,
-                     size_t ws_bytes, hipStream_t st) {
+                     size_t ws_bytes, hipStream_t st, EvdRun* run) {
     const EvdWs L = evd_layout(M);
     if (ws_bytes < L.total) return FW_ERR_WORKSPACE;
     char* base = reinterpret_cast<char*>(ws);
@@ -428,6 +428,7 @@ fw_status whiten_evd(const float* Phi_x, int M, const fw_evd_params* p, float* T
     FW_HIP_TRY(hipMemcpyAsync(verdict, cnt, sizeof(verdict), hipMemcpyDeviceToHost, st));
     FW_HIP_TRY(hipStreamSynchronize(st));
     const bool diagonal = verdict[0] == 0;
+    if (run) { run->one_launch = 0; run->diagonal = diagonal ? 1 : 0; run->sweeps = 0; }
     if (diagonal) {
         rc = sym_eig_load(Phi_x, M, mat[0], st);
         if (rc != FW_OK) return rc;
@@ -436,7 +437,7 @@ fw_status whiten_evd(const float* Phi_x, int M, const fw_evd_params* p, float* T
         hipLaunchKernelGGL(eig_kernel, dim3((M + 3) / 4), dim3(256), 0, st, W, V, ld, M, lam);
         FW_LAUNCH_CHECK();
     } else {
-        rc = sym_eig(Phi_x, M, verdict[1] != 0, mat, base + L.small, &V, &W, st);
+        rc = sym_eig(Phi_x, M, verdict[1] != 0, mat, base + L.small, &V, &W, st, run);
         if (rc != FW_OK) return rc;
         rc = sym_eig_check(Phi_x, M, V, W, mat[0], mat[1], base + L.small, kAccept, floor_abs, floor_rel, lam, cnt, st);
         if (rc != FW_OK) return rc;
@@ -477,6 +478,7 @@ fw_status whiten_evd(const float* Phi_x, int M, const fw_evd_params* p, float* T
             FW_HIP_TRY(hipMemcpyAsync(&rotations, cnt, sizeof(int), hipMemcpyDeviceToHost, st));
             FW_HIP_TRY(hipStreamSynchronize(st));
             converged = rotations == 0;
+            if (run) ++run->sweeps;
         }
         hipLaunchKernelGGL(eig_kernel, dim3((M + 3) / 4), dim3(256), 0, st, W, V, ld, M, lam);
         FW_LAUNCH_CHECK();

@@ -196,11 +196,20 @@ bool cond_refresh_plan(int M, size_t ws_bytes, fw_refresh_plan* plan);
 fw_status cond_state_refresh(const fw_cond_state* s, void* ws, size_t ws_bytes, hipStream_t st);
 fw_status cond_static_scratch(void** ptr, size_t* bytes);
 
+// Which way a decomposition takes and took, for tests of its fall-backs; no caller of the library has to know.
+struct EvdRun {
+    int by_rows;        // in: the reduction with a launch per row, as where the launch for all rows is not possible
+    int polls;          // in: rounds after which a wait of that launch gives up (0: the usual number)
+    int one_launch;     // out: rows were reduced in one launch
+    int diagonal;       // out: V = I was accepted
+    int sweeps;         // out: Jacobi sweeps, 0 where the direct decomposition was accepted
+};
+
 // ---- symeig.hip: eigenvectors of a symmetric matrix in float64 (rows, leading dimension sym_eig_ld)
 int sym_eig_ld(int M);
 size_t sym_eig_small_bytes(int M);
 size_t sym_eig_matrix_doubles(int M);
-fw_status sym_eig(const float* Phi, int M, bool dead, double* const buf[4], void* small, double** V, double** free_buf, hipStream_t st);
+fw_status sym_eig(const float* Phi, int M, bool dead, double* const buf[4], void* small, double** V, double** free_buf, hipStream_t st, EvdRun* run);
 fw_status sym_eig_check(const float* Phi, int M, const double* V, double* W, double* copy, double* scratch, void* small, double thr, double floor_abs,
                         double floor_rel, double* lam, int* flag, hipStream_t st);
 fw_status sym_eig_check_identity(const float* Phi, int M, void* small, double thr, double floor_abs, double floor_rel, int* flag,
@@ -212,6 +221,6 @@ fw_status sym_eig_spectral_products(const double* V, int M, const double* root_g
 // ---- evd.hip
 size_t evd_workspace_bytes(int M);
 fw_status whiten_evd(const float* Phi_x, int M, const fw_evd_params* p, float* T, float* Q, float* Qs, float* lambda,
-                     void* ws, size_t ws_bytes, hipStream_t st);
+                     void* ws, size_t ws_bytes, hipStream_t st, EvdRun* run = nullptr);
 
 }  // namespace fw

@@ -316,7 +316,7 @@ template <int T, int C, int RB>
 __global__ __launch_bounds__(T) void tri_rows_kernel(const double* __restrict__ A, int ld, int c0, int first, const double* __restrict__ vprev,
                                                      const double* __restrict__ pprev, double* __restrict__ Pslot, double* __restrict__ Xslot,
                                                      double* __restrict__ Vh, double* __restrict__ d, double* __restrict__ e,
-                                                     double* __restrict__ tau) {
+                                                     double* __restrict__ tau, int polls) {
     constexpr int NW = T / 64;
     __shared__ double vl[C * T + RB];             // reflector of the step before
     __shared__ double rowred[NW][RB], rowp[RB], col[RB], red[2][NW];
@@ -342,7 +342,7 @@ __global__ __launch_bounds__(T) void tri_rows_kernel(const double* __restrict__ 
         rowp[t] = (i0 + t <= c0 && !first) ? pprev[i0 + t] : 0.0;
         vl[C * T + t] = 0.0;
     }
-    if (t == 0) { s_bad = 0; s_pc = 0.0; }
+    if (t == 0) s_bad = 0;                        // read behind the barrier of the first row, set from the second row on
     double tp = first ? 0.0 : tau[c0 + 1];
     for (int c = c0; c >= 1; --c) {
         if (i0 >= c) return;                      // no row of this workgroup is left (workgroup 0 stays to the end)
@@ -372,7 +372,7 @@ __global__ __launch_bounds__(T) void tri_rows_kernel(const double* __restrict__ 
                 for (int q = 0; q < C; ++q) { there &= pb[q] != SENTINEL; there_x &= xb[q] != SENTINEL; }
                 have_x = __all(there_x);
                 if (have_x && __all(there)) break;
-                if (spin >= POLL_LIMIT) { s_bad = 1; break; }
+                if (spin + 1 >= polls) { s_bad = 1; break; }
             }
 #pragma unroll
             for (int q = 0; q < C; ++q) { w[q] = __longlong_as_double((long long)pb[q]); x[q] = __longlong_as_double((long long)xb[q]); }
@@ -381,7 +381,7 @@ __global__ __launch_bounds__(T) void tri_rows_kernel(const double* __restrict__ 
 #pragma unroll
         for (int q = 0; q < C; ++q) {
             dot += v[q] * w[q];
-            if (t + T * q == c) s_pc = w[q];
+            if (t + T * q == c) s_pc = w[q];          // one thread, in every row: nobody else writes it
         }
         dot = block_total<T>(dot, red[0]);
         if (s_bad) {
@@ -1637,8 +1637,8 @@ void step(double* A, int ld, int c, int first, const double* vp, const double* p
 // the workgroups at a time), nothing was launched.
 template <int T, int C, int RB>
 bool launch_rows(const double* A, int ld, int c, int first, const double* vp, const double* pp, double* Pslot, double* Xslot, double* Y, double* d,
-                 double* e, double* tau, hipStream_t st) {
-    void* args[] = {&A, &ld, &c, &first, &vp, &pp, &Pslot, &Xslot, &Y, &d, &e, &tau};
+                 double* e, double* tau, int polls, hipStream_t st) {
+    void* args[] = {&A, &ld, &c, &first, &vp, &pp, &Pslot, &Xslot, &Y, &d, &e, &tau, &polls};
     if (hipLaunchCooperativeKernel(reinterpret_cast<const void*>(tri_rows_kernel<T, C, RB>), dim3(c / RB + 1), dim3(T), args, 0, st) == hipSuccess) return true;
     (void)hipGetLastError();
     return false;
@@ -1647,9 +1647,9 @@ bool launch_rows(const double* A, int ld, int c, int first, const double* vp, co
 // 1811 (256 threads of two 1833), 576 features 2203 (256 of three 2274, 640 of one 2178), 768 features 2873 (256 of three 2977, 768 of one
 // 2921), 1024 features 3770 (1024 of one 4179), 1536 features 6261 (768 of two 6519), 2048 features 9285 (1024 of two 10466).
 bool rows(const double* A, int ld, int c, int first, const double* vp, const double* pp, double* Pslot, double* Xslot, double* Y, double* d,
-          double* e, double* tau, hipStream_t st) {
+          double* e, double* tau, int polls, hipStream_t st) {
     const int n = c + 1;
-#define FW_ROWS(T, C, RB) return launch_rows<T, C, RB>(A, ld, c, first, vp, pp, Pslot, Xslot, Y, d, e, tau, st)
+#define FW_ROWS(T, C, RB) return launch_rows<T, C, RB>(A, ld, c, first, vp, pp, Pslot, Xslot, Y, d, e, tau, polls, st)
     if (n <= 256) FW_ROWS(256, 1, 8);
     if (n <= 512) FW_ROWS(512, 1, 8);
     if (n <= 640) FW_ROWS(320, 2, 8);
@@ -1689,7 +1689,7 @@ size_t sym_eig_matrix_doubles(int M) {
 
 // Eigenvectors of the symmetric part of Phi as rows, ascending eigenvalues.  dead: some diagonal entry is zero.  buf[0..3]: four matrices of
 // sym_eig_matrix_doubles(M); on return *V and *free_buf name the buffer with the eigenvectors and one that is free.
-fw_status sym_eig(const float* Phi, int M, bool dead, double* const buf[4], void* small, double** V, double** free_buf, hipStream_t st) {
+fw_status sym_eig(const float* Phi, int M, bool dead, double* const buf[4], void* small, double** V, double** free_buf, hipStream_t st, EvdRun* run) {
     const int ld = sym_eig_ld(M);
     const SmallWs L = small_layout(M);
     char* sb = reinterpret_cast<char*>(small);
@@ -1710,7 +1710,9 @@ fw_status sym_eig(const float* Phi, int M, bool dead, double* const buf[4], void
     bool reduced = false;
     if (M > TAIL) {
         while (c >= ROWS_MAX_M) one_step();
-        reduced = rows(A, ld, c, first, vp(), p[cur ^ 1], Va, Vb, Y, d, e, tau, st);
+        if (!(run && run->by_rows))
+            reduced = rows(A, ld, c, first, vp(), p[cur ^ 1], Va, Vb, Y, d, e, tau, run && run->polls > 0 ? run->polls : POLL_LIMIT, st);
+        if (run) run->one_launch = reduced ? 1 : 0;
         if (!reduced)
             while (c >= TAIL) one_step();
     }

@@ -80,6 +80,48 @@ def reflected_diagonal(M, lam, seed):
     return form(torch.as_tensor(lam, device=DEV)), form
 
 
+class EvdRun(C.Structure):
+    _fields_ = [(n, C.c_int) for n in ("by_rows", "polls", "one_launch", "diagonal", "sweeps")]
+
+
+def whiten_evd(Phi, M, T, Q, lam, ws, **how):
+    """fw_whiten_evd with a look at the way it took (struct EvdRun of the sources); no Q_s."""
+    f = b.lib._ZN2fw10whiten_evdEPKfiPK13fw_evd_paramsPfS5_S5_S5_PvmP12ihipStream_tPNS_6EvdRunE
+    P = C.c_void_p
+    f.argtypes = [P, C.c_int, C.POINTER(b.fw_evd_params), P, P, P, P, P, C.c_size_t, P, C.POINTER(EvdRun)]
+    run = EvdRun(**how)
+    rc = f(Phi.data_ptr(), M, C.byref(b.evd_params()), T.data_ptr(), Q.data_ptr(), None, lam.data_ptr(), ws.data_ptr(), ws.numel(),
+           torch.cuda.current_stream().cuda_stream, C.byref(run))
+    assert rc == 0
+    return run
+
+
+def decompose_known(M, **how):
+    """Decomposition of a matrix whose T and Q are known, compared.  The matrix is stored as float32, so T and Q of a spectrum within
+    [0.05, 1] carry about 2^-24 / 0.05; from 1536 features on their products run on operands of 16 significant bits (5e-6)."""
+    lam = np.linspace(1.0, 0.05, M)
+    Phi, form = reflected_diagonal(M, lam, M)
+    T = torch.empty(M, M, device=DEV); Q = torch.empty(M, M, device=DEV); out = torch.empty(M, device=DEV)
+    ws = workspace(b.fw_workspace_bytes(b.FW_OP_WHITEN_EVD, M))
+    run = whiten_evd(Phi.float(), M, T, Q, out, ws, **how)
+    d = torch.as_tensor(lam, device=DEV)
+    rel = lambda x, y: float((x.double() - y).norm() / y.norm())
+    bound = 2e-5 if M >= b.FW_REFRESH_SPLIT_MIN_M else 2e-6
+    assert rel(T, form(d.rsqrt())) < bound and rel(Q, form(1 / d)) < bound
+    assert float((out.double() - d).abs().max()) < 5e-7
+    assert torch.equal(T, T.T) and torch.equal(Q, Q.T)
+    return run
+
+
+# Rows reduced one launch each before the launch for all others, which then starts from their last reflector: the direct decomposition is
+# accepted every time (the start raced once: one call in twenty to a hundred was off and went through the sweeps, a tenth as fast).
+@pytest.mark.parametrize("M", [2561, 2600, 3073])
+def test_reduction_after_rows_of_their_own(M):
+    for _ in range(12):
+        run = decompose_known(M)
+        assert run.one_launch and run.sweeps == 0
+
+
 # One size per range of the reduction's launch rule (columns per thread change at 256, 512, 768, 1024, 1536, 2048, 2560, 3072,
 # 4096, 5120, 8192 rows), the last 128 rows alone and with one row more, one leaf, two leaves, sizes where T and Q change form.
 # The matrix is stored as float32, so T and Q of a spectrum within [0.05, 1] carry about 2^-24 / 0.05; from 1536 features on
