@@ -122,47 +122,56 @@ def test_reduction_after_rows_of_their_own(M):
         assert run.one_launch and run.sweeps == 0
 
 
-# One size per range of the reduction's launch rule (columns per thread change at 256, 512, 768, 1024, 1536, 2048, 2560, 3072,
-# 4096, 5120, 8192 rows), the last 128 rows alone and with one row more, one leaf, two leaves, sizes where T and Q change form.
-# The matrix is stored as float32, so T and Q of a spectrum within [0.05, 1] carry about 2^-24 / 0.05; from 1536 features on
-# their products run on operands of 16 significant bits (5e-6).
+# One leaf, two leaves, the last 128 rows alone and with one row more, sizes where T and Q change form, and sizes whose first rows are
+# reduced one launch each (beyond 2560: columns per thread change at 3072, 4096, 5120, 8192 rows).  The direct decomposition
+# has to be the one that is accepted.
 @pytest.mark.parametrize("M", [1, 16, 17, 127, 128, 129, 257, 513, 769, 1025, 1535, 1537, 2049, 2561, 3073, 4097, 5121, 8193])
 def test_direct_decomposition_sizes(M):
-    lam = np.linspace(1.0, 0.05, M)
-    Phi, form = reflected_diagonal(M, lam, M)
-    T = torch.empty(M, M, device=DEV); Q = torch.empty(M, M, device=DEV); out = torch.empty(M, device=DEV)
-    ws = workspace(b.fw_workspace_bytes(b.FW_OP_WHITEN_EVD, M))
-    b.fw_whiten_evd(Phi.float(), M, b.evd_params(), T, Q, None, out, ws)
-    d = torch.as_tensor(lam, device=DEV)
-    rel = lambda x, y: float((x.double() - y).norm() / y.norm())
-    bound = 2e-5 if M >= b.FW_REFRESH_SPLIT_MIN_M else 2e-6
-    assert rel(T, form(d.rsqrt())) < bound and rel(Q, form(1 / d)) < bound
-    assert float((out.double() - d).abs().max()) < 5e-7
-    assert torch.equal(T, T.T) and torch.equal(Q, Q.T)
+    run = decompose_known(M)
+    assert run.sweeps == 0 and run.one_launch == (M > 128) and run.diagonal == (M == 1)
 
 
 # The reduction in one launch: workgroups of 8 rows (10 beyond 2048), the last one whole, with one row and with one row missing,
-# the largest and smallest of its range.  Same bounds as above.
+# the largest and smallest of its range.
 @pytest.mark.parametrize("M", [135, 136, 137, 256, 512, 768, 1024, 1536, 2047, 2048, 2050, 2051, 2559, 2560])
 def test_reduction_in_one_launch_sizes(M):
-    test_direct_decomposition_sizes(M)
+    run = decompose_known(M)
+    assert run.sweeps == 0 and run.one_launch
 
 
-def test_decompositions_on_two_streams():
-    """Two threads with a stream each: every one gets what it gets alone, bit for bit."""
+# What runs where that launch is not possible: a launch per row, one size per range of its rule (columns per thread change at 256, 512,
+# 768, 1024, 1536, 2048, 2560, 3072 rows).
+@pytest.mark.parametrize("M", [129, 257, 513, 769, 1025, 1537, 2049, 2560, 2561, 3073])
+def test_reduction_row_by_row_sizes(M):
+    run = decompose_known(M, by_rows=1)
+    assert run.sweeps == 0 and not run.one_launch
+
+
+@pytest.mark.parametrize("M", [300, 1100, 2304])
+def test_reduction_given_up(M):
+    """Waits that end after one round: the decomposition is not accepted, and the sweeps give the result."""
+    run = decompose_known(M, polls=1)
+    assert run.one_launch and run.sweeps > 0
+
+
+@pytest.mark.parametrize("sizes", [(300, 900), (2304, 2300), (2304, 600)])
+def test_decompositions_on_two_streams(sizes):
+    """Two threads with a stream each, whose workgroups the chip holds at a time or does not: every one gets what it gets alone, bit
+    for bit, without sweeps."""
     import threading
-    sizes, alone, got, errors = [300, 900], {}, {}, []
+    alone, got, errors = {}, {}, []
 
     def call(M, where, stream):
         try:
             with torch.cuda.stream(stream):
                 T = torch.empty(M, M, device=DEV); Q = torch.empty(M, M, device=DEV); out = torch.empty(M, device=DEV)
                 ws = workspace(b.fw_workspace_bytes(b.FW_OP_WHITEN_EVD, M))
-                for _ in range(3):
-                    b.fw_whiten_evd(Phi[M], M, b.evd_params(), T, Q, None, out, ws)
+                for _ in range(5):
+                    run = whiten_evd(Phi[M], M, T, Q, out, ws)
+                    assert run.one_launch and run.sweeps == 0
                 stream.synchronize()
                 where[M] = (T, Q, out)
-        except Exception as ex:  # noqa: BLE001
+        except BaseException as ex:  # noqa: BLE001
             errors.append(ex)
 
     Phi = {M: dev(wl.spd_matrix(M, M, np.logspace(0, -3, M)).astype(np.float32)) for M in sizes}
