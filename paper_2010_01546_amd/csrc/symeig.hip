@@ -24,6 +24,7 @@
 // Back-transformation: blocks of 64 reflectors in compact form I - Y^T F Y (rows of Y = reflectors, F upper triangular).
 #include "fw_internal.h"
 #include "lane_sums.h"
+#include <mutex>
 #include <type_traits>
 
 namespace fw {
@@ -266,20 +267,20 @@ __global__ __launch_bounds__(T) void tri_step_kernel(double* __restrict__ A, int
 
 // ---- the reduction in one launch, the matrix in registers
 // A step of the chain above costs a launch and a pass over the active block in memory, yet 2560 x 2560 doubles fit the registers of
-// the chip.  Here every workgroup keeps blocks of 8 rows in registers (block-cyclic; a thread owns fixed columns, as above) and what
+// the chip.  Here every workgroup keeps a block of 8 rows in registers (a thread owns fixed columns, as above) and what
 // a step exchanges is its product p = A v and the next row to eliminate, n entries each.  They go through memory into places written
 // once (a row of two buffers for each step, filled with SENTINEL before the launch): the owners store them past the caches, every
 // workgroup polls the entries of its own columns until none is SENTINEL any more.  So the value is its own signal, and nothing is ever reset; 8
 // rows in a row are 64 bytes of one owner (rows dealt out one by one, their lines written by sixteen owners: 2 to 3 us more a step).
-// All workgroups have to be resident at a time (cooperative launch).  A poll gives up after POLL_LIMIT rounds (seconds); the
-// workgroups that wait for this one then do so too, and d[0] = NaN makes the caller's acceptance fail.  Rows per workgroup: eight, ten where
-// eight would need more than 256 workgroups.
+// All workgroups have to be resident at a time (launch_rows).  A poll gives up after POLL_LIMIT rounds (some tenths of a second: two
+// processes on one card may meet); the workgroups that wait for this one then do so too, and d[0] = NaN makes the caller's
+// acceptance fail.  Rows per workgroup: eight, ten where eight would need more than 256 workgroups.
 // Bound by the round trip through the last-level cache (about 1.7 us a step, 2.5 at 2304 rows, where 230 workgroups read 37 KB each) and two
 // sums over the workgroup.  Whole call, launches per step -> this, the rest as it then was: 576 features 3.55 -> 2.85 ms, 2304 features
 // 22.8 -> 14.2 ms (polls at once instead of after POLL_DELAY: 15.0 ms; after twice the delay: 14.8 ms).  Up to 128 rows the single
 // workgroup is as fast.
 constexpr unsigned long long SENTINEL = ~0ull;    // a NaN that no arithmetic on widened float32 produces; publish() keeps it out for good
-constexpr int POLL_LIMIT = 1 << 21;
+constexpr int POLL_LIMIT = 1 << 18;
 constexpr int ROWS_MAX_M = 2560;
 constexpr int POLL_DELAY = 10;                    // of 64 clocks before the first poll: an early one only gets in the way of the stores
 
@@ -1633,15 +1634,49 @@ void step(double* A, int ld, int c, int first, const double* vp, const double* p
 #undef FW_STEP
 }
 
+// Workgroups that wait for each other have to be resident together.  The launch is an ordinary one behind two checks: the device
+// holds all of them at a time, and the stream may use all of its compute units.  Two such launches at a time, from two streams
+// or threads, could each hold a part of the chip, so every one waits on its stream for the one before on that device.
+// hipLaunchCooperativeKernel does this as well, but its first call adds a hardware queue to the process, and streams that ran side by
+// side before share one from then on: the largest benchmark configuration on two streams, after decompositions of the two smaller
+// ones, 1.44 ms without it, 1.69 ms with it, 1.41 ms like this (the decompositions themselves take as long either way).
+struct RowsTurn {
+    std::mutex lock;
+    hipEvent_t done = nullptr;      // behind the latest launch; lives as long as the process
+};
+constexpr int MAX_DEVICES = 64;
+RowsTurn rows_turns[MAX_DEVICES];
+bool rows_fit(const void* kernel, int threads, unsigned workgroups, int dev, hipStream_t st) {
+    int per_cu = 0, cus = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) != hipSuccess) return false;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return false;
+    uint32_t mask[32] = {};
+    if (hipExtStreamGetCUMask(st, 32, mask) != hipSuccess) return false;
+    int usable = 0;
+    for (uint32_t word : mask) usable += __builtin_popcount(word);
+    return usable >= cus && (long long)per_cu * cus >= (long long)workgroups;
+}
 // The reduction of the leading (c + 1) x (c + 1) block in one launch; false: not possible (too many rows, or the device does not hold
 // the workgroups at a time), nothing was launched.
 template <int T, int C, int RB>
 bool launch_rows(const double* A, int ld, int c, int first, const double* vp, const double* pp, double* Pslot, double* Xslot, double* Y, double* d,
                  double* e, double* tau, int polls, hipStream_t st) {
-    void* args[] = {&A, &ld, &c, &first, &vp, &pp, &Pslot, &Xslot, &Y, &d, &e, &tau, &polls};
-    if (hipLaunchCooperativeKernel(reinterpret_cast<const void*>(tri_rows_kernel<T, C, RB>), dim3(c / RB + 1), dim3(T), args, 0, st) == hipSuccess) return true;
+    const void* kernel = reinterpret_cast<const void*>(tri_rows_kernel<T, C, RB>);
+    const unsigned workgroups = c / RB + 1;
+    int dev = -1;
+    bool launched = false;
+    if (hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < MAX_DEVICES && rows_fit(kernel, T, workgroups, dev, st)) {
+        RowsTurn& turn = rows_turns[dev];
+        const std::lock_guard<std::mutex> hold(turn.lock);
+        const bool have = turn.done || hipEventCreateWithFlags(&turn.done, hipEventDisableTiming | hipEventDisableSystemFence) == hipSuccess;
+        if (have && (hipEventQuery(turn.done) == hipSuccess || hipStreamWaitEvent(st, turn.done, 0) == hipSuccess)) {
+            void* args[] = {&A, &ld, &c, &first, &vp, &pp, &Pslot, &Xslot, &Y, &d, &e, &tau, &polls};
+            launched = hipLaunchKernel(kernel, dim3(workgroups), dim3(T), args, 0, st) == hipSuccess;
+            if (launched && hipEventRecord(turn.done, st) != hipSuccess) (void)hipStreamSynchronize(st);
+        }
+    }
     (void)hipGetLastError();
-    return false;
+    return launched;
 }
 // Threads and columns per thread: few columns shorten the chain of a step, many wavefronts lengthen its sums.  Whole calls, us: 512 features
 // 1811 (256 threads of two 1833), 576 features 2203 (256 of three 2274, 640 of one 2178), 768 features 2873 (256 of three 2977, 768 of one
