@@ -253,7 +253,7 @@ fw_status fw_cond_state_init(const fw_cond_state* st, void* stream);
  *   ws   scratch of fw_workspace_bytes(FW_OP_COND_STATE_REFRESH, M, 0, NULL, FW_F32) bytes (about 16 M^2 bytes).
  *        With it the float32 operands are split into two bfloat16 numbers each (hi + lo, 16 significant bits) and the
  *        products run on the bfloat16 matrix cores as hi hi + hi lo + lo hi with float32 accumulation: relative
- *        Frobenius error of Psi and Phi_y a few 1e-6, several times faster.  Up to about 3000 features, M a multiple of 4,
+ *        Frobenius error of Psi and Phi_y a few 1e-6, several times faster.  Up to 2700 features, M a multiple of 4,
  *        up to 32 M^2 bytes: room for partial results, which let few tiles use the whole chip (without that room, with the
  *        16 M^2 bytes: as fast as tiles allow).
  *        With ws NULL or smaller than that, or M < FW_REFRESH_SPLIT_MIN_M (where the split form would not be faster), the

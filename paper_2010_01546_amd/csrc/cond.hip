@@ -1038,10 +1038,18 @@ static size_t refresh_xpart_bytes(int M) {
 static size_t refresh_split_bytes(int M) {
     return align_up((size_t)M * M * sizeof(float), 256) + 3 * gemm_split_packed_bytes(M, M) + refresh_xpart_bytes(M);
 }
-// Few 256-wide tiles leave compute units idle: both products then cut their contraction index into runs, which the passes behind
-// them (packing of Psi, mirror image of Phi_y) add up on the way.
+// Few 256-wide tiles leave compute units idle: the products then cut their contraction index into runs, which the passes behind
+// them (packing of Psi, mirror image of Phi_y) add up on the way.  What the runs fill is also what the sums of the next batch use on
+// a second stream, and beyond the lines below writing and reading them costs more than it saves.  Whole steps (12544 rows), us on one
+// stream | with the next sums on a second one, without runs / in the product for Psi alone / for Phi_y alone / in both:
+//   1584  339 / 326 / 316 / 301 | 266 / 275 / 260 / 249        2304  472 / 482 / 457 / 463 | 382 / 422 / 395 / 408
+//   2016  417 / 402 / 394 / 376 | 325 / 353 / 331 / 323        2592  630 / 642 / 615 / 624 | 569 / 586 / 556 / 571
+//   2052  470 / 465 / 443 / 438 | 374 / 379 / 380 / 379        2736  696 / 707 / 693 / 695 | 630 / 648 / 630 / 645
+//   2160  473 / 480 / 448 / 450 | 383 / 427 / 388 / 399        3312  818 / 816 / 829 / 828 | 792 / 792 / 803 / 803
+constexpr int REFRESH_RUNS_MAX_M = 2100, REFRESH_LOWER_RUNS_MAX_M = 2700;
 static int refresh_runs(int M, int lower) {
-    return M >= FW_REFRESH_SPLIT_MIN_M && (M & 3) == 0 ? gemm_split_caller_runs(M, M, M, lower) : 1;
+    if (M < FW_REFRESH_SPLIT_MIN_M || (M & 3) != 0 || M > (lower ? REFRESH_LOWER_RUNS_MAX_M : REFRESH_RUNS_MAX_M)) return 1;
+    return gemm_split_caller_runs(M, M, M, lower);
 }
 static size_t refresh_runs_bytes(int M) {
     const int a = refresh_runs(M, 0), b = refresh_runs(M, 1), n = a > b ? a : b;
@@ -1055,7 +1063,8 @@ bool cond_refresh_plan(int M, size_t ws_bytes, fw_refresh_plan* plan) {
     if (M <= 0 || M > 16384) return false;
     plan->split = (ws_bytes >= refresh_split_bytes(M) && M >= FW_REFRESH_SPLIT_MIN_M) ? 1 : 0;
     const bool runs = refresh_runs_bytes(M) > 0 && ws_bytes >= cond_refresh_workspace_bytes(M);
-    if (plan->split) plan->mfma_flops_issued = gemm_split_flops_issued(M, M, M, 0, false, runs) + gemm_split_flops_issued(M, M, M, 1, false, runs);
+    if (plan->split) plan->mfma_flops_issued = gemm_split_flops_issued(M, M, M, 0, false, runs && refresh_runs(M, 0) > 1) +
+                                               gemm_split_flops_issued(M, M, M, 1, false, runs && refresh_runs(M, 1) > 1);
     else if (refresh_in_rows(M)) {       // two products of every 16 x 16 tile, the contraction index in rounds of 64
         const double nt = (M + 15) / 16;
         plan->mfma_flops_issued = 2.0 * nt * nt * 2.0 * 256.0 * ((M + 63) / 64 * 64);

@@ -162,6 +162,23 @@ def test_refresh_plan():
         b.fw_cond_refresh_plan_query(0, 0)
 
 
+def test_refresh_workspace_and_runs():
+    """Room for the runs of the contraction index up to the line where they stop paying; with less than that, down to the operands'
+    planes, the split form all the same, and float32 below that."""
+    packed = lambda M: 16 * M * M + 16 * 64 * M                    # Psi and three operands, rows padded to 64; row sums besides
+    for M in (1536, 1600, 2052, 2304, 2592, 2700, 2704, 2880, 3312, 3840, 4608, 1538, 2049):
+        full = b.fw_workspace_bytes(b.FW_OP_COND_STATE_REFRESH, M)
+        assert b.fw_cond_refresh_plan_query(M, full).split == 1
+        if M <= 2700 and M % 4 == 0:
+            assert 23 * M * M <= full <= 33 * M * M, M
+            p = b.fw_cond_refresh_plan_query(M, full - 256)
+            assert p.split == 1 and 3 * 3.0 * M ** 3 <= p.mfma_flops_issued <= 3 * 3.0 * M ** 3 * 1.35, M
+            assert b.fw_cond_refresh_plan_query(M, packed(M) + 4 * (M // 64 + 1) * (M + 64) + 4096).split == 1
+        else:
+            assert full <= packed(M) + 4 * (M // 64 + 1) * (M + 64) + 4096, M
+        assert b.fw_cond_refresh_plan_query(M, 16 * M * M - 256).split == 0
+
+
 def test_grad_plan():
     """The gradient product takes the split form for float32 gradients of large products (size rule of the header) when the
     call has its whole workspace; its issued flops are then three bfloat16 terms on whole tiles."""

@@ -220,6 +220,35 @@ def test_refresh_for_a_new_block(M, leak, split):
     assert relF(run.host("Phi_y"), Tn @ Phi2 @ Tn.T) < 1e-4
 
 
+@pytest.mark.parametrize("M", [1536, 1604, 2052, 2160, 2304, 2700, 2704])
+def test_refresh_with_and_without_room_for_runs(M):
+    """The split form with the whole workspace (runs in both products, in the one for Phi_y alone beyond 2100 features, in none beyond
+    2700) and with what the operands' planes need: 16 significant bits per operand in either, so the tolerance of the test above."""
+    rng = np.random.default_rng(M)
+    P = rng.standard_normal((M, M)).astype(np.float32) / np.float32(np.sqrt(M))
+    P = ((P + P.T) / 2 + np.eye(M, dtype=np.float32)).astype(np.float32)
+    T = (np.eye(M) + 0.3 * rng.standard_normal((M, M)) / np.sqrt(M)).astype(np.float32)
+    Pd, Td = dev(P), dev(T)
+    want = [x.cpu().numpy() for x in (Td.double() @ Pd.double(), Td.double() @ Pd.double() @ Td.double().T)]
+    z = lambda *sh: torch.full(sh, float("nan"), device="cuda:0")  # noqa: E731
+    Q, lbar = dev(np.eye(M)), torch.ones(4, device="cuda:0")
+    full = b.fw_workspace_bytes(b.FW_OP_COND_STATE_REFRESH, M)
+    planes = 16 * M * M + 16 * 64 * M + 4 * (M // 64 + 1) * (M + 64) + 4096
+    for nbytes in (full, full - 256, planes):
+        if b.fw_cond_refresh_plan_query(M, nbytes).split == 0:
+            assert M > 2700 and nbytes == full - 256
+            continue
+        Py, Psi, xi2 = z(M, M), z(M, M), z(M)
+        ws = workspace(nbytes)
+        ws.fill_(0xFF)
+        b.fw_cond_state_refresh(b.cond_state(M, Pd, lbar, Td, Q, Q, Py, Psi, xi2), ws)
+        got = Py.cpu().numpy()
+        errs = relF(Psi.cpu().numpy(), want[0]), relF(got, want[1])
+        assert max(errs) < 2e-5 and min(errs) > 1e-6, (nbytes, errs)
+        assert np.array_equal(got, got.T)
+        assert relF(xi2.cpu().numpy(), (want[1] ** 2).sum(0)) < 4e-5
+
+
 @pytest.mark.timeout(600)
 def test_refresh_at_the_largest_config_size():
     """M = 4608, as the benchmark calls it (whole workspace: both products in the split form on 192 x 256 tiles, the second
