@@ -1036,8 +1036,8 @@ __global__ __launch_bounds__(256) void dc_vectors_kernel(DcArrays D, int M, int 
 // One 64 x 64 tile of C = A B per workgroup of four wavefronts (32 x 32 each) on v_mfma_f64_16x16x4_f64; chunks of 16
 // contraction entries in LDS as [k][row], the next chunk's loads in registers while the matrix cores work.  A 16x16x4
 // product takes 64 cycles of a SIMD for 1 KB of fragments, so nothing but the matrix cores is near its limit.
-// Operands are functors: load(k0, buf) fetches this thread's four entries of a chunk, KC tells how they lie (four along k
-// of one row, or four along the rows of one k); k_end must not lie beyond any operand's nk.
+// Operands are functors: load(k0, k_end, buf) fetches this thread's four entries of a chunk, zero from k_end on, KC tells how they lie
+// (four along k of one row, or four along the rows of one k); rows exist up to k_end at least.
 constexpr int GLD = 80;     // LDS row of 64 entries: 80 * 8 bytes put the two k of a half-wavefront 32 banks apart
 
 template <bool KC>
@@ -1052,17 +1052,17 @@ struct Slot {                // where a thread's four entries of a 64 x 16 chunk
         for (int q = 0; q < 4; ++q) s[KC ? (k + q) * GLD + r : k * GLD + r + q] = b[q];
     }
 };
-// row-major matrix p[row][k], rows row0 .. row0 + 63 (valid below nr), entries of k below nk
+// row-major matrix p[row][k], rows row0 .. row0 + 63 (valid below nr)
 struct RowsK {
     static constexpr bool kc = true;
-    const double* p; int ld, row0, nr, nk;
-    __device__ __forceinline__ void load(int k0, const Slot<true>& s, double (&b)[4]) const {
+    const double* p; int ld, row0, nr;
+    __device__ __forceinline__ void load(int k0, int k_end, const Slot<true>& s, double (&b)[4]) const {
         const int r = row0 + s.r, k = k0 + s.k;
         const double* q = p + (size_t)r * ld + k;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) b[i] = (r < nr && k + i < nk) ? q[i] : 0.0;
+        for (int i = 0; i < 4; ++i) b[i] = (r < nr && k + i < k_end) ? q[i] : 0.0;
     }
-    // entries k0 .. k0 + 15 all lie below nk: loads without a branch (a row beyond the end reads the last one; keep() makes it zero)
+    // entries k0 .. k0 + 15 all lie below k_end: loads without a branch (a row beyond the end reads the last one; keep() makes it zero)
     __device__ __forceinline__ void load_whole(int k0, const Slot<true>& s, double (&b)[4]) const {
         const double* q = p + (size_t)min(row0 + s.r, nr - 1) * ld + k0 + s.k;
         const doublex2 x = *reinterpret_cast<const doublex2*>(q), y = *reinterpret_cast<const doublex2*>(q + 2);
@@ -1073,13 +1073,13 @@ struct RowsK {
 // row-major matrix p[k][col]; optional list of rows
 struct ColsK {
     static constexpr bool kc = false;
-    const double* p; int ld, col0, nc, nk;
+    const double* p; int ld, col0, nc;
     const int* list;                       // row of entry k: list[k] if given
-    __device__ __forceinline__ void load(int k0, const Slot<false>& s, double (&b)[4]) const {
+    __device__ __forceinline__ void load(int k0, int k_end, const Slot<false>& s, double (&b)[4]) const {
         const int k = k0 + s.k, c = col0 + s.r;
 #pragma unroll
         for (int i = 0; i < 4; ++i) b[i] = 0.0;
-        if (k < nk) {
+        if (k < k_end) {
             const double* q = p + (size_t)(list ? list[k] : k) * ld + c;
 #pragma unroll
             for (int i = 0; i < 4; ++i) if (c + i < nc) b[i] = q[i];
@@ -1096,12 +1096,12 @@ struct ColsK {
 // the same with a factor per k, or its square
 struct ColsKScaled {
     static constexpr bool kc = false;
-    const double* p; int ld, col0, nc, nk; const double* g; bool square;
-    __device__ __forceinline__ void load(int k0, const Slot<false>& s, double (&b)[4]) const {
+    const double* p; int ld, col0, nc; const double* g; bool square;
+    __device__ __forceinline__ void load(int k0, int k_end, const Slot<false>& s, double (&b)[4]) const {
         const int k = k0 + s.k, c = col0 + s.r;
 #pragma unroll
         for (int i = 0; i < 4; ++i) b[i] = 0.0;
-        if (k < nk) {
+        if (k < k_end) {
             const double f = square ? g[k] * g[k] : g[k];
 #pragma unroll
             for (int i = 0; i < 4; ++i) if (c + i < nc) b[i] = f * p[(size_t)k * ld + c + i];
@@ -1181,8 +1181,8 @@ __device__ __forceinline__ void gemm64(const OA& A, const OB& B, int k_begin, in
         if (c < nfull) { multiply(c); barrier(); }
     }
     if (nfull * 16 < len) {
-        A.load(k_begin + 16 * nfull, sa, ra[0]);
-        B.load(k_begin + 16 * nfull, sb, rb[0]);
+        A.load(k_begin + 16 * nfull, k_end, sa, ra[0]);
+        B.load(k_begin + 16 * nfull, k_end, sb, rb[0]);
         sa.store(As[0], ra[0]);
         sb.store(Bs[0], rb[0]);
         barrier();
@@ -1209,8 +1209,8 @@ __global__ __launch_bounds__(256) void dc_product_kernel(DcArrays D, int M, int 
     // a child's vectors have nothing in the columns of the other: only the entries that reach into this tile's columns are summed over
     const int n1 = part_begin(2 * m + 1, 2 * P, M) - off, b1 = D.cnt[4 * m + 3] & 0xffff, b2 = D.cnt[4 * m + 3] >> 16;
     const int kb = col0 >= n1 ? b1 : 0, ke = col0 + 64 <= n1 ? b2 : k;
-    const RowsK A = {U + (size_t)off * ld + off, ld, row0, k, k};
-    const ColsK B = {V + off, ld, col0, n, k, D.urow + off};
+    const RowsK A = {U + (size_t)off * ld + off, ld, row0, k};
+    const ColsK B = {V + off, ld, col0, n, D.urow + off};
     const int* kpos = D.kpos + off;
     gemm64(A, B, kb, ke, [&](int r, int c, double x) {
         if (row0 + r < k && col0 + c < n) Vout[(size_t)kpos[row0 + r] * ld + off + col0 + c] = x;
@@ -1224,7 +1224,7 @@ __global__ __launch_bounds__(256) void wy_gram_kernel(const double* __restrict__
     const int ks = ((kmax + WY_SLICES - 1) / WY_SLICES + 15) / 16 * 16;
     const int kb = min(kmax, (int)blockIdx.y * ks), ke = min(kmax, kb + ks);
     double* dst = gram + ((size_t)blockIdx.x * WY_SLICES + blockIdx.y) * NB * NB;
-    const RowsK A = {Y, ld, c0, M, ke};
+    const RowsK A = {Y, ld, c0, M};
     gemm64(A, A, kb, ke, [&](int r, int c, double x) { dst[r * NB + c] = x; });
 }
 // F of a block: H_c0 H_c0+1 ... = I - Y^T F Y, upper triangular, F[:k][k] = -tau_k F[:k][:k] (Y y_k), F[k][k] = tau_k.  A row of F needs
@@ -1264,8 +1264,8 @@ __global__ __launch_bounds__(256) void wy_form_kernel(const double* __restrict__
     const int c0 = blockIdx.y * NB, nb = min(NB, M - c0), kmax = c0 + nb;
     const int col0 = blockIdx.x * 64;
     if (col0 >= kmax) return;
-    const RowsK A = {F + (size_t)blockIdx.y * NB * NB, NB, 0, NB, NB};
-    const ColsK B = {Y + (size_t)c0 * ld, ld, col0, kmax, nb, nullptr};
+    const RowsK A = {F + (size_t)blockIdx.y * NB * NB, NB, 0, NB};
+    const ColsK B = {Y + (size_t)c0 * ld, ld, col0, kmax, nullptr};
     gemm64(A, B, 0, nb, [&](int r, int c, double x) {
         if (r < nb && col0 + c < kmax) Z[(size_t)(c0 + r) * ld + col0 + c] = x;
     });
@@ -1276,8 +1276,8 @@ __global__ __launch_bounds__(256) void wy_project_kernel(const double* __restric
                                                          int kmax, int kslice, double* __restrict__ part) {
     const int row0 = blockIdx.x * 64;
     const int kb = blockIdx.y * kslice, ke = min(kmax, kb + kslice);
-    const RowsK A = {V, ld, row0, M, ke};
-    const RowsK B = {Y, ld, c0, M, ke};
+    const RowsK A = {V, ld, row0, M};
+    const RowsK B = {Y, ld, c0, M};
     double* dst = part + (size_t)blockIdx.y * M * NB;
     gemm64(A, B, kb, ke, [&](int r, int c, double x) {
         if (row0 + r < M) dst[(size_t)(row0 + r) * NB + c] = x;
@@ -1298,9 +1298,9 @@ __global__ __launch_bounds__(256) void wy_sum_kernel(const double* __restrict__ 
 __global__ __launch_bounds__(256) void wy_update_kernel(const double* __restrict__ Gm, const double* __restrict__ Y, int ld, int M, int c0,
                                                         int kmax, double* __restrict__ V) {
     const int row0 = blockIdx.y * 64, col0 = blockIdx.x * 64;
-    const RowsK A = {Gm, NB, row0, M, NB};
+    const RowsK A = {Gm, NB, row0, M};
     const int nb = min(NB, M - c0);
-    const ColsK B = {Y + (size_t)c0 * ld, ld, col0, kmax, nb, nullptr};
+    const ColsK B = {Y + (size_t)c0 * ld, ld, col0, kmax, nullptr};
     gemm64(A, B, 0, nb, [&](int r, int c, double x) {
         if (row0 + r < M && col0 + c < kmax) V[(size_t)(row0 + r) * ld + col0 + c] -= x;
     });
@@ -1417,8 +1417,8 @@ __global__ __launch_bounds__(512) void wy_strip_kernel(const double* __restrict_
 __global__ __launch_bounds__(256) void image_kernel(const double* __restrict__ V, const double* __restrict__ Phi, int ld, int M,
                                                     double* __restrict__ W) {
     const int row0 = blockIdx.y * 64, col0 = blockIdx.x * 64;
-    const RowsK A = {V, ld, row0, M, M};
-    const ColsK B = {Phi, ld, col0, M, M, nullptr};
+    const RowsK A = {V, ld, row0, M};
+    const ColsK B = {Phi, ld, col0, M, nullptr};
     gemm64(A, B, 0, M, [&](int r, int c, double x) {
         if (row0 + r < M && col0 + c < M) W[(size_t)(row0 + r) * ld + col0 + c] = x;
     });
@@ -1451,8 +1451,8 @@ __global__ __launch_bounds__(256) void residual_kernel(const double* __restrict_
     const int row0 = blockIdx.y * 64, col0 = blockIdx.x * 64;
     if (col0 > row0) return;
     const bool image = blockIdx.z == 0;
-    const RowsK A = {image ? W : V, ld, row0, M, M};
-    const RowsK B = {V, ld, col0, M, M};
+    const RowsK A = {image ? W : V, ld, row0, M};
+    const RowsK B = {V, ld, col0, M};
     const double floor = scale[M];
     int bad = 0;
     gemm64(A, B, 0, M, [&](int r, int c, double x) {
@@ -1575,8 +1575,8 @@ __global__ __launch_bounds__(256) void spectral_product_kernel(const double* __r
     const int row0 = blockIdx.y * 64, col0 = blockIdx.x * 64;
     if (col0 > row0) return;
     float* out = blockIdx.z == 0 ? o0 : o1;
-    const ColsKScaled A = {V, ld, row0, M, M, g, blockIdx.z == 1};
-    const ColsK B = {V, ld, col0, M, M, nullptr};
+    const ColsKScaled A = {V, ld, row0, M, g, blockIdx.z == 1};
+    const ColsK B = {V, ld, col0, M, nullptr};
     gemm64(A, B, 0, M, [&](int r, int c, double x) {
         const int i = row0 + r, j = col0 + c;
         if (i < M && j <= i) {
