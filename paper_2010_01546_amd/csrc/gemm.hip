@@ -314,7 +314,8 @@ inline StripChoice pick_strip(int S, int M, bool plain, bool can_split, bool low
 // Where M is no multiple of 4 it stands against grad_gemm_f32_small_kernel: 777^3 17.4 / 74, lower 16.4 / 48, 1137^3 38 / 170, 50 x 525 x 525
 // 12.1 / 14.4, 147 x 199 x 199 7.4 / 7.8, 147 x 147 x 147 6.8 / 6.5, 16 x 2047 x 2047 33 / 30.
 // A bfloat16 G needs no float32 copy there (2.3 us and more): 1000 x 512 x 512 9.5 / 13.7, 1000 x 1152 x 1152 22 / 39; 256 x 512 x 512
-// 9.3 / 7.1, 256 x 2304 x 2304 38 / 34.
+// 9.3 / 7.1, 256 x 2304 x 2304 38 / 34.  M no multiple of 4, 64 and 1000 rows: 81 features 7.0 and 7.2 / 6.9 and 7.3, 90 features 7.1 and 7.3 / 7.1 and
+// 7.6, 97 features 7.2 and 7.2 / 7.4 and 7.7, 189 features 8.4 and 8.5 / 11.3 and 12.3 (16 rows: even up to 129).
 bool planes_pay(int S, int M, bool a_bf16, bool plain, bool can_split, bool lower) {
     if ((M & 3) != 0) return a_bf16 ? M >= 96 : M >= 192 && S > 16;
     const double chunks = (double)((M + 31) / 32), tr = (double)((S + 63) / 64);

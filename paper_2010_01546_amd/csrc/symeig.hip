@@ -19,9 +19,11 @@
 // rotation.  The secular equation is solved in coordinates relative to the nearest pole by rational interpolation of its two
 // halves (Bunch, Nielsen, Sorensen 1978) inside a bracket, z is recomputed from the computed roots (Gu and Eisenstat), which
 // makes the vectors orthogonal to working precision whatever the clustering, and the product with the children's vectors runs
-// on the float64 matrix cores.  All merges of a level share their launches; sizes after deflation stay on the device.
+// on the float64 matrix cores, over entries grouped by the child whose columns they reach (J. D. Rutter 1994).  All merges of a level
+// share their launches; sizes after deflation stay on the device.
 //
-// Back-transformation: blocks of 64 reflectors in compact form I - Y^T F Y (rows of Y = reflectors, F upper triangular).
+// Back-transformation: blocks of 64 reflectors in compact form I - Y^T F Y (rows of Y = reflectors, F upper triangular; R. Schreiber,
+// C. Van Loan 1989).
 #include "fw_internal.h"
 #include "lane_sums.h"
 #include <mutex>
@@ -1679,15 +1681,16 @@ bool launch_rows(const double* A, int ld, int c, int first, const double* vp, co
     return launched;
 }
 // Threads and columns per thread: few columns shorten the chain of a step, many wavefronts lengthen its sums.  Whole calls, us: 512 features
-// 1811 (256 threads of two 1833), 576 features 2203 (256 of three 2274, 640 of one 2178), 768 features 2873 (256 of three 2977, 768 of one
-// 2921), 1024 features 3770 (1024 of one 4179), 1536 features 6261 (768 of two 6519), 2048 features 9285 (1024 of two 10466).
+// 1811 (256 threads of two 1833), 520 features 1929 (320 of two 1961), 576 features 2096 (320 of two 2117; in an earlier tree 2178, 256 of
+// three 2274), 640 features 2261 (320 of two 2283), 768 features 2873 (256 of three 2977, 768 of one 2921), 1024 features 3770 (1024 of one 4179),
+// 1536 features 6261 (768 of two 6519), 2048 features 9285 (1024 of two 10466).
 bool rows(const double* A, int ld, int c, int first, const double* vp, const double* pp, double* Pslot, double* Xslot, double* Y, double* d,
           double* e, double* tau, int polls, hipStream_t st) {
     const int n = c + 1;
 #define FW_ROWS(T, C, RB) return launch_rows<T, C, RB>(A, ld, c, first, vp, pp, Pslot, Xslot, Y, d, e, tau, polls, st)
     if (n <= 256) FW_ROWS(256, 1, 8);
     if (n <= 512) FW_ROWS(512, 1, 8);
-    if (n <= 640) FW_ROWS(320, 2, 8);
+    if (n <= 640) FW_ROWS(640, 1, 8);
     if (n <= 768) FW_ROWS(384, 2, 8);
     if (n <= 1024) FW_ROWS(512, 2, 8);
     if (n <= 1536) FW_ROWS(512, 3, 8);

@@ -133,7 +133,7 @@ def test_direct_decomposition_sizes(M):
 
 # The reduction in one launch: workgroups of 8 rows (10 beyond 2048), the last one whole, with one row and with one row missing,
 # the largest and smallest of its range.
-@pytest.mark.parametrize("M", [135, 136, 137, 256, 512, 768, 1024, 1536, 2047, 2048, 2050, 2051, 2559, 2560])
+@pytest.mark.parametrize("M", [135, 136, 137, 256, 512, 640, 641, 768, 1024, 1536, 2047, 2048, 2050, 2051, 2559, 2560])
 def test_reduction_in_one_launch_sizes(M):
     run = decompose_known(M)
     assert run.sweeps == 0 and run.one_launch
