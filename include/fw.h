@@ -144,7 +144,7 @@ fw_status fw_cov_finalize(const float* A, const float* s, long long n, int M, fl
  *               a few 1e-7; 1.5 to 2.6 times as fast)
  * dt = FW_F32: float32 matrix-core products, or, where that is faster, products of operands split into three bfloat16 numbers
  *   each (24 significant bits at any exponent, six products; error below that of the float32 instructions; results that an
- *   infinite entry or one above 2^119 enters are multiplied in float32 and so are what they are there).  In the split form a row with
+ *   infinite entry or one above 2^112 enters are multiplied in float32 and so are what they are there).  In the split form a row with
  *   an infinite entry comes out as NaN, entries above 3.38e38 count as infinite, and those below 2^-118 lose their 16 bits one by one.
  * dt = FW_BF16 with the workspace: the products have float32 accuracy with Q as it is -- G widened to float32 in the workspace,
  *   or taken as it is by the three-number form above (past the size rule above, with M a multiple of 4: the split form) --, G_out

@@ -308,16 +308,17 @@ inline StripChoice pick_strip(int S, int M, bool plain, bool can_split, bool low
 }
 
 // Is the three-plane form (gemm_planes.hip) the faster one?  Its time: chunks of 32 entries, for each about 0.45 us (a bfloat16 A: 0.25)
-// per tile of 64 x 64 that a compute unit holds.  Measured against the strips, us: 896^3 18.6 / 71, its lower triangle 17.3 / 48,
-// 1280^3 40.6 / 74, lower 27.1 / 43, 1472^3 66.7 / 79, lower 42.5 / 76, 384 x 2304 x 2304 46 / 60; the strips stay where they fill one
-// round: 512^3 11.3 / 6.5, 576^3 12.4 / 10.2, 1152^3 34.9 / 34.9, lower 24.2 / 20.0, 256 x 2304 x 2304 45 / 32.
-// Where M is no multiple of 4 it stands against grad_gemm_f32_small_kernel: 777^3 17.4 / 74, lower 16.4 / 48, 1137^3 38 / 170, 50 x 525 x 525
-// 12.1 / 14.4, 147 x 199 x 199 7.4 / 7.8, 147 x 147 x 147 6.8 / 6.5, 16 x 2047 x 2047 33 / 30.
-// A bfloat16 G needs no float32 copy there (2.3 us and more): 1000 x 512 x 512 9.5 / 13.7, 1000 x 1152 x 1152 22 / 39; 256 x 512 x 512
+// per tile of 64 x 64 that a compute unit holds.  Measured against the strips, us a call in a row of calls: 896^3 19 / 71, 1280^3 40 / 74,
+// 1472^3 67 / 78, 384 x 2304 x 2304 42 / 58, both products of a refresh at 896 features 44 / 129, 1280 74 / 126, 1472 117 / 165; the strips
+// stay where they fill one round: 512^3 11.3 / 6.5, 576^3 12.4 / 10.2, 1152^3 34.9 / 34.9, its lower triangle 24.2 / 20.0, 256 x 2304 x 2304 45 / 32.
+// Where M is no multiple of 4 it stands against grad_gemm_f32_small_kernel: 777^3 17.6 / 74, 1137^3 37 / 169, 64 x 193 x 193 7.6 / 7.8, 50 x 525 x
+// 525 12.8 / 14.3, 200 x 2047 x 2047 39 / 85; rows of half a tile cost that kernel less: 20, 24, 28 rows of 525 features 12.7 / 12.4, 12.7 / 12.6, 12.9
+// / 13.7, of 1023 features 20.8 / 19.3, 20.8 / 19.5, 21.1 / 21.2, of 2047 features 37 / 33, 37 / 33, 37.6 / 36.6; 147 x 147 x 147 6.8 / 6.5.
+// A bfloat16 G needs no float32 copy there (2.3 us and more): 1000 x 512 x 512 11.4 / 15.0, 1000 x 1152 x 1152 25 / 41; 256 x 512 x 512
 // 9.3 / 7.1, 256 x 2304 x 2304 38 / 34.  M no multiple of 4, 64 and 1000 rows: 81 features 7.0 and 7.2 / 6.9 and 7.3, 90 features 7.1 and 7.3 / 7.1 and
-// 7.6, 97 features 7.2 and 7.2 / 7.4 and 7.7, 189 features 8.4 and 8.5 / 11.3 and 12.3 (16 rows: even up to 129).
+// 7.6, 97 features 7.2 and 7.2 / 7.4 and 7.7, 189 features 8.4 and 8.5 / 11.3 and 12.3; one row, 97 features 5.0 / 5.4, 2047 27 / 32.
 bool planes_pay(int S, int M, bool a_bf16, bool plain, bool can_split, bool lower) {
-    if ((M & 3) != 0) return a_bf16 ? M >= 96 : M >= 192 && S > 16;
+    if ((M & 3) != 0) return a_bf16 ? M >= 96 : M >= 192 && S >= 28;
     const double chunks = (double)((M + 31) / 32), tr = (double)((S + 63) / 64);
     const double tiles = lower ? 0.5 * tr * (tr + 1.0) : tr * ((M + 63) / 64);
     const double held = (double)(((long long)tiles + 255) / 256);

@@ -9,7 +9,7 @@
 // factor share accumulators, one set for each half of a chunk, so that a rounding of a partial sum of the large products h h
 // happens K / 32 times in a chain and the five small ones do not add to it.
 //
-// Infinite entries, and those above 2^119, have no such sum, and sums of products above 2^112 overflow with it: the result is infinite or
+// Infinite entries, and those above 2^112, have no such sum, and sums of products above that overflow with it: the result is infinite or
 // NaN then.  A wavefront that sees such a result multiplies its 32 x 32 results once more in float32, so that they are what the
 // float32 instruction gives.
 //
@@ -38,7 +38,7 @@ __device__ __forceinline__ void split8(const float (&x)[8], uint4& h, uint4& m, 
         union { bf2 v; unsigned u; } p;
         p.v[0] = (__bf16)x0; p.v[1] = (__bf16)x1;
         hp[k] = p.u;
-        const float r0 = 65536.f * (x0 - __uint_as_float(p.u << 16)), r1 = 65536.f * (x1 - __uint_as_float(p.u & 0xffff0000u));
+        const float r0 = fmaf(-65536.f, __uint_as_float(p.u << 16), 65536.f * x0), r1 = fmaf(-65536.f, __uint_as_float(p.u & 0xffff0000u), 65536.f * x1);
         p.v[0] = (__bf16)r0; p.v[1] = (__bf16)r1;
         mp[k] = p.u;
         const float s0 = r0 - __uint_as_float(p.u << 16), s1 = r1 - __uint_as_float(p.u & 0xffff0000u);

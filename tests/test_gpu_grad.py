@@ -210,10 +210,10 @@ def test_largest_feature_count():
 
 
 # The three-plane form: tiles of 64 x 64 and chunks of 32 entries with one row, column or entry too many and too few, contraction
-# shorter than a chunk, sizes that are no multiple of 4 (from 192 features and 17 rows on; bfloat16 from 96 on) and multiples of 4 where it
+# shorter than a chunk, sizes that are no multiple of 4 (from 192 features and 28 rows on; bfloat16 from 96 on) and multiples of 4 where it
 # takes over from the strips.  Operands carry 24 bits and the chain of a result has M / 32 links: 2^-24 sqrt(M / 32) and the final
 # additions stay below 1e-6; bfloat16 results (8 significant bits) are rounded once, at most 2^-8 relative.
-@pytest.mark.parametrize("S,M", [(17, 193), (64, 223), (65, 225), (63, 255), (130, 321), (50, 525), (200, 1023), (900, 896), (2304, 256), (384, 2304)])
+@pytest.mark.parametrize("S,M", [(17, 193), (27, 193), (28, 193), (64, 223), (65, 225), (63, 255), (130, 321), (50, 525), (200, 1023), (900, 896), (2304, 256), (384, 2304)])
 def test_three_planes_f32(S, M):
     T32, Q64 = sym_Q(M, M + 9)
     Q32 = Q64.astype(np.float32)
