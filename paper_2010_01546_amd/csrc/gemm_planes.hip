@@ -208,10 +208,15 @@ __global__ __launch_bounds__(NT) void gemm_planes_kernel(const void* __restrict_
             big = __builtin_amdgcn_mfma_f32_32x32x2f32(x, y, big, 0, 0, 0);
         }
     }
+    const auto row_of = [&](int i) { return row0 + 32 * wr + 8 * (i >> 2) + 4 * half + (i & 3); };
+    if (Out.W && !Out.out) {
+        if (col < N) emit_update<16>(Out, row_of, col, S, N, big);
+        return;
+    }
     const bool plain = Out.out && !Out.out_bf16 && Out.taps == 1 && !Out.W;
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-        const int row = row0 + 32 * wr + 8 * (i >> 2) + 4 * half + (i & 3);
+        const int row = row_of(i);
         if (row < S && col < N) {
             if (plain) reinterpret_cast<float*>(Out.out)[(size_t)row * N + col] = big[i];
             else emit(Out, row, col, N, big[i]);
