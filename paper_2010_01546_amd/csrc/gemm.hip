@@ -257,7 +257,7 @@ __global__ __launch_bounds__(256) void grad_gemm_f32_strip_kernel(const float* _
 // workspace for partial strips is at hand, the contraction index is cut into up to STRIP_MAX_RUNS runs of whole chunks;
 // a run shorter than about 16 chunks is not worth it (filling the LDS ring and summing the four wavefronts' strips at
 // the end take about as long as ten chunks: measured, a 256 x 2304 x 2304 product got slower when cut in four).
-struct StripChoice { int mf, c, nks, kchunks; double us; };   // us: estimated time
+struct StripChoice { int mf, c, nks, kchunks; double us, rounds, cost; };   // us: estimated time; rounds of 256 strips, unit of cost below
 constexpr int STRIP_MAX_RUNS = 8;
 // strips of c tiles that touch the lower triangle of a square of t x t tiles
 inline long long lower_strips(long long t, int c) {
@@ -266,7 +266,7 @@ inline long long lower_strips(long long t, int c) {
 }
 inline StripChoice pick_strip(int S, int M, bool plain, bool can_split, bool lower) {
     static const int cs[6] = {9, 6, 4, 3, 2, 1};
-    StripChoice best = {32, 1, 1, 0, 0.0};
+    StripChoice best = {32, 1, 1, 0, 0.0, 0.0, 0.0};
     double best_cost = 1e300;
     long long best_wgs = 1;
     auto consider = [&](int mf, int c, bool low) {
@@ -282,7 +282,7 @@ inline StripChoice pick_strip(int S, int M, bool plain, bool can_split, bool low
         // a 16x16 tile is a quarter of the MFMA work of a 32x32 tile and reads twice the operands per flop;
         // a wider strip reads fewer operands per MFMA
         const double cost = rounds * c * (mf == 32 ? 1.0 : 0.25 * 1.06) * kpad * (1.0 + 0.02 / c);
-        if (cost < best_cost) { best_cost = cost; best = {mf, c, 1, 0, 0.0}; best_wgs = wgs; }
+        if (cost < best_cost) { best_cost = cost; best = {mf, c, 1, 0, 0.0, 0.0, 0.0}; best_wgs = wgs; }
     };
     for (int mf = 32; mf >= 16; mf -= 16)
         for (int ci = 0; ci < 6; ++ci) consider(mf, cs[ci], false);
@@ -303,28 +303,42 @@ inline StripChoice pick_strip(int S, int M, bool plain, bool can_split, bool low
     }
     // filling and draining the ring costs every round about 1.5 us (2.5 us with strips of one tile), an entry of the contraction
     // index and unit of cost 4.3 to 5 ns
-    best.us = 2.0 + (double)((best_wgs + 255) / 256) * (best.c == 1 ? 2.5 : 1.5) + 0.0048 * best_cost * M;
+    best.rounds = (double)((best_wgs + 255) / 256);
+    best.cost = best_cost;
+    best.us = 2.0 + best.rounds * (best.c == 1 ? 2.5 : 1.5) + 0.0048 * best_cost * M;
     return best;
 }
 
-// Is the three-plane form (gemm_planes.hip) the faster one?  Its time: chunks of 32 entries, for each about 0.45 us (a bfloat16 A: 0.25)
-// per tile of 64 x 64 that a compute unit holds.  Measured against the strips, us a call in a row of calls: 896^3 19 / 71, 1280^3 40 / 74,
+// Is the three-plane form (gemm_planes.hip) the faster one?  Its time: chunks of 32 entries, for each about 0.45 us per tile of 64 x 64 that a
+// compute unit holds.  Measured against the strips, us a call in a row of calls: 896^3 19 / 71, 1280^3 40 / 74,
 // 1472^3 67 / 78, 384 x 2304 x 2304 42 / 58, both products of a refresh at 896 features 44 / 129, 1280 74 / 126, 1472 117 / 165; the strips
 // stay where they fill one round: 512^3 11.3 / 6.5, 576^3 12.4 / 10.2, 1152^3 34.9 / 34.9, its lower triangle 24.2 / 20.0, 256 x 2304 x 2304 45 / 32.
 // Where M is no multiple of 4 it stands against grad_gemm_f32_small_kernel: 777^3 17.6 / 74, 1137^3 37 / 169, 64 x 193 x 193 7.6 / 7.8, 50 x 525 x
 // 525 12.8 / 14.3, 200 x 2047 x 2047 39 / 85; rows of half a tile cost that kernel less: 20, 24, 28 rows of 525 features 12.7 / 12.4, 12.7 / 12.6, 12.9
 // / 13.7, of 1023 features 20.8 / 19.3, 20.8 / 19.5, 21.1 / 21.2, of 2047 features 37 / 33, 37 / 33, 37.6 / 36.6; 147 x 147 x 147 6.8 / 6.5.
-// A bfloat16 G needs no float32 copy there (2.3 us and more): 1000 x 512 x 512 11.4 / 15.0, 1000 x 1152 x 1152 25 / 41; 256 x 512 x 512
-// 9.3 / 7.1, 256 x 2304 x 2304 38 / 34.  M no multiple of 4, 64 and 1000 rows: 81 features 7.0 and 7.2 / 6.9 and 7.3, 90 features 7.1 and 7.3 / 7.1 and
-// 7.6, 97 features 7.2 and 7.2 / 7.4 and 7.7, 189 features 8.4 and 8.5 / 11.3 and 12.3; one row, 97 features 5.0 / 5.4, 2047 27 / 32.
+// A bfloat16 G needs no float32 copy there, which took 2 us and more: 1000 x 512 x 512 11.4 / 15.0, 1000 x 1152 x 1152 25 / 41, 400 x 1024 x
+// 1024 21 / 34, 128 x 2304 x 2304 40 / 49, 1 x 96 x 96 3.9 / 4.2; 64 x 172 x 172 7.9 / 7.2, 64 x 256 x 256 8.1 / 6.1, 128 x 376 x 376 10.3 / 8.5, 256 x 2304 x
+// 2304 41 / 34.  Both sides' times there are least-squares fits to 1130 shapes (1 .. 3000 rows, 16 .. 4000 features; within 7 and 9 % in the
+// mean), with a margin that leaves four of them slower than the strips, by 6 % at most, and twenty where this form would have
+// been faster by 3 % or more.  M no multiple of 4, 64
+// and 1000 rows: 81 features 7.0 and 7.2 / 6.9 and 7.3, 90 features 7.1 and 7.3 / 7.1 and 7.6, 97 features 7.2 and 7.2 / 7.4 and 7.7, 189 features 8.4
+// and 8.5 / 11.3 and 12.3; one row, 97 features 5.0 / 5.4, 2047 27 / 32.
 bool planes_pay(int S, int M, bool a_bf16, bool plain, bool can_split, bool lower) {
     if ((M & 3) != 0) return a_bf16 ? M >= 96 : M >= 192 && S >= 28;
     const double chunks = (double)((M + 31) / 32), tr = (double)((S + 63) / 64);
     const double tiles = lower ? 0.5 * tr * (tr + 1.0) : tr * ((M + 63) / 64);
     const double held = (double)(((long long)tiles + 255) / 256);
-    const double planes = 3.5 + chunks * (a_bf16 ? 0.1 + 0.25 * held : 0.07 + 0.45 * held);
-    const double strips = pick_strip(S, M, plain, can_split && !lower, lower).us + (a_bf16 ? 3.0 : 0.0);
-    return planes < 0.95 * strips;
+    const StripChoice st = pick_strip(S, M, plain, can_split && !lower, lower);
+    if (a_bf16) {
+        if (S <= 2 && M > 200) return false;          // 1 x 256 x 256 6.1 / 5.1, 1 x 284 x 284 7.2 / 6.4, 2 x 288 x 288 6.6 / 6.3
+        const double rows = log2((double)(S < 32 ? S : 32));
+        const int kc = 4 * (st.mf == 32 ? 8 : 16) * strip_u(st.mf, st.c);
+        const double planes = 2.55 + chunks * (0.38 + 0.15 * (held - 1.0) + (tiles > 64.0 ? 0.075 : 0.0)) + ((M & 31) != 0 ? 0.3 : 0.0) + 0.47 * rows;
+        const double strips = 0.7 + st.rounds * (st.c == 1 ? 3.8 : 2.4) + (st.rounds > 1.0 ? 0.0061 : 0.0051) * st.cost * M + 7.5e-6 * S * M + 0.33 * rows +
+                              (M % kc != 0 ? 1.4 : 0.0);
+        return planes < 0.97 * strips;
+    }
+    return 3.5 + chunks * (0.07 + 0.45 * held) < 0.95 * st.us;
 }
 
 // sum of the partial strips of the runs, in run order, then the epilogue

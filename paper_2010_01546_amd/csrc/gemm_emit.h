@@ -30,7 +30,7 @@ __device__ __forceinline__ void emit(const GemmEpilogue& e, int row, int col, in
     }
 }
 
-// The same for N elements of a lane, element i at (row_of(i), col) where row_of(i) < S: the old values of W and V are all asked for before the
+// The same for N elements of a lane, element i at (row_of(i), col) where row_of(i) < S, no lane's row above that of a later lane: the old values of W and V are all asked for before the
 // first new one is stored (a load behind a store waits for it, a round trip per element: 16 elements a lane, 767 x 68 bfloat16
 // gradient, 14.7 us one by one).
 template <int N, class RowOf, class Values>
@@ -39,9 +39,11 @@ __device__ __forceinline__ void emit_update(const GemmEpilogue& e, const RowOf& 
 #pragma unroll
     for (int i = 0; i < N; ++i) {
         const int row = row_of(i);
+        w[i] = u[i] = 0.f;
+        if (__builtin_amdgcn_readfirstlane(row) >= S) continue;      // rows ascend with the lane
         const size_t idx = emit_index(e, row < S ? row : 0, col, M);
         w[i] = e.W[idx];
-        u[i] = e.V ? e.V[idx] : 0.f;
+        if (e.V) u[i] = e.V[idx];
     }
 #pragma unroll
     for (int i = 0; i < N; ++i) {
