@@ -1748,6 +1748,7 @@ fw_status sym_eig(const float* Phi, int M, bool dead, double* const buf[4], void
     bool reduced = false;
     if (M > TAIL) {
         while (c >= ROWS_MAX_M) one_step();
+        FW_LAUNCH_CHECK();                // launch_rows clears the error of its own checks, and would clear one of these launches
         if (!(run && run->by_rows))
             reduced = rows(A, ld, c, first, vp(), p[cur ^ 1], Va, Vb, Y, d, e, tau, run && run->polls > 0 ? run->polls : POLL_LIMIT, st);
         if (run) run->one_launch = reduced ? 1 : 0;
