@@ -30,9 +30,9 @@ __device__ __forceinline__ void emit(const GemmEpilogue& e, int row, int col, in
     }
 }
 
-// The same for N elements of a lane, element i at (row_of(i), col) where row_of(i) < S, no lane's row above that of a later lane: the old values of W and V are all asked for before the
-// first new one is stored (a load behind a store waits for it, a round trip per element: 16 elements a lane, 767 x 68 bfloat16
-// gradient, 14.7 us one by one).
+// The update of N elements of a lane, element i at (row_of(i), col) where row_of(i) < S, no lane's row above that of a later lane: the old
+// values of W and V are all asked for before the first new one is stored (a load behind a store waits for it, a round trip per
+// element: 16 elements a lane, 767 x 68 bfloat16 gradient, 14.7 us one by one).
 template <int N, class RowOf, class Values>
 __device__ __forceinline__ void emit_update(const GemmEpilogue& e, const RowOf& row_of, int col, int S, int M, const Values& v) {
     float w[N], u[N];
