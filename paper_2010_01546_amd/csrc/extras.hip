@@ -110,8 +110,7 @@ __global__ __launch_bounds__(1024) void diagnostics_final_kernel(const double* _
 // image already lies in the space built so far) is recorded in `st` on the device and the remaining launches return at once.
 struct ProbeState { int steps, done; double prev_beta; };
 constexpr int PROBE_MAX_K = 32;
-// above this, and with more than 16 basis vectors above half of it, the orthogonalisation of a step runs on many workgroups (a thread of
-// the single one would need more registers than it has)
+// above this the orthogonalisation of a step runs on many workgroups (a thread of the single one would need more registers than it has)
 constexpr int PROBE_SPREAD_MIN_M = 2048;
 
 // q_0 = b0 / |b0| (b0 = all ones when absent)
@@ -175,20 +174,40 @@ __global__ __launch_bounds__(256) void probe_matvec_kernel(const float* __restri
 // by every wavefront for itself in the order of the wavefronts, so a pass has one barrier.
 // M = 525: 4.6 us a step with up to 8 vectors, 6.1 us with up to 16 (the basis read again for every product and subtraction, three barriers
 // a pass: 10.3 us).
-template <int E, int NB>
+// H = 2: more vectors than registers, in two halves that take turns (four more rounds of loads from L2).  A step with 17 to 32 vectors, its
+// product included: 27 us at 1025 and 28 at 2048 features; spread over several workgroups in four launches 34 and 35; with the
+// basis read again for every product 25 and 38.
+template <int E, int NB, int H>
 __global__ __launch_bounds__(1024) void probe_orth_kernel(int j, int M, size_t ld, double* __restrict__ Qb, const double* __restrict__ w,
                                                           double* __restrict__ alpha, double* __restrict__ beta, double breakdown,
                                                           ProbeState* __restrict__ st) {
-    __shared__ double part[3][16][NB + 1];
+    __shared__ double part[3][16][H * NB + 1];
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
     double x[E], q[NB][E];
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-        const int m = t + 1024 * e;
-        x[e] = m < M ? w[m] : 0.0;
+    for (int e = 0; e < E; ++e) x[e] = t + 1024 * e < M ? w[t + 1024 * e] : 0.0;
+    // vectors h NB .. h NB + NB - 1.  One of several parts is read anew every time and behind the uses of the part before; masks would not
+    // fit the scalar registers, so entries from M on repeat the last one (x is zero there) and vectors beyond j repeat it (their
+    // coefficients are set to zero).
+    auto load = [&](int h) {
+        if constexpr (H == 1) {
 #pragma unroll
-        for (int i = 0; i < NB; ++i) q[i][e] = (i <= j && m < M) ? Qb[(size_t)i * ld + m] : 0.0;
-    }
+            for (int e = 0; e < E; ++e)
+#pragma unroll
+                for (int i = 0; i < NB; ++i) q[i][e] = (i <= j && t + 1024 * e < M) ? Qb[(size_t)i * ld + t + 1024 * e] : 0.0;
+        } else {
+            const double* src = Qb;
+            __builtin_amdgcn_sched_barrier(0);
+            asm volatile("" : "+s"(src));
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                const double* row = src + (size_t)min(h * NB + i, j) * ld;
+#pragma unroll
+                for (int e = 0; e < E; ++e) q[i][e] = row[min(t + 1024 * e, M - 1)];
+            }
+        }
+    };
+    load(0);
     if (st->done) return;
     // NB values per lane -> their sums over the wavefront in part[..][wave][0 .. NB - 1]
     auto sums_to = [&](const double (&v)[NB], double* out) {
@@ -210,36 +229,50 @@ __global__ __launch_bounds__(1024) void probe_orth_kernel(int j, int M, size_t l
     double n0 = 0.0, al = 0.0;
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
-        double v[NB];
 #pragma unroll
-        for (int i = 0; i < NB; ++i) {
-            v[i] = 0.0;
+        for (int h = 0; h < H; ++h) {
+            if (h > 0) load(h);
+            double v[NB];
 #pragma unroll
-            for (int e = 0; e < E; ++e) v[i] += q[i][e] * x[e];
+            for (int i = 0; i < NB; ++i) {
+                v[i] = 0.0;
+#pragma unroll
+                for (int e = 0; e < E; ++e) v[i] += q[i][e] * x[e];
+            }
+            sums_to(v, part[pass][wave] + h * NB);
         }
-        sums_to(v, part[pass][wave]);
         if (pass == 0) {
             const double s = square();
-            if (lane == 0) part[0][wave][NB] = s;
+            if (lane == 0) part[0][wave][H * NB] = s;
         }
         __syncthreads();
         // coefficient `lane` (and behind the last one the square of the first pass)
         double c = 0.0;
-        if (lane < NB + (pass == 0 ? 1 : 0)) {
+        if (lane < H * NB + (pass == 0 ? 1 : 0)) {
 #pragma unroll
             for (int g = 0; g < 16; ++g) c += part[pass][g][lane];
+            if (H > 1 && lane > j && lane < H * NB) c = 0.0;
         }
         auto from_lane = [&](int i) {
             const long long b = __double_as_longlong(c);
             const unsigned lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffll), i), hi = __builtin_amdgcn_readlane((int)(b >> 32), i);
             return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
         };
-        if (pass == 0) { n0 = sqrt(from_lane(NB)); al = from_lane(j); }
+        if (pass == 0) { n0 = sqrt(from_lane(H * NB)); al = from_lane(j); }
 #pragma unroll
-        for (int i = 0; i < NB; ++i) {
-            const double ci = from_lane(i);
+        for (int h = H - 1; h >= 0; --h) {            // the half at hand first
+            if (h < H - 1) load(h);
 #pragma unroll
-            for (int e = 0; e < E; ++e) x[e] -= ci * q[i][e];
+            for (int i = 0; i < NB; ++i) {
+                const double ci = from_lane(h * NB + i);
+#pragma unroll
+                for (int e = 0; e < E; ++e) x[e] -= ci * q[i][e];
+            }
+        }
+        if constexpr (H > 1) {
+#pragma unroll
+            for (int e = 0; e < E; ++e)
+                if (t + 1024 * e >= M) x[e] = 0.0;
         }
     }
     const double s = square();
@@ -457,8 +490,7 @@ fw_status cond_probe(const float* Phi_y, int M, const float* b0, int k, float* o
     hipLaunchKernelGGL(probe_init_kernel, dim3(1), dim3(1024), 0, st, b0, M, Qb, ps);
     for (int j = 0; j < k; ++j) {
         hipLaunchKernelGGL(probe_matvec_kernel, dim3((M + 3) / 4), dim3(256), 0, st, Phi_y, Qb + (size_t)j * L.ld, M, w, ps);
-        const bool two = M > PROBE_SPREAD_MIN_M / 2;
-        if (M > PROBE_SPREAD_MIN_M || (two && j >= 16)) {
+        if (M > PROBE_SPREAD_MIN_M) {
             // many features: the step spread over ceil(M / 256) workgroups, four launches
             const dim3 g((M + PROBE_WG - 1) / PROBE_WG), blk(PROBE_WG);
             hipLaunchKernelGGL(probe_orth_phase_kernel<1>, g, blk, 0, st, j, M, L.ld, Qb, w, part, alpha, beta, 1e-7, ps);
@@ -466,11 +498,15 @@ fw_status cond_probe(const float* Phi_y, int M, const float* b0, int k, float* o
             hipLaunchKernelGGL(probe_orth_phase_kernel<3>, g, blk, 0, st, j, M, L.ld, Qb, w, part, alpha, beta, 1e-7, ps);
             hipLaunchKernelGGL(probe_orth_phase_kernel<4>, g, blk, 0, st, j, M, L.ld, Qb, w, part, alpha, beta, 1e-7, ps);
         }
-#define FW_PROBE_ORTH(E, NB) hipLaunchKernelGGL((probe_orth_kernel<E, NB>), dim3(1), dim3(1024), 0, st, j, M, L.ld, Qb, w, alpha, beta, 1e-7, ps)
-        else if (two) { if (j < 8) FW_PROBE_ORTH(2, 8); else FW_PROBE_ORTH(2, 16); }
-        else if (j < 8) FW_PROBE_ORTH(1, 8);
-        else if (j < 16) FW_PROBE_ORTH(1, 16);
-        else FW_PROBE_ORTH(1, 32);
+#define FW_PROBE_ORTH(E, NB, H) hipLaunchKernelGGL((probe_orth_kernel<E, NB, H>), dim3(1), dim3(1024), 0, st, j, M, L.ld, Qb, w, alpha, beta, 1e-7, ps)
+        else if (M > 1024) {
+            if (j < 8) FW_PROBE_ORTH(2, 8, 1);
+            else if (j < 16) FW_PROBE_ORTH(2, 16, 1);
+            else FW_PROBE_ORTH(2, 16, 2);
+        }
+        else if (j < 8) FW_PROBE_ORTH(1, 8, 1);
+        else if (j < 16) FW_PROBE_ORTH(1, 16, 1);
+        else FW_PROBE_ORTH(1, 32, 1);
 #undef FW_PROBE_ORTH
     }
     hipLaunchKernelGGL(probe_final_kernel, dim3(1), dim3(2 * PROBE_CUTS), 0, st, alpha, beta, ps, out);

@@ -167,10 +167,11 @@ def test_condition_probe_against_the_oracle(M, k):
     assert g_cond <= w[-1] / w[0] * (1 + 1e-5)
 
 
-@pytest.mark.parametrize("M,k", [(63, 17), (525, 32), (1023, 16), (1025, 16), (2047, 9), (2048, 32), (2049, 5)])
+@pytest.mark.parametrize("M,k", [(63, 17), (525, 32), (1023, 16), (1024, 32), (1025, 16), (1025, 17), (1025, 32), (1500, 18), (2047, 9), (2047, 31),
+                                 (2048, 32), (2049, 5)])
 def test_condition_probe_orthogonalisation_edges(M, k):
     """Around the strips of the orthogonalisation (64 entries, 1024 threads), with odd M, with more basis vectors than
-    wavefronts, and on both sides of the size at which a step is spread over several workgroups."""
+    wavefronts, in one and in two halves, and on both sides of the size at which a step is spread over several workgroups."""
     test_condition_probe_against_the_oracle(M, k)
 
 
