@@ -35,12 +35,12 @@ HBM_PEAK = 8.0e12
 # --warmup 5` whose summary is profiles/whitened_update_step_hbm_traffic_counters.txt, each counter scaled by what it reads on
 # a 256 MiB device copy appended to the same run.  Default layout (kkc) only.
 PROFILED_TRAFFIC = {
-    "c2": {"cov_accumulate": (156.7e6, 121.9e6), "cond_reduce_step": (12.6e6, 6.6e6), "cond_state_refresh": (28.6e6, 3.2e6),
-           "grad_transform": (3.8e6, 0.1e6), "cov_finalize": (1.7e6, 1.3e6)},
-    "c3": {"cov_accumulate": (195.3e6, 116.2e6), "cond_reduce_step": (189.3e6, 104.1e6), "cond_state_refresh": (408.7e6, 102.7e6),
-           "grad_transform": (38.9e6, 2.3e6), "cov_finalize": (22.0e6, 21.3e6)},
-    "c4": {"cov_accumulate": (499.7e6, 184.1e6), "cond_reduce_step": (748.7e6, 413.2e6), "cond_state_refresh": (1925.4e6, 410.3e6),
-           "grad_transform": (272.0e6, 163.3e6), "cov_finalize": (85.5e6, 85.0e6)},
+    "c2": {"cov_accumulate": (154.2e6, 116.6e6), "cond_reduce_step": (14.1e6, 6.9e6), "cond_state_refresh": (32.6e6, 2.7e6),
+           "grad_transform": (4.0e6, 0.1e6), "cov_finalize": (1.7e6, 1.3e6)},
+    "c3": {"cov_accumulate": (194.2e6, 116.1e6), "cond_reduce_step": (197.0e6, 108.3e6), "cond_state_refresh": (376.7e6, 149.1e6),
+           "grad_transform": (40.4e6, 2.4e6), "cov_finalize": (22.0e6, 21.3e6)},
+    "c4": {"cov_accumulate": (497.8e6, 184.0e6), "cond_reduce_step": (779.1e6, 429.5e6), "cond_state_refresh": (1999.0e6, 426.7e6),
+           "grad_transform": (282.8e6, 169.9e6), "cov_finalize": (85.5e6, 85.0e6)},
 }
 TRAFFIC_SOURCE = ("profiles/whitened_update_step_hbm_traffic_counters.txt (rocprofv3 counters of an earlier run of this command, "
                   "not measured by this run)")
@@ -352,8 +352,8 @@ def rooflines_of(r, layer, b, cfg_key, layout_name):
     a2.update(traffic_of("grad_transform"))
     words = 16 if r["gamma"] < 1.0 else 10
     t3 = ex["cond_reduce_step"] * 1e-3
-    a3 = {"bound": "hbm", "export": "fw_cond_reduce_step", "kernel": "matvec_c + matvec_vt + matvec_u_vecmat + t_reduce_scalars + "
-          "matvec + update + partial_sum", "achieved": words * 4.0 * M * M / t3 / 1e9, "peak": HBM_PEAK / 1e9, "unit": "GB/s",
+    a3 = {"bound": "hbm", "export": "fw_cond_reduce_step", "kernel": "matvec_c + matvec_vt + matvec_u_vecmat + " +
+          ("t_reduce_scalars + " if M > 640 else "") + "update + partial_sum", "achieved": words * 4.0 * M * M / t3 / 1e9, "peak": HBM_PEAK / 1e9, "unit": "GB/s",
           "frac": words * 4.0 * M * M / t3 / HBM_PEAK, "ms": ex["cond_reduce_step"], "algorithmic_bytes": words * 4.0 * M * M,
           "note": ("achieved = the algorithmic 16 M^2 words (10 without leak) / time; the update pass reads the symmetric matrices' "
                    "tiles once for both mirrored positions, so fewer bytes than that move") if M > 1152 else
